@@ -131,10 +131,10 @@ static Layout compute_layout(int64_t n_total, int64_t S, int T, int D_max, int k
     L.lp_exp = take((size_t)S * L.lp_nchunk * sizeof(int32_t));
     L.lp_slices = take((size_t)L.lp_ns * S * L.lp_nchunk * LP_XC * 2);
     L.stat_bits = take(4 * sizeof(uint64_t));
-    // pre-pass + counters: theta, work counter, cand counter, cum table, prefixes, scores
-    L.pre = take(64 + (size_t)(S / 4 + 8) * sizeof(uint64_t) + PRE_Q * SISSO_MAX_D * sizeof(int32_t) +
-                 64 + (size_t)PRE_Q * S * d + PRE_Q * d + 1024 +
-                 (size_t)(SISSO_MAX_D + 1) * (S + 1) * sizeof(uint64_t) + 64 + 256);
+    // counters (theta, work counter, candidate counter), cum table, pre-pass
+    // state, binomial table, filter tasks
+    L.pre = take(64 + (size_t)(S / 4 + 8) * sizeof(uint64_t) + sizeof(PreState) +
+                 (size_t)(SISSO_MAX_D + 1) * (S + 1) * sizeof(uint64_t) + 2 * sizeof(int32_t));
     // one row of four (i1, j) records per j > i1 group: sum over groups of (S - 2 - 4 g)
     {
         const int64_t ng3 = S >= 3 ? (S - 3) / 4 + 1 : 0;
@@ -232,20 +232,14 @@ static void carve(sisso_l0 *h) {
     c.theta_bits = (unsigned long long *)p;
     c.work_counter = (unsigned int *)(p + 8);
     c.cand_counter = (unsigned int *)(p + 12);
-    c.pre_count = (int32_t *)(p + 16);
-    c.pre_done = (unsigned int *)(p + 20);
     c.mtq_taken = (unsigned int *)(p + 60);
     c.stats = (uint64_t *)(p + 24);
     c.merge_count = (unsigned int *)(p + 56);
     p += 64;
     c.cum = (uint64_t *)p;
     p += (size_t)(c.S / 4 + 8) * sizeof(uint64_t);
-    c.pre_prefix = (int32_t *)p;
-    p += align256(PRE_Q * SISSO_MAX_D * sizeof(int32_t));
-    c.pre_bound = (double *)p;
-    p += align256(PRE_Q * sizeof(double));
-    c.pre_sse = (double *)p;
-    p += align256((size_t)PRE_Q * c.S * sizeof(double));
+    c.pre = (PreState *)p;
+    p += sizeof(PreState);
     c.btab = (uint64_t *)p;
     p += (size_t)(SISSO_MAX_D + 1) * (c.S + 1) * sizeof(uint64_t);
     c.tstar = (int32_t *)p;

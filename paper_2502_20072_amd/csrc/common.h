@@ -24,7 +24,9 @@ constexpr int SEARCH_WGS_DEFAULT = 1024;
 constexpr int JBLK = 64;               // (D-1)-th indices per search work item (one per lane)
 constexpr int SUBP = 4;                // sub-prefixes sharing one Gram load (single task)
 constexpr int PRE_M = 16;              // features the threshold pre-pass starts from
-constexpr int PRE_Q = 8;               // best prefixes the pre-pass extends by every feature
+constexpr int PRE_Q = 8;               // prefixes a pre-pass round extends by every feature
+constexpr int PRE_R = SISSO_MAX_D - 1; // most pre-pass rounds
+constexpr int PRE_BINS = 2048;         // histogram bins of the pre-pass pool (64 per factor of two of SSE)
 constexpr int KP_MAX = 512;            // longest per-wave candidate list
 constexpr int LP_XC = 256;             // precision form: samples per slice-exponent chunk
 constexpr int PROP_NF = 8;             // learned proposal: features per prefix
@@ -220,6 +222,16 @@ __host__ __device__ inline int64_t s4_rows_below(int64_t S, int64_t i) {
     for (int64_t x = 1; x < i && x <= S - 3; ++x) acc += ((x + 3) / 4) * (S - 2 - x);
     return acc;
 }
+
+// Device state of the threshold pre-pass (reset by its selection).
+struct PreState {
+    double theta0;                            // upper bound of the KP-th best SSE (+inf: none)
+    int32_t count[PRE_R];                     // prefixes of each round
+    uint32_t done[PRE_R];                     // workgroups of each round that have finished
+    int32_t prefix[PRE_R][PRE_Q][SISSO_MAX_D];
+    unsigned long long best[PRE_R][PRE_Q];    // each prefix's best extension: FP32 SSE bits, then its index
+    uint32_t hist[PRE_BINS];                  // the pool's SSEs by size
+};
 
 // -------------------------------------------------------- workspace layout
 // Every region is 256-byte aligned; offsets in bytes from the workspace base.

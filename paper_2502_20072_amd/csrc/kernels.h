@@ -29,11 +29,7 @@ struct Ctx {
     uint64_t *stats;                 // [4]: candidates, work items, theta0 bits, final theta bits
     uint64_t *cum;                   // cumulative work items per j-block [S/JBLK + 2]
     uint64_t *btab;                  // binomials C(n, r), r <= SISSO_MAX_D, n <= S
-    int32_t *pre_prefix;             // pre-pass: chosen prefixes [PRE_Q][SISSO_MAX_D]
-    int32_t *pre_count;              // pre-pass: number of chosen prefixes
-    unsigned int *pre_done;          // pre-pass: extension blocks finished (the last one pools)
-    double *pre_sse;                 // pre-pass: extension scores [PRE_Q][S]
-    double *pre_bound;               // pre-pass: per-prefix L-th best [PRE_Q]
+    PreState *pre;                   // threshold pre-pass: prefixes, pool histogram, bound
     double *rec3;                    // D = 3: pair records of the filter task [ceil(S/4)][S][4][4] (null if absent)
     double *G1;                      // the filter task's matrix alone, one-task tiled layout (G itself when T = 1)
     double *rec4;                    // D = 4, one task: pair-group records [rows][S4_ROW] (null if absent)

@@ -285,8 +285,7 @@ __device__ void s4_tables(const Ctx &c);
 
 // s3: 0 = work-item table of the general kernel, 4 = the D = 4 record-table
 // tiles, other = the D = 3 record-table tiles
-__device__ void search_init_body(const Ctx &c, int64_t e, bool leader, int D, int R, int JB, int s3,
-                                 bool clear_pre = true) {
+__device__ void search_init_body(const Ctx &c, int64_t e, bool leader, int D, int R, int JB, int s3) {
     if (e < (int64_t)(SISSO_MAX_D + 1) * (c.S + 1)) {
         const int r = (int)(e / (c.S + 1));
         const int64_t n = e % (c.S + 1);
@@ -296,7 +295,6 @@ __device__ void search_init_body(const Ctx &c, int64_t e, bool leader, int D, in
         *c.work_counter = 0;
         *c.cand_counter = 0;
         *c.theta_bits = (unsigned long long)__double_as_longlong(INF);
-        if (clear_pre) *c.pre_count = 0;  // (else the pre-pass selection runs beside and sets it)
         *c.merge_count = 0;
         *c.mtq_taken = 0;
         c.flags[FLAG_CAPACITY] = 0;
@@ -336,9 +334,12 @@ __global__ void search_init_kernel(Ctx c, int D, int R, int JB, int s3) {
 // The search starts from an upper bound theta0 of the KP-th best SSE, so
 // that almost no tuple reaches the exact path.  It is built from a small,
 // structured set of real tuples: the best (D-1)-subsets of the PRE_M most
-// relevant features, each extended by every feature.  Any set of real
-// tuples gives a valid bound (below), so the selections may be heuristic;
-// they run as block-wide histogram thresholds, one thread per candidate.
+// relevant features, each extended by every feature, then (D - 2 more
+// rounds) the (D-1)-subsets of the best tuples found so far, extended again.
+// The tuples of all rounds are distinct, so the KP-th smallest SSE of the
+// pool bounds the KP-th best of the search.  Any set of real tuples gives a
+// valid bound, so the selections may be heuristic: block-wide histogram
+// thresholds for the first prefixes, a histogram of the pool for the bound.
 constexpr int PRE_WG = 1024;      // threads of the pre-pass workgroups
 constexpr int PRE_SORT = 4096;    // largest sorted candidate set
 constexpr int PRE_KEEP = PRE_SORT / PRE_WG;  // candidates a thread keeps when S > PRE_SORT
@@ -505,7 +506,9 @@ __device__ int block_pick_first(const double *key, int n, double t, int M, int *
 
 // pre_select: relevance of feature j = sum over tasks of b_tj^2 (its D=1
 // explained sum of squares); the PRE_M most relevant full-rank features;
-// every (D-1)-subset of them scored; the PRE_Q best subsets become prefixes.
+// every (D-1)-subset of them scored; the PRE_Q best subsets become the first
+// round's prefixes (D = 2: the PRE_Q most relevant features).  Resets the
+// pre-pass state.
 template <int D>
 __device__ void pre_select_body(const Ctx &c) {
     __shared__ double key[PRE_SORT];
@@ -515,12 +518,17 @@ __device__ void pre_select_body(const Ctx &c) {
     __shared__ SelScratch sc;
     const int tid = threadIdx.x;
     constexpr int q = D - 1;
-    if (tid == 0) {
-        *c.pre_count = 0;
-        *c.pre_done = 0;
+    constexpr int NM = q > 1 ? PRE_M : PRE_Q;
+    PreState &ps = *c.pre;
+    if (tid == 0) ps.theta0 = INF;
+    if (tid < PRE_R) {
+        ps.count[tid] = 0;
+        ps.done[tid] = 0;
     }
-    // 1. the PRE_M most relevant full-rank features (up to the last
-    //    histogram bin), in increasing index order
+    if (tid < PRE_R * PRE_Q) ps.best[tid / PRE_Q][tid % PRE_Q] = ~0ull;
+    for (int b = tid; b < PRE_BINS; b += PRE_WG) ps.hist[b] = 0;
+    // 1. the NM most relevant full-rank features (up to the last histogram
+    //    bin), in increasing index order
     const int N = gather_candidates(key, id, c.S, [&](int64_t j) {
         double r = 0.0;
         bool ok = true;
@@ -532,9 +540,9 @@ __device__ void pre_select_body(const Ctx &c) {
         return ok ? -r : INF;
     });
     __syncthreads();
-    double th = block_threshold(key, N, PRE_M, sc);
-    if (!(th < INF)) th = __DBL_MAX__;  // fewer than PRE_M full-rank features: take them all
-    const int M = block_pick_first(key, N, th, PRE_M, pick, sc);
+    double th = block_threshold(key, N, NM, sc);
+    if (!(th < INF)) th = __DBL_MAX__;  // fewer than NM full-rank features: take them all
+    const int M = block_pick_first(key, N, th, NM, pick, sc);
     // increasing feature index (positions are indices unless S > PRE_SORT)
     if (tid < M) {
         const int f = id[pick[tid]];
@@ -544,6 +552,11 @@ __device__ void pre_select_body(const Ctx &c) {
     }
     __syncthreads();
     if (M < q) return;
+    if constexpr (q == 1) {
+        if (tid < M) ps.prefix[0][tid][0] = sel[tid];
+        if (tid == 0) ps.count[0] = M;
+        return;
+    }
     // 2. score every q-subset of the selection (<= C(16, 3) = 560 of them)
     const int nsub = (int)binom(M, q);
     for (int e = tid; e < nsub; e += PRE_WG) {
@@ -561,9 +574,9 @@ __device__ void pre_select_body(const Ctx &c) {
     if (tid < Q) {
         int32_t loc[MAXD];
         colex_unrank_small((uint64_t)pick[tid], q, M, loc);
-        for (int m = 0; m < q; ++m) c.pre_prefix[tid * MAXD + m] = sel[loc[m]];
+        for (int m = 0; m < q; ++m) ps.prefix[0][tid][m] = sel[loc[m]];
     }
-    if (tid == 0) *c.pre_count = Q;
+    if (tid == 0) ps.count[0] = Q;
 }
 
 template <int D>
@@ -571,106 +584,225 @@ __global__ __launch_bounds__(PRE_WG) void pre_select_kernel(Ctx c) {
     pre_select_body<D>(c);
 }
 
-// pre_extend: block qq scores every tuple prefix_qq + {k} that does not
-// contain an earlier chosen prefix (so the tuples of different blocks are
-// distinct) and lies in the searched rank range, and records the L-th
-// smallest SSE among the candidates it kept.  Those are L distinct real
-// tuples at or below that value, so Q*L >= KP of them at or below the
-// maximum over blocks make that maximum an upper bound of the KP-th best
-// SSE of the search.
+// Bins of the pool histogram: 64 per factor of two (the top six mantissa
+// bits), the total sum of squares c 64 bins below the top; SSEs below
+// c 2^-30 share bin 0.  pool_edge(b) is the smallest value above bin b.
+constexpr int PRE_SHIFT = 46;
+__device__ inline int64_t pool_base(double ctot) {
+    const int64_t b = (__double_as_longlong(ctot) >> PRE_SHIFT) - (PRE_BINS - 64);
+    return b > 0 ? b : 0;
+}
+__device__ inline int pool_bin(double s, int64_t base) {
+    if (!(s > 0.0)) return 0;
+    const int64_t b = (__double_as_longlong(s) >> PRE_SHIFT) - base;
+    return b < 0 ? 0 : b < PRE_BINS ? (int)b : PRE_BINS - 1;
+}
+__device__ inline double pool_edge(int b, int64_t base) {
+    return b < PRE_BINS - 1 ? __longlong_as_double((base + b + 1) << PRE_SHIFT) : INF;
+}
+
+// pre_extend, round r: the workgroups of row qq score every tuple
+// prefix_qq + {k} that no earlier prefix of this or a previous round reaches
+// (so all tuples of the pool are distinct) and that lies in the searched
+// rank range, and add them to the pool's histogram; the last workgroup of
+// the round sets theta0 to the upper edge of the bin that holds the pool's
+// KP-th smallest (within 1/64 of it), and, unless the round is the last,
+// takes the next prefixes: the (D-1)-subsets of each prefix's best tuple,
+// best tuple first, that have not been prefixes yet.  Bound: one pass of
+// gathered G loads per round, spread over S / 256 workgroups per prefix.
+// With one round and the largest of the prefixes' own L-th best as the bound
+// theta0 was 1.7 to 8.8 times the true KP-th best on the benchmark's tree
+// columns, and the tuples between the two went through the exact path one by
+// one; the pooled bound is 1.0 to 1.25 times it after D - 1 rounds.
+constexpr int PRE_XT = 256;      // threads per workgroup
+constexpr int PRE_XBLOCKS = 64;  // most workgroups per prefix
 template <int D>
-__global__ __launch_bounds__(PRE_WG) void pre_extend_kernel(Ctx c, int ranged, uint64_t r0,
-                                                            uint64_t r1, int L) {
-    __shared__ double key[PRE_SORT];
-    __shared__ int id[PRE_SORT];
-    __shared__ SelScratch sc;
-    const int qq = blockIdx.x;
-    const int tid = threadIdx.x;
-    const int Q = *c.pre_count;
-    if (qq >= Q || L > PRE_SORT) {
-        if (tid == 0) c.pre_bound[qq] = INF;
-        return;
-    }
-    const int q = D - 1;
-    int32_t P[MAXD];
-    for (int m = 0; m < q; ++m) P[m] = c.pre_prefix[qq * MAXD + m];
-    const int N = gather_candidates(key, id, c.S, [&](int64_t k) {
-        int32_t tup[MAXD];
-        bool inP = false;
-        int n = 0;
-        for (int m = 0; m < q; ++m) inP |= (P[m] == k);
-        if (inP) return INF;
-        bool placed = false;
-        for (int m = 0; m < q; ++m) {
-            if (!placed && k < P[m]) {
-                tup[n++] = (int32_t)k;
-                placed = true;
-            }
-            tup[n++] = P[m];
-        }
-        if (!placed) tup[n++] = (int32_t)k;
-        for (int o = 0; o < qq; ++o) {
-            int hit = 0;
-            for (int m = 0; m < q; ++m) {
-                const int32_t v = c.pre_prefix[o * MAXD + m];
-                for (int u = 0; u < D; ++u) hit += (tup[u] == v);
-            }
-            if (hit == q) return INF;
-        }
-        if (ranged) {
-            const uint64_t rk = lex_rank(BinomTab{c.btab, c.S}, c.S, D, tup);
-            if (rk < r0 || rk >= r1) return INF;
-        }
-        return ne_sse_t<D>(c, tup);
-    });
-    __syncthreads();
-    // at least L of the kept candidates (distinct real tuples) are <= the bound
-    const double bound = block_threshold(key, N, L, sc);
-    if (tid == 0) c.pre_bound[qq] = bound;
-    if (c.T == 1) return;
-    // several tasks: the tuples of all blocks are distinct, so the KP-th
-    // smallest of their pooled scores is a bound as well, and usually far
-    // below the largest per-block one (the weakest prefix no longer sets it).
-    // The last block to finish computes it.
-    const int nk = N < c.S ? N : (int)c.S;
-    for (int x = tid; x < nk; x += PRE_WG) c.pre_sse[(int64_t)qq * c.S + x] = key[x];
+__global__ __launch_bounds__(PRE_XT) void pre_extend_kernel(Ctx c, int ranged, uint64_t r0, uint64_t r1, int round,
+                                                            int rounds) {
+    constexpr int q = D - 1;
+    constexpr int BPT = PRE_BINS / PRE_XT;  // bins per thread
+    __shared__ unsigned h[PRE_BINS];
+    __shared__ unsigned wsum[PRE_XT / 64];
+    __shared__ unsigned long long wbest[PRE_XT / 64];
+    __shared__ int exk[PRE_R * PRE_Q];
     __shared__ int s_last;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    PreState &ps = *c.pre;
+    const int qq = blockIdx.y, Q = ps.count[round];
+    double ctot = 0.0;
+    for (int t = 0; t < c.T; ++t) ctot += c.cyy[t];
+    const int64_t base = pool_base(ctot);
+    // this thread's BPT consecutive bins of h: the count before them
+    auto scan = [&](const unsigned (&v)[BPT]) {
+        unsigned own = 0;
+#pragma unroll
+        for (int b = 0; b < BPT; ++b) own += v[b];
+        unsigned incl = own;
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned y = __shfl_up(incl, o);
+            if (lane >= o) incl += y;
+        }
+        if (lane == 63) wsum[wave] = incl;
+        __syncthreads();
+        unsigned before = incl - own;
+        for (int w = 0; w < wave; ++w) before += wsum[w];
+        return before;
+    };
+    if (qq < Q) {
+        int32_t P[q];
+#pragma unroll
+        for (int m = 0; m < q; ++m) P[m] = ps.prefix[round][qq][m];
+        // an earlier prefix is part of P + {k} for one k at most: its only
+        // index outside P (-1: none or several)
+        if (tid < PRE_R * PRE_Q) {
+            const int orr = tid / PRE_Q, oq = tid % PRE_Q;
+            int out = -1, n = 0;
+            if ((orr < round && oq < ps.count[orr]) || (orr == round && oq < qq)) {
+#pragma unroll
+                for (int m = 0; m < q; ++m) {
+                    const int32_t v = ps.prefix[orr][oq][m];
+                    bool in = false;
+#pragma unroll
+                    for (int l = 0; l < q; ++l) in |= P[l] == v;
+                    if (!in) {
+                        out = v;
+                        ++n;
+                    }
+                }
+            }
+            exk[tid] = n == 1 ? out : -1;
+        }
+        for (int b = tid; b < PRE_BINS; b += PRE_XT) h[b] = 0;
+        __syncthreads();
+        const int nex = round * PRE_Q + qq;
+        unsigned long long best = ~0ull;
+        for (int64_t k = (int64_t)blockIdx.x * PRE_XT + tid; k < c.S; k += (int64_t)gridDim.x * PRE_XT) {
+            bool skip = false;
+#pragma unroll
+            for (int m = 0; m < q; ++m) skip |= P[m] == k;
+            for (int o = 0; o < nex; ++o) skip |= exk[o] == k;
+            if (skip) continue;
+            int32_t tup[MAXD];
+            int n = 0;
+            bool placed = false;
+#pragma unroll
+            for (int m = 0; m < q; ++m) {
+                if (!placed && k < P[m]) {
+                    tup[n++] = (int32_t)k;
+                    placed = true;
+                }
+                tup[n++] = P[m];
+            }
+            if (!placed) tup[n++] = (int32_t)k;
+            if (ranged) {
+                const uint64_t rk = lex_rank(BinomTab{c.btab, c.S}, c.S, D, tup);
+                if (rk < r0 || rk >= r1) continue;
+            }
+            const double s = ne_sse_t<D>(c, tup);
+            if (!(s < INF)) continue;
+            atomicAdd(&h[pool_bin(s, base)], 1u);
+            const unsigned long long pk =
+                ((unsigned long long)__float_as_uint((float)fmax(s, 0.0)) << 32) | (unsigned long long)(uint32_t)k;
+            best = pk < best ? pk : best;
+        }
+        for (int o = 32; o >= 1; o >>= 1) {
+            const unsigned long long y = (unsigned long long)__shfl_xor((long long)best, o);
+            best = y < best ? y : best;
+        }
+        if (lane == 0) wbest[wave] = best;
+        __syncthreads();
+        if (tid == 0) {
+            for (int w = 1; w < PRE_XT / 64; ++w) best = wbest[w] < best ? wbest[w] : best;
+            if (best != ~0ull) atomicMin(&ps.best[round][qq], best);
+        }
+        // bins past the workgroup's own KP smallest cannot hold the pool's KP-th
+        unsigned v[BPT];
+#pragma unroll
+        for (int b = 0; b < BPT; ++b) v[b] = h[tid * BPT + b];
+        unsigned before = scan(v);
+#pragma unroll
+        for (int b = 0; b < BPT; ++b) {
+            if (v[b] && before < (unsigned)c.KP) atomicAdd(&ps.hist[tid * BPT + b], v[b]);
+            before += v[b];
+        }
+    }
     __threadfence();
     __syncthreads();
-    if (tid == 0) s_last = atomicAdd(c.pre_done, 1u) == (unsigned)Q - 1u;  // blocks qq >= Q left above
+    if (tid == 0) s_last = atomicAdd(&ps.done[round], 1u) == gridDim.x * gridDim.y - 1u;
     __syncthreads();
     if (!s_last) return;
     __threadfence();
-    const int KP = c.KP;
-    const int64_t npool = (int64_t)Q * c.S;
-    const int NP = gather_candidates(key, id, npool, [&](int64_t x) {
-        // (every block kept the same count nk)
-        return x % c.S < nk ? __hip_atomic_load(&c.pre_sse[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : INF;
-    });
-    __syncthreads();
-    const double pooled = block_threshold(key, NP, KP, sc);
-    if (tid == 0 && pooled < INF) {
-        double mx = 0.0;
-        for (int b = 0; b < Q; ++b) mx = fmax(mx, c.pre_bound[b]);
-        const double th = fmin(mx, pooled);
-        for (int b = 0; b < Q; ++b) c.pre_bound[b] = th;
+    {
+        unsigned v[BPT];
+#pragma unroll
+        for (int b = 0; b < BPT; ++b)
+            v[b] = __hip_atomic_load(&ps.hist[tid * BPT + b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        unsigned before = scan(v);
+#pragma unroll
+        for (int b = 0; b < BPT; ++b) {
+            if (before < (unsigned)c.KP && before + v[b] >= (unsigned)c.KP) ps.theta0 = pool_edge(tid * BPT + b, base);
+            before += v[b];
+        }
     }
+    if (round + 1 >= rounds || wave != 0) return;
+    // the next prefixes, one candidate per lane: lane i drops index i % D of
+    // the tuple of rank i / D among the prefixes' best
+    unsigned long long bp = ~0ull;
+    if (lane < Q) bp = __hip_atomic_load(&ps.best[round][lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int src = -1;
+    for (int x = 0; x < PRE_Q; ++x) {
+        const unsigned long long bx = (unsigned long long)__shfl((long long)bp, x);
+        int rx = 0;
+        for (int y = 0; y < PRE_Q; ++y) {
+            const unsigned long long by = (unsigned long long)__shfl((long long)bp, y);
+            rx += by < bx || (by == bx && y < x);
+        }
+        if (rx == lane / D) src = x;
+    }
+    const bool have = lane < PRE_Q * D && src >= 0;
+    const unsigned long long bs = (unsigned long long)__shfl((long long)bp, have ? src : 0);
+    bool take = have && bs != ~0ull;
+    int32_t sub[q];
+    if (take) {
+        const int32_t k = (int32_t)(uint32_t)bs;
+        int32_t tup[D];
+#pragma unroll
+        for (int m = 0; m < q; ++m) tup[m] = ps.prefix[round][src][m];
+        tup[q] = k;
+#pragma unroll
+        for (int m = q; m > 0; --m)
+            if (tup[m] < tup[m - 1]) {
+                const int32_t x = tup[m];
+                tup[m] = tup[m - 1];
+                tup[m - 1] = x;
+            }
+        const int drop = lane % D;
+#pragma unroll
+        for (int m = 0; m < q; ++m) sub[m] = m < drop ? tup[m] : tup[m + 1];
+    }
+    const uint64_t key = take ? pack_tuple(sub, q) : ~0ull;
+    for (int r = 0; r <= round; ++r)
+        for (int o = 0; o < ps.count[r]; ++o) take = take && key != pack_tuple(ps.prefix[r][o], q);
+    for (int x = 0; x < PRE_Q * D; ++x) {
+        const uint64_t kx = (uint64_t)__shfl((long long)key, x);
+        if (x < lane) take = take && kx != key;
+    }
+    const unsigned long long m = __ballot(take);
+    const int at = __popcll(m & ((1ull << lane) - 1ull));
+    if (take && at < PRE_Q)
+#pragma unroll
+        for (int x = 0; x < q; ++x) ps.prefix[round + 1][at][x] = sub[x];
+    if (lane == 0) ps.count[round + 1] = __popcll(m) < PRE_Q ? __popcll(m) : PRE_Q;
 }
 
 template <class CtxT>
-__device__ double theta0_from_prepass(const CtxT &c, int L, int KP) {
-    const int Q = *c.pre_count;
-    if ((int64_t)Q * L < KP) return INF;
-    double th = 0.0;
-    for (int q = 0; q < Q; ++q) th = fmax(th, c.pre_bound[q]);
-    return th;
-}
+__device__ double theta0_of(const CtxT &c) { return c.pre->theta0; }
 
 // --------------------------------------------------------- search kernel
 constexpr int MT_RECS = 512;  // records per work item with many tasks (JB * TP)
 
 struct SearchArgs {
-    int D, TL, JB, R, KP, L, ranged;
+    int D, TL, JB, R, KP, ranged;
     uint64_t r0, r1;
 };
 
@@ -823,7 +955,7 @@ __global__ __launch_bounds__(256) void search_kernel(Ctx c, SearchArgs a) {
     }
     double theta_pub = INF;  // last value this wave published
     unsigned offered = 0;    // tuples offered to the list (diagnostics; one atomic per wave)
-    const double theta0 = theta0_from_prepass(c, a.L, KP);
+    const double theta0 = theta0_of(c);
     // the FP32 form's filter bound is widened by an absolute margin (a
     // multiple of the FP32 rounding of SSEs of size up to c)
     double ctot = 0.0;
@@ -1254,7 +1386,7 @@ __host__ __device__ inline int64_t s3_rows(int64_t S) {
 __global__ __launch_bounds__(PRE_WG) void rec3_kernel(Ctx c, double *__restrict__ rec) {
     const int64_t ex = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t g = blockIdx.y;
-    search_init_body(c, g * (int64_t)gridDim.x * blockDim.x + ex, ex == 0 && g == 0, 3, SUBP, JBLK, 1, false);
+    search_init_body(c, g * (int64_t)gridDim.x * blockDim.x + ex, ex == 0 && g == 0, 3, SUBP, JBLK, 1);
     if (blockIdx.x == gridDim.x - 1 && g == 0) {
         pre_select_body<3>(c);
         return;
@@ -1768,7 +1900,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) v
     __builtin_amdgcn_wave_barrier();
     double theta_pub = INF;
     unsigned offered = 0;
-    const double theta0 = theta0_from_prepass(c, a.L, KP);
+    const double theta0 = theta0_of(c);
     const uint64_t ntiles = tcum[s3_nblocks(c.S)];
     const int64_t gw = (int64_t)blockIdx.x * SEARCH_WAVES + wave;
     // several tasks: flagged steps are queued in chunks of MTQ_CHUNK and scored
@@ -1857,14 +1989,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3B_WPE))) 
             cur_ctx = cp;
             cur = p;
             a.KP = c.KP;
-            a.L = (c.KP + PRE_Q - 1) / PRE_Q;
             for (int m = lane; m < a.KP; m += 64) {
                 Ls[m] = INF;
                 Lr[m] = ~0ull;
             }
             __atomic_signal_fence(__ATOMIC_SEQ_CST);
             __builtin_amdgcn_wave_barrier();
-            theta0 = theta0_from_prepass(c, a.L, a.KP);
+            theta0 = theta0_of(c);
             theta_pub = INF;
             offered = 0;
         }
@@ -2066,7 +2197,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S4_WPE))) v
     __builtin_amdgcn_wave_barrier();
     double theta_pub = INF;
     unsigned offered = 0;
-    const double theta0 = theta0_from_prepass(c, a.L, KP);
+    const double theta0 = theta0_of(c);
     const int64_t S = c.S;
     const int64_t nb = s4_nblocks(S);
     const uint64_t ntiles = tcum[nb];
@@ -2373,7 +2504,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) v
     const uint64_t total = nreg > 0 ? c.mtq_pre[nreg] : 0;
     const uint64_t per = (total + nw - 1) / nw;
     const uint64_t e0 = (uint64_t)gw * per, e1 = e0 + per < total ? e0 + per : total;
-    double th = fmin(theta0_from_prepass(c, a.L, KP), theta_load(c.theta_bits));
+    double th = fmin(theta0_of(c), theta_load(c.theta_bits));
     const double theta_f = th < INF ? th * (1.0 + THETA_SLACK) : INF;
     __shared__ uint64_t s_bk[SEARCH_WAVES][MT_BUF];
     __shared__ double s_be[SEARCH_WAVES][MT_BUF];
@@ -2785,21 +2916,21 @@ __device__ void bitonic_sort_lds(double *ks, uint64_t *kr, int N) {
 // and the prefix is appended to the candidate array at an atomically
 // reserved offset.  The candidate set does not depend on the append order,
 // and keys are unique, so the selection below is deterministic.
-__device__ inline double merge_bound(const Ctx &c, int L, int KP, int use_pre) {
+__device__ inline double merge_bound(const Ctx &c, int use_pre) {
     double bound = theta_load(c.theta_bits);
-    if (use_pre) bound = fmin(bound, theta0_from_prepass(c, L, KP));
+    if (use_pre) bound = fmin(bound, theta0_of(c));
     return bound < INF ? bound * (1.0 + THETA_SLACK) : INF;
 }
 
 // nl_dev (may be null): the number of lists written, read on the device (at
 // most nlists; the batched search writes a variable number per problem)
-__global__ __launch_bounds__(MERGE_THREADS) void merge_compact_kernel(Ctx c, int nlists, int KP, int L,
-                                                                      int use_pre, const uint32_t *nl_dev) {
+__global__ __launch_bounds__(MERGE_THREADS) void merge_compact_kernel(Ctx c, int nlists, int KP, int use_pre,
+                                                                      const uint32_t *nl_dev) {
     const int lane = threadIdx.x & 63;
     const int64_t l = (int64_t)blockIdx.x * (MERGE_THREADS / 64) + (threadIdx.x >> 6);
     const int64_t nl = nl_dev ? (int64_t)min(*nl_dev, (uint32_t)nlists) : (int64_t)nlists;
     if (l >= nl) return;
-    const double bound = merge_bound(c, L, KP, use_pre);
+    const double bound = merge_bound(c, use_pre);
     const double *ls = c.list_sse + l * KP;
     const uint64_t *lr = c.list_rank + l * KP;
     // sorted: the entries at or below the bound are a prefix, which ends at
@@ -2846,7 +2977,7 @@ __device__ void drop_adjacent_duplicates(double *ks, uint64_t *kr, int N) {
     if (__syncthreads_or(nd)) bitonic_sort_lds(ks, kr, N);
 }
 
-__global__ __launch_bounds__(MERGE_THREADS) void merge_select_kernel(Ctx c, int KP, int L, int use_pre, int dedupe,
+__global__ __launch_bounds__(MERGE_THREADS) void merge_select_kernel(Ctx c, int KP, int use_pre, int dedupe,
                                                                      int nlists, const uint32_t *nl_dev) {
     __shared__ double ks[MERGE_CAP];
     __shared__ uint64_t kr[MERGE_CAP];
@@ -2854,7 +2985,7 @@ __global__ __launch_bounds__(MERGE_THREADS) void merge_select_kernel(Ctx c, int 
     const int tid = threadIdx.x;
     const int64_t total = *c.merge_count;
     if (tid == 0) {
-        const double th0 = use_pre ? theta0_from_prepass(c, L, KP) : INF;
+        const double th0 = use_pre ? theta0_of(c) : INF;
         c.stats[0] = *c.cand_counter;
         c.stats[2] = (uint64_t)__double_as_longlong(th0);
         c.stats[3] = (uint64_t)__double_as_longlong(theta_load(c.theta_bits));
@@ -3306,9 +3437,13 @@ static void launch_rescore_final(const Ctx &c, int D, int k, hipStream_t st) {
 }
 
 template <int D>
-static void launch_prepass(const Ctx &c, const SearchCall &sc, int L, hipStream_t st, bool select = true) {
+static void launch_prepass(const Ctx &c, const SearchCall &sc, hipStream_t st, bool select = true) {
     if (select) hipLaunchKernelGGL((pre_select_kernel<D>), dim3(1), dim3(PRE_WG), 0, st, c);
-    hipLaunchKernelGGL((pre_extend_kernel<D>), dim3(PRE_Q), dim3(PRE_WG), 0, st, c, sc.ranged, sc.r0, sc.r1, L);
+    const int64_t nb = (c.S + PRE_XT - 1) / PRE_XT;
+    const dim3 grid((unsigned)(nb < PRE_XBLOCKS ? nb : PRE_XBLOCKS), PRE_Q);
+    constexpr int rounds = D - 1;
+    for (int r = 0; r < rounds; ++r)
+        hipLaunchKernelGGL((pre_extend_kernel<D>), grid, dim3(PRE_XT), 0, st, c, sc.ranged, sc.r0, sc.r1, r, rounds);
 }
 
 template <int D, bool MT>
@@ -3319,12 +3454,12 @@ static void launch_one(const Ctx &c, const SearchArgs &a, size_t lds, hipStream_
         hipLaunchKernelGGL((search_kernel<D, MT, double>), dim3(c.search_wgs), dim3(SEARCH_WG), lds, st, c, a);
 }
 
-static void launch_merge(const Ctx &c, int nlists, int L, int use_pre, hipStream_t st, int dedupe = 0,
+static void launch_merge(const Ctx &c, int nlists, int use_pre, hipStream_t st, int dedupe = 0,
                          const uint32_t *nl_dev = nullptr) {
     const int per = MERGE_THREADS / 64;
     hipLaunchKernelGGL(merge_compact_kernel, dim3((nlists + per - 1) / per), dim3(MERGE_THREADS), 0, st, c, nlists,
-                       c.KP, L, use_pre, nl_dev);
-    hipLaunchKernelGGL(merge_select_kernel, dim3(1), dim3(MERGE_THREADS), 0, st, c, c.KP, L, use_pre, dedupe, nlists,
+                       c.KP, use_pre, nl_dev);
+    hipLaunchKernelGGL(merge_select_kernel, dim3(1), dim3(MERGE_THREADS), 0, st, c, c.KP, use_pre, dedupe, nlists,
                        nl_dev);
 }
 
@@ -3336,7 +3471,7 @@ bool s3_batchable(const Ctx &c, int D) {
 
 // record table + initialisation + pre-pass selection (one launch), then the
 // pre-pass extension: everything before the sweep of the one-task D = 3 path
-static void s3_prologue(const Ctx &c, const SearchCall &sc, int L, hipStream_t st) {
+static void s3_prologue(const Ctx &c, const SearchCall &sc, hipStream_t st) {
     const unsigned init_blocks = (unsigned)(((SISSO_MAX_D + 1) * (c.S + 1) + 255) / 256);
     const int64_t ngr = (c.S - 3) / S3_NR + 1;
     int64_t bx = ((c.S - 2) * S3_NR + PRE_WG - 1) / PRE_WG;
@@ -3344,11 +3479,11 @@ static void s3_prologue(const Ctx &c, const SearchCall &sc, int L, hipStream_t s
     if (bx * PRE_WG * ngr < ninit) bx = (ninit / ngr + PRE_WG - 1) / PRE_WG + 1;
     // one more column: its first workgroup runs the pre-pass selection
     hipLaunchKernelGGL(rec3_kernel, dim3((unsigned)(bx + 1), (unsigned)ngr), dim3(PRE_WG), 0, st, c, c.rec3);
-    launch_prepass<3>(c, sc, L, st, false);
+    launch_prepass<3>(c, sc, st, false);
 }
 
 int launch_batch_prologue(const Ctx &c, const SearchCall &sc, hipStream_t st) {
-    s3_prologue(c, sc, (c.KP + PRE_Q - 1) / PRE_Q, st);
+    s3_prologue(c, sc, st);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -3361,7 +3496,7 @@ int launch_batch_search3(const BatchSearchArgs &b, int wgs, hipStream_t st) {
 }
 
 int launch_batch_epilogue(const Ctx &c, const SearchCall &sc, hipStream_t st) {
-    launch_merge(c, c.nwaves, (c.KP + PRE_Q - 1) / PRE_Q, 1, st, 0, c.flags + FLAG_NLISTS);
+    launch_merge(c, c.nwaves, 1, st, 0, c.flags + FLAG_NLISTS);
     launch_rescore_final(c, 3, sc.k, st);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -3379,7 +3514,6 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
     // many tasks: JB * TP <= MT_RECS records of the item in LDS (JB <= 64)
     a.JB = MT ? (64 < MT_RECS / c.TP ? 64 : MT_RECS / c.TP) : JBLK;
     a.R = MT ? 1 : SUBP;
-    a.L = (c.KP + PRE_Q - 1) / PRE_Q;
     const int q = D - 2;
     const int RECW = q + 4;
     const int QA = q > 0 ? q : 1;
@@ -3397,7 +3531,7 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
         hipLaunchKernelGGL(search_d1_kernel, dim3(wgs), dim3(SEARCH_WG), lds_lists, st, c, a);
         phase_end(c, SISSO_PHASE_SEARCH, st);
         phase_begin(c, SISSO_PHASE_MERGE, st);
-        launch_merge(c, wgs * SEARCH_WAVES, a.L, 0, st);
+        launch_merge(c, wgs * SEARCH_WAVES, 0, st);
         phase_end(c, SISSO_PHASE_MERGE, st);
     } else {
         phase_begin(c, SISSO_PHASE_PREPASS, st);
@@ -3425,9 +3559,9 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
             hipLaunchKernelGGL(search_init_kernel, dim3(init_blocks), dim3(256), 0, st, c, D, a.R, a.JB, 0);
         }
         switch (D) {
-            case 2: launch_prepass<2>(c, sc, a.L, st); break;
-            case 3: launch_prepass<3>(c, sc, a.L, st, !s3); break;
-            default: launch_prepass<4>(c, sc, a.L, st); break;
+            case 2: launch_prepass<2>(c, sc, st); break;
+            case 3: launch_prepass<3>(c, sc, st, !s3); break;
+            default: launch_prepass<4>(c, sc, st); break;
         }
         if (s4) {
             // the pair-group record table (part of the set-up, like rec3 above)
@@ -3460,7 +3594,7 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
         }
         phase_end(c, SISSO_PHASE_SEARCH, st);
         phase_begin(c, SISSO_PHASE_MERGE, st);
-        launch_merge(c, c.search_wgs * SEARCH_WAVES, a.L, 1, st);
+        launch_merge(c, c.search_wgs * SEARCH_WAVES, 1, st);
         phase_end(c, SISSO_PHASE_MERGE, st);
     }
     launch_rescore_final(c, D, sc.k, st);
@@ -3585,7 +3719,7 @@ int launch_list_search(const Ctx &c, int D, int k, const int32_t *pre, int64_t n
     }
     phase_end(c, SISSO_PHASE_SEARCH, st);
     phase_begin(c, SISSO_PHASE_MERGE, st);
-    launch_merge(c, (int)wgs * SEARCH_WAVES, 1, 0, st, 1);
+    launch_merge(c, (int)wgs * SEARCH_WAVES, 0, st, 1);
     phase_end(c, SISSO_PHASE_MERGE, st);
     launch_rescore_final(c, D, k, st);
     return hipGetLastError() == hipSuccess ? 0 : -1;
