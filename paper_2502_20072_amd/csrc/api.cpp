@@ -125,7 +125,34 @@ static Layout compute_layout(int64_t n_total, int64_t S, int T, int D_max, int k
     L.bhat = take((size_t)S * L.TP * d);
     const size_t Sp = (size_t)((S + GT - 1) / GT) * GT;
     L.G = take(Sp * Sp * L.TP * d);
-    L.part = take((size_t)L.nsplit * T * S * S * d);
+    // FP64 Gram: residues of at most GM_RES_MAX bytes at a time (at least one
+    // K-step), and a residue plane per modulus over the upper tile pairs.
+    // Tile edge: 256-wide tiles run one to a CU at 2.0e15 products/s over whole
+    // rounds of the 256 CUs, 128-wide ones three to a CU at 1.45e15 (measured
+    // at S = 4096, n = 50,000 and S = 1000, n = 8192); the smaller time wins.
+    {
+        auto pairs = [&](int64_t tile) {
+            const int64_t q = (S + tile - 1) / tile;
+            return (double)(q * (q + 1) / 2) * GM_NP * T;
+        };
+        const double wide = ceil(pairs(256) / 256) * 4;
+        const double narrow = std::max(1.0, pairs(128) / 256) * 1.37;
+        L.gm_tile = wide < narrow ? 256 : 128;
+    }
+    L.gm_bk = L.gm_tile == 256 ? GM_BK : GM_BK_S;
+    const int64_t kpad = (n_total + GM_BK - 1) / GM_BK * GM_BK + (int64_t)(T - 1) * GM_BK;
+    int64_t kc = (int64_t)(GM_RES_MAX / ((unsigned long long)GM_NP * S)) / GM_BK * GM_BK;
+    kc = std::min<int64_t>(std::max<int64_t>(kc, GM_BK), GM_KC_MAX);
+    L.gm_kc = std::min(kc, kpad);
+    if (L.lp_ns) {
+        L.part = take((size_t)L.nsplit * T * S * S * d);
+    } else {
+        const size_t nt = (size_t)((S + L.gm_tile - 1) / L.gm_tile);
+        const size_t planes = nt * (nt + 1) / 2 * T * GM_NP * L.gm_tile * L.gm_tile;
+        L.part = take(std::max((size_t)S * S * d, planes));
+    }
+    L.gm_kb = take((size_t)(T + 1) * sizeof(int64_t));
+    L.gm_res = take(L.lp_ns ? 0 : (size_t)GM_NP * S * L.gm_kc);
     L.flags = take(64 * sizeof(uint32_t));
     L.lp_cbase = take((size_t)(T + 1) * sizeof(int32_t));
     L.lp_exp = take((size_t)S * L.lp_nchunk * sizeof(int32_t));
@@ -222,6 +249,10 @@ static void carve(sisso_l0 *h) {
     c.G = (double *)(base + L.G);
     c.part = (double *)(base + L.part);
     c.flags = (uint32_t *)(base + L.flags);
+    c.gm_kb = (int64_t *)(base + L.gm_kb);
+    c.gm_res = (uint8_t *)(base + L.gm_res);
+    c.gm_tile = L.gm_tile;
+    c.gm_kc = L.gm_kc;
     c.lp_cbase = (int32_t *)(base + L.lp_cbase);
     c.lp_exp = (int32_t *)(base + L.lp_exp);
     c.lp_slices = (__bf16 *)(base + L.lp_slices);
@@ -309,6 +340,11 @@ extern "C" int32_t sisso_l0_create(const sisso_l0_desc *d, sisso_l0 **out) {
     std::vector<int32_t> cbase(d->T + 1, 0);
     for (int t = 0; t < d->T; ++t) cbase[t + 1] = cbase[t] + (int32_t)((o[t + 1] - o[t] + LP_XC - 1) / LP_XC);
     h->ctx.lp_nchunk = h->lay.lp_ns ? cbase[d->T] : 0;
+    // FP64 Gram: every task starts at a multiple of GM_BK padded samples
+    std::vector<int64_t> kb(d->T + 1, 0);
+    for (int t = 0; t < d->T; ++t)
+        kb[t + 1] = kb[t] + (o[t + 1] - o[t] + h->lay.gm_bk - 1) / h->lay.gm_bk * h->lay.gm_bk;
+    h->ctx.gm_kpad = kb[d->T];
     // the Gram's workgroups of the largest tasks go first (a task's
     // workgroups take time in proportion to its rows)
     std::vector<int32_t> order(d->T);
@@ -321,6 +357,8 @@ extern "C" int32_t sisso_l0_create(const sisso_l0_desc *d, sisso_l0 **out) {
                        h->stream) != hipSuccess ||
         hipMemcpyAsync(h->ctx.torder, order.data(), d->T * sizeof(int32_t), hipMemcpyHostToDevice,
                        h->stream) != hipSuccess ||
+        hipMemcpyAsync(h->ctx.gm_kb, kb.data(), (d->T + 1) * sizeof(int64_t), hipMemcpyHostToDevice, h->stream) !=
+            hipSuccess ||
         hipMemcpyAsync(h->ctx.lp_cbase, cbase.data(), (d->T + 1) * sizeof(int32_t), hipMemcpyHostToDevice,
                        h->stream) != hipSuccess ||
         hipStreamSynchronize(h->stream) != hipSuccess) {

@@ -12,11 +12,7 @@ namespace sl0 {
 constexpr int WAVE = 64;               // CDNA wavefront width
 constexpr double RANK_EPS = 1e-10;     // pivot ratio at or below which a tuple is rank-deficient
 constexpr double RANK_EPS_F32 = 1e-5;  // the same for the FP32 solve form (a few hundred units of 2^-23)
-constexpr int GRAM_TILE = 128;         // Gram output tile (rows = cols)
-#ifndef GRAM_KC_SAMPLES
-#define GRAM_KC_SAMPLES 16
-#endif
-constexpr int GRAM_KC = GRAM_KC_SAMPLES;  // samples per LDS stage of the Gram (divides 256)
+constexpr int GRAM_TILE = 128;         // precision forms: Gram output tile (rows = cols)
 constexpr int SEARCH_WG = 256;         // threads per search workgroup (4 waves)
 constexpr int SEARCH_WAVES = SEARCH_WG / WAVE;
 constexpr int SEARCH_WGS_MAX = 2048;   // largest persistent search grid (lists are sized for it)
@@ -29,6 +25,11 @@ constexpr int PRE_R = SISSO_MAX_D - 1; // most pre-pass rounds
 constexpr int PRE_BINS = 2048;         // histogram bins of the pre-pass pool (64 per factor of two of SSE)
 constexpr int KP_MAX = 512;            // longest per-wave candidate list
 constexpr int LP_XC = 256;             // precision form: samples per slice-exponent chunk
+constexpr int GM_NP = 15;              // FP64 Gram: moduli of the residue products
+constexpr int GM_BK = 128;             // FP64 Gram: a task's samples are padded to whole K-steps of 128 (256-wide
+constexpr int GM_BK_S = 64;            // tiles) or 64 (128-wide tiles)
+constexpr int GM_KC_MAX = 65536;       // FP64 Gram: most samples per chunk (32-bit sums of byte products: 2^30)
+constexpr unsigned long long GM_RES_MAX = 4ull << 30;  // FP64 Gram: most bytes of residues held at a time
 constexpr int PROP_NF = 8;             // learned proposal: features per prefix
 
 // ---------------------------------------------------------------- binomials
@@ -170,6 +171,40 @@ __host__ __device__ inline int64_t gidx(int64_t i, int64_t k, int64_t nt, int TP
     return ((((i >> 6) * nt + (k >> 6)) << 12) + ((i & 63) << 6) + (k & 63)) * TP + t;
 }
 
+// Upper tile pairs (i <= j) of an n x n tile grid in groups of 8 tile rows,
+// column by column: 64 consecutive pairs touch 8 rows and 8 columns, and the
+// mirror tiles (j, i) of consecutive pairs lie next to each other (at
+// S = 50,000 the Gram's finishing pass took 28.7 ms in row-by-row order,
+// 13 ms in this one).
+__host__ __device__ inline void gm_tile_pair(int64_t pr, int n, int &ti, int &tk) {
+    for (int r0 = 0;; r0 += 8) {
+        const int g = n - r0 < 8 ? n - r0 : 8;
+        const int64_t tri = g * (g + 1) / 2, cnt = tri + (int64_t)g * (n - r0 - g);
+        if (pr >= cnt) {
+            pr -= cnt;
+            continue;
+        }
+        if (pr < tri) {
+            int k = 0;
+            while ((k + 1) * (k + 2) / 2 <= pr) ++k;
+            tk = r0 + k;
+            ti = r0 + (int)(pr - k * (k + 1) / 2);
+        } else {
+            const int64_t q = pr - tri;
+            tk = r0 + g + (int)(q / g);
+            ti = r0 + (int)(q % g);
+        }
+        return;
+    }
+}
+// position of pair (ti, tk) in that order
+__host__ __device__ inline int64_t gm_pair_index(int ti, int tk, int n) {
+    const int64_t r0 = ti & ~7;
+    const int64_t g = n - r0 < 8 ? n - r0 : 8, k = tk - r0;
+    const int64_t before = r0 * n - r0 * (r0 - 1) / 2;  // pairs of the rows above
+    return before + (k < g ? k * (k + 1) / 2 : g * (g + 1) / 2 + (k - g) * g) + (ti - r0);
+}
+
 // Colexicographic unranking for the small sub-prefix lengths of the search
 // (q <= 2 in closed form, larger q by bisection), no table lookups.
 __host__ __device__ inline void colex_unrank_small(uint64_t r, int q, int64_t N, int32_t *t) {
@@ -244,7 +279,14 @@ struct Layout {
     size_t inv_s;      // double [T][S] 1/|x - mean| (0 for a constant column)
     size_t bhat;       // double [S][TP] normalised F_t^T y_t
     size_t G;          // double [S][S][TP] correlation matrices, task fastest
-    size_t part;       // double [nsplit][T][S][S] raw centred Gram partial sums
+    size_t part;       // precision forms: double [nsplit][T][S][S] raw centred Gram partial sums;
+                       // FP64: residue planes, bytes [T][tile pairs][GM_NP][gm_tile^2]; scratch of
+                       // sisso_gram_read (at least S^2 doubles)
+    size_t gm_kb;      // FP64 Gram: int64 [T+1] first padded sample of each task
+    size_t gm_res;     // FP64 Gram: residues, bytes [GM_NP][S][gm_kc]
+    int gm_tile;       // FP64 Gram: tile edge of the products (128 or 256)
+    int64_t gm_kc;     // FP64 Gram: padded samples per chunk
+    int gm_bk;         // FP64 Gram: samples per K-step
     size_t flags;      // uint32 [64] device status words
     size_t lp_cbase;   // int32 [T+1] precision form: first chunk of each task
     size_t lp_exp;     // int32 [S][nchunk] precision form: chunk exponents

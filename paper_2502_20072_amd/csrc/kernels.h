@@ -18,6 +18,10 @@ struct Ctx {
     int32_t *torder;                 // tasks by decreasing row count (the Gram's launch order)
     double *ybar, *cyy, *mu, *inv_s, *bhat, *G, *part;
     uint32_t *flags;
+    int64_t *gm_kb;                  // FP64 Gram: first padded sample of each task [T+1]
+    uint8_t *gm_res;                 // FP64 Gram: residues [GM_NP][S][gm_kc]
+    int64_t gm_kpad, gm_kc;          // FP64 Gram: padded samples in all, per chunk
+    int gm_tile;                     // FP64 Gram: tile edge of the products
     int32_t *lp_cbase;               // precision form: first chunk of each task [T+1]
     int32_t *lp_exp;                 // precision form: chunk exponents [S][lp_nchunk]
     __bf16 *lp_slices;               // precision form: slices [NS][S][lp_nchunk * LP_XC]
@@ -78,7 +82,8 @@ uint64_t s3_tiles_host(int64_t S);  // tiles of the D = 3 record-table sweep
 int s3_rows_per_tile();             // rows j per tile of that sweep (its steps per tile, at most)
 uint64_t s4_tiles_host(int64_t S);  // tiles of the D = 4 record-table sweep
 int launch_stats(const Ctx &c, hipStream_t st);
-int launch_gram(const Ctx &c, hipStream_t st);  // FP64 MFMA or precision form, then finish
+int launch_gram(const Ctx &c, hipStream_t st);  // correlation matrices: FP64 or precision form
+int launch_gram_mod(const Ctx &c, hipStream_t st);
 int launch_gram_lp(const Ctx &c, int NS, hipStream_t st);
 int launch_gram_check(const Ctx &c, int nsample, unsigned long long *out_bits, hipStream_t st);
 int launch_untile(const Ctx &c, int t, double *dst, hipStream_t st);
