@@ -117,6 +117,7 @@ static Layout compute_layout(int64_t n_total, int64_t S, int T, int D_max, int k
     L.self = take(sizeof(Ctx));
     L.btab = take(S3B_TABLE_BYTES);
     L.off_dev = take((T + 1) * sizeof(int64_t));
+    L.gm_kb = take((T + 1) * sizeof(int64_t));
     L.torder = take(T * sizeof(int32_t));
     L.ybar = take(T * d);
     L.cyy = take(T * d);
@@ -124,9 +125,49 @@ static Layout compute_layout(int64_t n_total, int64_t S, int T, int D_max, int k
     L.inv_s = take((size_t)T * S * d);
     L.bhat = take((size_t)S * L.TP * d);
     const size_t Sp = (size_t)((S + GT - 1) / GT) * GT;
+    L.flags = take(64 * sizeof(uint32_t));
+    L.lp_cbase = take((size_t)(T + 1) * sizeof(int32_t));
+    L.lp_exp = take((size_t)S * L.lp_nchunk * sizeof(int32_t));
+    L.lp_slices = take((size_t)L.lp_ns * S * L.lp_nchunk * LP_XC * 2);
+    L.stat_bits = take(4 * sizeof(uint64_t));
+    // counters (theta, work counter, candidate counter), cum table, pre-pass
+    // state, binomial table, filter tasks
+    L.pre = take(64 + (size_t)(S / 4 + 8) * sizeof(uint64_t) + sizeof(PreState) +
+                 (size_t)(SISSO_MAX_D + 1) * (S + 1) * sizeof(uint64_t) + 2 * sizeof(int32_t));
+    // Zone of the matrices and the search's tables, pools and lists, none of
+    // which holds anything while the Gram's products run: the FP64 Gram's
+    // residues lie over it (below)
+    const size_t zone = o;
     L.G = take(Sp * Sp * L.TP * d);
-    // FP64 Gram: residues of at most GM_RES_MAX bytes at a time (at least one
-    // K-step), and a residue plane per modulus over the upper tile pairs.
+    // one row of four (i1, j) records per j > i1 group: sum over groups of (S - 2 - 4 g)
+    {
+        const int64_t ng3 = S >= 3 ? (S - 3) / 4 + 1 : 0;
+        const int64_t rows3 = ng3 * (S - 2) - 4 * (ng3 * (ng3 - 1) / 2);
+        L.rec3_bytes = (D_max >= 3 && S >= 3 && !fp32) ? (size_t)rows3 * 16 * d : 0;
+    }
+    L.rec3 = take(L.rec3_bytes);
+    L.recg = take(L.rec3_bytes ? (size_t)s3_group_rows(S) * 16 * d : 0);
+    L.gfac = take(L.rec3_bytes ? (size_t)(S / 8 + 1) * 2 * 16 * d : 0);
+    // D = 4, one task: a record row per (pair group, j); kept only while the
+    // table stays within S4_TABLE_MAX (else the general kernel runs)
+    {
+        const int64_t rows4 = S >= 4 ? s4_rows_below(S, S - 2) : 0;
+        const size_t b4 = (size_t)rows4 * S4_ROW * d;
+        L.rec4_bytes = (D_max >= 4 && T == 1 && S >= 4 && !fp32 && b4 <= S4_TABLE_MAX && s4_tiles_host(S) < (1ull << 31)) ? b4 : 0;
+    }
+    L.rec4 = take(L.rec4_bytes);
+    L.r4off = take(L.rec4_bytes ? (size_t)(S + 1) * sizeof(int64_t) : 0);
+    L.G1_bytes = (D_max >= 3 && S >= 3 && T > 1) ? Sp * Sp * d : 0;
+    L.G1 = take(L.G1_bytes);
+    // D = 3: per tile and group up to s3_lanes candidates or 8 row items
+    const size_t pt3 = L.rec3_bytes ? s3_pool_tiles(S) : 0;
+    L.s3_cands = take(pt3 * 2 * s3_lanes(T) * sizeof(uint64_t));
+    L.s3_rows = take(pt3 * 2 * 8 * sizeof(uint64_t));
+    L.s3_count = take(L.rec3_bytes ? (size_t)SEARCH_WGS_MAX * 2 * sizeof(uint32_t) : 0);
+    L.lists = take((size_t)nlists * L.KP * 2 * d + (size_t)nlists * L.KP * 2 * d);
+    // FP64 Gram: the residues take the zone above, GM_KC_MIN samples at a time
+    // or as many as fit (more chunks cost a read and a write of the residue
+    // planes each); and a residue plane per modulus over the upper tile pairs.
     // Tile edge: 256-wide tiles run one to a CU at 2.0e15 products/s over whole
     // rounds of the 256 CUs, 128-wide ones three to a CU at 1.45e15 (measured
     // at S = 4096, n = 50,000 and S = 1000, n = 8192); the smaller time wins.
@@ -140,61 +181,18 @@ static Layout compute_layout(int64_t n_total, int64_t S, int T, int D_max, int k
         L.gm_tile = wide < narrow ? 256 : 128;
     }
     L.gm_bk = L.gm_tile == 256 ? GM_BK : GM_BK_S;
-    const int64_t kpad = (n_total + GM_BK - 1) / GM_BK * GM_BK + (int64_t)(T - 1) * GM_BK;
-    int64_t kc = (int64_t)(GM_RES_MAX / ((unsigned long long)GM_NP * S)) / GM_BK * GM_BK;
-    kc = std::min<int64_t>(std::max<int64_t>(kc, GM_BK), GM_KC_MAX);
-    L.gm_kc = std::min(kc, kpad);
     if (L.lp_ns) {
         L.part = take((size_t)L.nsplit * T * S * S * d);
     } else {
+        const int64_t kpad = (n_total + GM_BK - 1) / GM_BK * GM_BK + (int64_t)(T - 1) * GM_BK;
+        const size_t least = (size_t)GM_NP * S * std::min(kpad, S < 1024 ? GM_KC_MIN : GM_KC_WIDE);
+        if (o - zone < least) o = align256(zone + least);
+        L.gm_res = zone;
+        L.gm_kc = std::min({(int64_t)((o - zone) / ((size_t)GM_NP * S)) / GM_BK * GM_BK, kpad, GM_KC_MAX});
         const size_t nt = (size_t)((S + L.gm_tile - 1) / L.gm_tile);
         const size_t planes = nt * (nt + 1) / 2 * T * GM_NP * L.gm_tile * L.gm_tile;
         L.part = take(std::max((size_t)S * S * d, planes));
     }
-    L.gm_kb = take((size_t)(T + 1) * sizeof(int64_t));
-    L.gm_res = take(L.lp_ns ? 0 : (size_t)GM_NP * S * L.gm_kc);
-    L.flags = take(64 * sizeof(uint32_t));
-    L.lp_cbase = take((size_t)(T + 1) * sizeof(int32_t));
-    L.lp_exp = take((size_t)S * L.lp_nchunk * sizeof(int32_t));
-    L.lp_slices = take((size_t)L.lp_ns * S * L.lp_nchunk * LP_XC * 2);
-    L.stat_bits = take(4 * sizeof(uint64_t));
-    // counters (theta, work counter, candidate counter), cum table, pre-pass
-    // state, binomial table, filter tasks
-    L.pre = take(64 + (size_t)(S / 4 + 8) * sizeof(uint64_t) + sizeof(PreState) +
-                 (size_t)(SISSO_MAX_D + 1) * (S + 1) * sizeof(uint64_t) + 2 * sizeof(int32_t));
-    // one row of four (i1, j) records per j > i1 group: sum over groups of (S - 2 - 4 g)
-    {
-        const int64_t ng3 = S >= 3 ? (S - 3) / 4 + 1 : 0;
-        const int64_t rows3 = ng3 * (S - 2) - 4 * (ng3 * (ng3 - 1) / 2);
-        L.rec3_bytes = (D_max >= 3 && S >= 3 && !fp32) ? (size_t)rows3 * 16 * d : 0;
-    }
-    L.rec3 = take(L.rec3_bytes);
-    // D = 4, one task: a record row per (pair group, j); kept only while the
-    // table stays within S4_TABLE_MAX (else the general kernel runs)
-    {
-        const int64_t rows4 = S >= 4 ? s4_rows_below(S, S - 2) : 0;
-        const size_t b4 = (size_t)rows4 * S4_ROW * d;
-        L.rec4_bytes = (D_max >= 4 && T == 1 && S >= 4 && !fp32 && b4 <= S4_TABLE_MAX && s4_tiles_host(S) < (1ull << 31)) ? b4 : 0;
-    }
-    L.rec4 = take(L.rec4_bytes);
-    L.r4off = take(L.rec4_bytes ? (size_t)(S + 1) * sizeof(int64_t) : 0);
-    L.G1_bytes = (D_max >= 3 && S >= 3 && T > 1) ? Sp * Sp * d : 0;
-    L.G1 = take(L.G1_bytes);
-    // several tasks, D = 3: a pool with a record for every step of the sweep
-    // plus one partly filled chunk per wave, so that it cannot run out (the
-    // pool grows as S^3: 2 GB at S = 5000); above MTQ_POOL_MAX bytes of
-    // records the several-task search keeps its general kernel
-    L.mtq_chunks = 0;
-    if (L.G1_bytes) {
-        const uint64_t steps = s3_tiles_host(S) * (uint64_t)s3_rows_per_tile();
-        const uint64_t chunks = (steps + MTQ_CHUNK - 1) / MTQ_CHUNK + (uint64_t)nlists;
-        if (chunks * MTQ_CHUNK * 3 * sizeof(uint64_t) <= MTQ_POOL_MAX) L.mtq_chunks = (int)chunks;
-    }
-    const size_t nch = (size_t)L.mtq_chunks;
-    L.mtq = take(nch * MTQ_CHUNK * 3 * sizeof(uint64_t));
-    L.mtq_n = take(nch * sizeof(uint32_t));
-    L.mtq_pre = take(nch ? (nch + 1) * sizeof(uint64_t) : 0);
-    L.lists = take((size_t)nlists * L.KP * 2 * d + (size_t)nlists * L.KP * 2 * d);
     L.merged = take((size_t)L.KP * 2 * d);
     L.rescored = take((size_t)L.KP * d);
     L.coef = take((size_t)L.KP * T * (D_max + 1) * d);
@@ -263,7 +261,6 @@ static void carve(sisso_l0 *h) {
     c.theta_bits = (unsigned long long *)p;
     c.work_counter = (unsigned int *)(p + 8);
     c.cand_counter = (unsigned int *)(p + 12);
-    c.mtq_taken = (unsigned int *)(p + 60);
     c.stats = (uint64_t *)(p + 24);
     c.merge_count = (unsigned int *)(p + 56);
     p += 64;
@@ -275,13 +272,14 @@ static void carve(sisso_l0 *h) {
     p += (size_t)(SISSO_MAX_D + 1) * (c.S + 1) * sizeof(uint64_t);
     c.tstar = (int32_t *)p;
     c.rec3 = L.rec3_bytes ? (double *)(base + L.rec3) : nullptr;
+    c.recg = L.rec3_bytes ? (double *)(base + L.recg) : nullptr;
+    c.gfac = L.rec3_bytes ? (double *)(base + L.gfac) : nullptr;
     c.G1 = L.G1_bytes ? (double *)(base + L.G1) : c.G;
     c.rec4 = L.rec4_bytes ? (double *)(base + L.rec4) : nullptr;
     c.r4off = L.rec4_bytes ? (int64_t *)(base + L.r4off) : nullptr;
-    c.mtq_chunks = L.mtq_chunks;
-    c.mtq = L.mtq_chunks ? (uint64_t *)(base + L.mtq) : nullptr;
-    c.mtq_n = L.mtq_chunks ? (uint32_t *)(base + L.mtq_n) : nullptr;
-    c.mtq_pre = L.mtq_chunks ? (uint64_t *)(base + L.mtq_pre) : nullptr;
+    c.s3_cands = L.rec3_bytes ? (uint64_t *)(base + L.s3_cands) : nullptr;
+    c.s3_rows = L.rec3_bytes ? (uint64_t *)(base + L.s3_rows) : nullptr;
+    c.s3_count = L.rec3_bytes ? (uint32_t *)(base + L.s3_count) : nullptr;
     const int64_t nl = L.nwaves;
     char *q = base + L.lists;
     c.list_sse = (double *)q;
@@ -643,7 +641,6 @@ extern "C" int32_t sisso_l0_topk(sisso_l0 *h, int32_t k, int32_t *idx, double *s
     uint32_t flags[4];
     memcpy(flags, h->stage, sizeof(flags));
     if (flags[FLAG_NONFINITE]) return fail(h, SISSO_EINVAL, "F or y holds a non-finite value");
-    if (flags[FLAG_CAPACITY]) return fail(h, SISSO_EDEVICE, "internal step queue overflow (results incomplete)");
     memcpy(sse, h->stage + (L.res_sse - L.res), (size_t)k * sizeof(double));
     memcpy(idx, h->stage + (L.res_idx - L.res), (size_t)k * D * sizeof(int32_t));
     if (coef) memcpy(coef, h->stage + (L.res_coef - L.res), (size_t)k * T * (D + 1) * sizeof(double));

@@ -28,8 +28,10 @@ constexpr int LP_XC = 256;             // precision form: samples per slice-expo
 constexpr int GM_NP = 15;              // FP64 Gram: moduli of the residue products
 constexpr int GM_BK = 128;             // FP64 Gram: a task's samples are padded to whole K-steps of 128 (256-wide
 constexpr int GM_BK_S = 64;            // tiles) or 64 (128-wide tiles)
-constexpr int GM_KC_MAX = 65536;       // FP64 Gram: most samples per chunk (32-bit sums of byte products: 2^30)
-constexpr unsigned long long GM_RES_MAX = 4ull << 30;  // FP64 Gram: most bytes of residues held at a time
+constexpr int64_t GM_KC_MAX = 65536;   // FP64 Gram: most samples per chunk (32-bit sums of byte products: 2^30)
+constexpr int64_t GM_KC_MIN = 4096;    // FP64 Gram: samples per chunk that the workspace holds at least, and from
+constexpr int64_t GM_KC_WIDE = 16384;  // 1024 features on (a chunk's pass over the residue planes costs as much as 425
+                                       // samples' products)
 constexpr int PROP_NF = 8;             // learned proposal: features per prefix
 
 // ---------------------------------------------------------------- binomials
@@ -165,8 +167,6 @@ __host__ __device__ inline void unpack_tuple(uint64_t k, int D, int32_t *t) {
 // nt = ceil(S / 64).  A search step reads one row of one tile, so a chunk of
 // 64 steps stays inside 32 KB of contiguous memory.
 constexpr int GT = 64;
-constexpr int MTQ_CHUNK = 256;  // queued sweep steps per pool chunk (several tasks, D = 3)
-constexpr unsigned long long MTQ_POOL_MAX = 8ull << 30;  // largest pool of queued steps (bytes)
 __host__ __device__ inline int64_t gidx(int64_t i, int64_t k, int64_t nt, int TP, int t) {
     return ((((i >> 6) * nt + (k >> 6)) << 12) + ((i & 63) << 6) + (k & 63)) * TP + t;
 }
@@ -283,7 +283,7 @@ struct Layout {
                        // FP64: residue planes, bytes [T][tile pairs][GM_NP][gm_tile^2]; scratch of
                        // sisso_gram_read (at least S^2 doubles)
     size_t gm_kb;      // FP64 Gram: int64 [T+1] first padded sample of each task
-    size_t gm_res;     // FP64 Gram: residues, bytes [GM_NP][S][gm_kc]
+    size_t gm_res;     // FP64 Gram: residues, bytes [GM_NP][S][gm_kc], over G and the regions of the search
     int gm_tile;       // FP64 Gram: tile edge of the products (128 or 256)
     int64_t gm_kc;     // FP64 Gram: padded samples per chunk
     int gm_bk;         // FP64 Gram: samples per K-step
@@ -295,6 +295,8 @@ struct Layout {
     size_t pre;        // pre-pass scratch
     size_t rec3;       // D = 3: pair records of the filter task, double [ceil(S/4)][S][4][4] (0 bytes otherwise)
     size_t rec3_bytes;
+    size_t recg;       //   group records, double [rows][2][8], and group factors, double [groups][16]
+    size_t gfac;
     size_t G1;         // D = 3, several tasks: the filter task's matrix alone, double [S][S] tiled (0 bytes otherwise)
     size_t G1_bytes;
     size_t rec4;       // D = 4, one task: pair-group records, double [rows][S4_ROW] (0 bytes otherwise)
@@ -302,10 +304,9 @@ struct Layout {
     size_t self;       // a device copy of the handle's Ctx (read by the batched search)
     size_t btab;       // batched search: item prefix and context table, when this handle leads a batch
     size_t r4off;      //   int64 [S + 1] record rows of the groups below each i2
-    size_t mtq;        // D = 3, several tasks: flagged sweep steps, uint64 [mtq_chunks][MTQ_CHUNK][3]
-    size_t mtq_n;      //   uint32 [mtq_chunks] keys per chunk
-    size_t mtq_pre;    //   uint64 [mtq_chunks + 1] exclusive prefix of the counts
-    int mtq_chunks;    //   chunks in the pool (0: no queue)
+    size_t s3_cands;   // D = 3: pools of flagged candidates and rows, and their counts per workgroup
+    size_t s3_rows;
+    size_t s3_count;
     size_t lists;      // per-wave top lists: (double sse, uint64 rank) [nwaves][KP]
     size_t merged;     // merged candidates [KP] (sse, rank)
     size_t rescored;   // rescored candidates [KP] (sse, rank)
@@ -337,7 +338,6 @@ inline int next_pow2(int x) {
 // device status flag indices
 enum {
     FLAG_NONFINITE = 0,
-    FLAG_CAPACITY = 1,
     FLAG_CAND = 2,
     FLAG_THETA = 4,   /* uint64 at 4..5 */
     FLAG_BATCHQ = 8,  /* batched search: next queue item (read on the batch's first problem) */

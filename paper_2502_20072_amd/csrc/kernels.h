@@ -35,14 +35,14 @@ struct Ctx {
     uint64_t *btab;                  // binomials C(n, r), r <= SISSO_MAX_D, n <= S
     PreState *pre;                   // threshold pre-pass: prefixes, pool histogram, bound
     double *rec3;                    // D = 3: pair records of the filter task [ceil(S/4)][S][4][4] (null if absent)
+    double *recg;                    // D = 3: group records of the filter task [rows of group pairs][2][8] (null if absent)
+    double *gfac;                    //   group factors [groups, padded to even][16]
     double *G1;                      // the filter task's matrix alone, one-task tiled layout (G itself when T = 1)
     double *rec4;                    // D = 4, one task: pair-group records [rows][S4_ROW] (null if absent)
     int64_t *r4off;                  //   record rows of the groups with i2 below each index [S + 1]
-    uint64_t *mtq;                   // several tasks, D = 3: flagged sweep steps [mtq_chunks][MTQ_CHUNK][3]
-    uint32_t *mtq_n;                 //   keys per chunk
-    uint64_t *mtq_pre;               //   exclusive prefix of mtq_n over the chunks taken [+1]
-    unsigned int *mtq_taken;         //   chunks taken from the pool (may run past mtq_chunks)
-    int mtq_chunks;                  //   chunks in the pool (0: none)
+    uint64_t *s3_cands;              // D = 3: flagged (group, row, column) candidates, a segment per workgroup
+    uint64_t *s3_rows;               //   and flagged rows of dense (group, row block, column chunk)s
+    uint32_t *s3_count;              //   of each segment: candidates, row items [SEARCH_WGS_MAX][2]
     int32_t *tstar;                  // filter tasks [2]: the tasks of largest and second largest
                                      // |y_t - ybar_t|^2 (0 and -1 when T = 1)
     double *list_sse;                // per-wave lists [nwaves][KP]
@@ -79,7 +79,9 @@ struct SearchCall {
 };
 
 uint64_t s3_tiles_host(int64_t S);  // tiles of the D = 3 record-table sweep
-int s3_rows_per_tile();             // rows j per tile of that sweep (its steps per tile, at most)
+size_t s3_pool_tiles(int64_t S);    // tiles its item pools have to hold
+int s3_lanes(int T);                // candidates per (tile, group) in them
+int64_t s3_group_rows(int64_t S);   // rows of its group-record table
 uint64_t s4_tiles_host(int64_t S);  // tiles of the D = 4 record-table sweep
 int launch_stats(const Ctx &c, hipStream_t st);
 int launch_gram(const Ctx &c, hipStream_t st);  // correlation matrices: FP64 or precision form
@@ -98,7 +100,7 @@ int launch_list_search(const Ctx &c, int D, int k, const int32_t *pre, int64_t n
 // batched one-task D = 3 search: per-problem prologue, one search launch for
 // all problems, per-problem epilogue (merge, re-score, final ordering)
 constexpr int S3B_MAXP = 128;  // problems per batched search launch
-constexpr int S3B_RUN = 16;    // consecutive tiles per queue item
+constexpr int S3B_RUN = 8;    // consecutive tiles per queue item
 struct BatchSearchArgs {
     int P;                          // problems, ordered by decreasing tile count
     int KPmax;                      // longest list among them

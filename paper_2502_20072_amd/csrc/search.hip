@@ -250,6 +250,68 @@ __device__ void list_insert(double *Ls, uint64_t *Lr, int KP, double s, uint64_t
     __builtin_amdgcn_wave_barrier();
 }
 
+// Inserts the entries of the lanes in take (distinct keys, none in the list)
+// into the wave's list; offered counts them.  One by one an insertion costs
+// a pass over the list; from LIST_BULK on all are merged in one: an entry's
+// new place is its rank among the new ones plus the number of old ones before
+// it, and an old one moves up by the number of new ones before it (64 entries
+// into 128: about 3 us against 45).
+constexpr int LIST_BULK = 4;
+__device__ void list_insert_lanes(double *Ls, uint64_t *Lr, int KP, bool take, uint64_t key, double sse,
+                                  unsigned &offered) {
+    const int lane = threadIdx.x & 63;
+    unsigned long long m = __ballot(take);
+    const int n = __popcll(m);
+    if (!n) return;
+    offered += (unsigned)n;
+    if (n < LIST_BULK) {
+        while (m) {
+            const int src = __ffsll((long long)m) - 1;
+            m &= m - 1;
+            list_insert(Ls, Lr, KP, __shfl(sse, src), (uint64_t)__shfl((long long)key, src));
+        }
+        return;
+    }
+    // new entries of the lanes in m before (s, r)
+    auto before = [&](double s, uint64_t r) {
+        int c = 0;
+        for (unsigned long long q = m; q; q &= q - 1) {
+            const int src = __ffsll((long long)q) - 1;
+            const double bs = uni(__shfl(sse, src));
+            const uint64_t br = uni((uint64_t)__shfl((long long)key, src));
+            c += key_less(bs, br, s, r);
+        }
+        return c;
+    };
+    // old entries before this lane's (the list is sorted)
+    int at = 0;
+    for (int step = KP >> 1; step; step >>= 1)
+        if (key_less(Ls[at + step - 1], Lr[at + step - 1], sse, key)) at += step;
+    if (at == KP - 1 && key_less(Ls[at], Lr[at], sse, key)) ++at;
+    at += before(sse, key);
+    // old entries move up, the highest chunk first
+    for (int x = KP - 64; x >= 0; x -= 64) {
+        const int e = x + lane;
+        const double vs = Ls[e];
+        const uint64_t vr = Lr[e];
+        const int to = e + before(vs, vr);
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_wave_barrier();
+        if (to != e && to < KP) {
+            Ls[to] = vs;
+            Lr[to] = vr;
+        }
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (take && at < KP) {
+        Ls[at] = sse;
+        Lr[at] = key;
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Sorts a wave's LDS list of KP (power of two) entries by (SSE, key).
 __device__ void wave_sort_list(double *Ls, uint64_t *Lr, int KP) {
     const int lane = threadIdx.x & 63;
@@ -296,8 +358,6 @@ __device__ void search_init_body(const Ctx &c, int64_t e, bool leader, int D, in
         *c.cand_counter = 0;
         *c.theta_bits = (unsigned long long)__double_as_longlong(INF);
         *c.merge_count = 0;
-        *c.mtq_taken = 0;
-        c.flags[FLAG_CAPACITY] = 0;
         c.flags[FLAG_BATCHQ] = 0;
         c.flags[FLAG_NLISTS] = 0;
         c.stats[1] = 0;
@@ -904,15 +964,7 @@ __device__ inline double slow_path(const Ctx &c, const SearchArgs &a, double *Ls
                 if (lr < a.r0 || lr >= a.r1) take = false;
             }
         }
-        unsigned long long m = __ballot(take);
-        offered += (unsigned)__popcll(m);
-        while (m) {
-            const int src = __ffsll((long long)m) - 1;
-            m &= m - 1;
-            const double cs = __shfl(es, src);
-            const uint64_t cr = (uint64_t)__shfl((long long)rk, src);
-            list_insert(Ls, Lr, KP, cs, cr);
-        }
+        list_insert_lanes(Ls, Lr, KP, take, rk, es, offered);
     }
     const double tw = Ls[KP - 1];
     if (tw < theta_pub) {
@@ -1334,22 +1386,33 @@ __global__ __launch_bounds__(256) void search_kernel(Ctx c, SearchArgs a) {
     list_store(c.list_sse + gw * KP, c.list_rank + gw * KP, Ls, Lr, KP);
 }
 
-// ------------------------------------------- D = 3, one task: record table
-// With one task and D = 3 the Cholesky row of every pair (i1, j) is built
-// once per search into a table (rec3_kernel), and the sweep reads the rows
-// of four consecutive i1 for one j with scalar loads: lanes run over the
-// last index k, so a record is the same for every lane and enters the FP64
-// instructions as a scalar operand, at no LDS or vector-memory cost.  A
-// work tile is (group of four i1, S3_JR rows j from j0, S3_KC columns k from
-// j0 + 1 + S3_KC c); lane l takes k = kb + l and kb + 64 + l (one load of
-// G[j][k] each serves 4 tuples), so only chunk 0 holds tuples with k <= j
-// (in its first half), and a last chunk with at most 64 columns left runs
-// its first half only.  Tiles are dealt to single waves round-robin, so no
-// wave waits on another.  Per tuple the arithmetic is the same as search_kernel's
-// single-task path: u = g - v w', d = d' - alpha u^2, zeta = zeta' - zs u,
-// pass iff zeta^2 >= (p - theta) d.
+// ---------------------------------------------- D = 3: record-table sweep
+// Per search two tables of Cholesky rows are built (rec3_kernel): one row per
+// pair (i1, j), and one per (group of four consecutive i1, j) for the group
+// and j together.  A tuple's SSE is at least that of any superset, so the
+// sweep first tests, per (group, j, k), the fit on all six features {the
+// group, j, k}: 10 FP64 instructions for four tuples, against 28 for testing
+// the four one by one.  Only where that bound is at or below the threshold
+// are the group's tuples tested themselves.  (Bound on k: on operator-tree
+// columns 0.1 to 1 in 1000 of the six-feature fits pass.)
+//
+// Lanes run over the last index k, so a record is the same for every lane
+// and is read with scalar loads: it enters the FP64 instructions as a scalar
+// operand, at no LDS or vector-memory cost.  A work tile is (two groups of
+// four i1, S3_JR rows j from j0, S3_KC columns k from j0 + 1 + S3_KC c); lane
+// l takes k = kb + l and kb + 64 + l (one load of G[j][k] each serves 8
+// tuples), so only chunk 0 holds tuples with k <= j (in its first half), and
+// a last chunk with at most 64 columns left runs its first half only.  Tiles
+// are dealt to single waves round-robin, so no wave waits on another.
+// Per tuple, the arithmetic of the group's own test is that of
+// search_kernel's single-task path: u = g - v w', d = d' - alpha u^2, zeta =
+// zeta' - zs u, pass iff zeta^2 >= (p - theta) d; the group's bound is the
+// same with four v and w'.
 constexpr int S3_NR = 4;              // i1 per tile (a group)
+constexpr int S3_GP = 2;              // groups per tile
 constexpr int S3_KC = 128;            // k per tile: two per lane, 64 apart
+constexpr int S3_LANES = 64;          // flagged (row, column) pairs of a tile's group taken one per lane, one task
+constexpr int S3_LANES_MT = 256;      //   the same, several tasks; with more, the flagged rows are swept whole
 #ifndef S3_JR
 #define S3_JR 64                      // j rows per tile (divides 64)
 #endif
@@ -1377,8 +1440,110 @@ __host__ __device__ inline int64_t s3_rows(int64_t S) {
 // with v = G[i1][j], d_j = 1 - v^2, s_j = sqrt(d_j), z_j = (b_j - v b_i1) / s_j,
 // p = c - b_i1^2 - z_j^2 (the SSE of the pair); p = NaN (fails every
 // comparison) unless i1 < j, column i1 is live and d_j > RANK_EPS.
+// Group records: group g's own factor (correlations of its live columns, in
+// index order) projects any column x onto the group's span: w = R^-1 G[g, x].
+// Row (pair of groups h, j), j = 8 h + 1 .. S - 2, of 2 x 8 doubles:
+//   {v0..v3, alpha = 1/d, zs = e/d, p, zs^2} with v = w(j), e = b_j - v.z, d = 1 - |v|^2,
+//   z = R^-1 b_g, p = c - |z|^2 - e^2/d (the SSE of the group and j),
+// and per group the factor {R^-1 (10), z (4), 0, 0}.  The bound is computed
+// with group pivots above S3_TAU only and compared with slacks (S3_DSLACK on
+// d, S3_TSLACK c on theta) above the rounding that leaves: p = 0 marks a row
+// whose group or j is too close to dependent (it always passes), p = S3_NEVER
+// one without a tuple (j constant, or no i1 < j).  A j of the group itself
+// leaves the group alone (v = 0, 1/d = 0).
+constexpr double S3_TAU = 1e-5, S3_DSLACK = 1e-7, S3_TSLACK = 1e-7, S3_ESLACK = 1e-13, S3_NEVER = 1e300;
+constexpr int S3_GREC = 8;   // doubles per group record
+constexpr int S3_GFAC = 16;  // doubles per group factor
+__host__ __device__ inline int64_t s3g_rowoff(int64_t S, int64_t h) {
+    // sum over h' < h of (S - 2 - 8 h')
+    return h * (S - 2) - (int64_t)S3_NR * S3_GP * (h * (h - 1) / 2);
+}
+int64_t s3_group_rows(int64_t S) { return S >= 3 ? s3g_rowoff(S, (S - 3) / (S3_NR * S3_GP) + 1) : 0; }
+
+__device__ void s3_group_record(const Ctx &c, int64_t g, int64_t x) {
+    const int64_t S = c.S, nt = c.Gnt;
+    const int64_t h = g / S3_GP, j = (int64_t)S3_NR * S3_GP * h + 1 + x;
+    if (h > (S - 3) / (S3_NR * S3_GP) || j > S - 2) return;
+    const int ts = c.tstar[0], TP = c.TP;
+    const double *__restrict__ G1 = c.G1;
+    // the group's factor (the same for every thread of the group)
+    double Li[S3_NR][S3_NR], L[S3_NR][S3_NR], z[S3_NR], pg = c.cyy[ts];
+    bool bad = false;
+#pragma unroll
+    for (int m = 0; m < S3_NR; ++m) {
+        const int64_t i = S3_NR * g + m;
+        const bool live = i < S && G1[gidx(i, i, nt, 1, 0)] > 0.5;
+        double d = 1.0;
+#pragma unroll
+        for (int l = 0; l < m; ++l) {
+            double s = live ? G1[gidx(S3_NR * g + l, i, nt, 1, 0)] : 0.0;
+#pragma unroll
+            for (int q = 0; q < l; ++q) s -= L[m][q] * L[l][q];
+            L[m][l] = s * Li[l][l];
+            d -= L[m][l] * L[m][l];
+        }
+        bad |= live && !(d > S3_TAU);
+        Li[m][m] = live && d > S3_TAU ? 1.0 / sqrt(d) : 0.0;
+        double zz = 0.0;
+#pragma unroll
+        for (int l = 0; l < m; ++l) {
+            double s = 0.0;
+#pragma unroll
+            for (int q = l; q < m; ++q) s += L[m][q] * Li[q][l];
+            Li[m][l] = -Li[m][m] * s;
+            zz += Li[m][l] * c.bhat[(S3_NR * g + l < S ? S3_NR * g + l : 0) * TP + ts];
+        }
+        if (live) zz += Li[m][m] * c.bhat[i * TP + ts];
+        z[m] = zz;
+        pg -= zz * zz;
+    }
+    if (x == 0) {
+        double *f = c.gfac + g * S3_GFAC;
+        int e = 0;
+#pragma unroll
+        for (int m = 0; m < S3_NR; ++m)
+#pragma unroll
+            for (int l = 0; l <= m; ++l) f[e++] = Li[m][l];
+#pragma unroll
+        for (int m = 0; m < S3_NR; ++m) f[e++] = z[m];
+        f[e] = f[e + 1] = 0.0;
+    }
+    double v[S3_NR] = {0.0, 0.0, 0.0, 0.0}, al = 0.0, zs = 0.0, p = pg;
+    if (S3_NR * g >= j || !(G1[gidx(j, j, nt, 1, 0)] > 0.5)) {
+        p = S3_NEVER;
+    } else if (bad) {
+        p = 0.0;
+    } else if (j >= S3_NR * (g + 1)) {
+        double d = 1.0, e = c.bhat[j * TP + ts];
+#pragma unroll
+        for (int m = 0; m < S3_NR; ++m) {
+            double s = 0.0;
+#pragma unroll
+            for (int l = 0; l <= m; ++l) s += Li[m][l] * G1[gidx(S3_NR * g + l, j, nt, 1, 0)];
+            v[m] = s;
+            d -= s * s;
+            e -= s * z[m];
+        }
+        if (d > S3_TAU) {
+            al = 1.0 / d;
+            zs = e * al;
+            p = pg - e * zs;
+        } else {
+            p = 0.0;
+        }
+    }
+    double *o = c.recg + ((s3g_rowoff(S, h) + x) * S3_GP + g % S3_GP) * S3_GREC;
+#pragma unroll
+    for (int m = 0; m < S3_NR; ++m) o[m] = v[m];
+    o[4] = al;
+    o[5] = zs;
+    o[6] = p;
+    o[7] = zs * zs;
+}
+
 // (its grid also does the per-search initialisation of search_init_kernel)
-// Grid: x over (j, r) of one group, y over groups (blockIdx.y = g).
+// Grid: x over (j, r) of one group, y over groups (blockIdx.y = g); z = 1
+// builds the group records, x over j.
 // Launched with PRE_WG threads per workgroup and one workgroup column more
 // than the records need: workgroup (last, 0) runs the pre-pass selection
 // (independent of the table and of the initialisation, which leaves the
@@ -1386,6 +1551,10 @@ __host__ __device__ inline int64_t s3_rows(int64_t S) {
 __global__ __launch_bounds__(PRE_WG) void rec3_kernel(Ctx c, double *__restrict__ rec) {
     const int64_t ex = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t g = blockIdx.y;
+    if (blockIdx.z == 1) {
+        s3_group_record(c, g, ex);
+        return;
+    }
     search_init_body(c, g * (int64_t)gridDim.x * blockDim.x + ex, ex == 0 && g == 0, 3, SUBP, JBLK, 1);
     if (blockIdx.x == gridDim.x - 1 && g == 0) {
         pre_select_body<3>(c);
@@ -1424,14 +1593,14 @@ __global__ __launch_bounds__(PRE_WG) void rec3_kernel(Ctx c, double *__restrict_
 }
 
 // Tiles of j-block jb (j in [S3_JR jb, S3_JR jb + S3_JR) and j <= S - 2):
-// nkb column chunks (k from j0 + 1 to S - 1) times groups g < ng (the
-// group's first i1 lies below the block's last j).
-__host__ __device__ inline void s3_block(int64_t S, int64_t jb, int64_t &nkb, int64_t &ng) {
+// nkb column chunks (k from j0 + 1 to S - 1) times pairs of groups h < nh
+// (the pair's first i1 lies below the block's last j).
+__host__ __device__ inline void s3_block(int64_t S, int64_t jb, int64_t &nkb, int64_t &nh) {
     const int64_t j0 = jb * S3_JR;
     int64_t jmax = j0 + S3_JR - 1;
     if (jmax > S - 2) jmax = S - 2;
     nkb = (S - j0 - 1 + S3_KC - 1) / S3_KC;
-    ng = jmax >= 1 ? (jmax - 1) / S3_NR + 1 : 0;
+    nh = jmax >= 1 ? (jmax - 1) / (S3_NR * S3_GP) + 1 : 0;
 }
 __host__ __device__ inline int64_t s3_nblocks(int64_t S) { return S >= 3 ? (S - 2) / S3_JR + 1 : 0; }
 
@@ -1441,23 +1610,23 @@ __device__ void s3_tile_table(const Ctx &c) {
     uint64_t acc = 0;
     c.cum[0] = 0;
     for (int64_t b = 0; b < nb; ++b) {
-        int64_t nkb, ng;
-        s3_block(c.S, b, nkb, ng);
-        acc += (uint64_t)(nkb * ng);
+        int64_t nkb, nh;
+        s3_block(c.S, b, nkb, nh);
+        acc += (uint64_t)(nkb * nh);
         c.cum[b + 1] = acc;
     }
     c.stats[1] = acc;
 }
 
-int s3_rows_per_tile() { return S3_JR; }
+int s3_steps_per_tile() { return S3_JR * S3_GP; }
 
 uint64_t s3_tiles_host(int64_t S) {
     const int64_t nb = s3_nblocks(S);
     uint64_t acc = 0;
     for (int64_t b = 0; b < nb; ++b) {
-        int64_t nkb, ng;
-        s3_block(S, b, nkb, ng);
-        acc += (uint64_t)(nkb * ng);
+        int64_t nkb, nh;
+        s3_block(S, b, nkb, nh);
+        acc += (uint64_t)(nkb * nh);
     }
     return acc;
 }
@@ -1465,16 +1634,12 @@ uint64_t s3_tiles_host(int64_t S) {
 #ifndef S3_WPE
 #define S3_WPE 4                      // waves per SIMD the register budget is sized for
 #endif
-// Several tasks, D = 3: the exact scoring of queued sweep steps, in two
-// phases per wave.  mt_step_candidates redoes, for one step (row j of group
-// g, column chunk kcx, the flag masks of the step's two columns per lane),
-// the filter task's test per i1 and column with a true division, and appends
-// the tuples that pass (key, filter-task SSE) to the wave's LDS buffer.
-// mt_flush then takes up to 64 buffered tuples, one per lane: the second
-// largest task's SSE is added (a tighter lower bound), and the survivors are
-// scored over every task, 64 / LT tuples at a time with LT lanes each (lane
-// q LT + l sums the tasks t = l mod LT of tuple q, then a butterfly sum and
-// rank flag), and inserted into the wave's list.
+// Several tasks, D = 3: tuples that pass the filter task's own test are
+// buffered in LDS (key, filter-task SSE), and mt_flush takes up to 64 of them,
+// one per lane: the second largest task's SSE is added (a tighter lower
+// bound), and the survivors are scored over every task, 64 / LT tuples at a
+// time with LT lanes each (lane q LT + l sums the tasks t = l mod LT of tuple
+// q, then a butterfly sum and rank flag), and inserted into the wave's list.
 constexpr int MT_BUF = 128;  // buffered tuples per wave (a flush takes 64)
 
 __device__ __forceinline__ unsigned mt_flush(const Ctx &c, double *Ls, uint64_t *Lr, int KP, const uint64_t *bk,
@@ -1539,126 +1704,85 @@ __device__ __forceinline__ unsigned mt_flush(const Ctx &c, double *Ls, uint64_t 
     return offered;
 }
 
-__device__ __forceinline__ unsigned mt_step(const Ctx &c, const SearchArgs &a, const double *__restrict__ rec,
-                                            double *Ls, uint64_t *Lr, int KP, uint64_t *bk, double *be, int &nbuf,
-                                            int64_t j, int64_t g, int64_t kcx, unsigned long long fm0,
-                                            unsigned long long fm1, double theta_f) {
+// a wave's buffer of tuples that passed the filter task (several tasks)
+struct MtBuf {
+    uint64_t *key;
+    double *sse;
+    int n;
+};
+
+// Appends the tuples of the lanes in take to the buffer and flushes it from 64 on.
+__device__ __forceinline__ void mt_append(const Ctx &c, double *Ls, uint64_t *Lr, int KP, MtBuf &mb, bool take,
+                                          uint64_t key, double sse, double theta_f, unsigned &offered) {
     const int lane = threadIdx.x & 63;
-    const int64_t S = c.S, nt = c.Gnt;
-    const int TP = c.TP, ts = c.tstar[0];
-    const double *__restrict__ G1 = c.G1;
-    const double *__restrict__ inv_st = c.inv_s + (int64_t)ts * S;
-    const int64_t kb = j - j % S3_JR + 1 + kcx * S3_KC;  // the tile's first column
-    const int64_t k0 = kb + lane, k1 = kb + 64 + lane;
-    const bool kv0 = k0 < S, kv1 = k1 < S;
-    const int64_t kk = kv0 ? k0 : S - 1, kd1 = kv1 ? k1 : S - 1;
-    const double gvx = G1[gidx(j, kk, nt, 1, 0)], gvy = G1[gidx(j, kd1, nt, 1, 0)];
-    const double gd0 = inv_st[kk] > 0.0 ? 1.0 : 0.0, gd1 = inv_st[kd1] > 0.0 ? 1.0 : 0.0;
-    const double b0 = c.bhat[kk * TP + ts], b1 = c.bhat[kd1 * TP + ts];
-    const double *rp = rec + (s3_rowoff(S, g) + j - S3_NR * g - 1) * (S3_NR * 4);
-    unsigned offered = 0;
-#pragma unroll
-    for (int r = 0; r < S3_NR; ++r) {
-        const int64_t i1 = S3_NR * g + r, i1c = i1 < S ? i1 : S - 1;
-        const double v = rp[4 * r], al = rp[4 * r + 1], zs = rp[4 * r + 2], p = rp[4 * r + 3];
-        const double zp = c.bhat[i1c * TP + ts];
-        const double wvx = G1[gidx(i1c, kk, nt, 1, 0)], wvy = G1[gidx(i1c, kd1, nt, 1, 0)];
-#pragma unroll
-        for (int sl = 0; sl < 2; ++sl) {
-            const double w = sl ? wvy : wvx, gg = sl ? gvy : gvx, gd = sl ? gd1 : gd0;
-            const int64_t k = sl ? k1 : k0;
-            const double dq = ((sl ? kv1 : kv0) && gd > RANK_EPS) ? gd - w * w : __builtin_nan("");
-            const double zq = (sl ? b1 : b0) - w * zp;
-            const double u = fma(-v, w, gg);
-            const double d = fma(-al, u * u, dq);
-            const double z = fma(-zs, u, zq);
-            const double es = (d > RANK_EPS) ? p - z * z / d : INF;
-            const int32_t tup[3] = {(int32_t)i1, (int32_t)j, (int32_t)k};
-            bool take = (((sl ? fm1 : fm0) >> lane) & 1ull) && k < S && k > j && es <= theta_f;
-            if (take && a.ranged) {
-                const uint64_t lr = lex_rank(BinomTab{c.btab, c.S}, c.S, 3, tup);
-                if (lr < a.r0 || lr >= a.r1) take = false;
-            }
-            const unsigned long long m = __ballot(take);
-            if (m) {
-                if (take) {
-                    const int at = nbuf + __popcll(m & ((1ull << lane) - 1ull));
-                    bk[at] = pack_tuple(tup, 3);
-                    be[at] = es;
-                }
-                nbuf += __popcll(m);
-                __atomic_signal_fence(__ATOMIC_SEQ_CST);
-                __builtin_amdgcn_wave_barrier();
-                if (nbuf >= 64) {
-                    offered += mt_flush(c, Ls, Lr, KP, bk, be, 64, theta_f);
-                    // keep the rest (fewer than 64) at the front
-                    const int rest = nbuf - 64;
-                    uint64_t kx = 0;
-                    double ex = 0.0;
-                    if (lane < rest) {
-                        kx = bk[64 + lane];
-                        ex = be[64 + lane];
-                    }
-                    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-                    __builtin_amdgcn_wave_barrier();
-                    if (lane < rest) {
-                        bk[lane] = kx;
-                        be[lane] = ex;
-                    }
-                    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-                    __builtin_amdgcn_wave_barrier();
-                    nbuf = rest;
-                }
-            }
-        }
+    const unsigned long long m = __ballot(take);
+    if (!m) return;
+    if (take) {
+        const int at = mb.n + __popcll(m & ((1ull << lane) - 1ull));
+        mb.key[at] = key;
+        mb.sse[at] = sse;
     }
-    return offered;
+    mb.n += __popcll(m);
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_wave_barrier();
+    if (mb.n < 64) return;
+    offered += mt_flush(c, Ls, Lr, KP, mb.key, mb.sse, 64, theta_f);
+    // keep the rest (fewer than 64) at the front
+    const int rest = mb.n - 64;
+    uint64_t kx = 0;
+    double ex = 0.0;
+    if (lane < rest) {
+        kx = mb.key[64 + lane];
+        ex = mb.sse[64 + lane];
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_wave_barrier();
+    if (lane < rest) {
+        mb.key[lane] = kx;
+        mb.sse[lane] = ex;
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_wave_barrier();
+    mb.n = rest;
 }
 
-// One tile of the D = 3 record-table sweep (see search3_kernel): the tile's
-// k-dependent terms, the sweep over its rows, exact scoring of the flagged
-// steps into the wave's list (one task) or their queueing (several tasks),
-// and the publication of the wave's bound.  Shared by the one-problem kernel
-// and the batched kernel.
+// Tables that a launch only reads, in the constant address space: where the
+// address is uniform the loads are scalar, also in a kernel that stores.
+typedef const __attribute__((address_space(4))) double CDouble;
+typedef const __attribute__((address_space(4))) char CChar;
+__device__ inline CDouble *cptr(const double *p) { return (CDouble *)(uintptr_t)p; }
+
+// Where a tile lies: row block jb, its rows jlo .. jhi, column chunk kcx from
+// column kb.
+struct S3Tile {
+    int64_t j0, jhi, kb, kcx;
+};
+
+// The rows jlo .. jhi of a tile for one group: the tile's k-dependent terms, the
+// tuples' own test over the rows, exact scoring of the flagged steps into the
+// wave's list (one task) or buffer (several tasks), and the publication of the
+// wave's bound.
 // CtxT: Ctx (a kernel argument) or a Ctx in the constant address space (a
 // copy in device memory, read by the batched kernel): both let the compiler
 // read the fields with scalar loads into scalar registers.
 template <bool MT, class CtxT>
-__device__ __forceinline__ void s3_tile(const CtxT &c, const SearchArgs &a, const double *__restrict__ rec,
-                                        const uint64_t *__restrict__ tcum, uint64_t t, double *Ls, uint64_t *Lr,
-                                        double theta0, double &theta_pub, unsigned &offered, int &qchunk, int &qn,
-                                        unsigned long long (*s_qw)[2], int *s_qjw) {
+__device__ __forceinline__ void s3_group(const CtxT &c, const SearchArgs &a, const double *__restrict__ rec,
+                                         const S3Tile &tl, int64_t g, int64_t jlo, int64_t jhi, double *Ls,
+                                         uint64_t *Lr, double theta0, double &theta_pub, unsigned &offered,
+                                         MtBuf &mb, unsigned long long (*s_qw)[2], int *s_qjw) {
     const int KP = a.KP;
     const int lane = threadIdx.x & 63;
     const int64_t S = c.S;
-    const int64_t nb = s3_nblocks(S);
     const int64_t nt = c.Gnt;
     const double *__restrict__ Gb = c.G1;
     const int TP = c.TP;
     const int ts = c.tstar[0];
     const double *__restrict__ inv_st = c.inv_s + (int64_t)ts * S;
     {
-        // tile -> (j-block, column chunk, group)
-        int64_t lo = 0, hi = nb - 1;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi + 1) >> 1;
-            if (tcum[mid] <= t) lo = mid; else hi = mid - 1;
-        }
-        const int64_t jb = lo;
-        int64_t nkb, ng;
-        s3_block(S, jb, nkb, ng);
-        // column chunk fastest: the waves of a workgroup usually take chunks
-        // of one (block, group) and share its records in the scalar cache;
-        // a run of tiles on one XCD covers a few groups over the same chunks
-        // of G
-        const int64_t rem = (int64_t)(t - tcum[jb]);
-        const int64_t kcx = rem % nkb;
-        const int64_t g = rem / nkb;
-        const int64_t j0 = jb * S3_JR;
-        const int64_t jlo = j0 > S3_NR * g + 1 ? j0 : S3_NR * g + 1;
-        const int64_t jhi = (j0 + S3_JR - 1 < S - 2) ? j0 + S3_JR - 1 : S - 2;
+        const int64_t kcx = tl.kcx;
+        const int64_t j0 = tl.j0;
         const int nrow = (int)(jhi - jlo);  // steps 0..nrow
-        const int64_t kb = j0 + 1 + kcx * S3_KC;
+        const int64_t kb = tl.kb;
         const int64_t k0 = kb + lane, k1 = kb + 64 + lane;
         const bool kv0 = k0 < S, kv1 = k1 < S;
         // columns read for lanes past S: any valid one (never passes)
@@ -1687,10 +1811,10 @@ __device__ __forceinline__ void s3_tile(const CtxT &c, const SearchArgs &a, cons
                 w[r][0] = wv.x;
                 w[r][1] = wv.y;
                 // a lane past S or on a constant column never passes
-                dq[r][0] = (kv0 && gd0 > RANK_EPS) ? gd0 - wv.x * wv.x : __builtin_nan("");
-                dq[r][1] = (kv1 && gd1 > RANK_EPS) ? gd1 - wv.y * wv.y : __builtin_nan("");
-                zq[r][0] = b0 - wv.x * zp;
-                zq[r][1] = b1 - wv.y * zp;
+                dq[r][0] = (kv0 && gd0 > RANK_EPS) ? fma(-wv.x, wv.x, gd0) : __builtin_nan("");
+                dq[r][1] = (kv1 && gd1 > RANK_EPS) ? fma(-wv.y, wv.y, gd1) : __builtin_nan("");
+                zq[r][0] = fma(-wv.x, zp, b0);
+                zq[r][1] = fma(-wv.y, zp, b1);
             }
         }
         // G[j][k] for the block's rows: j >> 6 is the same for the whole block
@@ -1701,8 +1825,7 @@ __device__ __forceinline__ void s3_tile(const CtxT &c, const SearchArgs &a, cons
         const uint32_t voff0 = (uint32_t)((((kk0 >> 6) << 12) + (kk0 & 63) + ((jlo & 63) << 6)) * 8);
         const uint32_t voff1 = (uint32_t)((((kk1 >> 6) << 12) + (kk1 & 63) + ((jlo & 63) << 6)) * 8);
         // records of row jlo + x are 128 bytes at recj + 128 x (uniform)
-        const char *__restrict__ recj =
-            reinterpret_cast<const char *>(rec + (size_t)(s3_rowoff(S, g) + jlo - S3_NR * g - 1) * (S3_NR * 4));
+        CChar *recj = (CChar *)(cptr(rec) + (size_t)(s3_rowoff(S, g) + jlo - S3_NR * g - 1) * (S3_NR * 4));
         int nq = 0;
         auto sweep = [&](auto diagc, auto halfc) {
             constexpr bool DIAG = decltype(diagc)::value;
@@ -1722,7 +1845,7 @@ __device__ __forceinline__ void s3_tile(const CtxT &c, const SearchArgs &a, cons
             // loads may return out of order, so the half in flight is waited for
             // (lgkmcnt(0)) before the next one is issued.
             auto load_half = [&](double (&rv)[8], int jr, int h) {
-                const double *rp = reinterpret_cast<const double *>(recj + (size_t)jr * 128 + h * 64);
+                CDouble *rp = (CDouble *)(recj + (size_t)jr * 128 + h * 64);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) rv[e] = rp[e];
             };
@@ -1800,31 +1923,7 @@ __device__ __forceinline__ void s3_tile(const CtxT &c, const SearchArgs &a, cons
             const int jr = s_qjw[e];
             const int64_t j = jlo + jr;
             const unsigned long long fm[2] = {s_qw[e][0], s_qw[e][1]};
-            if (MT) {
-                // several tasks: queue the step (row j of group g, chunk kcx,
-                // the flags); a later, evenly spread kernel scores it.  The
-                // pool holds a record per sweep step plus a partly filled
-                // chunk per wave, so a take past its end cannot happen; it
-                // would be reported, not dropped silently
-                if (qchunk >= 0 && qn == MTQ_CHUNK) {
-                    if (lane == 0) c.mtq_n[qchunk] = (uint32_t)qn;
-                    unsigned got = 0;
-                    if (lane == 0) got = atomicAdd(c.mtq_taken, 1u);
-                    got = (unsigned)__shfl((int)got, 0) + gridDim.x * SEARCH_WAVES;
-                    qchunk = got < (unsigned)c.mtq_chunks ? (int)got : -2;
-                    if (qchunk == -2 && lane == 0) atomicOr(&c.flags[FLAG_CAPACITY], 1u);
-                    qn = 0;
-                }
-                if (qchunk >= 0) {
-                    if (lane < 3) {
-                        const uint64_t w0 = ((uint64_t)j << 40) | ((uint64_t)g << 20) | (uint64_t)kcx;
-                        c.mtq[((int64_t)qchunk * MTQ_CHUNK + qn) * 3 + lane] = lane == 0 ? w0 : lane == 1 ? fm[0] : fm[1];
-                    }
-                    ++qn;
-                }
-                continue;
-            }
-            const double *rp = reinterpret_cast<const double *>(recj + (size_t)jr * 128);
+            CDouble *rp = (CDouble *)(recj + (size_t)jr * 128);
             const double2 gv = {*reinterpret_cast<const double *>(gtile + (voff0 + (uint32_t)jr * 512u)),
                                 *reinterpret_cast<const double *>(gtile + (voff1 + (uint32_t)jr * 512u))};
             // (r, sl) are wave-uniform here: pick the k-data by selects, so
@@ -1851,22 +1950,16 @@ __device__ __forceinline__ void s3_tile(const CtxT &c, const SearchArgs &a, cons
                     // the step's flag covers all four i1 of the group: this
                     // i1's own terms decide (NaN records: i1 >= j or a rank
                     // deficient pair)
-                    const double es = (d > RANK_EPS) ? p - z * z / d : INF;
-                    bool take = ((fm[sl] >> lane) & 1ull) && k < S && k > j && es <= fmin(theta_f, Ls[KP - 1]);
+                    const double es = (d > RANK_EPS) ? p - (z * z) / d : INF;
+                    bool take = ((fm[sl] >> lane) & 1ull) && k < S && k > j &&
+                                es <= (MT ? theta_f : fmin(theta_f, Ls[KP - 1]));
                     if (take && a.ranged) {
                         const uint64_t lr = lex_rank(BinomTab{c.btab, c.S}, c.S, 3, tup);
                         if (lr < a.r0 || lr >= a.r1) take = false;
                     }
-                    unsigned long long m = __ballot(take);
                     const uint64_t rk = take ? pack_tuple(tup, 3) : 0;
-                    offered += (unsigned)__popcll(m);
-                    while (m) {
-                        const int src = __ffsll((long long)m) - 1;
-                        m &= m - 1;
-                        const double cs = __shfl(es, src);
-                        const uint64_t cr = (uint64_t)__shfl((long long)rk, src);
-                        list_insert(Ls, Lr, KP, cs, cr);
-                    }
+                    if constexpr (MT) mt_append(c, Ls, Lr, KP, mb, take, rk, es, theta_f, offered);
+                    else list_insert_lanes(Ls, Lr, KP, take, rk, es, offered);
                 }
             }
         }
@@ -1878,38 +1971,318 @@ __device__ __forceinline__ void s3_tile(const CtxT &c, const SearchArgs &a, cons
     }
 }
 
-// MT: several tasks (the sweep filters on the filter task alone, the exact
-// path sums every task); a template parameter so that the one-task kernel's
-// registers are not shaped by the several-task exact path
-template <bool MT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) void search3_kernel(Ctx c, SearchArgs a, const double *__restrict__ rec,
-                                                      const uint64_t *__restrict__ tcum) {
-    extern __shared__ double smem[];
-    __shared__ unsigned long long s_q[SEARCH_WAVES][S3_JR][2];
-    __shared__ int s_qj[SEARCH_WAVES][S3_JR];
+// 64 candidates, one per lane: (group g, row j, column k) whose bound passed.
+// Each lane tests the group's four tuples (the terms of s3_group, the same
+// arithmetic).
+template <bool MT, class CtxT>
+__device__ __forceinline__ void s3_candidates(const CtxT &c, const SearchArgs &a, const double *__restrict__ rec,
+                                              bool have, uint64_t key, double *Ls, uint64_t *Lr, double theta0,
+                                              double &theta_pub, unsigned &offered, MtBuf &mb) {
     const int KP = a.KP;
+    const int64_t S = c.S, nt = c.Gnt;
+    const int TP = c.TP, ts = c.tstar[0];
+    const double *__restrict__ G1 = c.G1;
+    const int64_t g = have ? (int64_t)(key >> 44) : 0, j = have ? (int64_t)((key >> 22) & 0x3FFFFF) : 1;
+    const int64_t k = have ? (int64_t)(key & 0x3FFFFF) : 2;
+    double th = fmin(theta0, theta_load(c.theta_bits));
+    th = fmin(th, Ls[KP - 1]);
+    const double theta_f = th < INF ? th * (1.0 + THETA_SLACK) : INF;
+    const double gg = G1[gidx(j, k, nt, 1, 0)];
+    const double gd = c.inv_s[(int64_t)ts * S + k] > 0.0 ? 1.0 : 0.0;
+    const double bk = c.bhat[k * TP + ts];
+    const double *__restrict__ rp = rec + (s3_rowoff(S, g) + j - S3_NR * g - 1) * (S3_NR * 4);
+    double es[S3_NR];
+#pragma unroll
+    for (int r = 0; r < S3_NR; ++r) {
+        int64_t i1 = S3_NR * g + r;
+        i1 = i1 < S ? i1 : S - 1;  // past S: the record is NaN
+        const double v = rp[4 * r], al = rp[4 * r + 1], zs = rp[4 * r + 2], p = rp[4 * r + 3];
+        const double w = G1[gidx(i1, k, nt, 1, 0)], zp = c.bhat[i1 * TP + ts];
+        const double dq = gd > RANK_EPS ? fma(-w, w, gd) : __builtin_nan("");
+        const double zq = fma(-w, zp, bk);
+        const double u = fma(-v, w, gg);
+        const double d = fma(-al, u * u, dq);
+        const double z = fma(-zs, u, zq);
+        es[r] = (d > RANK_EPS) ? p - (z * z) / d : INF;
+    }
+#pragma unroll
+    for (int r = 0; r < S3_NR; ++r) {
+        const int32_t tup[3] = {(int32_t)(S3_NR * g + r), (int32_t)j, (int32_t)k};
+        bool take = have && es[r] <= (MT ? theta_f : fmin(theta_f, Ls[KP - 1]));
+        if (take && a.ranged) {
+            const uint64_t lr = lex_rank(BinomTab{c.btab, c.S}, c.S, 3, tup);
+            if (lr < a.r0 || lr >= a.r1) take = false;
+        }
+        const uint64_t rk = pack_tuple(tup, 3);
+        if constexpr (MT) mt_append(c, Ls, Lr, KP, mb, take, rk, es[r], theta_f, offered);
+        else list_insert_lanes(Ls, Lr, KP, take, rk, es[r], offered);
+    }
+    const double tw = Ls[KP - 1];
+    if (tw < theta_pub) {
+        theta_pub = tw;
+        if ((threadIdx.x & 63) == 0) theta_publish(c.theta_bits, tw);
+    }
+}
+
+// Where the bound does not help (both groups of a tile pass it for more pairs
+// than are taken one by one) a wave leaves it out for the next 1, 3, .. 31 tiles, so a
+// problem whose six-feature fits all reach the threshold pays a few per cent.
+struct S3Skip {
+    int left = 0, fails = 0;
+};
+
+// tile t: its row block, column chunk and pair of groups h
+__device__ __forceinline__ int64_t s3_locate(int64_t S, const uint64_t *__restrict__ tcum, uint64_t t, S3Tile &tl) {
+    int64_t lo = 0, hi = s3_nblocks(S) - 1;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi + 1) >> 1;
+        if (tcum[mid] <= t) lo = mid; else hi = mid - 1;
+    }
+    int64_t nkb, nh;
+    s3_block(S, lo, nkb, nh);
+    // column chunk fastest: the waves of a workgroup usually take chunks of
+    // one (block, pair) and share its records in the scalar cache; a run of
+    // tiles on one XCD covers a few groups over the same chunks of G
+    const int64_t rem = (int64_t)(t - tcum[lo]);
+    tl.kcx = rem % nkb;
+    tl.j0 = lo * S3_JR;
+    tl.jhi = (tl.j0 + S3_JR - 1 < S - 2) ? tl.j0 + S3_JR - 1 : S - 2;
+    tl.kb = tl.j0 + 1 + tl.kcx * S3_KC;
+    return rem / nkb;
+}
+
+// The groups' bounds over the rows of a tile (threshold th): bit x of
+// rows[q] says that group S3_GP h + q has to be looked at on row j0 + x, and
+// mask[x][q] holds the lanes (first and second column) that passed there;
+// lanes[q] counts them.  Without a bound (th infinite, or left out) every
+// row is set, and lanes[q] is more than any limit.
+// Bound by FP64 issue: 20 instructions per lane, row and group (two columns)
+// against 56 for the tuples' own tests.
+template <class CtxT>
+__device__ __forceinline__ void s3_bound(const CtxT &c, const double *__restrict__ recg,
+                                         const double *__restrict__ gfac, const S3Tile &tl, int64_t h, double th, S3Skip &skip, int limit,
+                                         unsigned long long (*mask)[S3_GP][2], unsigned long long (&rows)[S3_GP],
+                                         int (&lanes)[S3_GP]) {
+    const int lane = threadIdx.x & 63;
+    const int64_t S = c.S;
+    const int64_t nt = c.Gnt;
+    const double *__restrict__ Gb = c.G1;
+    const int TP = c.TP;
+    const int ts = c.tstar[0];
+    const double *__restrict__ inv_st = c.inv_s + (int64_t)ts * S;
+    const int64_t jlo = tl.j0 > S3_NR * S3_GP * h + 1 ? tl.j0 : S3_NR * S3_GP * h + 1;
+    const int nrow = (int)(tl.jhi - jlo);  // steps 0..nrow
+    rows[0] = rows[1] = ~0ull;
+    lanes[0] = lanes[1] = 1 << 30;
+    const int x0 = (int)(jlo - tl.j0);
+    // a group's first step with a tuple (the second group's rows start later)
+    const int lo1[S3_GP] = {0, (int)(S3_NR * (S3_GP * h + 1) + 1 - jlo)};
+    if (skip.left > 0) {
+        --skip.left;
+    } else if (th < INF) {
+        const double theta_s = th * (1.0 + THETA_SLACK) + S3_TSLACK * c.cyy[ts];
+        const int64_t k0 = tl.kb + lane, k1 = tl.kb + 64 + lane;
+        const bool kv0 = k0 < S, kv1 = k1 < S;
+        const int64_t kk0 = kv0 ? k0 : S - 1, kk1 = kv1 ? k1 : S - 1;
+        const bool diag = tl.kcx == 0, half = S - tl.kb <= 64;
+        // k-dependent part of each group's solve, for both columns of the lane
+        double w[S3_GP][S3_NR][2], dq[S3_GP][2], z2[S3_GP][2], zz[S3_GP][2];  // z2 = -2 zeta', zz = zeta'^2
+        const double neg = -S3_ESLACK * c.cyy[ts];
+        {
+            const bool lv0 = kv0 && inv_st[kk0] > 0.0, lv1 = kv1 && inv_st[kk1] > 0.0;
+            const double b0 = c.bhat[kk0 * TP + ts], b1 = c.bhat[kk1 * TP + ts];
+#pragma unroll
+            for (int q = 0; q < S3_GP; ++q) {
+                CDouble *f = cptr(gfac) + (S3_GP * h + q) * S3_GFAC;
+                double x0[S3_NR], x1[S3_NR];
+#pragma unroll
+                for (int l = 0; l < S3_NR; ++l) {
+                    int64_t i = S3_NR * (S3_GP * h + q) + l;
+                    i = i < S ? i : S - 1;  // past S: the factor's row is zero
+                    x0[l] = Gb[gidx(i, kk0, nt, 1, 0)];
+                    x1[l] = Gb[gidx(i, kk1, nt, 1, 0)];
+                }
+                double d0 = 1.0 - S3_DSLACK, d1 = 1.0 - S3_DSLACK, e0 = b0, e1 = b1;
+#pragma unroll
+                for (int m = 0; m < S3_NR; ++m) {
+                    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+                    for (int l = 0; l <= m; ++l) {
+                        s0 = fma(f[m * (m + 1) / 2 + l], x0[l], s0);
+                        s1 = fma(f[m * (m + 1) / 2 + l], x1[l], s1);
+                    }
+                    w[q][m][0] = s0;
+                    w[q][m][1] = s1;
+                    d0 = fma(-s0, s0, d0);
+                    d1 = fma(-s1, s1, d1);
+                    e0 = fma(-s0, f[10 + m], e0);
+                    e1 = fma(-s1, f[10 + m], e1);
+                }
+                // a lane past S or on a constant column never passes
+                dq[q][0] = lv0 ? d0 : S3_NEVER;
+                dq[q][1] = lv1 ? d1 : S3_NEVER;
+                z2[q][0] = -2.0 * e0;
+                z2[q][1] = -2.0 * e1;
+                zz[q][0] = e0 * e0;
+                zz[q][1] = e1 * e1;
+            }
+        }
+        // G[j][k] for the block's rows: j >> 6 is the same for the whole block
+        // (S3_JR divides 64), so one uniform tile-row base plus 32-bit per-lane
+        // byte offsets (column part + row j & 63) address every step
+        const char *__restrict__ gtile = reinterpret_cast<const char *>(Gb + (((tl.j0 >> 6) * nt) << 12));
+        const uint32_t voff0 = (uint32_t)((((kk0 >> 6) << 12) + (kk0 & 63) + ((jlo & 63) << 6)) * 8);
+        const uint32_t voff1 = (uint32_t)((((kk1 >> 6) << 12) + (kk1 & 63) + ((jlo & 63) << 6)) * 8);
+        // records of row jlo + x are 128 bytes at recj + 128 x (uniform)
+        CChar *recj =
+            (CChar *)(cptr(recg) + (size_t)(s3g_rowoff(S, h) + jlo - S3_NR * S3_GP * h - 1) * (S3_GP * S3_GREC));
+        auto sweep = [&](auto diagc, auto halfc) {
+            constexpr bool DIAG = decltype(diagc)::value;
+            constexpr bool HALF = decltype(halfc)::value;
+            constexpr int JG = S3_JG;
+            unsigned long long rw[S3_GP] = {0, 0};
+            int ln[S3_GP] = {0, 0};
+            double2 ga[JG], gb[JG];  // g(j, k0), g(j, k1)
+            auto fetch = [&](double2 (&dst)[JG], int jg) {
+#pragma unroll
+                for (int x = 0; x < JG; ++x) {
+                    const uint32_t jr = (uint32_t)(jg + x < nrow ? jg + x : nrow);
+                    dst[x].x = *reinterpret_cast<const double *>(gtile + (voff0 + jr * 512u));
+                    dst[x].y = HALF ? 0.0 : *reinterpret_cast<const double *>(gtile + (voff1 + jr * 512u));
+                }
+            };
+            // the two groups' records of one step are two halves of 64 bytes,
+            // each loaded while the other is scored (scalar loads may return
+            // out of order, so the half in flight is waited for before the
+            // next one is issued)
+            auto load_half = [&](double (&rv)[S3_GREC], int jr, int q) {
+                CDouble *rp = (CDouble *)(recj + (size_t)jr * 128 + q * 64);
+#pragma unroll
+                for (int e = 0; e < S3_GREC; ++e) rv[e] = rp[e];
+            };
+            // z^2 - (p - theta) d as a polynomial in u, with A = zs^2 + (p -
+            // theta) alpha per step: q + u (A u - 2 zeta' zs), q = zeta'^2 -
+            // (p - theta) d'.  A lane passes unless that is below -eps (a
+            // slack above the rounding of the terms, which cancel): a NaN
+            // passes, and so does any lane when p is at or below theta
+            auto score_half = [&](const double (&rv)[S3_GREC], const double2 gv, int q, int jr) {
+                const double pi = fmax(rv[6] - theta_s, 0.0);
+                const double A = fma(pi, rv[4], rv[7]);
+                unsigned long long m0, m1 = 0;
+                {
+                    double u = gv.x;
+#pragma unroll
+                    for (int e = 0; e < S3_NR; ++e) u = fma(-rv[e], w[q][e][0], u);
+                    const double x = fma(u, fma(A, u, rv[5] * z2[q][0]), fma(-pi, dq[q][0], zz[q][0]));
+                    m0 = __ballot(!(x < neg));
+                    if (DIAG) m0 &= __ballot(k0 > jlo + jr);  // k1 > j0 + 64 > j
+                }
+                if (!HALF) {
+                    double u = gv.y;
+#pragma unroll
+                    for (int e = 0; e < S3_NR; ++e) u = fma(-rv[e], w[q][e][1], u);
+                    const double x = fma(u, fma(A, u, rv[5] * z2[q][1]), fma(-pi, dq[q][1], zz[q][1]));
+                    m1 = __ballot(!(x < neg));
+                }
+                if ((m0 | m1) && jr <= nrow && jr >= lo1[q]) {
+                    m0 &= __ballot(kv0);
+                    m1 &= __ballot(kv1);
+                    if (lane == 0) {
+                        mask[x0 + jr][q][0] = m0;
+                        mask[x0 + jr][q][1] = m1;
+                    }
+                    rw[q] |= 1ull << (x0 + jr);
+                    ln[q] += __popcll(m0) + __popcll(m1);
+                }
+            };
+            double ra[S3_GREC], rb[S3_GREC];
+            load_half(ra, 0, 0);
+            auto score = [&](const double2 (&src)[JG], int jg) {
+#pragma unroll
+                for (int x = 0; x < JG; ++x) {
+                    const int jr = jg + x;
+                    const int jc = jr <= nrow ? jr : nrow;
+                    __builtin_amdgcn_s_waitcnt(0xC07F);
+                    load_half(rb, jc, 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    score_half(ra, src[x], 0, jr);
+                    __builtin_amdgcn_s_waitcnt(0xC07F);
+                    load_half(ra, jr + 1 <= nrow ? jr + 1 : nrow, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    score_half(rb, src[x], 1, jr);
+                }
+            };
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+            fetch(ga, 0);
+            for (int jg = 0;; jg += 2 * JG) {
+                fetch(gb, jg + JG);
+                score(ga, jg);
+                fetch(ga, jg + 2 * JG);
+                score(gb, jg + JG);
+                if (jg + 2 * JG > nrow) break;
+            }
+#pragma unroll
+            for (int q = 0; q < S3_GP; ++q) {
+                rows[q] = rw[q];
+                lanes[q] = ln[q];
+            }
+        };
+        if (diag) {
+            if (half) sweep(std::true_type{}, std::true_type{});
+            else sweep(std::true_type{}, std::false_type{});
+        } else {
+            if (half) sweep(std::false_type{}, std::true_type{});
+            else sweep(std::false_type{}, std::false_type{});
+        }
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_wave_barrier();
+        if (lanes[0] > limit && lanes[1] > limit) {
+            skip.fails = skip.fails < 5 ? skip.fails + 1 : 5;
+            skip.left = (1 << skip.fails) - 1;
+        } else {
+            skip.fails = 0;
+        }
+    }
+    // rows without a tuple of the group are left out
+#pragma unroll
+    for (int q = 0; q < S3_GP; ++q) {
+        const int64_t g = S3_GP * h + q;
+        const int64_t gl = tl.j0 > S3_NR * g + 1 ? tl.j0 : S3_NR * g + 1;  // the group's own first row
+        const int lo = (int)(gl - tl.j0), n = (int)(tl.jhi - tl.j0);
+        rows[q] = lo > n ? 0 : rows[q] & (~0ull >> (63 - n)) & (~0ull << lo);
+        if (!rows[q]) lanes[q] = 0;
+    }
+}
+
+__device__ inline uint64_t s3_cand(int64_t g, int64_t j, int64_t k) {
+    return ((uint64_t)g << 44) | ((uint64_t)j << 22) | (uint64_t)k;
+}
+
+// The bound pass of the single search.  What it flags goes to the workgroup's
+// own segments of two pools (no shared counter: same-address atomics
+// serialise): the (group, row, column) pairs of a tile's group one by one
+// while there are at most `limit`, else the group's flagged rows, eight to an
+// item.  The groups of the best features are flagged on most rows, so the
+// pools are scored by a kernel of their own, spread evenly: scored where they
+// were found they left a few waves running long after the rest (n = 2000, S =
+// 1000: 145 us against 105 without the bound).
+__device__ inline uint64_t s3_row_item(int64_t octet, int64_t g, int64_t kcx, unsigned mask) {
+    return ((uint64_t)octet << 42) | ((uint64_t)g << 22) | ((uint64_t)kcx << 8) | mask;
+}
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) void search3_kernel(
+    Ctx c, const double *__restrict__ recg, const double *__restrict__ gfac, const uint64_t *__restrict__ tcum,
+    uint64_t t0, uint64_t t1, uint32_t wg_tiles, int limit) {
+    __shared__ unsigned long long s_m[SEARCH_WAVES][S3_JR][S3_GP][2];
+    __shared__ unsigned s_n[2];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    double *Ls = smem + (size_t)wave * KP * 2;
-    uint64_t *Lr = reinterpret_cast<uint64_t *>(Ls + KP);
-    for (int m = lane; m < KP; m += 64) {
-        Ls[m] = INF;
-        Lr[m] = ~0ull;
-    }
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_wave_barrier();
-    double theta_pub = INF;
-    unsigned offered = 0;
-    const double theta0 = theta0_of(c);
-    const uint64_t ntiles = tcum[s3_nblocks(c.S)];
-    const int64_t gw = (int64_t)blockIdx.x * SEARCH_WAVES + wave;
-    // several tasks: flagged steps are queued in chunks of MTQ_CHUNK and scored
-    // by a later, evenly spread kernel (the steps cluster in the few tiles of
-    // the best features); wave gw owns chunk gw, further chunks come from the
-    // pool above the launched waves' own, one atomic each
-    int qchunk = MT ? (int)gw : -1, qn = 0;
-
-    // Tiles are dealt round-robin over the waves (their costs are nearly
+    uint64_t *__restrict__ cands = c.s3_cands + (size_t)blockIdx.x * wg_tiles * S3_GP * limit;
+    uint64_t *__restrict__ items = c.s3_rows + (size_t)blockIdx.x * wg_tiles * S3_GP * (S3_JR / 8);
+    if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
+    __syncthreads();
+    const double th = fmin(theta0_of(c), theta_load(c.theta_bits));
+    S3Skip skip;
+    // Tiles t0 .. t1 - 1 are dealt round-robin over the waves (their costs are nearly
     // equal; a shared counter would serialise on one address), XCD-aware:
     // workgroups are placed on the eight XCDs in turn (workgroup b on XCD
     // b mod 8), and runs of S3_XCD_RUN consecutive tiles, which share blocks
@@ -1920,12 +2293,199 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) v
     const uint64_t U = (uint64_t)gridDim.x / nx * SEARCH_WAVES;      // waves per XCD
     const uint64_t u0 = (uint64_t)blockIdx.x / nx * SEARCH_WAVES + wave;
     for (uint64_t sx = u0;; sx += U) {
-        const uint64_t t = ((sx / S3_XCD_RUN) * nx + xcd) * S3_XCD_RUN + sx % S3_XCD_RUN;
-        if (t >= ntiles) break;
-        s3_tile<MT, Ctx>(c, a, rec, tcum, t, Ls, Lr, theta0, theta_pub, offered, qchunk, qn, s_q[wave], s_qj[wave]);
+        const uint64_t t = t0 + ((sx / S3_XCD_RUN) * nx + xcd) * S3_XCD_RUN + sx % S3_XCD_RUN;
+        if (t >= t1) break;
+        S3Tile tl;
+        const int64_t h = s3_locate(c.S, tcum, t, tl);
+        unsigned long long rows[S3_GP];
+        int lanes[S3_GP];
+        s3_bound<Ctx>(c, recg, gfac, tl, h, th, skip, limit, s_m[wave], rows, lanes);
+#pragma unroll
+        for (int q = 0; q < S3_GP; ++q) {
+            if (!rows[q]) continue;
+            const int64_t g = S3_GP * h + q;
+            if (lanes[q] > limit) {
+                const unsigned m = lane < 8 ? (unsigned)(rows[q] >> (8 * lane)) & 0xffu : 0u;  // rows 8 lane ..
+                const unsigned long long b = __ballot(m != 0);
+                unsigned at = 0;
+                if (lane == 0) at = atomicAdd(&s_n[1], (unsigned)__popcll(b));
+                at = (unsigned)__shfl((int)at, 0);
+                if (m)
+                    items[at + __popcll(b & ((1ull << lane) - 1ull))] = s3_row_item((tl.j0 >> 3) + lane, g, tl.kcx, m);
+                continue;
+            }
+            unsigned at = 0;
+            if (lane == 0) at = atomicAdd(&s_n[0], (unsigned)lanes[q]);
+            at = (unsigned)__shfl((int)at, 0);
+            unsigned long long r = rows[q];
+            while (r) {
+                const int x = __builtin_ctzll(r);
+                r &= r - 1;
+#pragma unroll
+                for (int sl = 0; sl < 2; ++sl) {
+                    const unsigned long long m = s_m[wave][x][q][sl];
+                    if ((m >> lane) & 1ull)
+                        cands[at + __popcll(m & ((1ull << lane) - 1ull))] =
+                            s3_cand(g, tl.j0 + x, tl.kb + 64 * sl + lane);
+                    at += (unsigned)__popcll(m);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) c.s3_count[2 * blockIdx.x + threadIdx.x] = s_n[threadIdx.x];
+}
+
+// tiles a workgroup of a launch of wgs takes at most
+static uint64_t s3_wg_tiles(uint64_t ntiles, int wgs) {
+    const uint64_t nx = wgs % S3_XCDS == 0 ? S3_XCDS : 1;
+    const uint64_t U = (uint64_t)wgs / nx * SEARCH_WAVES;
+    const uint64_t pos = (ntiles + S3_XCD_RUN * nx - 1) / (S3_XCD_RUN * nx) * S3_XCD_RUN;  // positions of an XCD
+    return (pos + U - 1) / U * SEARCH_WAVES;
+}
+// A large search runs in passes of S3_PASS tiles (bound, then scoring), which
+// bounds the pools (1.2 GB with one task, 4.3 GB with several; S = 5000 is one
+// pass).  Tiles that the segments of every grid of up to SEARCH_WGS_MAX
+// workgroups cover: all positions, and one tile more per wave.
+constexpr uint64_t S3_PASS = 1ull << 20;
+size_t s3_pool_tiles(int64_t S) {
+    const uint64_t n = s3_tiles_host(S);
+    return (size_t)((n < S3_PASS ? n : S3_PASS) + (uint64_t)S3_XCD_RUN * S3_XCDS + (uint64_t)SEARCH_WGS_MAX * SEARCH_WAVES);
+}
+int s3_lanes(int T) { return T > 1 ? S3_LANES_MT : S3_LANES; }
+
+// Scores the pools: the candidates 64 at a time, one per lane, and the row
+// items in equal contiguous runs, one run per wave (consecutive items of one
+// group, row block and column chunk are swept together).  Every workgroup
+// scans the segments' counts itself (a scan kernel in between cost 7 us).
+// resume: the waves' lists of the previous pass are carried on.
+template <bool MT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) void s3_eval_kernel(
+    Ctx c, SearchArgs a, const double *__restrict__ rec, uint32_t nseg, uint32_t wg_tiles, int limit, int resume) {
+    extern __shared__ double smem[];
+    __shared__ unsigned long long s_q[SEARCH_WAVES][S3_JR][2];
+    __shared__ int s_qj[SEARCH_WAVES][S3_JR];
+    __shared__ uint64_t s_bk[MT ? SEARCH_WAVES : 1][MT ? MT_BUF : 1];
+    __shared__ double s_be[MT ? SEARCH_WAVES : 1][MT ? MT_BUF : 1];
+    __shared__ unsigned long long s_w[2][SEARCH_WAVES];
+    const int KP = a.KP;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    double *Ls = smem + (size_t)wave * KP * 2;
+    uint64_t *Lr = reinterpret_cast<uint64_t *>(Ls + KP);
+    // first[p][s]: items of pool p in the segments before s
+    uint64_t *first[2];
+    first[0] = reinterpret_cast<uint64_t *>(smem + (size_t)SEARCH_WAVES * KP * 2);
+    first[1] = first[0] + nseg + 1;
+    const int64_t gw = (int64_t)blockIdx.x * SEARCH_WAVES + wave;
+    const uint64_t nw = (uint64_t)gridDim.x * SEARCH_WAVES;
+    // thread i owns segments i per .. (i + 1) per - 1
+    const uint32_t per = (nseg + 255) / 256;
+    unsigned long long own[2] = {0, 0}, incl[2];
+    for (uint32_t x = 0; x < per; ++x) {
+        const uint32_t s = tid * per + x;
+        if (s < nseg)
+            for (int p = 0; p < 2; ++p) own[p] += c.s3_count[2 * s + p];
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        incl[p] = own[p];
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned long long y = (unsigned long long)__shfl_up((long long)incl[p], o);
+            if (lane >= o) incl[p] += y;
+        }
+        if (lane == 63) s_w[p][wave] = incl[p];
+    }
+    if (resume) {
+        list_load(Ls, Lr, c.list_sse + gw * KP, c.list_rank + gw * KP, KP);
+    } else {
+        for (int m = lane; m < KP; m += 64) {
+            Ls[m] = INF;
+            Lr[m] = ~0ull;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        unsigned long long at = incl[p] - own[p];
+        for (int w = 0; w < wave; ++w) at += s_w[p][w];
+        for (uint32_t x = 0; x < per; ++x) {
+            const uint32_t s = tid * per + x;
+            if (s >= nseg) break;
+            first[p][s] = at;
+            at += c.s3_count[2 * s + p];
+        }
+        if (tid == 255) first[p][nseg] = at;
+    }
+    __syncthreads();
+    // the segment of item e of pool p
+    auto segment = [&](int p, uint64_t e) {
+        uint32_t lo = 0, hi = nseg - 1;
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi + 1) >> 1;
+            if (first[p][mid] <= e) lo = mid; else hi = mid - 1;
+        }
+        return lo;
+    };
+    const uint64_t ncand = uni(first[0][nseg]), nitem = uni(first[1][nseg]);
+    const double theta0 = theta0_of(c);
+    double theta_pub = INF;
+    unsigned offered = 0;
+    MtBuf mb{s_bk[MT ? wave : 0], s_be[MT ? wave : 0], 0};
+    // the last waves take the first candidates: the first ones get the items
+    for (uint64_t b = nw - 1 - (uint64_t)gw; b * 64 < ncand; b += nw) {
+        const uint64_t e = b * 64 + lane;
+        const bool in = e < ncand;
+        uint64_t key = 0;
+        if (in) {
+            const uint32_t s = segment(0, e);
+            key = c.s3_cands[(size_t)s * wg_tiles * S3_GP * limit + (e - first[0][s])];
+        }
+        s3_candidates<MT, Ctx>(c, a, rec, in, key, Ls, Lr, theta0, theta_pub, offered, mb);
+    }
+    const uint64_t run = (nitem + nw - 1) / nw;
+    uint64_t e = uni((uint64_t)((uint64_t)gw * run));
+    const uint64_t e1 = uni((uint64_t)(e + run < nitem ? e + run : nitem));
+    if (e < e1) {
+        uint32_t s = segment(1, e);
+        auto item = [&]() {
+            while (first[1][s + 1] <= e) ++s;
+            return uni(c.s3_rows[(size_t)s * wg_tiles * S3_GP * (S3_JR / 8) + (e - first[1][s])]);
+        };
+        constexpr uint64_t OCTET = 7ull << 42;  // the rows' place in their block
+        uint64_t it = item();
+        for (;;) {
+            const int64_t g = (int64_t)((it >> 22) & 0xFFFFF);
+            S3Tile tl;
+            tl.kcx = (int64_t)((it >> 8) & 0x3FFF);
+            tl.j0 = (int64_t)(it >> 42) * 8 / S3_JR * S3_JR;
+            tl.kb = tl.j0 + 1 + tl.kcx * S3_KC;
+            const uint64_t same = (it & ~OCTET) >> 8;  // group, column chunk, row block
+            unsigned long long rows = 0;
+            bool more = true;
+            for (;;) {
+                rows |= (unsigned long long)(it & 0xff) << (8 * ((it >> 42) & 7));
+                if (++e >= e1) {
+                    more = false;
+                    break;
+                }
+                it = item();
+                if ((it & ~OCTET) >> 8 != same) break;
+            }
+            const int x0 = __builtin_ctzll(rows), x1 = 63 - __builtin_clzll(rows);
+            s3_group<MT, Ctx>(c, a, rec, tl, g, tl.j0 + x0, tl.j0 + x1, Ls, Lr, theta0, theta_pub, offered, mb,
+                              s_q[wave], s_qj[wave]);
+            if (!more) break;
+        }
+    }
+    if constexpr (MT) {
+        if (mb.n > 0) {
+            const double th = fmin(theta0, theta_load(c.theta_bits));
+            const double theta_f = th < INF ? th * (1.0 + THETA_SLACK) : INF;
+            offered += mt_flush(c, Ls, Lr, KP, mb.key, mb.sse, mb.n, theta_f);
+        }
     }
     if (lane == 0 && offered) atomicAdd(c.cand_counter, offered);
-    if (MT && qchunk >= 0 && lane == 0) c.mtq_n[qchunk] = (uint32_t)qn;
     list_store(c.list_sse + gw * KP, c.list_rank + gw * KP, Ls, Lr, KP);
 }
 
@@ -1949,13 +2509,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3B_WPE))) 
     extern __shared__ double smem[];
     __shared__ unsigned long long s_q[SEARCH_WAVES][S3_JR][2];
     __shared__ int s_qj[SEARCH_WAVES][S3_JR];
+    __shared__ unsigned long long s_m[SEARCH_WAVES][S3_JR][S3_GP][2];
+    __shared__ uint64_t s_k[SEARCH_WAVES][S3_LANES];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     double *Ls = smem + (size_t)wave * b.KPmax * 2;
     uint64_t *Lr = reinterpret_cast<uint64_t *>(Ls + b.KPmax);
     uint32_t *queue = b.ctx[0]->flags + FLAG_BATCHQ;
     const uint32_t nitems = b.item_end[b.P - 1];
-    int cur = -1, qchunk = -1, qn = 0;
+    int cur = -1;
+    S3Skip skip;
+    MtBuf mb{nullptr, nullptr, 0};
     const Ctx *cur_ctx = nullptr;
     double theta0 = INF, theta_pub = INF;
     unsigned offered = 0;
@@ -1998,13 +2562,53 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3B_WPE))) 
             theta0 = theta0_of(c);
             theta_pub = INF;
             offered = 0;
+            skip = S3Skip{};
         }
         const uint64_t ntiles = c.cum[s3_nblocks(c.S)];
         const uint64_t t0 = (uint64_t)(it - first) * S3B_RUN;
         const uint64_t t1 = t0 + S3B_RUN < ntiles ? t0 + S3B_RUN : ntiles;
         for (uint64_t t = t0; t < t1; ++t)
-            s3_tile<false, CCtx>(c, a, c.rec3, c.cum, t, Ls, Lr, theta0, theta_pub, offered, qchunk, qn, s_q[wave],
-                                 s_qj[wave]);
+        {
+            S3Tile tl;
+            const int64_t h = s3_locate(c.S, c.cum, t, tl);
+            unsigned long long rows[S3_GP];
+            int lanes[S3_GP];
+            s3_bound<CCtx>(c, c.recg, c.gfac, tl, h, fmin(fmin(theta0, theta_load(c.theta_bits)), Ls[a.KP - 1]), skip, S3_LANES,
+                           s_m[wave], rows, lanes);
+#pragma unroll 1
+            for (int q = 0; q < S3_GP; ++q) {
+                const int64_t g = S3_GP * h + q;
+                unsigned long long r = q ? rows[1] : rows[0];
+                const int n = q ? lanes[1] : lanes[0];
+                if (!r) continue;
+                if (n > S3_LANES) {
+                    const int x0 = __builtin_ctzll(r), x1 = 63 - __builtin_clzll(r);
+                    s3_group<false, CCtx>(c, a, c.rec3, tl, g, tl.j0 + x0, tl.j0 + x1, Ls, Lr, theta0, theta_pub,
+                                          offered, mb, s_q[wave], s_qj[wave]);
+                    continue;
+                }
+                // at most 64 pairs: one per lane
+                int cnt = 0;
+                while (r) {
+                    const int x = __builtin_ctzll(r);
+                    r &= r - 1;
+#pragma unroll
+                    for (int sl = 0; sl < 2; ++sl) {
+                        const unsigned long long m = s_m[wave][x][q][sl];
+                        if ((m >> lane) & 1ull)
+                            s_k[wave][cnt + __popcll(m & ((1ull << lane) - 1ull))] =
+                                s3_cand(g, tl.j0 + x, tl.kb + 64 * sl + lane);
+                        cnt += __popcll(m);
+                    }
+                }
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                __builtin_amdgcn_wave_barrier();
+                const uint64_t key = lane < cnt ? s_k[wave][lane] : 0;
+                s3_candidates<false, CCtx>(c, a, c.rec3, lane < cnt, key, Ls, Lr, theta0, theta_pub, offered, mb);
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
     }
     if (cur >= 0) flush(*cur_ctx);
 }
@@ -2438,16 +3042,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S4_WPE))) v
                         const uint64_t lr = lex_rank(BinomTab{c.btab, c.S}, c.S, 4, tup);
                         if (lr < a.r0 || lr >= a.r1) take = false;
                     }
-                    unsigned long long m = __ballot(take);
-                    const uint64_t rk = take ? pack_tuple(tup, 4) : 0;
-                    offered += (unsigned)__popcll(m);
-                    while (m) {
-                        const int src = __ffsll((long long)m) - 1;
-                        m &= m - 1;
-                        const double cs = __shfl(es, src);
-                        const uint64_t cr = (uint64_t)__shfl((long long)rk, src);
-                        list_insert(Ls, Lr, KP, cs, cr);
-                    }
+                    list_insert_lanes(Ls, Lr, KP, take, take ? pack_tuple(tup, 4) : 0, es, offered);
                 }
             }
         }
@@ -2457,77 +3052,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S4_WPE))) v
             if (lane == 0) theta_publish(c.theta_bits, tw);
         }
         }
-    }
-    if (lane == 0 && offered) atomicAdd(c.cand_counter, offered);
-    list_store(c.list_sse + gw * KP, c.list_rank + gw * KP, Ls, Lr, KP);
-}
-
-// Several tasks, D = 3: exclusive prefix of the queued chunks' counts (one
-// workgroup of PRE_WG threads, PRE_WG consecutive counts per pass).
-__global__ __launch_bounds__(PRE_WG) void mt_scan_kernel(Ctx c, int nown) {
-    __shared__ unsigned wsum[PRE_WG / 64];
-    __shared__ unsigned long long carry;
-    const int nreg = (int)min(*c.mtq_taken + (unsigned)nown, (unsigned)c.mtq_chunks);
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    for (int base = 0; base < nreg; base += PRE_WG) {
-        const int r = base + (int)threadIdx.x;
-        const unsigned v = r < nreg ? c.mtq_n[r] : 0u;
-        const unsigned incl = block_scan(v, wsum);
-        const unsigned long long cy = carry;
-        if (r < nreg) c.mtq_pre[r] = cy + incl - v;
-        __syncthreads();
-        if (threadIdx.x == PRE_WG - 1) carry = cy + incl;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) c.mtq_pre[nreg] = carry;
-}
-
-// Several tasks, D = 3: scores the queued sweep steps.  The steps, in chunk
-// order, are cut into equal contiguous runs, one per wave.  For each step the
-// wave scores the steps with mt_step and mt_flush.  Wave gw starts from the
-// sweep's list gw.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) void mt_eval_kernel(
-    Ctx c, SearchArgs a, const double *__restrict__ rec, int nown) {
-    extern __shared__ double smem[];
-    const int KP = a.KP;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t gw = (int64_t)blockIdx.x * SEARCH_WAVES + wave;
-    const int64_t nw = (int64_t)gridDim.x * SEARCH_WAVES;
-    double *Ls = smem + (size_t)wave * KP * 2;
-    uint64_t *Lr = reinterpret_cast<uint64_t *>(Ls + KP);
-    list_load(Ls, Lr, c.list_sse + gw * KP, c.list_rank + gw * KP, KP);
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_wave_barrier();
-    const int nreg = (int)min(*c.mtq_taken + (unsigned)nown, (unsigned)c.mtq_chunks);
-    const uint64_t total = nreg > 0 ? c.mtq_pre[nreg] : 0;
-    const uint64_t per = (total + nw - 1) / nw;
-    const uint64_t e0 = (uint64_t)gw * per, e1 = e0 + per < total ? e0 + per : total;
-    double th = fmin(theta0_of(c), theta_load(c.theta_bits));
-    const double theta_f = th < INF ? th * (1.0 + THETA_SLACK) : INF;
-    __shared__ uint64_t s_bk[SEARCH_WAVES][MT_BUF];
-    __shared__ double s_be[SEARCH_WAVES][MT_BUF];
-    uint64_t *bk = s_bk[wave];
-    double *be = s_be[wave];
-    int nbuf = 0;
-    unsigned offered = 0;
-    if (e0 < e1) {
-        int lo = 0, hi = nreg - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (c.mtq_pre[mid] <= e0) lo = mid; else hi = mid - 1;
-        }
-        int reg = lo;
-        for (uint64_t e = e0; e < e1; ++e) {
-            while (reg + 1 <= nreg - 1 && c.mtq_pre[reg + 1] <= e) ++reg;
-            const int64_t at = ((int64_t)reg * MTQ_CHUNK + (int64_t)(e - c.mtq_pre[reg])) * 3;
-            const uint64_t w0 = c.mtq[at];
-            offered += mt_step(c, a, rec, Ls, Lr, KP, bk, be, nbuf, (int64_t)(w0 >> 40),
-                               (int64_t)((w0 >> 20) & 0xFFFFF), (int64_t)(w0 & 0xFFFFF), c.mtq[at + 1],
-                               c.mtq[at + 2], theta_f);
-        }
-        if (nbuf > 0) offered += mt_flush(c, Ls, Lr, KP, bk, be, nbuf, theta_f);
     }
     if (lane == 0 && offered) atomicAdd(c.cand_counter, offered);
     list_store(c.list_sse + gw * KP, c.list_rank + gw * KP, Ls, Lr, KP);
@@ -2561,12 +3085,8 @@ __global__ __launch_bounds__(256) void search_d1_kernel(Ctx c, SearchArgs a) {
             }
             if (a.ranged && ((uint64_t)k < a.r0 || (uint64_t)k >= a.r1)) s = INF;
         }
-        unsigned long long m = __ballot(s < INF && s <= Ls[KP - 1]);
-        while (m) {
-            const int src = __ffsll((long long)m) - 1;
-            m &= m - 1;
-            list_insert(Ls, Lr, KP, __shfl(s, src), (uint64_t)(kb + src));
-        }
+        unsigned offered = 0;
+        list_insert_lanes(Ls, Lr, KP, s < INF && s <= Ls[KP - 1], (uint64_t)k, s, offered);
     }
     list_store(c.list_sse + gw * KP, c.list_rank + gw * KP, Ls, Lr, KP);
 }
@@ -3478,7 +3998,7 @@ static void s3_prologue(const Ctx &c, const SearchCall &sc, hipStream_t st) {
     const int64_t ninit = (int64_t)init_blocks * 256;
     if (bx * PRE_WG * ngr < ninit) bx = (ninit / ngr + PRE_WG - 1) / PRE_WG + 1;
     // one more column: its first workgroup runs the pre-pass selection
-    hipLaunchKernelGGL(rec3_kernel, dim3((unsigned)(bx + 1), (unsigned)ngr), dim3(PRE_WG), 0, st, c, c.rec3);
+    hipLaunchKernelGGL(rec3_kernel, dim3((unsigned)(bx + 1), (unsigned)ngr, 2), dim3(PRE_WG), 0, st, c, c.rec3);
     launch_prepass<3>(c, sc, st, false);
 }
 
@@ -3538,8 +4058,7 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
         // one task, D = 3: record table + tile sweep (tile count within the 32-bit work counter)
         // D = 3: the record-table sweep, on the filter task's matrix when
         // there are several tasks
-        const bool s3 = D == 3 && !c.fp32 && c.rec3 != nullptr && s3_tiles_host(c.S) < (1ull << 31) &&
-                        (!MT || c.mtq_chunks > 0);
+        const bool s3 = D == 3 && !c.fp32 && c.rec3 != nullptr && s3_tiles_host(c.S) < (1ull << 31);
         // one task, D = 4: the pair-group record table (sized at create only
         // while it stays within S4_TABLE_MAX and 2^31 tiles)
         const bool s4 = D == 4 && !MT && !c.fp32 && c.rec4 != nullptr;
@@ -3554,7 +4073,7 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
             const int64_t ninit = (int64_t)init_blocks * 256;
             if (bx * PRE_WG * ngr < ninit) bx = (ninit / ngr + PRE_WG - 1) / PRE_WG + 1;
             // one more column: its first workgroup runs the pre-pass selection
-            hipLaunchKernelGGL(rec3_kernel, dim3((unsigned)(bx + 1), (unsigned)ngr), dim3(PRE_WG), 0, st, c, c.rec3);
+            hipLaunchKernelGGL(rec3_kernel, dim3((unsigned)(bx + 1), (unsigned)ngr, 2), dim3(PRE_WG), 0, st, c, c.rec3);
         } else {
             hipLaunchKernelGGL(search_init_kernel, dim3(init_blocks), dim3(256), 0, st, c, D, a.R, a.JB, 0);
         }
@@ -3575,17 +4094,25 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
         if (s4) {
             hipLaunchKernelGGL(search4_kernel, dim3(c.search_wgs), dim3(SEARCH_WG), lds_lists, st, c, a,
                                (const double *)c.rec4, (const uint64_t *)c.cum);
-        } else if (s3 && MT) {
-            hipLaunchKernelGGL(search3_kernel<true>, dim3(c.search_wgs), dim3(SEARCH_WG), lds_lists, st, c, a,
-                               (const double *)c.rec3, (const uint64_t *)c.cum);
-            const int nown = c.search_wgs * SEARCH_WAVES;  // the sweep waves' own chunks
-            hipLaunchKernelGGL(mt_scan_kernel, dim3(1), dim3(PRE_WG), 0, st, c, nown);
-            hipLaunchKernelGGL(mt_eval_kernel, dim3(c.search_wgs), dim3(SEARCH_WG), lds_lists, st, c, a,
-                               (const double *)c.rec3, nown);
+        } else if (s3) {
+            const uint64_t ntiles = s3_tiles_host(c.S);
+            const uint32_t nseg = (uint32_t)c.search_wgs;
+            const int limit = s3_lanes(c.T);
+            const size_t lds3 = lds_lists + (size_t)2 * (nseg + 1) * sizeof(uint64_t);
+            for (uint64_t t0 = 0; t0 < ntiles; t0 += S3_PASS) {
+                const uint64_t t1 = t0 + S3_PASS < ntiles ? t0 + S3_PASS : ntiles;
+                const uint32_t tiles = (uint32_t)s3_wg_tiles(t1 - t0, c.search_wgs);
+                hipLaunchKernelGGL(search3_kernel, dim3(c.search_wgs), dim3(SEARCH_WG), 0, st, c,
+                                   (const double *)c.recg, (const double *)c.gfac, (const uint64_t *)c.cum, t0, t1,
+                                   tiles, limit);
+                if (MT)
+                    hipLaunchKernelGGL(s3_eval_kernel<true>, dim3(c.search_wgs), dim3(SEARCH_WG), lds3, st, c, a,
+                                       (const double *)c.rec3, nseg, tiles, limit, t0 > 0);
+                else
+                    hipLaunchKernelGGL(s3_eval_kernel<false>, dim3(c.search_wgs), dim3(SEARCH_WG), lds3, st, c, a,
+                                       (const double *)c.rec3, nseg, tiles, limit, t0 > 0);
+            }
         }
-        else if (s3)
-            hipLaunchKernelGGL(search3_kernel<false>, dim3(c.search_wgs), dim3(SEARCH_WG), lds_lists, st, c, a,
-                               (const double *)c.rec3, (const uint64_t *)c.cum);
         else switch (D) {
             case 2: MT ? launch_one<2, true>(c, a, lds, st) : launch_one<2, false>(c, a, lds, st); break;
             case 3: MT ? launch_one<3, true>(c, a, lds, st) : launch_one<3, false>(c, a, lds, st); break;
