@@ -148,21 +148,21 @@ static Layout compute_layout(int64_t n_total, int64_t S, int T, int D_max, int k
     L.rec3 = take(L.rec3_bytes);
     L.recg = take(L.rec3_bytes ? (size_t)s3_group_rows(S) * 16 * d : 0);
     L.gfac = take(L.rec3_bytes ? (size_t)(S / 8 + 1) * 2 * 16 * d : 0);
-    // D = 4, one task: a record row per (pair group, j); kept only while the
+    // D = 4, one task: a record per (pair of groups, j); kept only while the
     // table stays within S4_TABLE_MAX (else the general kernel runs)
     {
-        const int64_t rows4 = S >= 4 ? s4_rows_below(S, S - 2) : 0;
-        const size_t b4 = (size_t)rows4 * S4_ROW * d;
+        const size_t b4 = (size_t)s4_rows_host(S) * 12 * d;
         L.rec4_bytes = (D_max >= 4 && T == 1 && S >= 4 && !fp32 && b4 <= S4_TABLE_MAX && s4_tiles_host(S) < (1ull << 31)) ? b4 : 0;
     }
     L.rec4 = take(L.rec4_bytes);
-    L.r4off = take(L.rec4_bytes ? (size_t)(S + 1) * sizeof(int64_t) : 0);
+    L.fac4 = take(L.rec4_bytes ? (size_t)s4_pairs_host(S) * 48 * d : 0);
     L.G1_bytes = (D_max >= 3 && S >= 3 && T > 1) ? Sp * Sp * d : 0;
     L.G1 = take(L.G1_bytes);
-    // D = 3: per tile and group up to s3_lanes candidates or 8 row items
-    const size_t pt3 = L.rec3_bytes ? s3_pool_tiles(S) : 0;
-    L.s3_cands = take(pt3 * 2 * s3_lanes(T) * sizeof(uint64_t));
-    L.s3_rows = take(pt3 * 2 * 8 * sizeof(uint64_t));
+    // D = 3: per tile and group up to s3_lanes candidates or 8 row items;
+    // D = 4: per tile up to S4_LANES candidates or 4 items
+    const size_t pt3 = L.rec3_bytes ? s3_pool_tiles(S) : 0, pt4 = L.rec4_bytes ? s4_pool_tiles(S) : 0;
+    L.s3_cands = take(std::max(pt3 * 2 * s3_lanes(T), pt4 * S4_LANES) * sizeof(uint64_t));
+    L.s3_rows = take(std::max(pt3 * 2 * 8, pt4 * 4) * sizeof(uint64_t));
     L.s3_count = take(L.rec3_bytes ? (size_t)SEARCH_WGS_MAX * 2 * sizeof(uint32_t) : 0);
     L.lists = take((size_t)nlists * L.KP * 2 * d + (size_t)nlists * L.KP * 2 * d);
     // FP64 Gram: the residues take the zone above, GM_KC_MIN samples at a time
@@ -276,7 +276,7 @@ static void carve(sisso_l0 *h) {
     c.gfac = L.rec3_bytes ? (double *)(base + L.gfac) : nullptr;
     c.G1 = L.G1_bytes ? (double *)(base + L.G1) : c.G;
     c.rec4 = L.rec4_bytes ? (double *)(base + L.rec4) : nullptr;
-    c.r4off = L.rec4_bytes ? (int64_t *)(base + L.r4off) : nullptr;
+    c.fac4 = L.rec4_bytes ? (double *)(base + L.fac4) : nullptr;
     c.s3_cands = L.rec3_bytes ? (uint64_t *)(base + L.s3_cands) : nullptr;
     c.s3_rows = L.rec3_bytes ? (uint64_t *)(base + L.s3_rows) : nullptr;
     c.s3_count = L.rec3_bytes ? (uint32_t *)(base + L.s3_count) : nullptr;

@@ -234,29 +234,8 @@ __host__ __device__ inline void colex_unrank_small(uint64_t r, int q, int64_t N,
     colex_unrank(BinomCalc{}, r, q, N, t);
 }
 
-// ----------------------------------------- D = 4, one task: record table
-// Pairs (i1, i2) of a D = 4 prefix are grouped four at a time: group
-// (i2, h) holds i1 = 4h .. 4h + 3 (those >= i2 are void), so a group exists
-// for h < ceil(i2 / 4).  Groups are ordered by i2, then h.
-constexpr int S4_NR = 4;        // pairs per group
-constexpr int S4_RECW = 5;      // doubles per pair record: v0, v1, 1/d_j, z_j / s_j, p
-constexpr int S4_ROW = S4_NR * S4_RECW;  // doubles per record row (160 bytes)
-constexpr int S4_KC = 128;      // k per tile: two adjacent per lane
-constexpr int S4_JR = 32;       // j rows per tile (divides 64)
-constexpr size_t S4_TABLE_MAX = (size_t)4 << 30;  // largest record table kept in the workspace
-
-// groups with i2 < i: sum over i' < i of ceil(i' / 4)
-__host__ __device__ inline int64_t s4_groups_below(int64_t i) {
-    if (i <= 1) return 0;
-    const int64_t N = i - 1, a = N / 4, b = N % 4;
-    return (i - 1) + 2 * a * (a - 1) + b * a;
-}
-// record rows of the groups with i2 < i: sum over i' < i of ceil(i'/4) (S - 2 - i')
-__host__ __device__ inline int64_t s4_rows_below(int64_t S, int64_t i) {
-    int64_t acc = 0;
-    for (int64_t x = 1; x < i && x <= S - 3; ++x) acc += ((x + 3) / 4) * (S - 2 - x);
-    return acc;
-}
+constexpr size_t S4_TABLE_MAX = (size_t)4 << 30;  // largest D = 4 record table kept in the workspace
+constexpr int S4_LANES = 1024;  // D = 4: most flagged candidates of a tile that are scored one by one
 
 // Device state of the threshold pre-pass (reset by its selection).
 struct PreState {
@@ -299,12 +278,12 @@ struct Layout {
     size_t gfac;
     size_t G1;         // D = 3, several tasks: the filter task's matrix alone, double [S][S] tiled (0 bytes otherwise)
     size_t G1_bytes;
-    size_t rec4;       // D = 4, one task: pair-group records, double [rows][S4_ROW] (0 bytes otherwise)
+    size_t rec4;       // D = 4, one task: group-pair records, double [rows][12] (0 bytes otherwise)
     size_t rec4_bytes;
+    size_t fac4;       //   and group-pair factors, double [pairs][48]
     size_t self;       // a device copy of the handle's Ctx (read by the batched search)
     size_t btab;       // batched search: item prefix and context table, when this handle leads a batch
-    size_t r4off;      //   int64 [S + 1] record rows of the groups below each i2
-    size_t s3_cands;   // D = 3: pools of flagged candidates and rows, and their counts per workgroup
+    size_t s3_cands;   // D = 3, 4: pools of flagged candidates and rows, and their counts per workgroup
     size_t s3_rows;
     size_t s3_count;
     size_t lists;      // per-wave top lists: (double sse, uint64 rank) [nwaves][KP]

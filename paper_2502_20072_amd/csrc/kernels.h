@@ -38,9 +38,9 @@ struct Ctx {
     double *recg;                    // D = 3: group records of the filter task [rows of group pairs][2][8] (null if absent)
     double *gfac;                    //   group factors [groups, padded to even][16]
     double *G1;                      // the filter task's matrix alone, one-task tiled layout (G itself when T = 1)
-    double *rec4;                    // D = 4, one task: pair-group records [rows][S4_ROW] (null if absent)
-    int64_t *r4off;                  //   record rows of the groups with i2 below each index [S + 1]
-    uint64_t *s3_cands;              // D = 3: flagged (group, row, column) candidates, a segment per workgroup
+    double *rec4;                    // D = 4, one task: group-pair records [rows][12] (null if absent)
+    double *fac4;                    //   group-pair factors [pairs][48]
+    uint64_t *s3_cands;              // D = 3, 4: flagged (group, row, column) candidates, a segment per workgroup
     uint64_t *s3_rows;               //   and flagged rows of dense (group, row block, column chunk)s
     uint32_t *s3_count;              //   of each segment: candidates, row items [SEARCH_WGS_MAX][2]
     int32_t *tstar;                  // filter tasks [2]: the tasks of largest and second largest
@@ -83,6 +83,9 @@ size_t s3_pool_tiles(int64_t S);    // tiles its item pools have to hold
 int s3_lanes(int T);                // candidates per (tile, group) in them
 int64_t s3_group_rows(int64_t S);   // rows of its group-record table
 uint64_t s4_tiles_host(int64_t S);  // tiles of the D = 4 record-table sweep
+size_t s4_pool_tiles(int64_t S);    // tiles its item pools have to hold
+int64_t s4_rows_host(int64_t S);    // rows of its record table
+int64_t s4_pairs_host(int64_t S);   // pairs of groups
 int launch_stats(const Ctx &c, hipStream_t st);
 int launch_gram(const Ctx &c, hipStream_t st);  // correlation matrices: FP64 or precision form
 int launch_gram_mod(const Ctx &c, hipStream_t st);

@@ -343,7 +343,7 @@ __device__ void wave_sort_list(double *Ls, uint64_t *Lr, int KP) {
 // {0..N_jb-2}, grouped R at a time.
 __device__ void s3_tile_table(const Ctx &c);
 
-__device__ void s4_tables(const Ctx &c);
+__device__ void s4_tile_table(const Ctx &c);
 
 // s3: 0 = work-item table of the general kernel, 4 = the D = 4 record-table
 // tiles, other = the D = 3 record-table tiles
@@ -362,7 +362,7 @@ __device__ void search_init_body(const Ctx &c, int64_t e, bool leader, int D, in
         c.flags[FLAG_NLISTS] = 0;
         c.stats[1] = 0;
         if (s3 == 4) {
-            s4_tables(c);
+            s4_tile_table(c);
             return;
         }
         if (s3) {
@@ -2354,6 +2354,52 @@ size_t s3_pool_tiles(int64_t S) {
 }
 int s3_lanes(int T) { return T > 1 ? S3_LANES_MT : S3_LANES; }
 
+// first[p][s] = items of pool p in the segments before s, first[p][nseg] = all
+// of them (workgroup-wide, 256 threads; ends with a barrier)
+__device__ void pool_scan(const uint32_t *__restrict__ count, uint32_t nseg, uint64_t *const (&first)[2],
+                          unsigned long long (*s_w)[SEARCH_WAVES]) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // thread i owns segments i per .. (i + 1) per - 1
+    const uint32_t per = (nseg + 255) / 256;
+    unsigned long long own[2] = {0, 0}, incl[2];
+    for (uint32_t x = 0; x < per; ++x) {
+        const uint32_t s = tid * per + x;
+        if (s < nseg)
+            for (int p = 0; p < 2; ++p) own[p] += count[2 * s + p];
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        incl[p] = own[p];
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned long long y = (unsigned long long)__shfl_up((long long)incl[p], o);
+            if (lane >= o) incl[p] += y;
+        }
+        if (lane == 63) s_w[p][wave] = incl[p];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        unsigned long long at = incl[p] - own[p];
+        for (int w = 0; w < wave; ++w) at += s_w[p][w];
+        for (uint32_t x = 0; x < per; ++x) {
+            const uint32_t s = tid * per + x;
+            if (s >= nseg) break;
+            first[p][s] = at;
+            at += count[2 * s + p];
+        }
+        if (tid == 255) first[p][nseg] = at;
+    }
+    __syncthreads();
+}
+__device__ inline uint32_t pool_segment(const uint64_t *first, uint32_t nseg, uint64_t e) {
+    uint32_t lo = 0, hi = nseg - 1;
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi + 1) >> 1;
+        if (first[mid] <= e) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
+
 // Scores the pools: the candidates 64 at a time, one per lane, and the row
 // items in equal contiguous runs, one run per wave (consecutive items of one
 // group, row block and column chunk are swept together).  Every workgroup
@@ -2369,8 +2415,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) v
     __shared__ double s_be[MT ? SEARCH_WAVES : 1][MT ? MT_BUF : 1];
     __shared__ unsigned long long s_w[2][SEARCH_WAVES];
     const int KP = a.KP;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     double *Ls = smem + (size_t)wave * KP * 2;
     uint64_t *Lr = reinterpret_cast<uint64_t *>(Ls + KP);
     // first[p][s]: items of pool p in the segments before s
@@ -2379,23 +2425,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) v
     first[1] = first[0] + nseg + 1;
     const int64_t gw = (int64_t)blockIdx.x * SEARCH_WAVES + wave;
     const uint64_t nw = (uint64_t)gridDim.x * SEARCH_WAVES;
-    // thread i owns segments i per .. (i + 1) per - 1
-    const uint32_t per = (nseg + 255) / 256;
-    unsigned long long own[2] = {0, 0}, incl[2];
-    for (uint32_t x = 0; x < per; ++x) {
-        const uint32_t s = tid * per + x;
-        if (s < nseg)
-            for (int p = 0; p < 2; ++p) own[p] += c.s3_count[2 * s + p];
-    }
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        incl[p] = own[p];
-        for (int o = 1; o < 64; o <<= 1) {
-            const unsigned long long y = (unsigned long long)__shfl_up((long long)incl[p], o);
-            if (lane >= o) incl[p] += y;
-        }
-        if (lane == 63) s_w[p][wave] = incl[p];
-    }
     if (resume) {
         list_load(Ls, Lr, c.list_sse + gw * KP, c.list_rank + gw * KP, KP);
     } else {
@@ -2404,29 +2433,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) v
             Lr[m] = ~0ull;
         }
     }
-    __syncthreads();
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        unsigned long long at = incl[p] - own[p];
-        for (int w = 0; w < wave; ++w) at += s_w[p][w];
-        for (uint32_t x = 0; x < per; ++x) {
-            const uint32_t s = tid * per + x;
-            if (s >= nseg) break;
-            first[p][s] = at;
-            at += c.s3_count[2 * s + p];
-        }
-        if (tid == 255) first[p][nseg] = at;
-    }
-    __syncthreads();
+    pool_scan(c.s3_count, nseg, first, s_w);
     // the segment of item e of pool p
-    auto segment = [&](int p, uint64_t e) {
-        uint32_t lo = 0, hi = nseg - 1;
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi + 1) >> 1;
-            if (first[p][mid] <= e) lo = mid; else hi = mid - 1;
-        }
-        return lo;
-    };
+    auto segment = [&](int p, uint64_t e) { return pool_segment(first[p], nseg, e); };
     const uint64_t ncand = uni(first[0][nseg]), nitem = uni(first[1][nseg]);
     const double theta0 = theta0_of(c);
     double theta_pub = INF;
@@ -2614,402 +2623,639 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3B_WPE))) 
 }
 
 // ------------------------------------------- D = 4, one task: record table
-// The D = 3 design one level up.  For every prefix (i1, i2, j) the Cholesky
-// row of j against the pair is built once per search into a table
-// (rec4_kernel); the sweep reads the rows of one pair group (four i1 with
-// the same i2) for one j with scalar loads, so the records enter the FP64
-// instructions as scalar operands.  A work tile is (pair group, S4_JR rows j
-// from j0, S4_KC columns k from j0 + 1 + S4_KC c): lane l takes k = kb + l and
-// kb + 64 + l, so only chunk 0 holds tuples with k <= j (in its first half),
-// and a last chunk with at most 64 columns left runs its first half only.
-// Per tuple, with the pair's
-// k-dependent terms w0 = G[i1][k], w1 = (G[i2][k] - r w0) / s (r = G[i1][i2],
-// s = sqrt(1 - r^2)), d' = G[k][k] - w0^2 - w1^2 and zeta' = b_k - w0 z0 -
-// w1 z1 held in registers for the tile:
-//   u = g - v0 w0 - v1 w1,  d = d' - alpha u^2,  zeta = zeta' - zs u,
-//   pass iff zeta^2 >= (p - theta) d.
-// Record of (i1, i2, j), i1 = 4 h + r in group (i2, h), row
-// R = r4off[i2] + h (S - 2 - i2) + j - i2 - 1:
-//   rec[(R S4_NR + r) S4_RECW + {0..4}] = {v0, v1, 1/d_j, z_j / s_j, p}
-// with v0 = G[i1][j], v1 = (G[i2][j] - r v0) / s, d_j = G[j][j] - v0^2 - v1^2,
-// z0 = b_i1, z1 = (b_i2 - r z0) / s, z_j = (b_j - v0 z0 - v1 z1) / s_j,
-// s_j = sqrt(d_j), p = c - z0^2 - z1^2 - z_j^2 (the SSE of the triple);
-// p = NaN (fails every comparison) unless i1 < i2 < j, column i1 is live,
-// 1 - r^2 > RANK_EPS and d_j > RANK_EPS.
+// The D = 3 design one level up, with a larger superset.  The indices are cut
+// into groups of four; per pair of groups (g1 <= g2) and j the Cholesky row of
+// j against the pair's eight columns is built once per search (rec4_kernel).
+// The sweep tests, per (pair, j, k), the fit on all ten features {g1, g2, j,
+// k}: 13 FP64 instructions for sixteen tuples i1 in g1, i2 in g2, against 144
+// for testing the tuples one by one.  A tuple's SSE is at least that of any
+// superset, so only where that bound is at or below the threshold are the
+// sixteen tuples tested themselves (on operator-tree columns, n = 2000, S =
+// 600: 0.4 in 1000).  A work tile is (pair, S3_JR rows j from j0, S3_KC columns k
+// from j0 + 1 + S3_KC c), its lanes as in search3_kernel; what a tile flags
+// goes to its workgroup's segments of two pools, which s4_eval_kernel scores:
+// the candidates (g1, g2, j, k) one per lane while there are at most S4_LANES
+// of them, else (also without a threshold) the whole tile, one item per i2.
+// Bound by FP64 issue.  n = 2000, S = 600: @@
 #ifndef S4_WPE
-#define S4_WPE 3                      // waves per SIMD the register budget is sized for
+#define S4_WPE 4                      // waves per SIMD the register budget is sized for
 #endif
-#ifndef S4_WRUN
-#define S4_WRUN 4                     // consecutive tiles per wave
-#endif
-// row block jb: nkb column chunks (k from j0 + 1 to S - 1) and ng pair groups
-__host__ __device__ inline void s4_block(int64_t S, int64_t jb, int64_t &nkb, int64_t &ng) {
-    const int64_t j0 = jb * S4_JR;
-    int64_t jmax = j0 + S4_JR - 1;
+constexpr int S4_NR = 4;              // indices per group
+constexpr int S4_REC = 12;            // doubles per record: v0..v7, 1/d, zs, p, zs^2 (as in the D = 3 group records)
+constexpr int S4_FAC = 48;            // doubles per factor: R^-1 (36), z (8), SSE of the pair, dependent columns
+constexpr double S4_NORM = 1e6;       // largest squared Frobenius norm of R^-1 the slacks cover
+// A large search runs in passes of S4_PASS tiles (bound, then scoring), which
+// bounds the candidate pool at 1.1 GB.
+constexpr uint64_t S4_PASS = 1ull << 17;
+
+// groups with a tuple (i2 in the group, j = i2 + 1 <= S - 2)
+__host__ __device__ inline int64_t s4_groups(int64_t S) { return S >= 4 ? (S - 3) / S4_NR + 1 : 0; }
+__host__ __device__ inline int64_t s4_pairs_below(int64_t g) { return g * (g + 1) / 2; }  // pairs with g2 < g
+// Record rows of pair (g1, g2): j = 4 g2 + 1 .. S - 2, from row
+// sum over g < g2 of (g + 1) (S - 2 - 4 g), and g1 (S - 2 - 4 g2) more
+__host__ __device__ inline int64_t s4_rowoff(int64_t S, int64_t g1, int64_t g2) {
+    return (S - 2) * s4_pairs_below(g2) - S4_NR * ((g2 - 1) * g2 * (g2 + 1) / 3) + g1 * (S - 2 - S4_NR * g2);
+}
+// pairs with rows in row block jb
+__host__ __device__ inline int64_t s4_block_pairs(int64_t S, int64_t jb) {
+    int64_t jmax = jb * S3_JR + S3_JR - 1;
     if (jmax > S - 2) jmax = S - 2;
-    nkb = (S - j0 - 1 + S4_KC - 1) / S4_KC;
-    ng = jmax >= 2 ? s4_groups_below(jmax) : 0;  // groups with i2 < jmax
+    return jmax >= 1 ? s4_pairs_below((jmax - 1) / S4_NR + 1) : 0;
 }
-__host__ __device__ inline int64_t s4_nblocks(int64_t S) { return S >= 4 ? (S - 2) / S4_JR + 1 : 0; }
-
-// pair group index -> (i2, h): i2 is the largest index whose groups start at or before g
-__device__ inline int64_t s4_group_i2(int64_t S, int64_t g) {
-    int64_t lo = 1, hi = S - 3;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi + 1) >> 1;
-        if (s4_groups_below(mid) <= g) lo = mid; else hi = mid - 1;
-    }
-    return lo;
+__host__ __device__ inline int64_t s4_block_chunks(int64_t S, int64_t jb) {
+    return (S - jb * S3_JR - 1 + S3_KC - 1) / S3_KC;
+}
+__device__ inline void s4_pair(int64_t p, int64_t &g1, int64_t &g2) {
+    g2 = (int64_t)((sqrt(8.0 * (double)p + 1.0) - 1.0) * 0.5);
+    while (s4_pairs_below(g2) > p) --g2;
+    while (s4_pairs_below(g2 + 1) <= p) ++g2;
+    g1 = p - s4_pairs_below(g2);
 }
 
-// tcum[jb] = tiles of the blocks before jb; r4off[i] = record rows of the
-// groups with i2 < i (serial, leader thread of the initialisation)
-__device__ void s4_tables(const Ctx &c) {
-    const int64_t S = c.S;
-    const int64_t nb = s4_nblocks(S);
+int64_t s4_rows_host(int64_t S) { return S >= 4 ? s4_rowoff(S, 0, s4_groups(S)) : 0; }
+int64_t s4_pairs_host(int64_t S) { return s4_pairs_below(s4_groups(S)); }
+uint64_t s4_tiles_host(int64_t S) {
+    uint64_t acc = 0;
+    for (int64_t b = 0; S >= 4 && b < s3_nblocks(S); ++b) acc += (uint64_t)(s4_block_pairs(S, b) * s4_block_chunks(S, b));
+    return acc;
+}
+size_t s4_pool_tiles(int64_t S) {
+    const uint64_t n = s4_tiles_host(S);
+    return (size_t)((n < S4_PASS ? n : S4_PASS) + (uint64_t)S3_XCD_RUN * S3_XCDS + (uint64_t)SEARCH_WGS_MAX * SEARCH_WAVES);
+}
+
+// tcum[jb] = tiles of the blocks before jb
+__device__ void s4_tile_table(const Ctx &c) {
+    const int64_t nb = s3_nblocks(c.S);
     uint64_t acc = 0;
     c.cum[0] = 0;
     for (int64_t b = 0; b < nb; ++b) {
-        int64_t nkb, ng;
-        s4_block(S, b, nkb, ng);
-        acc += (uint64_t)(nkb * ng);
+        acc += (uint64_t)(s4_block_pairs(c.S, b) * s4_block_chunks(c.S, b));
         c.cum[b + 1] = acc;
     }
     c.stats[1] = acc;
-    int64_t rows = 0;
-    for (int64_t i = 0; i <= S; ++i) {
-        c.r4off[i] = rows;
-        if (i >= 1 && i <= S - 3) rows += ((i + 3) / 4) * (S - 2 - i);
-    }
 }
 
-uint64_t s4_tiles_host(int64_t S) {
-    const int64_t nb = s4_nblocks(S);
-    uint64_t acc = 0;
-    for (int64_t b = 0; b < nb; ++b) {
-        int64_t nkb, ng;
-        s4_block(S, b, nkb, ng);
-        acc += (uint64_t)(nkb * ng);
+// The factor of pair e = (g1, g2): of its live columns in index order, G =
+// R^T R, {R^-1 by rows, z = R^-T b, c - |z|^2, and whether a column is too close to
+// dependent for the bound}.  The columns past S, the constant ones and, with
+// g1 = g2, the second four have zero rows.
+__device__ void s4_factor(const Ctx &c, int64_t e) {
+    int64_t g1, g2;
+    s4_pair(e, g1, g2);
+    const int64_t S = c.S, nt = c.Gnt;
+    const double *__restrict__ G1 = c.G1;
+    constexpr int N = 2 * S4_NR;
+    int64_t id[N];
+    bool live[N];
+#pragma unroll
+    for (int m = 0; m < N; ++m) {
+        const int64_t i = S4_NR * (m < S4_NR ? g1 : g2) + m % S4_NR;
+        id[m] = i < S ? i : S - 1;
+        live[m] = i < S && c.inv_s[id[m]] > 0.0 && (m < S4_NR || g1 != g2);
     }
-    return acc;
+    double L[N][N], Li[N][N], pg = c.cyy[0], norm = 0.0;
+    bool bad = false;
+    double *f = c.fac4 + e * S4_FAC;
+#pragma unroll
+    for (int m = 0; m < N; ++m) {
+        double d = 1.0;
+#pragma unroll
+        for (int l = 0; l < m; ++l) {
+            double s = live[m] ? G1[gidx(id[l], id[m], nt, 1, 0)] : 0.0;
+#pragma unroll
+            for (int q = 0; q < l; ++q) s -= L[m][q] * L[l][q];
+            L[m][l] = s * Li[l][l];
+            d -= L[m][l] * L[m][l];
+        }
+        bad |= live[m] && !(d > S3_TAU);
+        Li[m][m] = live[m] && d > S3_TAU ? 1.0 / sqrt(d) : 0.0;
+        double zz = Li[m][m] * c.bhat[id[m]];
+#pragma unroll
+        for (int l = 0; l < m; ++l) {
+            double s = 0.0;
+#pragma unroll
+            for (int q = l; q < m; ++q) s += L[m][q] * Li[q][l];
+            Li[m][l] = -Li[m][m] * s;
+            zz += Li[m][l] * c.bhat[id[l]];
+        }
+#pragma unroll
+        for (int l = 0; l <= m; ++l) {
+            f[m * (m + 1) / 2 + l] = Li[m][l];
+            norm += Li[m][l] * Li[m][l];
+        }
+        f[36 + m] = zz;
+        pg -= zz * zz;
+    }
+    f[44] = pg;
+    f[45] = bad || !(norm <= S4_NORM) ? 1.0 : 0.0;
+    f[46] = f[47] = 0.0;
 }
 
-// first record row and row count of tile t
-__device__ inline void s4_tile_rows(const Ctx &c, const uint64_t *__restrict__ tcum, int64_t nb, uint64_t t,
-                                    int64_t &row, int64_t &nrows) {
-    const int64_t S = c.S;
-    int64_t lo = 0, hi = nb - 1;
+__global__ __launch_bounds__(64) void s4_init_kernel(Ctx c) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    search_init_body(c, e, e == 0, 4, SUBP, JBLK, 4);
+    if (e < s4_pairs_below(s4_groups(c.S))) s4_factor(c, e);
+}
+
+// One wave per (row block, pair), one lane per j.  The records are staged in
+// LDS and written out as consecutive doubles (full cache lines).  Bound by the
+// writes: @@
+__global__ __launch_bounds__(256) void rec4_kernel(Ctx c, int64_t nitem) {
+    __shared__ double stage[SEARCH_WAVES][64 * S4_REC];
+    static_assert(S3_JR == 64, "a lane per row");
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int64_t it = (int64_t)blockIdx.x * SEARCH_WAVES + wave;
+    if (it >= nitem) return;
+    const int64_t S = c.S, nt = c.Gnt;
+    int64_t jb = 0;
+    for (;; ++jb) {
+        const int64_t n = s4_block_pairs(S, jb);
+        if (it < n) break;
+        it -= n;
+    }
+    int64_t g1, g2;
+    s4_pair(it, g1, g2);
+    g1 = uni(g1);
+    g2 = uni(g2);
+    const double *__restrict__ G1 = c.G1;
+    CDouble *f = cptr(c.fac4) + (s4_pairs_below(g2) + g1) * S4_FAC;
+    const int64_t j0 = jb * S3_JR, jlo = j0 > S4_NR * g2 + 1 ? j0 : S4_NR * g2 + 1;
+    const int64_t jhi = j0 + S3_JR - 1 < S - 2 ? j0 + S3_JR - 1 : S - 2;
+    const int64_t j = jlo + lane <= jhi ? jlo + lane : jhi;
+    constexpr int N = 2 * S4_NR;
+    double x[N], v[N], al = 0.0, zs = 0.0, p = f[44];
+#pragma unroll
+    for (int m = 0; m < N; ++m) {
+        const int64_t i = S4_NR * (m < S4_NR ? g1 : g2) + m % S4_NR;
+        x[m] = G1[gidx(i < S ? i : S - 1, j, nt, 1, 0)];
+        v[m] = 0.0;
+    }
+    if (!(c.inv_s[j] > 0.0)) {
+        p = S3_NEVER;
+    } else if (f[45] != 0.0) {
+        p = 0.0;
+    } else if (j >= S4_NR * (g2 + 1)) {  // (a j of g2 itself leaves the pair alone)
+        double d = 1.0, e = c.bhat[j];
+#pragma unroll
+        for (int m = 0; m < N; ++m) {
+            double s = 0.0;
+#pragma unroll
+            for (int l = 0; l <= m; ++l) s += f[m * (m + 1) / 2 + l] * x[l];
+            v[m] = s;
+            d -= s * s;
+            e -= s * f[36 + m];
+        }
+        if (d > S3_TAU) {
+            al = 1.0 / d;
+            zs = e * al;
+            p = p - e * zs;
+        } else {
+            p = 0.0;
+        }
+    }
+    double *o = stage[wave] + lane * S4_REC;
+#pragma unroll
+    for (int m = 0; m < N; ++m) o[m] = v[m];
+    o[8] = al;
+    o[9] = zs;
+    o[10] = p;
+    o[11] = zs * zs;
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_wave_barrier();
+    const int nvals = (int)(jhi - jlo + 1) * S4_REC;
+    double *out = c.rec4 + (s4_rowoff(S, g1, g2) + jlo - S4_NR * g2 - 1) * S4_REC;
+    for (int q = lane; q < nvals; q += 64) out[q] = stage[wave][q];
+}
+
+// tile t: its row block, column chunk and pair of groups (chunk fastest: the
+// waves of a workgroup share the records of a pair)
+__device__ __forceinline__ void s4_locate(int64_t S, const uint64_t *__restrict__ tcum, uint64_t t, S3Tile &tl,
+                                          int64_t &g1, int64_t &g2) {
+    int64_t lo = 0, hi = s3_nblocks(S) - 1;
     while (lo < hi) {
         const int64_t mid = (lo + hi + 1) >> 1;
         if (tcum[mid] <= t) lo = mid; else hi = mid - 1;
     }
-    int64_t nkb, ng;
-    s4_block(S, lo, nkb, ng);
-    const int64_t grp = (int64_t)(t - tcum[lo]) / nkb;
-    const int64_t i2 = s4_group_i2(S, grp);
-    const int64_t hh = grp - s4_groups_below(i2);
-    const int64_t j0 = lo * S4_JR;
-    const int64_t jlo = j0 > i2 + 1 ? j0 : i2 + 1;
-    const int64_t jhi = (j0 + S4_JR - 1 < S - 2) ? j0 + S4_JR - 1 : S - 2;
-    row = c.r4off[i2] + hh * (S - 2 - i2) + (jlo - i2 - 1);
-    nrows = jhi - jlo + 1;
+    const int64_t nkb = s4_block_chunks(S, lo);
+    const int64_t rem = (int64_t)(t - tcum[lo]);
+    tl.kcx = rem % nkb;
+    tl.j0 = lo * S3_JR;
+    tl.jhi = (tl.j0 + S3_JR - 1 < S - 2) ? tl.j0 + S3_JR - 1 : S - 2;
+    tl.kb = tl.j0 + 1 + tl.kcx * S3_KC;
+    s4_pair(rem / nkb, g1, g2);
+    g1 = uni(g1);
+    g2 = uni(g2);
 }
 
-__global__ void s4_init_kernel(Ctx c) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    search_init_body(c, e, e == 0, 4, SUBP, JBLK, 4);
-}
-
-// One thread per record, over the table in storage order: the row's pair
-// group comes from a search of r4off (the threads of a workgroup share it
-// but for the workgroups that straddle two values of i2).
-// zs = z_j / s_j = e / d_j and z_j^2 = e^2 / d_j with e = b_j - v0 z0 - v1 z1,
-// so a record takes one division and no root.
-__global__ __launch_bounds__(256) void rec4_kernel(Ctx c, double *__restrict__ rec, int64_t nrec) {
-    // the workgroup's records are staged in LDS and written out as
-    // consecutive doubles (full cache lines), not as S4_RECW strided stores
-    __shared__ double stage[256 * S4_RECW];
-    const int64_t S = c.S;
-    const int64_t e0 = (int64_t)blockIdx.x * blockDim.x;
-    const int64_t e = e0 + threadIdx.x;
-    const int64_t ecl = e < nrec ? e : nrec - 1;  // a thread past the end computes the last record, unwritten
-    const int r = (int)(ecl & (S4_NR - 1));
-    const int64_t row = ecl / S4_NR;
-    // i2: the largest index in [1, S - 3] whose rows start at or before row
-    int64_t lo = 1, hi = S - 3;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi + 1) >> 1;
-        if (c.r4off[mid] <= row) lo = mid; else hi = mid - 1;
-    }
-    const int64_t i2 = lo;
-    const int64_t nrow = S - 2 - i2;
-    const int64_t loc = row - c.r4off[i2];
-    const int64_t h = loc / nrow;
-    const int64_t j = i2 + 1 + (loc - h * nrow);
-    const int64_t i1 = S4_NR * h + r;
-    const int64_t nt = c.Gnt;
-    const double *__restrict__ G = c.G;
-    double v0 = 0.0, v1 = 0.0, al = 0.0, zs = 0.0, p = __builtin_nan("");
-    if (i1 < i2 && G[gidx(i1, i1, nt, 1, 0)] > RANK_EPS) {
-        const double rr = G[gidx(i1, i2, nt, 1, 0)];
-        const double s2 = G[gidx(i2, i2, nt, 1, 0)] - rr * rr;
-        if (s2 > RANK_EPS) {
-            const double isp = 1.0 / sqrt(s2);
-            const double z0 = c.bhat[i1];
-            const double z1 = (c.bhat[i2] - rr * z0) * isp;
-            const double a0 = G[gidx(i1, j, nt, 1, 0)];
-            const double a1 = (G[gidx(i2, j, nt, 1, 0)] - rr * a0) * isp;
-            const double d = G[gidx(j, j, nt, 1, 0)] - a0 * a0 - a1 * a1;
-            if (d > RANK_EPS) {
-                const double id = 1.0 / d;
-                const double ee = c.bhat[j] - a0 * z0 - a1 * z1;
-                v0 = a0;
-                v1 = a1;
-                al = id;
-                zs = ee * id;
-                p = c.cyy[0] - z0 * z0 - z1 * z1 - ee * zs;
-            }
-        }
-    }
-    double *o = stage + threadIdx.x * S4_RECW;
-    o[0] = v0;
-    o[1] = v1;
-    o[2] = al;
-    o[3] = zs;
-    o[4] = p;
-    __syncthreads();
-    const int64_t nvals = (nrec - e0 < 256 ? nrec - e0 : 256) * S4_RECW;
-    double *out = rec + e0 * S4_RECW;
-    for (int64_t q = threadIdx.x; q < nvals; q += 256) out[q] = stage[q];
+__device__ inline uint64_t s4_cand(int64_t g1, int64_t g2, int64_t j, int64_t k) {
+    return ((uint64_t)g1 << 48) | ((uint64_t)g2 << 32) | ((uint64_t)j << 16) | (uint64_t)k;
 }
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S4_WPE))) void search4_kernel(
-    Ctx c, SearchArgs a, const double *__restrict__ rec, const uint64_t *__restrict__ tcum) {
-    extern __shared__ double smem[];
-    __shared__ unsigned long long s_q[SEARCH_WAVES][S4_JR][2];
-    __shared__ int s_qj[SEARCH_WAVES][S4_JR];
-    const int KP = a.KP;
+    Ctx c, const double *__restrict__ rec, const double *__restrict__ fac, const uint64_t *__restrict__ tcum,
+    uint64_t t0, uint64_t t1, uint32_t wg_tiles) {
+    __shared__ unsigned long long s_m[SEARCH_WAVES][S3_JR][2];
+    __shared__ unsigned s_n[2];
+    constexpr int N = 2 * S4_NR;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    double *Ls = smem + (size_t)wave * KP * 2;
-    uint64_t *Lr = reinterpret_cast<uint64_t *>(Ls + KP);
-    for (int m = lane; m < KP; m += 64) {
-        Ls[m] = INF;
-        Lr[m] = ~0ull;
-    }
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_wave_barrier();
-    double theta_pub = INF;
-    unsigned offered = 0;
-    const double theta0 = theta0_of(c);
-    const int64_t S = c.S;
-    const int64_t nb = s4_nblocks(S);
-    const uint64_t ntiles = tcum[nb];
-    const int64_t nt = c.Gnt;
-    const double *__restrict__ Gb = c.G;
-    const int64_t gw = (int64_t)blockIdx.x * SEARCH_WAVES + wave;
-    const double *__restrict__ inv_st = c.inv_s;
-
+    uint64_t *__restrict__ cands = c.s3_cands + (size_t)blockIdx.x * wg_tiles * S4_LANES;
+    uint64_t *__restrict__ items = c.s3_rows + (size_t)blockIdx.x * wg_tiles * S4_NR;
+    if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t S = c.S, nt = c.Gnt;
+    const double *__restrict__ Gb = c.G1;
+    const double *__restrict__ inv_s = c.inv_s;
+    const double *__restrict__ bhat = c.bhat;
+    const double th = fmin(theta0_of(c), theta_load(c.theta_bits));
+    const double ctot = c.cyy[0];
+    const double theta_s = th * (1.0 + THETA_SLACK) + S3_TSLACK * ctot, neg = -S3_ESLACK * ctot;
+    S3Skip skip;
     // tiles dealt round-robin, XCD-aware, as in search3_kernel
     const bool xa = (gridDim.x % S3_XCDS) == 0;
     const uint64_t xcd = xa ? blockIdx.x % S3_XCDS : 0;
     const uint64_t nx = xa ? S3_XCDS : 1;
     const uint64_t U = (uint64_t)gridDim.x / nx * SEARCH_WAVES;
     const uint64_t u0 = (uint64_t)blockIdx.x / nx * SEARCH_WAVES + wave;
-    // a wave takes S4_WRUN consecutive tiles (the column chunks of one pair
-    // group and row block share its record rows, which the later ones find in
-    // L2); runs are dealt round-robin and XCD-aware as tiles are in
-    // search3_kernel
     for (uint64_t sx = u0;; sx += U) {
-        const uint64_t run = ((sx / S3_XCD_RUN) * nx + xcd) * S3_XCD_RUN + sx % S3_XCD_RUN;
-        if (run * S4_WRUN >= ntiles) break;
-        const uint64_t tend = run * S4_WRUN + S4_WRUN < ntiles ? run * S4_WRUN + S4_WRUN : ntiles;
-        for (uint64_t t = run * S4_WRUN; t < tend; ++t) {
-        int64_t lo = 0, hi = nb - 1;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi + 1) >> 1;
-            if (tcum[mid] <= t) lo = mid; else hi = mid - 1;
-        }
-        const int64_t jb = lo;
-        int64_t nkb, ng;
-        s4_block(S, jb, nkb, ng);
-        const int64_t rem = (int64_t)(t - tcum[jb]);
-        const int64_t kcx = rem % nkb;
-        const int64_t grp = uni(rem / nkb);
-        const int64_t i2 = uni(s4_group_i2(S, grp));
-        const int64_t hh = grp - s4_groups_below(i2);
-        const int64_t j0 = jb * S4_JR;
-        const int64_t jlo = j0 > i2 + 1 ? j0 : i2 + 1;
-        const int64_t jhi = (j0 + S4_JR - 1 < S - 2) ? j0 + S4_JR - 1 : S - 2;
-        const int nrow = (int)(jhi - jlo);  // steps 0..nrow (>= 0: i2 < jhi)
-        // the next tile of this wave that starts a new pair group: touch each
-        // 128-byte line of its record rows now, so that its scalar loads find
-        // them in L2
-        double pf = 0.0;
-        {
-            uint64_t tn = ~0ull;
-            if (t + 1 < tend) {
-                if ((rem + 1) % nkb == 0) tn = t + 1;
+        const uint64_t t = t0 + ((sx / S3_XCD_RUN) * nx + xcd) * S3_XCD_RUN + sx % S3_XCD_RUN;
+        if (t >= t1) break;
+        S3Tile tl;
+        int64_t g1, g2;
+        s4_locate(S, tcum, t, tl, g1, g2);
+        const int64_t jlo = tl.j0 > S4_NR * g2 + 1 ? tl.j0 : S4_NR * g2 + 1;
+        const int nrow = (int)(tl.jhi - jlo);  // steps 0..nrow
+        CDouble *f = cptr(fac) + (s4_pairs_below(g2) + g1) * S4_FAC;
+        unsigned long long rows = 0;
+        int lanes = 1 << 30;
+        if (skip.left > 0) {
+            --skip.left;
+        } else if (th < INF && f[45] == 0.0) {
+            CChar *recj = (CChar *)(cptr(rec) + (size_t)(s4_rowoff(S, g1, g2) + jlo - S4_NR * g2 - 1) * S4_REC);
+            // touch the 128-byte lines of the tile's records, so that the
+            // scalar loads below find them in L2
+            double pf = 0.0;
+            if (lane * 128 < (nrow + 1) * S4_REC * 8)
+                pf = rec[(size_t)(s4_rowoff(S, g1, g2) + jlo - S4_NR * g2 - 1) * S4_REC + lane * 16];
+            const int64_t k0 = tl.kb + lane, k1 = tl.kb + 64 + lane;
+            const bool kv0 = k0 < S, kv1 = k1 < S;
+            // columns read for lanes past S: any valid one (masked below)
+            const int64_t kk0 = kv0 ? k0 : S - 1, kk1 = kv1 ? k1 : S - 1;
+            const bool diag = tl.kcx == 0, half = S - tl.kb <= 64;
+            // k-dependent part of the pair's solve, for both columns of the lane
+            double w[N][2], dq[2], z2[2], zz[2];  // z2 = -2 zeta', zz = zeta'^2
+            {
+                double x0[N], x1[N];
+#pragma unroll
+                for (int m = 0; m < N; ++m) {
+                    int64_t i = S4_NR * (m < S4_NR ? g1 : g2) + m % S4_NR;
+                    i = i < S ? i : S - 1;  // past S: the factor's row is zero
+                    x0[m] = Gb[gidx(i, kk0, nt, 1, 0)];
+                    x1[m] = Gb[gidx(i, kk1, nt, 1, 0)];
+                }
+                double d0 = 1.0 - S3_DSLACK, d1 = 1.0 - S3_DSLACK, e0 = bhat[kk0], e1 = bhat[kk1];
+#pragma unroll
+                for (int m = 0; m < N; ++m) {
+                    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+                    for (int l = 0; l <= m; ++l) {
+                        s0 = fma(f[m * (m + 1) / 2 + l], x0[l], s0);
+                        s1 = fma(f[m * (m + 1) / 2 + l], x1[l], s1);
+                    }
+                    w[m][0] = s0;
+                    w[m][1] = s1;
+                    d0 = fma(-s0, s0, d0);
+                    d1 = fma(-s1, s1, d1);
+                    e0 = fma(-s0, f[36 + m], e0);
+                    e1 = fma(-s1, f[36 + m], e1);
+                }
+                // a lane past S or on a constant column never passes
+                dq[0] = kv0 && inv_s[kk0] > 0.0 ? d0 : S3_NEVER;
+                dq[1] = kv1 && inv_s[kk1] > 0.0 ? d1 : S3_NEVER;
+                z2[0] = -2.0 * e0;
+                z2[1] = -2.0 * e1;
+                zz[0] = e0 * e0;
+                zz[1] = e1 * e1;
+            }
+            const char *__restrict__ gtile = reinterpret_cast<const char *>(Gb + (((tl.j0 >> 6) * nt) << 12));
+            const uint32_t voff0 = (uint32_t)((((kk0 >> 6) << 12) + (kk0 & 63) + ((jlo & 63) << 6)) * 8);
+            const uint32_t voff1 = (uint32_t)((((kk1 >> 6) << 12) + (kk1 & 63) + ((jlo & 63) << 6)) * 8);
+            lanes = 0;
+            auto sweep = [&](auto diagc, auto halfc) {
+                constexpr bool DIAG = decltype(diagc)::value;
+                constexpr bool HALF = decltype(halfc)::value;
+                constexpr int JG = S3_JG;
+                static_assert(JG % 2 == 0, "the record buffers alternate by row");
+                double2 ga[JG], gb[JG];  // g(j, k0), g(j, k1)
+                auto fetch = [&](double2 (&dst)[JG], int jg) {
+#pragma unroll
+                    for (int x = 0; x < JG; ++x) {
+                        const uint32_t jr = (uint32_t)(jg + x < nrow ? jg + x : nrow);
+                        dst[x].x = *reinterpret_cast<const double *>(gtile + (voff0 + jr * 512u));
+                        dst[x].y = HALF ? 0.0 : *reinterpret_cast<const double *>(gtile + (voff1 + jr * 512u));
+                    }
+                };
+                // a step's record is loaded while the step before is scored
+                auto load = [&](double (&rv)[S4_REC], int jr) {
+                    CDouble *rp = (CDouble *)(recj + (size_t)(jr < nrow ? jr : nrow) * (S4_REC * 8));
+#pragma unroll
+                    for (int e = 0; e < S4_REC; ++e) rv[e] = rp[e];
+                };
+                // the bound as a polynomial in u, as in s3_bound
+                auto step = [&](const double (&rv)[S4_REC], const double2 gv, int jr) {
+                    const double pi = fmax(rv[10] - theta_s, 0.0);
+                    const double A = fma(pi, rv[8], rv[11]);
+                    unsigned long long m0, m1 = 0;
+                    {
+                        double u = gv.x;
+#pragma unroll
+                        for (int e = 0; e < N; ++e) u = fma(-rv[e], w[e][0], u);
+                        const double x = fma(u, fma(A, u, rv[9] * z2[0]), fma(-pi, dq[0], zz[0]));
+                        m0 = __ballot(!(x < neg));
+                        if (DIAG) m0 &= __ballot(k0 > jlo + jr);  // k1 > j0 + 64 > j
+                    }
+                    if (!HALF) {
+                        double u = gv.y;
+#pragma unroll
+                        for (int e = 0; e < N; ++e) u = fma(-rv[e], w[e][1], u);
+                        const double x = fma(u, fma(A, u, rv[9] * z2[1]), fma(-pi, dq[1], zz[1]));
+                        m1 = __ballot(!(x < neg));
+                    }
+                    if ((m0 | m1) && jr <= nrow) {
+                        m0 &= __ballot(kv0);
+                        m1 &= __ballot(kv1);
+                        if (lane == 0) {
+                            s_m[wave][jr][0] = m0;
+                            s_m[wave][jr][1] = m1;
+                        }
+                        rows |= 1ull << jr;
+                        lanes += __popcll(m0) + __popcll(m1);
+                    }
+                };
+                double ra[S4_REC], rb[S4_REC];
+                load(ra, 0);
+                auto score = [&](const double2 (&src)[JG], int jg) {
+#pragma unroll
+                    for (int x = 0; x < JG; x += 2) {
+                        __builtin_amdgcn_s_waitcnt(0xC07F);
+                        load(rb, jg + x + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                        step(ra, src[x], jg + x);
+                        __builtin_amdgcn_s_waitcnt(0xC07F);
+                        load(ra, jg + x + 2);
+                        __builtin_amdgcn_sched_barrier(0);
+                        step(rb, src[x + 1], jg + x + 1);
+                    }
+                };
+                __builtin_amdgcn_s_waitcnt(0x0F70);
+                fetch(ga, 0);
+                for (int jg = 0;; jg += 2 * JG) {
+                    fetch(gb, jg + JG);
+                    score(ga, jg);
+                    fetch(ga, jg + 2 * JG);
+                    score(gb, jg + JG);
+                    if (jg + 2 * JG > nrow) break;
+                }
+            };
+            if (diag) {
+                if (half) sweep(std::true_type{}, std::true_type{});
+                else sweep(std::true_type{}, std::false_type{});
             } else {
-                const uint64_t sn = sx + U;
-                const uint64_t rn = ((sn / S3_XCD_RUN) * nx + xcd) * S3_XCD_RUN + sn % S3_XCD_RUN;
-                if (rn * S4_WRUN < ntiles) tn = rn * S4_WRUN;
+                if (half) sweep(std::false_type{}, std::true_type{});
+                else sweep(std::false_type{}, std::false_type{});
             }
-            if (tn != ~0ull) {
-                int64_t prow, pn;
-                s4_tile_rows(c, tcum, nb, tn, prow, pn);
-                const int64_t bytes = pn * S4_ROW * 8;
-                if ((int64_t)lane * 128 < bytes)
-                    pf = rec[(size_t)prow * S4_ROW + (size_t)lane * 16];
+            asm volatile("; touched %0" ::"v"(pf));  // the load stays (its value is not needed)
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            __builtin_amdgcn_wave_barrier();
+            if (lanes > S4_LANES) {
+                skip.fails = skip.fails < 5 ? skip.fails + 1 : 5;
+                skip.left = (1 << skip.fails) - 1;
+            } else {
+                skip.fails = 0;
             }
         }
-        const int64_t kb = j0 + 1 + kcx * S4_KC;
-        const int64_t k0 = kb + lane, k1 = kb + 64 + lane;
-        const bool kv0 = k0 < S, kv1 = k1 < S;
-        // columns read for lanes past S: any valid one (never passes)
-        const int64_t kk0 = kv0 ? k0 : S - 1, kk1 = kv1 ? k1 : S - 1;
-        const bool diag = kcx == 0;            // k <= j only in chunk 0, first half
-        const bool half = S - kb <= 64;        // no column in the second half
+        if (lanes > S4_LANES) {
+            // the whole tile, an item per i2 with a tuple in it
+            const int64_t i2 = S4_NR * g2 + lane;
+            const bool in = lane < S4_NR && i2 > S4_NR * g1 && i2 < tl.jhi && inv_s[i2 < S ? i2 : S - 1] > 0.0;
+            const unsigned long long b = __ballot(in);
+            unsigned at = 0;
+            if (lane == 0) at = atomicAdd(&s_n[1], (unsigned)__popcll(b));
+            at = (unsigned)__shfl((int)at, 0);
+            if (in) items[at + __popcll(b & ((1ull << lane) - 1ull))] = t * S4_NR + lane;
+            continue;
+        }
+        if (!lanes) continue;
+        unsigned at = 0;
+        if (lane == 0) at = atomicAdd(&s_n[0], (unsigned)lanes);
+        at = (unsigned)__shfl((int)at, 0);
+        while (rows) {
+            const int x = __builtin_ctzll(rows);
+            rows &= rows - 1;
+#pragma unroll
+            for (int sl = 0; sl < 2; ++sl) {
+                const unsigned long long m = s_m[wave][x][sl];
+                if ((m >> lane) & 1ull)
+                    cands[at + __popcll(m & ((1ull << lane) - 1ull))] = s4_cand(g1, g2, jlo + x, tl.kb + 64 * sl + lane);
+                at += (unsigned)__popcll(m);
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) c.s3_count[2 * blockIdx.x + threadIdx.x] = s_n[threadIdx.x];
+}
 
+// The terms of the pair (i1, i2) in a tuple's solve: r = G[i1][i2], 1/s with
+// s^2 = 1 - r^2 (0: rank deficient), z0 = b_i1, z1 = (b_i2 - r z0) / s; and
+// the row of a column x against the pair: x0 = G[i1][x], x1 = (G[i2][x] - r x0) / s.
+struct S4Pair {
+    double r, is, z0, z1;
+    __device__ S4Pair(double rr, double b1, double b2, bool valid) : r(rr), z0(b1) {
+        const double s2 = 1.0 - rr * rr;
+        is = valid && s2 > RANK_EPS ? 1.0 / sqrt(s2) : 0.0;
+        z1 = (b2 - rr * b1) * is;
+    }
+};
+
+// A tuple's record {v0, v1, 1/d_j, z_j / s_j, p} (as a D = 3 record, against
+// the pair); p = NaN (fails every comparison) where the triple is rank
+// deficient.
+__device__ inline void s4_record(const S4Pair &q, double g1j, double g2j, double bj, double ctot, double (&o)[5]) {
+    const double a0 = g1j, a1 = (g2j - q.r * g1j) * q.is;
+    const double d = 1.0 - a0 * a0 - a1 * a1;
+    const bool ok = q.is > 0.0 && d > RANK_EPS;
+    const double id = ok ? 1.0 / d : 0.0;
+    const double ee = bj - a0 * q.z0 - a1 * q.z1;
+    o[0] = a0;
+    o[1] = a1;
+    o[2] = id;
+    o[3] = ee * id;
+    o[4] = ok ? ctot - q.z0 * q.z0 - q.z1 * q.z1 - ee * o[3] : __builtin_nan("");
+}
+
+// 64 candidates, one per lane: (group g1, group g2, j, k) whose bound passed.
+// Each lane scores the sixteen tuples.
+__device__ __forceinline__ void s4_candidates(const Ctx &c, const SearchArgs &a, bool have, uint64_t key, double *Ls,
+                                              uint64_t *Lr, double theta0, double &theta_pub, unsigned &offered) {
+    const int KP = a.KP;
+    const int64_t S = c.S, nt = c.Gnt;
+    const double *__restrict__ G1 = c.G1;
+    const double ctot = c.cyy[0];
+    const int64_t g1 = have ? (int64_t)(key >> 48) : 0, g2 = have ? (int64_t)((key >> 32) & 0xFFFF) : 0;
+    const int64_t j = have ? (int64_t)((key >> 16) & 0xFFFF) : 2, k = have ? (int64_t)(key & 0xFFFF) : 3;
+    double th = fmin(theta0, theta_load(c.theta_bits));
+    th = fmin(th, Ls[KP - 1]);
+    const double theta_f = th < INF ? th * (1.0 + THETA_SLACK) : INF;
+    const double gjk = G1[gidx(j, k, nt, 1, 0)], bj = c.bhat[j], bk = c.bhat[k];
+    have = have && c.inv_s[j] > 0.0 && c.inv_s[k] > 0.0;
+    double gj[S4_NR], gk[S4_NR], b1[S4_NR];
+    bool lv[S4_NR];
+#pragma unroll
+    for (int r = 0; r < S4_NR; ++r) {
+        const int64_t i = S4_NR * g1 + r < S ? S4_NR * g1 + r : S - 1;
+        gj[r] = G1[gidx(i, j, nt, 1, 0)];
+        gk[r] = G1[gidx(i, k, nt, 1, 0)];
+        b1[r] = c.bhat[i];
+        lv[r] = c.inv_s[i] > 0.0;
+    }
+    for (int y = 0; y < S4_NR; ++y) {
+        const int64_t i2 = S4_NR * g2 + y, ii = i2 < S ? i2 : S - 1;
+        const bool in2 = have && i2 < j && c.inv_s[ii] > 0.0;
+        const double g2j = G1[gidx(ii, j, nt, 1, 0)], g2k = G1[gidx(ii, k, nt, 1, 0)], b2 = c.bhat[ii];
+        double es[S4_NR];
+        bool any = false;
+#pragma unroll
+        for (int r = 0; r < S4_NR; ++r) {
+            const int64_t i1 = S4_NR * g1 + r < S ? S4_NR * g1 + r : S - 1;
+            const S4Pair q(G1[gidx(i1, ii, nt, 1, 0)], b1[r], b2, in2 && S4_NR * g1 + r < i2 && lv[r]);
+            double o[5];
+            s4_record(q, gj[r], g2j, bj, ctot, o);
+            const double w1 = (g2k - q.r * gk[r]) * q.is;
+            const double u = fma(-o[1], w1, fma(-o[0], gk[r], gjk));
+            const double d = fma(-o[2], u * u, 1.0 - gk[r] * gk[r] - w1 * w1);
+            const double z = fma(-o[3], u, bk - gk[r] * q.z0 - w1 * q.z1);
+            es[r] = (d > RANK_EPS) ? o[4] - z * z / d : INF;
+            any |= es[r] <= theta_f;
+        }
+        if (!__ballot(any)) continue;
+#pragma unroll
+        for (int r = 0; r < S4_NR; ++r) {
+            const int32_t tup[4] = {(int32_t)(S4_NR * g1 + r), (int32_t)i2, (int32_t)j, (int32_t)k};
+            bool take = es[r] <= fmin(theta_f, Ls[KP - 1]);
+            if (take && a.ranged) {
+                const uint64_t lr = lex_rank(BinomTab{c.btab, c.S}, c.S, 4, tup);
+                if (lr < a.r0 || lr >= a.r1) take = false;
+            }
+            list_insert_lanes(Ls, Lr, KP, take, pack_tuple(tup, 4), es[r], offered);
+        }
+    }
+    const double tw = Ls[KP - 1];
+    if (tw < theta_pub) {
+        theta_pub = tw;
+        if ((threadIdx.x & 63) == 0) theta_publish(c.theta_bits, tw);
+    }
+}
+
+constexpr int S4_DR = 16;  // rows of a dense item swept at a time (their records lie in LDS)
+
+// All tuples of a tile with second index i2 and first index in group g1, by
+// the wave: S4_DR rows at a time, whose records are built in LDS and read by
+// all lanes at one address.
+__device__ __forceinline__ void s4_dense(const Ctx &c, const SearchArgs &a, const S3Tile &tl, int64_t g1, int64_t i2,
+                                         double *Ls, uint64_t *Lr, double theta0, double &theta_pub, unsigned &offered,
+                                         double (*s_r)[S4_NR][6], unsigned long long (*s_q)[2]) {
+    const int KP = a.KP;
+    const int lane = threadIdx.x & 63;
+    const int64_t S = c.S, nt = c.Gnt;
+    const double *__restrict__ Gb = c.G1;
+    const double *__restrict__ inv_s = c.inv_s;
+    const double ctot = c.cyy[0];
+    const int64_t k0 = tl.kb + lane, k1 = tl.kb + 64 + lane;
+    const bool kv0 = k0 < S, kv1 = k1 < S;
+    const int64_t kk0 = kv0 ? k0 : S - 1, kk1 = kv1 ? k1 : S - 1;
+    // k-dependent part of each pair's solve, for both columns of the lane
+    double w0[S4_NR][2], w1[S4_NR][2], dq[S4_NR][2], zq[S4_NR][2];
+    {
+        const bool lk0 = kv0 && inv_s[kk0] > 0.0, lk1 = kv1 && inv_s[kk1] > 0.0;
+        const double b0 = c.bhat[kk0], b1 = c.bhat[kk1];
+        const double x2 = Gb[gidx(i2, kk0, nt, 1, 0)], y2 = Gb[gidx(i2, kk1, nt, 1, 0)];
+#pragma unroll
+        for (int r = 0; r < S4_NR; ++r) {
+            const bool pin = S4_NR * g1 + r < i2;
+            const int64_t i1 = pin ? S4_NR * g1 + r : i2;  // a void pair reads valid memory and never passes
+            const S4Pair q(Gb[gidx(i1, i2, nt, 1, 0)], c.bhat[i1], c.bhat[i2], pin && inv_s[i1] > 0.0);
+            const double a0 = Gb[gidx(i1, kk0, nt, 1, 0)], a1 = Gb[gidx(i1, kk1, nt, 1, 0)];
+            const double c0 = (x2 - q.r * a0) * q.is, c1 = (y2 - q.r * a1) * q.is;
+            w0[r][0] = a0;
+            w0[r][1] = a1;
+            w1[r][0] = c0;
+            w1[r][1] = c1;
+            // a lane past S, a constant column or a void pair never passes
+            dq[r][0] = q.is > 0.0 && lk0 ? 1.0 - a0 * a0 - c0 * c0 : __builtin_nan("");
+            dq[r][1] = q.is > 0.0 && lk1 ? 1.0 - a1 * a1 - c1 * c1 : __builtin_nan("");
+            zq[r][0] = b0 - a0 * q.z0 - c0 * q.z1;
+            zq[r][1] = b1 - a1 * q.z0 - c1 * q.z1;
+        }
+    }
+    const int64_t jfirst = tl.j0 > i2 + 1 ? tl.j0 : i2 + 1;
+    for (int64_t jlo = jfirst; jlo <= tl.jhi; jlo += S4_DR) {
+        const int nr = (int)(tl.jhi - jlo + 1 < S4_DR ? tl.jhi - jlo + 1 : S4_DR);
         double th = fmin(theta0, theta_load(c.theta_bits));
         th = fmin(th, Ls[KP - 1]);
         const double theta_f = th < INF ? th * (1.0 + THETA_SLACK) : INF;
-
-        // k-dependent part of each pair's solve, for both columns of the lane
-        double w0[S4_NR][2], w1[S4_NR][2], dq[S4_NR][2], zq[S4_NR][2];
-        {
-            const double gd0 = inv_st[kk0] > 0.0 ? 1.0 : 0.0;
-            const double gd1 = inv_st[kk1] > 0.0 ? 1.0 : 0.0;
-            const double b0 = c.bhat[kk0], b1 = c.bhat[kk1];
-            const double w2x = Gb[gidx(i2, kk0, nt, 1, 0)], w2y = Gb[gidx(i2, kk1, nt, 1, 0)];
-            const double zb2 = c.bhat[i2];
-            const bool live2 = inv_st[i2] > 0.0;
-#pragma unroll
-            for (int r = 0; r < S4_NR; ++r) {
-                int64_t i1 = S4_NR * hh + r;
-                const bool pin = i1 < i2;
-                if (!pin) i1 = i2;  // a void pair reads valid memory and never passes
-                const double rr = Gb[gidx(i1, i2, nt, 1, 0)];
-                const double s2 = (live2 ? 1.0 : 0.0) - rr * rr;
-                const bool pv = pin && inv_st[i1] > 0.0 && s2 > RANK_EPS;
-                const double isp = pv ? 1.0 / sqrt(s2) : 0.0;
-                const double z0 = c.bhat[i1];
-                const double z1 = (zb2 - rr * z0) * isp;
-                const double a0 = Gb[gidx(i1, kk0, nt, 1, 0)], a1 = Gb[gidx(i1, kk1, nt, 1, 0)];
-                const double c0 = (w2x - rr * a0) * isp, c1 = (w2y - rr * a1) * isp;
-                w0[r][0] = a0;
-                w0[r][1] = a1;
-                w1[r][0] = c0;
-                w1[r][1] = c1;
-                // a lane past S, a constant column or a void pair never passes
-                dq[r][0] = (pv && kv0 && gd0 > RANK_EPS) ? gd0 - a0 * a0 - c0 * c0 : __builtin_nan("");
-                dq[r][1] = (pv && kv1 && gd1 > RANK_EPS) ? gd1 - a1 * a1 - c1 * c1 : __builtin_nan("");
-                zq[r][0] = b0 - a0 * z0 - c0 * z1;
-                zq[r][1] = b1 - a1 * z0 - c1 * z1;
-            }
-        }
-        const char *__restrict__ gtile = reinterpret_cast<const char *>(Gb + (((j0 >> 6) * nt) << 12));
-        // byte offsets of (jlo, k) in the 64 x 64 tile row of j0 (rows jlo .. jhi stay in it)
-        const uint32_t voff0 = (uint32_t)((((kk0 >> 6) << 12) + (kk0 & 63) + ((jlo & 63) << 6)) * 8);
-        const uint32_t voff1 = (uint32_t)((((kk1 >> 6) << 12) + (kk1 & 63) + ((jlo & 63) << 6)) * 8);
-        // records of row jlo + x are S4_ROW doubles at recj + S4_ROW x (uniform)
-        const double *__restrict__ recj =
-            rec + (size_t)(c.r4off[i2] + hh * (S - 2 - i2) + (jlo - i2 - 1)) * S4_ROW;
-        int nq = 0;
-        auto sweep = [&](auto diagc, auto halfc) {
-            constexpr bool DIAG = decltype(diagc)::value;
-            constexpr bool HALF = decltype(halfc)::value;
-            constexpr int JG = S3_JG;
-            double2 ga[JG], gb[JG];  // g(j, k0), g(j, k1)
-            auto fetch = [&](double2 (&dst)[JG], int jg) {
-#pragma unroll
-                for (int x = 0; x < JG; ++x) {
-                    const uint32_t jr = (uint32_t)(jg + x < nrow ? jg + x : nrow);
-                    dst[x].x = *reinterpret_cast<const double *>(gtile + (voff0 + jr * 512u));
-                    dst[x].y = HALF ? 0.0 : *reinterpret_cast<const double *>(gtile + (voff1 + jr * 512u));
-                }
-            };
-            // records of one step: two halves of two pairs (10 doubles each),
-            // each loaded while the other is scored (scalar loads return out of
-            // order, so the half in flight is waited for before the next issue)
-            constexpr int HW = 2 * S4_RECW;
-            auto load_half = [&](double (&rv)[HW], int jr, int h) {
-                const double *rp = recj + (size_t)jr * S4_ROW + h * HW;
-#pragma unroll
-                for (int e = 0; e < HW; ++e) rv[e] = rp[e];
-            };
-            auto score_half = [&](const double (&rv)[HW], const double2 gv, int h, unsigned long long &m0,
-                                  unsigned long long &m1) {
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const int r = 2 * h + q;
-                    const double *x = rv + q * S4_RECW;
-                    const double pi = x[4] - theta_f;
-                    {
-                        const double u = fma(-x[1], w1[r][0], fma(-x[0], w0[r][0], gv.x));
-                        const double d = fma(-x[2], u * u, dq[r][0]);
-                        const double z = fma(-x[3], u, zq[r][0]);
-                        m0 |= __ballot(z * z >= pi * d);
-                    }
-                    if (!HALF) {
-                        const double u = fma(-x[1], w1[r][1], fma(-x[0], w0[r][1], gv.y));
-                        const double d = fma(-x[2], u * u, dq[r][1]);
-                        const double z = fma(-x[3], u, zq[r][1]);
-                        m1 |= __ballot(z * z >= pi * d);
-                    }
-                }
-            };
-            double ra[HW], rb[HW];
-            load_half(ra, 0, 0);
-            auto score = [&](const double2 (&src)[JG], int jg) {
-#pragma unroll
-                for (int x = 0; x < JG; ++x) {
-                    const int jr = jg + x;
-                    const int jc = jr <= nrow ? jr : nrow;
-                    unsigned long long m0 = 0, m1 = 0;
-                    __builtin_amdgcn_s_waitcnt(0xC07F);
-                    load_half(rb, jc, 1);
-                    __builtin_amdgcn_sched_barrier(0);
-                    score_half(ra, src[x], 0, m0, m1);
-                    __builtin_amdgcn_s_waitcnt(0xC07F);
-                    load_half(ra, jr + 1 <= nrow ? jr + 1 : nrow, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    score_half(rb, src[x], 1, m0, m1);
-                    if (DIAG) m0 &= __ballot(k0 > jlo + jr);  // k1 > j0 + 64 > j
-                    if (jr > nrow) m0 = m1 = 0;
-                    if (m0 | m1) {
-                        if (lane == 0) {
-                            s_q[wave][nq][0] = m0;
-                            s_q[wave][nq][1] = m1;
-                            s_qj[wave][nq] = jr;
-                        }
-                        ++nq;
-                    }
-                }
-            };
-            __builtin_amdgcn_s_waitcnt(0x0F70);
-            fetch(ga, 0);
-            for (int jg = 0;; jg += 2 * JG) {
-                fetch(gb, jg + JG);
-                score(ga, jg);
-                fetch(ga, jg + 2 * JG);
-                score(gb, jg + JG);
-                if (jg + 2 * JG > nrow) break;
-            }
-        };
-        if (diag) {
-            if (half) sweep(std::true_type{}, std::true_type{});
-            else sweep(std::true_type{}, std::false_type{});
-        } else {
-            if (half) sweep(std::false_type{}, std::true_type{});
-            else sweep(std::false_type{}, std::false_type{});
-        }
-        asm volatile("; prefetched %0" ::"v"(pf));  // the load stays (its value is not needed)
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         __builtin_amdgcn_wave_barrier();
-
-        // exact scoring of the flagged steps (rare): the same terms, a true
-        // division, the rank test and the current bound
+        for (int e = lane; e < S4_DR * S4_NR; e += 64) {
+            const int x = e % S4_DR, r = e / S4_DR;
+            const int64_t j = x < nr ? jlo + x : jlo + nr - 1;
+            const bool pin = S4_NR * g1 + r < i2;
+            const int64_t i1 = pin ? S4_NR * g1 + r : i2;
+            const S4Pair q(Gb[gidx(i1, i2, nt, 1, 0)], c.bhat[i1], c.bhat[i2],
+                           pin && inv_s[i1] > 0.0 && inv_s[j] > 0.0);
+            double o[5];
+            s4_record(q, Gb[gidx(i1, j, nt, 1, 0)], Gb[gidx(i2, j, nt, 1, 0)], c.bhat[j], ctot, o);
+#pragma unroll
+            for (int z = 0; z < 5; ++z) s_r[x][r][z] = o[z];
+        }
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_wave_barrier();
+        unsigned rows = 0;
+        for (int x = 0; x < nr; ++x) {
+            const int64_t j = jlo + x;
+            const double gx = Gb[gidx(j, kk0, nt, 1, 0)], gy = Gb[gidx(j, kk1, nt, 1, 0)];
+            unsigned long long m0 = 0, m1 = 0;
+#pragma unroll
+            for (int r = 0; r < S4_NR; ++r) {
+                const double v0 = s_r[x][r][0], v1 = s_r[x][r][1], al = s_r[x][r][2], zs = s_r[x][r][3];
+                const double pi = s_r[x][r][4] - theta_f;
+                {
+                    const double u = fma(-v1, w1[r][0], fma(-v0, w0[r][0], gx));
+                    const double d = fma(-al, u * u, dq[r][0]);
+                    const double z = fma(-zs, u, zq[r][0]);
+                    m0 |= __ballot(z * z >= pi * d);
+                }
+                {
+                    const double u = fma(-v1, w1[r][1], fma(-v0, w0[r][1], gy));
+                    const double d = fma(-al, u * u, dq[r][1]);
+                    const double z = fma(-zs, u, zq[r][1]);
+                    m1 |= __ballot(z * z >= pi * d);
+                }
+            }
+            m0 &= __ballot(k0 > j);
+            if (m0 | m1) {
+                if (lane == 0) {
+                    s_q[x][0] = m0;
+                    s_q[x][1] = m1;
+                }
+                rows |= 1u << x;
+            }
+        }
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_wave_barrier();
+        // exact scoring of the flagged rows: the same terms, a true division,
+        // the rank test and the current bound
         auto pick = [&](const double (&arr)[S4_NR][2], int r, int sl) {
             double v = arr[0][0];
 #pragma unroll
@@ -3019,23 +3265,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S4_WPE))) v
                     if (q == r && h == sl) v = arr[q][h];
             return v;
         };
-        for (int e = 0; e < nq; ++e) {
-            const int jr = s_qj[wave][e];
-            const int64_t j = jlo + jr;
-            const unsigned long long fm[2] = {s_q[wave][e][0], s_q[wave][e][1]};
-            const double *rp = recj + (size_t)jr * S4_ROW;
-            const double gv0 = *reinterpret_cast<const double *>(gtile + (voff0 + (uint32_t)jr * 512u));
-            const double gv1 = *reinterpret_cast<const double *>(gtile + (voff1 + (uint32_t)jr * 512u));
+        while (rows) {
+            const int x = __builtin_ctz(rows);
+            rows &= rows - 1;
+            const int64_t j = jlo + x;
+            const unsigned long long fm[2] = {s_q[x][0], s_q[x][1]};
+            const double gx = Gb[gidx(j, kk0, nt, 1, 0)], gy = Gb[gidx(j, kk1, nt, 1, 0)];
             for (int r = 0; r < S4_NR; ++r) {
-                const double *x = rp + r * S4_RECW;
-                const double v0 = x[0], v1 = x[1], al = x[2], zs = x[3], p = x[4];
+                const double v0 = s_r[x][r][0], v1 = s_r[x][r][1], al = s_r[x][r][2], zs = s_r[x][r][3];
+                const double p = s_r[x][r][4];
                 for (int sl = 0; sl < 2; ++sl) {
-                    const double gg = sl ? gv1 : gv0;
                     const int64_t k = sl ? k1 : k0;
-                    const double u = fma(-v1, pick(w1, r, sl), fma(-v0, pick(w0, r, sl), gg));
+                    const double u = fma(-v1, pick(w1, r, sl), fma(-v0, pick(w0, r, sl), sl ? gy : gx));
                     const double d = fma(-al, u * u, pick(dq, r, sl));
                     const double z = fma(-zs, u, pick(zq, r, sl));
-                    const int32_t tup[4] = {(int32_t)(S4_NR * hh + r), (int32_t)i2, (int32_t)j, (int32_t)k};
+                    const int32_t tup[4] = {(int32_t)(S4_NR * g1 + r), (int32_t)i2, (int32_t)j, (int32_t)k};
                     const double es = (d > RANK_EPS) ? p - z * z / d : INF;
                     bool take = ((fm[sl] >> lane) & 1ull) && k < S && k > j && es <= fmin(theta_f, Ls[KP - 1]);
                     if (take && a.ranged) {
@@ -3051,7 +3295,59 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S4_WPE))) v
             theta_pub = tw;
             if (lane == 0) theta_publish(c.theta_bits, tw);
         }
+    }
+}
+
+// Scores the pools, as s3_eval_kernel does.
+__global__ __launch_bounds__(256) void s4_eval_kernel(Ctx c, SearchArgs a, const uint64_t *__restrict__ tcum,
+                                                      uint32_t nseg, uint32_t wg_tiles, int resume) {
+    extern __shared__ double smem[];
+    __shared__ double s_r[SEARCH_WAVES][S4_DR][S4_NR][6];
+    __shared__ unsigned long long s_q[SEARCH_WAVES][S4_DR][2];
+    __shared__ unsigned long long s_w[2][SEARCH_WAVES];
+    const int KP = a.KP;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double *Ls = smem + (size_t)wave * KP * 2;
+    uint64_t *Lr = reinterpret_cast<uint64_t *>(Ls + KP);
+    uint64_t *first[2];
+    first[0] = reinterpret_cast<uint64_t *>(smem + (size_t)SEARCH_WAVES * KP * 2);
+    first[1] = first[0] + nseg + 1;
+    const int64_t gw = (int64_t)blockIdx.x * SEARCH_WAVES + wave;
+    const uint64_t nw = (uint64_t)gridDim.x * SEARCH_WAVES;
+    if (resume) {
+        list_load(Ls, Lr, c.list_sse + gw * KP, c.list_rank + gw * KP, KP);
+    } else {
+        for (int m = lane; m < KP; m += 64) {
+            Ls[m] = INF;
+            Lr[m] = ~0ull;
         }
+    }
+    pool_scan(c.s3_count, nseg, first, s_w);
+    const uint64_t ncand = uni(first[0][nseg]), nitem = uni(first[1][nseg]);
+    const double theta0 = theta0_of(c);
+    double theta_pub = INF;
+    unsigned offered = 0;
+    // the last waves take the first candidates: the first ones get the items
+    for (uint64_t b = nw - 1 - (uint64_t)gw; b * 64 < ncand; b += nw) {
+        const uint64_t e = b * 64 + lane;
+        const bool in = e < ncand;
+        uint64_t key = 0;
+        if (in) {
+            const uint32_t s = pool_segment(first[0], nseg, e);
+            key = c.s3_cands[(size_t)s * wg_tiles * S4_LANES + (e - first[0][s])];
+        }
+        s4_candidates(c, a, in, key, Ls, Lr, theta0, theta_pub, offered);
+    }
+    // the items round-robin: consecutive ones lie on different waves
+    for (uint64_t e = (uint64_t)gw; e < nitem; e += nw) {
+        const uint32_t s = pool_segment(first[1], nseg, e);
+        const uint64_t it = uni(c.s3_rows[(size_t)s * wg_tiles * S4_NR + (e - first[1][s])]);
+        S3Tile tl;
+        int64_t g1, g2;
+        s4_locate(c.S, tcum, it / S4_NR, tl, g1, g2);
+        s4_dense(c, a, tl, g1, S4_NR * g2 + (int64_t)(it % S4_NR), Ls, Lr, theta0, theta_pub, offered, s_r[wave],
+                 s_q[wave]);
     }
     if (lane == 0 && offered) atomicAdd(c.cand_counter, offered);
     list_store(c.list_sse + gw * KP, c.list_rank + gw * KP, Ls, Lr, KP);
@@ -4059,11 +4355,12 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
         // D = 3: the record-table sweep, on the filter task's matrix when
         // there are several tasks
         const bool s3 = D == 3 && !c.fp32 && c.rec3 != nullptr && s3_tiles_host(c.S) < (1ull << 31);
-        // one task, D = 4: the pair-group record table (sized at create only
-        // while it stays within S4_TABLE_MAX and 2^31 tiles)
+        // one task, D = 4: the record table of group pairs (sized at create
+        // only while it stays within S4_TABLE_MAX and 2^31 tiles)
         const bool s4 = D == 4 && !MT && !c.fp32 && c.rec4 != nullptr;
         if (s4) {
-            hipLaunchKernelGGL(s4_init_kernel, dim3(init_blocks), dim3(256), 0, st, c);
+            const int64_t nt = std::max((int64_t)(SISSO_MAX_D + 1) * (c.S + 1), s4_pairs_below(s4_groups(c.S)));
+            hipLaunchKernelGGL(s4_init_kernel, dim3((unsigned)((nt + 63) / 64)), dim3(64), 0, st, c);
         } else if (s3) {
             // record table + initialisation in one launch (its grid covers the binomial table)
             // x: the rows of one group (j, r); y: groups; the grid also covers
@@ -4083,17 +4380,29 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
             default: launch_prepass<4>(c, sc, st); break;
         }
         if (s4) {
-            // the pair-group record table (part of the set-up, like rec3 above)
-            const int64_t nrec = s4_rows_below(c.S, c.S - 2) * S4_NR;
-            hipLaunchKernelGGL(rec4_kernel, dim3((unsigned)((nrec + 255) / 256)), dim3(256), 0, st, c, c.rec4, nrec);
+            // the record table (part of the set-up, like rec3 above)
+            int64_t nitem = 0;
+            for (int64_t jb = 0; jb < s3_nblocks(c.S); ++jb) nitem += s4_block_pairs(c.S, jb);
+            hipLaunchKernelGGL(rec4_kernel, dim3((unsigned)((nitem + SEARCH_WAVES - 1) / SEARCH_WAVES)),
+                               dim3(SEARCH_WG), 0, st, c, nitem);
         }
         phase_end(c, SISSO_PHASE_PREPASS, st);
         phase_begin(c, SISSO_PHASE_SEARCH, st);
         const size_t nrec = MT ? (size_t)a.JB * c.TP : (size_t)SEARCH_WG;
         const size_t lds = lds_lists + nrec * RECW * sizeof(double) + (size_t)64 * SUBW * sizeof(double);
         if (s4) {
-            hipLaunchKernelGGL(search4_kernel, dim3(c.search_wgs), dim3(SEARCH_WG), lds_lists, st, c, a,
-                               (const double *)c.rec4, (const uint64_t *)c.cum);
+            const uint64_t ntiles = s4_tiles_host(c.S);
+            const uint32_t nseg = (uint32_t)c.search_wgs;
+            const size_t lds4 = lds_lists + (size_t)2 * (nseg + 1) * sizeof(uint64_t);
+            for (uint64_t t0 = 0; t0 < ntiles; t0 += S4_PASS) {
+                const uint64_t t1 = t0 + S4_PASS < ntiles ? t0 + S4_PASS : ntiles;
+                const uint32_t tiles = (uint32_t)s3_wg_tiles(t1 - t0, c.search_wgs);
+                hipLaunchKernelGGL(search4_kernel, dim3(c.search_wgs), dim3(SEARCH_WG), 0, st, c,
+                                   (const double *)c.rec4, (const double *)c.fac4, (const uint64_t *)c.cum, t0, t1,
+                                   tiles);
+                hipLaunchKernelGGL(s4_eval_kernel, dim3(c.search_wgs), dim3(SEARCH_WG), lds4, st, c, a,
+                                   (const uint64_t *)c.cum, nseg, tiles, t0 > 0);
+            }
         } else if (s3) {
             const uint64_t ntiles = s3_tiles_host(c.S);
             const uint32_t nseg = (uint32_t)c.search_wgs;

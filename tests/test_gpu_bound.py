@@ -95,6 +95,57 @@ def test_search_in_several_passes(T):
     assert np.array_equal(got[1], ref[1]) and np.array_equal(got[2], ref[2])
 
 
+@pytest.mark.parametrize("kind", ["planted", "noise", "dependent", "constant", "exact"])
+@pytest.mark.parametrize("S", [4, 5, 8, 9, 13, 65, 68, 71])
+def test_d4(kind, S):
+    """D = 4, one task: pairs of groups (the ten-feature fit bounds sixteen
+    tuples), over the edges of groups, pairs and tiles."""
+    p = problem(kind, S, 1, 4, 4000 + S)
+    k = max(1, min(20, math.comb(S, 4) // 2))
+    print(f"{kind} S={S}", flush=True)
+    gi, gs, gc = search(p, 4, k)
+    oi, os_, _ = oracle.topk(p.F, p.y, 4, k, p.task_offsets)
+    compare_topk(p, 4, k, gi, gs, oi, os_)
+
+
+@pytest.mark.parametrize("kind", ["planted", "noise", "dependent"])
+def test_d4_grids_and_ranges(kind):
+    """Every search grid gives the same result bit for bit; a range of ranks
+    gives the oracle's list of that range, also one with fewer tuples than the
+    list holds (no threshold: every tile is scored whole)."""
+    S, k = 68, 15
+    p = problem(kind, S, 1, 4, 91)
+    ref = search(p, 4, k)
+    for grid in (1, 3, 8, 64, 2048):
+        got = search(p, 4, k, grid=grid)
+        for a, b in zip(ref, got):
+            assert np.array_equal(a, b), grid
+    r0 = sum(math.comb(S - 1 - i, 3) for i in range(3))
+    r1 = sum(math.comb(S - 1 - i, 3) for i in range(6))
+    gi, gs, _ = search(p, 4, k, rng=(r0, r1))
+    oi, os_, _ = oracle.topk(p.F, p.y, 4, k, p.task_offsets, i1_range=(3, 6))
+    compare_topk(p, 4, k, gi, gs, oi, os_)
+    # first index S - 6: C(5, 3) = 10 tuples
+    r0 = sum(math.comb(S - 1 - i, 3) for i in range(S - 6))
+    gi, gs, _ = search(p, 4, 10, rng=(r0, r0 + 10))
+    oi, os_, _ = oracle.topk(p.F, p.y, 4, 10, p.task_offsets, i1_range=(S - 6, S - 5))
+    compare_topk(p, 4, 10, gi, gs, oi, os_)
+
+
+def test_d4_search_in_several_passes():
+    """S = 760 takes two passes over the tiles (one holds 2^17).  Three of four
+    columns are constant, so the result is that of the 190 live columns alone."""
+    p = tiny_problem(45, S=190, n=80, D=4, k=30, sigma=0.3)
+    ref = search(p, 4, 30)
+    wide = tiny_problem(45, S=4, n=80, D=4, k=1)
+    wide.F = np.full((760, p.n), 0.5)
+    wide.F[::4] = p.F
+    wide.y, wide.task_offsets = p.y, p.task_offsets
+    got = search(wide, 4, 30)
+    assert np.array_equal(got[0], 4 * ref[0])
+    assert np.array_equal(got[1], ref[1]) and np.array_equal(got[2], ref[2])
+
+
 def test_batch_of_weakly_bounded_problems():
     """The batched search takes the bound's flagged tuples inline: equal to
     the single searches bit for bit on planted, noise and dependent columns."""
