@@ -146,23 +146,21 @@ static Layout compute_layout(int64_t n_total, int64_t S, int T, int D_max, int k
         L.rec3_bytes = (D_max >= 3 && S >= 3 && !fp32) ? (size_t)rows3 * 16 * d : 0;
     }
     L.rec3 = take(L.rec3_bytes);
-    L.recg = take(L.rec3_bytes ? (size_t)s3_group_rows(S) * 16 * d : 0);
-    L.gfac = take(L.rec3_bytes ? (size_t)(S / 8 + 1) * 2 * 16 * d : 0);
-    // D = 4, one task: a record per (pair of groups, j); kept only while the
+    L.recg = take(L.rec3_bytes ? (size_t)s3_group_doubles(S) * d : 0);
+    // D = 4, one task: a table per pair of groups; kept only while the
     // table stays within S4_TABLE_MAX (else the general kernel runs)
     {
-        const size_t b4 = (size_t)s4_rows_host(S) * 12 * d;
-        L.rec4_bytes = (D_max >= 4 && T == 1 && S >= 4 && !fp32 && b4 <= S4_TABLE_MAX && s4_tiles_host(S) < (1ull << 31)) ? b4 : 0;
+        const size_t b4 = (size_t)s4_doubles_host(S) * d;
+        L.rec4_bytes = (D_max >= 4 && T == 1 && S >= 4 && !fp32 && b4 <= S4_TABLE_MAX) ? b4 : 0;
     }
     L.rec4 = take(L.rec4_bytes);
     L.fac4 = take(L.rec4_bytes ? (size_t)s4_pairs_host(S) * 48 * d : 0);
     L.G1_bytes = (D_max >= 3 && S >= 3 && T > 1) ? Sp * Sp * d : 0;
     L.G1 = take(L.G1_bytes);
-    // D = 3: per tile and group up to s3_lanes candidates or 8 row items;
-    // D = 4: per tile up to S4_LANES candidates or 4 items
-    const size_t pt3 = L.rec3_bytes ? s3_pool_tiles(S) : 0, pt4 = L.rec4_bytes ? s4_pool_tiles(S) : 0;
-    L.s3_cands = take(std::max(pt3 * 2 * s3_lanes(T), pt4 * S4_LANES) * sizeof(uint64_t));
-    L.s3_rows = take(std::max(pt3 * 2 * 8, pt4 * 4) * sizeof(uint64_t));
+    // per unit up to s3_lanes (S4_LANES) candidates, or 8 (D = 4: 16) items
+    const size_t pt3 = L.rec3_bytes ? s3_pool_units(S) : 0, pt4 = L.rec4_bytes ? s4_pool_units(S) : 0;
+    L.s3_cands = take(std::max(pt3 * s3_lanes(T), pt4 * S4_LANES) * sizeof(uint64_t));
+    L.s3_rows = take(std::max(pt3 * 8, pt4 * 16) * sizeof(uint64_t));
     L.s3_count = take(L.rec3_bytes ? (size_t)SEARCH_WGS_MAX * 2 * sizeof(uint32_t) : 0);
     L.lists = take((size_t)nlists * L.KP * 2 * d + (size_t)nlists * L.KP * 2 * d);
     // FP64 Gram: the residues take the zone above, GM_KC_MIN samples at a time
@@ -273,7 +271,6 @@ static void carve(sisso_l0 *h) {
     c.tstar = (int32_t *)p;
     c.rec3 = L.rec3_bytes ? (double *)(base + L.rec3) : nullptr;
     c.recg = L.rec3_bytes ? (double *)(base + L.recg) : nullptr;
-    c.gfac = L.rec3_bytes ? (double *)(base + L.gfac) : nullptr;
     c.G1 = L.G1_bytes ? (double *)(base + L.G1) : c.G;
     c.rec4 = L.rec4_bytes ? (double *)(base + L.rec4) : nullptr;
     c.fac4 = L.rec4_bytes ? (double *)(base + L.fac4) : nullptr;
@@ -842,7 +839,7 @@ extern "C" int32_t sisso_l0_batch_create(sisso_l0 *const *hs, int32_t P, int32_t
     for (int p = 0; p < P; ++p)
         if (s3_batchable(b->hs[p]->ctx, D)) shared.push_back(p);
     std::stable_sort(shared.begin(), shared.end(), [&](int x, int y) {
-        return s3_tiles_host(b->hs[x]->desc.S) > s3_tiles_host(b->hs[y]->desc.S);
+        return s3_items_host(b->hs[x]->desc.S) > s3_items_host(b->hs[y]->desc.S);
     });
     std::vector<char> in_shared(P, 0);
     for (int p : shared) in_shared[p] = 1;
@@ -859,7 +856,7 @@ extern "C" int32_t sisso_l0_batch_create(sisso_l0 *const *hs, int32_t P, int32_t
         uint32_t acc = 0;
         for (int q = 0; q < a.P; ++q) {
             sisso_l0 *h = b->hs[shared[g0 + q]];
-            acc += (uint32_t)((s3_tiles_host(h->desc.S) + S3B_RUN - 1) / S3B_RUN);
+            acc += (uint32_t)((s3_items_host(h->desc.S) + S3B_RUN - 1) / S3B_RUN);
             ends[q] = acc;
             ptrs[q] = (const Ctx *)((const char *)h->desc.workspace + h->lay.self);
             a.KPmax = std::max(a.KPmax, h->ctx.KP);

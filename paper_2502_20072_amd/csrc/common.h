@@ -235,7 +235,7 @@ __host__ __device__ inline void colex_unrank_small(uint64_t r, int q, int64_t N,
 }
 
 constexpr size_t S4_TABLE_MAX = (size_t)4 << 30;  // largest D = 4 record table kept in the workspace
-constexpr int S4_LANES = 1024;  // D = 4: most flagged candidates of a tile that are scored one by one
+constexpr int S4_LANES = 512;  // D = 4: most flagged candidates of a unit that are scored one by one
 
 // Device state of the threshold pre-pass (reset by its selection).
 struct PreState {
@@ -274,11 +274,10 @@ struct Layout {
     size_t pre;        // pre-pass scratch
     size_t rec3;       // D = 3: pair records of the filter task, double [ceil(S/4)][S][4][4] (0 bytes otherwise)
     size_t rec3_bytes;
-    size_t recg;       //   group records, double [rows][2][8], and group factors, double [groups][16]
-    size_t gfac;
+    size_t recg;       //   group tables, double [groups][9][S - 4 g]
     size_t G1;         // D = 3, several tasks: the filter task's matrix alone, double [S][S] tiled (0 bytes otherwise)
     size_t G1_bytes;
-    size_t rec4;       // D = 4, one task: group-pair records, double [rows][12] (0 bytes otherwise)
+    size_t rec4;       // D = 4, one task: group-pair tables, double [pairs][13][S - 4 g2] (0 bytes otherwise)
     size_t rec4_bytes;
     size_t fac4;       //   and group-pair factors, double [pairs][48]
     size_t self;       // a device copy of the handle's Ctx (read by the batched search)

@@ -35,10 +35,9 @@ struct Ctx {
     uint64_t *btab;                  // binomials C(n, r), r <= SISSO_MAX_D, n <= S
     PreState *pre;                   // threshold pre-pass: prefixes, pool histogram, bound
     double *rec3;                    // D = 3: pair records of the filter task [ceil(S/4)][S][4][4] (null if absent)
-    double *recg;                    // D = 3: group records of the filter task [rows of group pairs][2][8] (null if absent)
-    double *gfac;                    //   group factors [groups, padded to even][16]
+    double *recg;                    // D = 3: group tables of the filter task [groups][9][S - 4 g] (null if absent)
     double *G1;                      // the filter task's matrix alone, one-task tiled layout (G itself when T = 1)
-    double *rec4;                    // D = 4, one task: group-pair records [rows][12] (null if absent)
+    double *rec4;                    // D = 4, one task: group-pair tables [pairs][13][S - 4 g2] (null if absent)
     double *fac4;                    //   group-pair factors [pairs][48]
     uint64_t *s3_cands;              // D = 3, 4: flagged (group, row, column) candidates, a segment per workgroup
     uint64_t *s3_rows;               //   and flagged rows of dense (group, row block, column chunk)s
@@ -78,13 +77,12 @@ struct SearchCall {
     uint64_t r0, r1;
 };
 
-uint64_t s3_tiles_host(int64_t S);  // tiles of the D = 3 record-table sweep
-size_t s3_pool_tiles(int64_t S);    // tiles its item pools have to hold
-int s3_lanes(int T);                // candidates per (tile, group) in them
-int64_t s3_group_rows(int64_t S);   // rows of its group-record table
-uint64_t s4_tiles_host(int64_t S);  // tiles of the D = 4 record-table sweep
-size_t s4_pool_tiles(int64_t S);    // tiles its item pools have to hold
-int64_t s4_rows_host(int64_t S);    // rows of its record table
+uint64_t s3_items_host(int64_t S);  // items of the D = 3 record-table sweep
+size_t s3_pool_units(int64_t S);    // units its pools have to hold
+int s3_lanes(int T);                // candidates per unit in them
+int64_t s3_group_doubles(int64_t S);  // size of its group tables
+size_t s4_pool_units(int64_t S);    // D = 4: units its pools have to hold
+int64_t s4_doubles_host(int64_t S);  // size of its group-pair tables
 int64_t s4_pairs_host(int64_t S);   // pairs of groups
 int launch_stats(const Ctx &c, hipStream_t st);
 int launch_gram(const Ctx &c, hipStream_t st);  // correlation matrices: FP64 or precision form
@@ -103,7 +101,7 @@ int launch_list_search(const Ctx &c, int D, int k, const int32_t *pre, int64_t n
 // batched one-task D = 3 search: per-problem prologue, one search launch for
 // all problems, per-problem epilogue (merge, re-score, final ordering)
 constexpr int S3B_MAXP = 128;  // problems per batched search launch
-constexpr int S3B_RUN = 8;    // consecutive tiles per queue item
+constexpr int S3B_RUN = 4;    // consecutive items per queue entry
 struct BatchSearchArgs {
     int P;                          // problems, ordered by decreasing tile count
     int KPmax;                      // longest list among them

@@ -1388,41 +1388,36 @@ __global__ __launch_bounds__(256) void search_kernel(Ctx c, SearchArgs a) {
 
 // ---------------------------------------------- D = 3: record-table sweep
 // Per search two tables of Cholesky rows are built (rec3_kernel): one row per
-// pair (i1, j), and one per (group of four consecutive i1, j) for the group
-// and j together.  A tuple's SSE is at least that of any superset, so the
-// sweep first tests, per (group, j, k), the fit on all six features {the
-// group, j, k}: 10 FP64 instructions for four tuples, against 28 for testing
-// the four one by one.  Only where that bound is at or below the threshold
-// are the group's tuples tested themselves.  (Bound on k: on operator-tree
-// columns 0.1 to 1 in 1000 of the six-feature fits pass.)
+// pair (i1, j), and one per (group of four consecutive i1, column) for the
+// group and the column together.  A tuple's SSE is at least that of any
+// superset, so the sweep first tests, per (group, j, k), the fit on all six
+// features {the group, j, k}: a product with four terms and 5 FP64
+// instructions for four tuples, against 28 for testing the four one by one.
+// Only where that bound is at or below the threshold are the group's tuples
+// tested themselves.  (Bound on k: on operator-tree columns 0.1 to 1 in 1000 of the
+// six-feature fits pass.)
 //
-// Lanes run over the last index k, so a record is the same for every lane
-// and is read with scalar loads: it enters the FP64 instructions as a scalar
-// operand, at no LDS or vector-memory cost.  A work tile is (two groups of
-// four i1, S3_JR rows j from j0, S3_KC columns k from j0 + 1 + S3_KC c); lane
-// l takes k = kb + l and kb + 64 + l (one load of G[j][k] each serves 8
-// tuples), so only chunk 0 holds tuples with k <= j (in its first half), and
-// a last chunk with at most 64 columns left runs its first half only.  Tiles
-// are dealt to single waves round-robin, so no wave waits on another.
-// Per tuple, the arithmetic of the group's own test is that of
-// search_kernel's single-task path: u = g - v w', d = d' - alpha u^2, zeta =
-// zeta' - zs u, pass iff zeta^2 >= (p - theta) d; the group's bound is the
-// same with four v and w'.
-constexpr int S3_NR = 4;              // i1 per tile (a group)
-constexpr int S3_GP = 2;              // groups per tile
-constexpr int S3_KC = 128;            // k per tile: two per lane, 64 apart
-constexpr int S3_LANES = 64;          // flagged (row, column) pairs of a tile's group taken one per lane, one task
-constexpr int S3_LANES_MT = 256;      //   the same, several tasks; with more, the flagged rows are swept whole
-#ifndef S3_JR
-#define S3_JR 64                      // j rows per tile (divides 64)
+// The bound's unit of work is (group, BU rows j from j0, BU columns k from j0
+// + BU c) (bound_unit); an item is a run of groups over one block of G, which
+// a workgroup holds in LDS while its waves take the groups in turn.  Per
+// tuple, the arithmetic of the group's own test is that of search_kernel's
+// single-task path: u = g - v w', d = d' - alpha u^2, zeta = zeta' - zs u, pass
+// iff zeta^2 >= (p - theta) d; the group's bound is the same with four v and
+// w'.  s3_group tests whole rows of a unit: lanes run over k, so a record is
+// the same for every lane and is read with scalar loads; it enters the FP64
+// instructions as a scalar operand, at no LDS or vector-memory cost.
+constexpr int S3_NR = 4;              // i1 per group
+constexpr int BU = 64;                // rows and columns of a unit (a tile of G)
+#ifndef BU_WGS
+#define BU_WGS 1024                   // workgroups of the bound kernels: four per CU (LDS)
 #endif
+constexpr int S3_LANES = 32;          // flagged (row, column) pairs of a unit taken one per lane, one task
+constexpr int S3_LANES_MT = 128;      //   the same, several tasks; with more, the flagged rows are swept whole
+constexpr int S3_JR = BU;
 #ifndef S3_JG
 #define S3_JG 2                       // G rows per prefetch group (two groups in flight)
 #endif
 constexpr int S3_XCDS = 8;            // XCDs of the chip
-#ifndef S3_XCD_RUN
-#define S3_XCD_RUN 64                 // consecutive tiles dealt within one XCD
-#endif
 
 // Rows of the record table: group g (i1 = S3_NR g .. S3_NR g + 3) holds rows
 // j = S3_NR g + 1 .. S - 2, starting at row s3_rowoff(S, g).
@@ -1440,30 +1435,29 @@ __host__ __device__ inline int64_t s3_rows(int64_t S) {
 // with v = G[i1][j], d_j = 1 - v^2, s_j = sqrt(d_j), z_j = (b_j - v b_i1) / s_j,
 // p = c - b_i1^2 - z_j^2 (the SSE of the pair); p = NaN (fails every
 // comparison) unless i1 < j, column i1 is live and d_j > RANK_EPS.
-// Group records: group g's own factor (correlations of its live columns, in
-// index order) projects any column x onto the group's span: w = R^-1 G[g, x].
-// Row (pair of groups h, j), j = 8 h + 1 .. S - 2, of 2 x 8 doubles:
-//   {v0..v3, alpha = 1/d, zs = e/d, p, zs^2} with v = w(j), e = b_j - v.z, d = 1 - |v|^2,
-//   z = R^-1 b_g, p = c - |z|^2 - e^2/d (the SSE of the group and j),
-// and per group the factor {R^-1 (10), z (4), 0, 0}.  The bound is computed
+// Group tables: group g's own factor (correlations of its live columns, in
+// index order, G = R^T R) projects any column x onto the group's span, v = R^-T
+// G[g, x].  Columns x = 4 g .. S - 1, field by field (columns consecutive):
+//   v0..v3, alpha = 1/d, zs = e/d, p, d, e with e = b_x - v.z, d = 1 - |v|^2,
+//   z = R^-T b_g, p = c - |z|^2 - e^2/d (the SSE of the group and x).
+// A tuple's j reads alpha, zs, p, its k reads d and e.  The bound is computed
 // with group pivots above S3_TAU only and compared with slacks (S3_DSLACK on
-// d, S3_TSLACK c on theta) above the rounding that leaves: p = 0 marks a row
-// whose group or j is too close to dependent (it always passes), p = S3_NEVER
-// one without a tuple (j constant, or no i1 < j).  A j of the group itself
-// leaves the group alone (v = 0, 1/d = 0).
+// d, S3_TSLACK c on theta) above the rounding that leaves: p = 0 marks a j
+// whose group or column is too close to dependent (it always passes), p =
+// S3_NEVER one without a tuple (a constant column), d = S3_NEVER a constant k.
+// A column of the group itself leaves the group alone (v = 0, alpha = 0).
 constexpr double S3_TAU = 1e-5, S3_DSLACK = 1e-7, S3_TSLACK = 1e-7, S3_ESLACK = 1e-13, S3_NEVER = 1e300;
-constexpr int S3_GREC = 8;   // doubles per group record
-constexpr int S3_GFAC = 16;  // doubles per group factor
-__host__ __device__ inline int64_t s3g_rowoff(int64_t S, int64_t h) {
-    // sum over h' < h of (S - 2 - 8 h')
-    return h * (S - 2) - (int64_t)S3_NR * S3_GP * (h * (h - 1) / 2);
-}
-int64_t s3_group_rows(int64_t S) { return S >= 3 ? s3g_rowoff(S, (S - 3) / (S3_NR * S3_GP) + 1) : 0; }
+// fields of a table over K features
+enum { BF_AL, BF_ZS, BF_P, BF_D, BF_E, BF_N };  // after the K entries of v
+constexpr int S3_FIELDS = S3_NR + BF_N;
+// columns of the groups before g (S - 4 g' each)
+__host__ __device__ inline int64_t s3g_off(int64_t S, int64_t g) { return g * S - (int64_t)S3_NR * (g * (g - 1) / 2); }
+int64_t s3_group_doubles(int64_t S) { return S >= 3 ? s3g_off(S, (S - 3) / S3_NR + 1) * S3_FIELDS : 0; }
 
 __device__ void s3_group_record(const Ctx &c, int64_t g, int64_t x) {
     const int64_t S = c.S, nt = c.Gnt;
-    const int64_t h = g / S3_GP, j = (int64_t)S3_NR * S3_GP * h + 1 + x;
-    if (h > (S - 3) / (S3_NR * S3_GP) || j > S - 2) return;
+    const int64_t j = S3_NR * g + x;
+    if (g > (S - 3) / S3_NR || j > S - 1) return;
     const int ts = c.tstar[0], TP = c.TP;
     const double *__restrict__ G1 = c.G1;
     // the group's factor (the same for every thread of the group)
@@ -1497,24 +1491,14 @@ __device__ void s3_group_record(const Ctx &c, int64_t g, int64_t x) {
         z[m] = zz;
         pg -= zz * zz;
     }
-    if (x == 0) {
-        double *f = c.gfac + g * S3_GFAC;
-        int e = 0;
-#pragma unroll
-        for (int m = 0; m < S3_NR; ++m)
-#pragma unroll
-            for (int l = 0; l <= m; ++l) f[e++] = Li[m][l];
-#pragma unroll
-        for (int m = 0; m < S3_NR; ++m) f[e++] = z[m];
-        f[e] = f[e + 1] = 0.0;
-    }
-    double v[S3_NR] = {0.0, 0.0, 0.0, 0.0}, al = 0.0, zs = 0.0, p = pg;
-    if (S3_NR * g >= j || !(G1[gidx(j, j, nt, 1, 0)] > 0.5)) {
-        p = S3_NEVER;
+    double v[S3_NR] = {0.0, 0.0, 0.0, 0.0}, al = 0.0, zs = 0.0, p = pg, d = 0.0, e = 0.0;
+    if (!(G1[gidx(j, j, nt, 1, 0)] > 0.5)) {
+        p = d = S3_NEVER;
     } else if (bad) {
         p = 0.0;
     } else if (j >= S3_NR * (g + 1)) {
-        double d = 1.0, e = c.bhat[j * TP + ts];
+        d = 1.0;
+        e = c.bhat[j * TP + ts];
 #pragma unroll
         for (int m = 0; m < S3_NR; ++m) {
             double s = 0.0;
@@ -1532,13 +1516,16 @@ __device__ void s3_group_record(const Ctx &c, int64_t g, int64_t x) {
             p = 0.0;
         }
     }
-    double *o = c.recg + ((s3g_rowoff(S, h) + x) * S3_GP + g % S3_GP) * S3_GREC;
+    const int64_t len = S - S3_NR * g;
+    double *o = c.recg + s3g_off(S, g) * S3_FIELDS + x;
 #pragma unroll
-    for (int m = 0; m < S3_NR; ++m) o[m] = v[m];
-    o[4] = al;
-    o[5] = zs;
-    o[6] = p;
-    o[7] = zs * zs;
+    for (int m = 0; m < S3_NR; ++m) o[m * len] = v[m];
+    o += S3_NR * len;
+    o[BF_AL * len] = al;
+    o[BF_ZS * len] = zs;
+    o[BF_P * len] = p;
+    o[BF_D * len] = d;
+    o[BF_E * len] = e;
 }
 
 // (its grid also does the per-search initialisation of search_init_kernel)
@@ -1592,44 +1579,57 @@ __global__ __launch_bounds__(PRE_WG) void rec3_kernel(Ctx c, double *__restrict_
     o[3] = p;
 }
 
-// Tiles of j-block jb (j in [S3_JR jb, S3_JR jb + S3_JR) and j <= S - 2):
-// nkb column chunks (k from j0 + 1 to S - 1) times pairs of groups h < nh
-// (the pair's first i1 lies below the block's last j).
-__host__ __device__ inline void s3_block(int64_t S, int64_t jb, int64_t &nkb, int64_t &nh) {
-    const int64_t j0 = jb * S3_JR;
-    int64_t jmax = j0 + S3_JR - 1;
+// Row blocks jb: j in [BU jb, BU jb + BU), j <= S - 2; each has the column
+// chunks from its own on (k >= j0).  The bases of class q (a base is a group, D
+// = 4 a pair of groups) are those whose first row lies in row block q; class
+// q's units are its bases times the s3_class_units(S, q) blocks of G.  Items
+// are numbered by class, then by run of bases, then by block of G, so that the
+// items at work at one time read few bases' tables, and these from L2.
+__host__ __device__ inline int64_t s3_nblocks(int64_t S) { return S >= 3 ? (S - 2) / BU + 1 : 0; }
+// blocks of G in the first r row blocks of class q
+__host__ __device__ inline int64_t s3_class_below(int64_t S, int64_t q, int64_t r) {
+    return r * ((S + BU - 1) / BU - q) - r * (r - 1) / 2;
+}
+__host__ __device__ inline int64_t s3_class_units(int64_t S, int64_t q) {
+    return s3_class_below(S, q, s3_nblocks(S) - q);
+}
+// groups with a first row 4 g + 1 below row block q's end
+__host__ __device__ inline int64_t s3_groups_to(int64_t S, int64_t q) {
+    int64_t jmax = q * BU + BU - 1;
     if (jmax > S - 2) jmax = S - 2;
-    nkb = (S - j0 - 1 + S3_KC - 1) / S3_KC;
-    nh = jmax >= 1 ? (jmax - 1) / (S3_NR * S3_GP) + 1 : 0;
+    return q >= 0 && jmax >= 1 ? (jmax - 1) / S3_NR + 1 : 0;
 }
-__host__ __device__ inline int64_t s3_nblocks(int64_t S) { return S >= 3 ? (S - 2) / S3_JR + 1 : 0; }
+// bases below class q (pairs: of groups g1 <= g2)
+struct S3Groups {
+    static __host__ __device__ int64_t below(int64_t S, int64_t q) { return s3_groups_to(S, q - 1); }
+};
 
-// tcum[jb] = tiles of the blocks before jb (tcum[nblocks] = all tiles)
-__device__ void s3_tile_table(const Ctx &c) {
-    const int64_t nb = s3_nblocks(c.S);
+// Bases per item: a block of G (32 KB) is read once per run, and the runs
+// have to fill the chip: 16 from 8192 units on (4 a wave), down to one a wave.
+__host__ __device__ inline int bound_run(uint64_t units) { return units <= 4096 ? 4 : units <= 8192 ? 8 : 16; }
+template <class B>
+__host__ __device__ inline uint64_t bound_units(int64_t S) {
     uint64_t acc = 0;
-    c.cum[0] = 0;
-    for (int64_t b = 0; b < nb; ++b) {
-        int64_t nkb, nh;
-        s3_block(c.S, b, nkb, nh);
-        acc += (uint64_t)(nkb * nh);
-        c.cum[b + 1] = acc;
-    }
-    c.stats[1] = acc;
+    for (int64_t q = 0; q < s3_nblocks(S); ++q)
+        acc += (uint64_t)((B::below(S, q + 1) - B::below(S, q)) * s3_class_units(S, q));
+    return acc;
 }
-
-int s3_steps_per_tile() { return S3_JR * S3_GP; }
-
-uint64_t s3_tiles_host(int64_t S) {
-    const int64_t nb = s3_nblocks(S);
+// all items; cum[q] = items of the classes before q
+template <class B>
+__host__ __device__ inline uint64_t bound_items(int64_t S, int run, uint64_t *cum) {
     uint64_t acc = 0;
-    for (int64_t b = 0; b < nb; ++b) {
-        int64_t nkb, nh;
-        s3_block(S, b, nkb, nh);
-        acc += (uint64_t)(nkb * nh);
+    if (cum) cum[0] = 0;
+    for (int64_t q = 0; q < s3_nblocks(S); ++q) {
+        const int64_t nb = B::below(S, q + 1) - B::below(S, q);
+        acc += (uint64_t)((nb + run - 1) / run * s3_class_units(S, q));
+        if (cum) cum[q + 1] = acc;
     }
     return acc;
 }
+__device__ void s3_tile_table(const Ctx &c) {
+    c.stats[1] = bound_items<S3Groups>(c.S, bound_run(bound_units<S3Groups>(c.S)), c.cum);
+}
+uint64_t s3_items_host(int64_t S) { return bound_items<S3Groups>(S, bound_run(bound_units<S3Groups>(S)), nullptr); }
 
 #ifndef S3_WPE
 #define S3_WPE 4                      // waves per SIMD the register budget is sized for
@@ -1752,13 +1752,12 @@ typedef const __attribute__((address_space(4))) double CDouble;
 typedef const __attribute__((address_space(4))) char CChar;
 __device__ inline CDouble *cptr(const double *p) { return (CDouble *)(uintptr_t)p; }
 
-// Where a tile lies: row block jb, its rows jlo .. jhi, column chunk kcx from
-// column kb.
+// Where a unit lies: its rows j0 .. jhi, column chunk kcx, from column kb.
 struct S3Tile {
     int64_t j0, jhi, kb, kcx;
 };
 
-// The rows jlo .. jhi of a tile for one group: the tile's k-dependent terms, the
+// The rows jlo .. jhi of a unit for one group: the unit's k-dependent terms, the
 // tuples' own test over the rows, exact scoring of the flagged steps into the
 // wave's list (one task) or buffer (several tasks), and the publication of the
 // wave's bound.
@@ -1769,7 +1768,7 @@ template <bool MT, class CtxT>
 __device__ __forceinline__ void s3_group(const CtxT &c, const SearchArgs &a, const double *__restrict__ rec,
                                          const S3Tile &tl, int64_t g, int64_t jlo, int64_t jhi, double *Ls,
                                          uint64_t *Lr, double theta0, double &theta_pub, unsigned &offered,
-                                         MtBuf &mb, unsigned long long (*s_qw)[2], int *s_qjw) {
+                                         MtBuf &mb, unsigned long long *s_qw, int *s_qjw) {
     const int KP = a.KP;
     const int lane = threadIdx.x & 63;
     const int64_t S = c.S;
@@ -1783,38 +1782,33 @@ __device__ __forceinline__ void s3_group(const CtxT &c, const SearchArgs &a, con
         const int64_t j0 = tl.j0;
         const int nrow = (int)(jhi - jlo);  // steps 0..nrow
         const int64_t kb = tl.kb;
-        const int64_t k0 = kb + lane, k1 = kb + 64 + lane;
-        const bool kv0 = k0 < S, kv1 = k1 < S;
+        const int64_t k0 = kb + lane;
+        const bool kv0 = k0 < S;
         // columns read for lanes past S: any valid one (never passes)
-        const int64_t kk0 = kv0 ? k0 : S - 1, kk1 = kv1 ? k1 : S - 1;
-        const bool diag = kcx == 0;            // k <= j only in chunk 0, first half
-        const bool half = S - kb <= 64;        // no column in the second half
+        const int64_t kk0 = kv0 ? k0 : S - 1;
+        const bool diag = kcx == 0;            // k <= j only in chunk 0
 
         double th = fmin(theta0, theta_load(c.theta_bits));
         th = fmin(th, Ls[KP - 1]);
         const double theta_f = th < INF ? th * (1.0 + THETA_SLACK) : INF;
 
-        // k-dependent part of each i1's solve, for both columns of the lane
-        double w[S3_NR][2], dq[S3_NR][2], zq[S3_NR][2];
+        // k-dependent part of each i1's solve
+        double w[S3_NR], dq[S3_NR], zq[S3_NR];
         {
             // G[k][k] is 1 for a live column and 0 for a constant one; the
             // contiguous 1/|x - mean| row says which (0 = constant)
             const double gd0 = inv_st[kk0] > 0.0 ? 1.0 : 0.0;
-            const double gd1 = inv_st[kk1] > 0.0 ? 1.0 : 0.0;
-            const double b0 = c.bhat[kk0 * TP + ts], b1 = c.bhat[kk1 * TP + ts];
+            const double b0 = c.bhat[kk0 * TP + ts];
 #pragma unroll
             for (int r = 0; r < S3_NR; ++r) {
                 int64_t i1 = S3_NR * g + r;
                 if (i1 > S - 1) i1 = S - 1;
                 const double zp = c.bhat[i1 * TP + ts];
-                const double2 wv = {Gb[gidx(i1, kk0, nt, 1, 0)], Gb[gidx(i1, kk1, nt, 1, 0)]};
-                w[r][0] = wv.x;
-                w[r][1] = wv.y;
+                const double wv = Gb[gidx(i1, kk0, nt, 1, 0)];
+                w[r] = wv;
                 // a lane past S or on a constant column never passes
-                dq[r][0] = (kv0 && gd0 > RANK_EPS) ? fma(-wv.x, wv.x, gd0) : __builtin_nan("");
-                dq[r][1] = (kv1 && gd1 > RANK_EPS) ? fma(-wv.y, wv.y, gd1) : __builtin_nan("");
-                zq[r][0] = fma(-wv.x, zp, b0);
-                zq[r][1] = fma(-wv.y, zp, b1);
+                dq[r] = (kv0 && gd0 > RANK_EPS) ? fma(-wv, wv, gd0) : __builtin_nan("");
+                zq[r] = fma(-wv, zp, b0);
             }
         }
         // G[j][k] for the block's rows: j >> 6 is the same for the whole block
@@ -1823,21 +1817,18 @@ __device__ __forceinline__ void s3_group(const CtxT &c, const SearchArgs &a, con
         const char *__restrict__ gtile =
             reinterpret_cast<const char *>(Gb + (((j0 >> 6) * nt) << 12));
         const uint32_t voff0 = (uint32_t)((((kk0 >> 6) << 12) + (kk0 & 63) + ((jlo & 63) << 6)) * 8);
-        const uint32_t voff1 = (uint32_t)((((kk1 >> 6) << 12) + (kk1 & 63) + ((jlo & 63) << 6)) * 8);
         // records of row jlo + x are 128 bytes at recj + 128 x (uniform)
         CChar *recj = (CChar *)(cptr(rec) + (size_t)(s3_rowoff(S, g) + jlo - S3_NR * g - 1) * (S3_NR * 4));
         int nq = 0;
-        auto sweep = [&](auto diagc, auto halfc) {
+        auto sweep = [&](auto diagc) {
             constexpr bool DIAG = decltype(diagc)::value;
-            constexpr bool HALF = decltype(halfc)::value;
             constexpr int JG = S3_JG;
-            double2 ga[JG], gb[JG];  // g(j, k0), g(j, k1)
-            auto fetch = [&](double2 (&dst)[JG], int jg) {
+            double ga[JG], gb[JG];  // g(j, k)
+            auto fetch = [&](double (&dst)[JG], int jg) {
 #pragma unroll
                 for (int x = 0; x < JG; ++x) {
                     const uint32_t jr = (uint32_t)(jg + x < nrow ? jg + x : nrow);
-                    dst[x].x = *reinterpret_cast<const double *>(gtile + (voff0 + jr * 512u));
-                    dst[x].y = HALF ? 0.0 : *reinterpret_cast<const double *>(gtile + (voff1 + jr * 512u));
+                    dst[x] = *reinterpret_cast<const double *>(gtile + (voff0 + jr * 512u));
                 }
             };
             // records of one step are two halves of 64 bytes (i1 = 4g, 4g+1 and
@@ -1849,48 +1840,38 @@ __device__ __forceinline__ void s3_group(const CtxT &c, const SearchArgs &a, con
 #pragma unroll
                 for (int e = 0; e < 8; ++e) rv[e] = rp[e];
             };
-            auto score_half = [&](const double (&rv)[8], const double2 gv, int h, unsigned long long &m0,
-                                  unsigned long long &m1) {
+            auto score_half = [&](const double (&rv)[8], const double gv, int h, unsigned long long &m0) {
 #pragma unroll
                 for (int rr = 0; rr < 2; ++rr) {
                     const int r = 2 * h + rr;
                     const double pi = rv[4 * rr + 3] - theta_f;
-                    {
-                        const double u = fma(-rv[4 * rr], w[r][0], gv.x);
-                        const double d = fma(-rv[4 * rr + 1], u * u, dq[r][0]);
-                        const double z = fma(-rv[4 * rr + 2], u, zq[r][0]);
-                        m0 |= __ballot(z * z >= pi * d);
-                    }
-                    if (!HALF) {
-                        const double u = fma(-rv[4 * rr], w[r][1], gv.y);
-                        const double d = fma(-rv[4 * rr + 1], u * u, dq[r][1]);
-                        const double z = fma(-rv[4 * rr + 2], u, zq[r][1]);
-                        m1 |= __ballot(z * z >= pi * d);
-                    }
+                    const double u = fma(-rv[4 * rr], w[r], gv);
+                    const double d = fma(-rv[4 * rr + 1], u * u, dq[r]);
+                    const double z = fma(-rv[4 * rr + 2], u, zq[r]);
+                    m0 |= __ballot(z * z >= pi * d);
                 }
             };
             double ra[8], rb[8];
             load_half(ra, 0, 0);
-            auto score = [&](const double2 (&src)[JG], int jg) {
+            auto score = [&](const double (&src)[JG], int jg) {
 #pragma unroll
                 for (int x = 0; x < JG; ++x) {
                     const int jr = jg + x;
                     const int jc = jr <= nrow ? jr : nrow;
-                    unsigned long long m0 = 0, m1 = 0;
+                    unsigned long long m0 = 0;
                     __builtin_amdgcn_s_waitcnt(0xC07F);
                     load_half(rb, jc, 1);
                     __builtin_amdgcn_sched_barrier(0);
-                    score_half(ra, src[x], 0, m0, m1);
+                    score_half(ra, src[x], 0, m0);
                     __builtin_amdgcn_s_waitcnt(0xC07F);
                     load_half(ra, jr + 1 <= nrow ? jr + 1 : nrow, 0);
                     __builtin_amdgcn_sched_barrier(0);
-                    score_half(rb, src[x], 1, m0, m1);
-                    if (DIAG) m0 &= __ballot(k0 > jlo + jr);  // k1 > j0 + 64 > j
-                    if (jr > nrow) m0 = m1 = 0;
-                    if (m0 | m1) {
+                    score_half(rb, src[x], 1, m0);
+                    if (DIAG) m0 &= __ballot(k0 > jlo + jr);
+                    if (jr > nrow) m0 = 0;
+                    if (m0) {
                         if (lane == 0) {
-                            s_qw[nq][0] = m0;
-                            s_qw[nq][1] = m1;
+                            s_qw[nq] = m0;
                             s_qjw[nq] = jr;
                         }
                         ++nq;
@@ -1907,13 +1888,8 @@ __device__ __forceinline__ void s3_group(const CtxT &c, const SearchArgs &a, con
                 if (jg + 2 * JG > nrow) break;
             }
         };
-        if (diag) {
-            if (half) sweep(std::true_type{}, std::true_type{});
-            else sweep(std::true_type{}, std::false_type{});
-        } else {
-            if (half) sweep(std::false_type{}, std::true_type{});
-            else sweep(std::false_type{}, std::false_type{});
-        }
+        if (diag) sweep(std::true_type{});
+        else sweep(std::false_type{});
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         __builtin_amdgcn_wave_barrier();
 
@@ -1922,45 +1898,37 @@ __device__ __forceinline__ void s3_group(const CtxT &c, const SearchArgs &a, con
         for (int e = 0; e < nq; ++e) {
             const int jr = s_qjw[e];
             const int64_t j = jlo + jr;
-            const unsigned long long fm[2] = {s_qw[e][0], s_qw[e][1]};
+            const unsigned long long fm = s_qw[e];
             CDouble *rp = (CDouble *)(recj + (size_t)jr * 128);
-            const double2 gv = {*reinterpret_cast<const double *>(gtile + (voff0 + (uint32_t)jr * 512u)),
-                                *reinterpret_cast<const double *>(gtile + (voff1 + (uint32_t)jr * 512u))};
-            // (r, sl) are wave-uniform here: pick the k-data by selects, so
-            // the arrays stay in registers (an indexed read would move them to
-            // scratch memory, stored on every tile)
-            auto pick = [&](const double (&arr)[S3_NR][2], int r, int sl) {
-                double v = arr[0][0];
+            const double gg = *reinterpret_cast<const double *>(gtile + (voff0 + (uint32_t)jr * 512u));
+            // r is wave-uniform here: pick the k-data by selects, so the
+            // arrays stay in registers (an indexed read would move them to
+            // scratch memory, stored on every unit)
+            auto pick = [&](const double (&arr)[S3_NR], int r) {
+                double v = arr[0];
 #pragma unroll
-                for (int q = 0; q < S3_NR; ++q)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-                        if (q == r && h == sl) v = arr[q][h];
+                for (int q = 1; q < S3_NR; ++q)
+                    if (q == r) v = arr[q];
                 return v;
             };
             for (int r = 0; r < S3_NR; ++r) {
                 const double v = rp[4 * r], al = rp[4 * r + 1], zs = rp[4 * r + 2], p = rp[4 * r + 3];
-                for (int sl = 0; sl < 2; ++sl) {
-                    const double gg = sl ? gv.y : gv.x;
-                    const int64_t k = sl ? k1 : k0;
-                    const double u = fma(-v, pick(w, r, sl), gg);
-                    const double d = fma(-al, u * u, pick(dq, r, sl));
-                    const double z = fma(-zs, u, pick(zq, r, sl));
-                    const int32_t tup[3] = {(int32_t)(S3_NR * g + r), (int32_t)j, (int32_t)k};
-                    // the step's flag covers all four i1 of the group: this
-                    // i1's own terms decide (NaN records: i1 >= j or a rank
-                    // deficient pair)
-                    const double es = (d > RANK_EPS) ? p - (z * z) / d : INF;
-                    bool take = ((fm[sl] >> lane) & 1ull) && k < S && k > j &&
-                                es <= (MT ? theta_f : fmin(theta_f, Ls[KP - 1]));
-                    if (take && a.ranged) {
-                        const uint64_t lr = lex_rank(BinomTab{c.btab, c.S}, c.S, 3, tup);
-                        if (lr < a.r0 || lr >= a.r1) take = false;
-                    }
-                    const uint64_t rk = take ? pack_tuple(tup, 3) : 0;
-                    if constexpr (MT) mt_append(c, Ls, Lr, KP, mb, take, rk, es, theta_f, offered);
-                    else list_insert_lanes(Ls, Lr, KP, take, rk, es, offered);
+                const double u = fma(-v, pick(w, r), gg);
+                const double d = fma(-al, u * u, pick(dq, r));
+                const double z = fma(-zs, u, pick(zq, r));
+                const int32_t tup[3] = {(int32_t)(S3_NR * g + r), (int32_t)j, (int32_t)k0};
+                // the step's flag covers all four i1 of the group: this i1's own
+                // terms decide (NaN records: i1 >= j or a rank deficient pair)
+                const double es = (d > RANK_EPS) ? p - (z * z) / d : INF;
+                bool take =
+                    ((fm >> lane) & 1ull) && kv0 && k0 > j && es <= (MT ? theta_f : fmin(theta_f, Ls[KP - 1]));
+                if (take && a.ranged) {
+                    const uint64_t lr = lex_rank(BinomTab{c.btab, c.S}, c.S, 3, tup);
+                    if (lr < a.r0 || lr >= a.r1) take = false;
                 }
+                const uint64_t rk = take ? pack_tuple(tup, 3) : 0;
+                if constexpr (MT) mt_append(c, Ls, Lr, KP, mb, take, rk, es, theta_f, offered);
+                else list_insert_lanes(Ls, Lr, KP, take, rk, es, offered);
             }
         }
         const double tw = Ls[KP - 1];
@@ -2024,233 +1992,253 @@ __device__ __forceinline__ void s3_candidates(const CtxT &c, const SearchArgs &a
     }
 }
 
-// Where the bound does not help (both groups of a tile pass it for more pairs
-// than are taken one by one) a wave leaves it out for the next 1, 3, .. 31 tiles, so a
-// problem whose six-feature fits all reach the threshold pays a few per cent.
+// Where the bound does not help (a wave's units pass it in succession for more
+// pairs than are taken one by one) a wave leaves it out for the next 1, 3, ..
+// 31 units, so a problem whose fits all reach the threshold pays a few per cent.
 struct S3Skip {
     int left = 0, fails = 0;
+    __device__ bool skip() {
+        if (left == 0) return false;
+        --left;
+        return true;
+    }
+    __device__ void result(bool failed) {
+        fails = failed ? (fails < 6 ? fails + 1 : 6) : 0;
+        left = fails < 2 ? 0 : (1 << (fails - 1)) - 1;
+    }
 };
 
-// tile t: its row block, column chunk and pair of groups h
-__device__ __forceinline__ int64_t s3_locate(int64_t S, const uint64_t *__restrict__ tcum, uint64_t t, S3Tile &tl) {
-    int64_t lo = 0, hi = s3_nblocks(S) - 1;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi + 1) >> 1;
-        if (tcum[mid] <= t) lo = mid; else hi = mid - 1;
+// item t: its block of G and its bases b0 .. b1 - 1
+template <class B>
+__device__ __forceinline__ void bound_locate(int64_t S, const uint64_t *__restrict__ cum, uint64_t t, int run,
+                                             S3Tile &tl, int64_t &b0, int64_t &b1) {
+    int64_t q = 0, hi = s3_nblocks(S) - 1;
+    while (q < hi) {
+        const int64_t mid = (q + hi + 1) >> 1;
+        if (cum[mid] <= t) q = mid; else hi = mid - 1;
     }
-    int64_t nkb, nh;
-    s3_block(S, lo, nkb, nh);
-    // column chunk fastest: the waves of a workgroup usually take chunks of
-    // one (block, pair) and share its records in the scalar cache; a run of
-    // tiles on one XCD covers a few groups over the same chunks of G
-    const int64_t rem = (int64_t)(t - tcum[lo]);
-    tl.kcx = rem % nkb;
-    tl.j0 = lo * S3_JR;
-    tl.jhi = (tl.j0 + S3_JR - 1 < S - 2) ? tl.j0 + S3_JR - 1 : S - 2;
-    tl.kb = tl.j0 + 1 + tl.kcx * S3_KC;
-    return rem / nkb;
+    const uint32_t nu = (uint32_t)s3_class_units(S, q), rem = (uint32_t)(t - cum[q]);
+    const uint32_t u = rem % nu;
+    b0 = B::below(S, q) + (int64_t)(rem / nu) * run;
+    b1 = b0 + run < B::below(S, q + 1) ? b0 + run : B::below(S, q + 1);
+    // u = s3_class_below(S, q, r) + column chunk
+    const float m = (float)((S + BU - 1) / BU - q) + 0.5f;
+    int64_t r = (int64_t)(m - sqrtf(fmaxf(m * m - 2.0f * (float)u, 0.0f)));
+    while (s3_class_below(S, q, r) > (int64_t)u) --r;
+    while (s3_class_below(S, q, r + 1) <= (int64_t)u) ++r;
+    r = uni(r);
+    tl.kcx = (int64_t)u - s3_class_below(S, q, r);
+    tl.j0 = (q + r) * BU;
+    tl.jhi = (tl.j0 + BU - 1 < S - 2) ? tl.j0 + BU - 1 : S - 2;
+    tl.kb = tl.j0 + tl.kcx * BU;
 }
 
-// The groups' bounds over the rows of a tile (threshold th): bit x of
-// rows[q] says that group S3_GP h + q has to be looked at on row j0 + x, and
-// mask[x][q] holds the lanes (first and second column) that passed there;
-// lanes[q] counts them.  Without a bound (th infinite, or left out) every
-// row is set, and lanes[q] is more than any limit.
-// Bound by FP64 issue: 20 instructions per lane, row and group (two columns)
-// against 56 for the tuples' own tests.
-template <class CtxT>
-__device__ __forceinline__ void s3_bound(const CtxT &c, const double *__restrict__ recg,
-                                         const double *__restrict__ gfac, const S3Tile &tl, int64_t h, double th, S3Skip &skip, int limit,
-                                         unsigned long long (*mask)[S3_GP][2], unsigned long long (&rows)[S3_GP],
-                                         int (&lanes)[S3_GP]) {
-    const int lane = threadIdx.x & 63;
-    const int64_t S = c.S;
-    const int64_t nt = c.Gnt;
-    const double *__restrict__ Gb = c.G1;
-    const int TP = c.TP;
-    const int ts = c.tstar[0];
-    const double *__restrict__ inv_st = c.inv_s + (int64_t)ts * S;
-    const int64_t jlo = tl.j0 > S3_NR * S3_GP * h + 1 ? tl.j0 : S3_NR * S3_GP * h + 1;
-    const int nrow = (int)(tl.jhi - jlo);  // steps 0..nrow
-    rows[0] = rows[1] = ~0ull;
-    lanes[0] = lanes[1] = 1 << 30;
-    const int x0 = (int)(jlo - tl.j0);
-    // a group's first step with a tuple (the second group's rows start later)
-    const int lo1[S3_GP] = {0, (int)(S3_NR * (S3_GP * h + 1) + 1 - jlo)};
-    if (skip.left > 0) {
-        --skip.left;
-    } else if (th < INF) {
-        const double theta_s = th * (1.0 + THETA_SLACK) + S3_TSLACK * c.cyy[ts];
-        const int64_t k0 = tl.kb + lane, k1 = tl.kb + 64 + lane;
-        const bool kv0 = k0 < S, kv1 = k1 < S;
-        const int64_t kk0 = kv0 ? k0 : S - 1, kk1 = kv1 ? k1 : S - 1;
-        const bool diag = tl.kcx == 0, half = S - tl.kb <= 64;
-        // k-dependent part of each group's solve, for both columns of the lane
-        double w[S3_GP][S3_NR][2], dq[S3_GP][2], z2[S3_GP][2], zz[S3_GP][2];  // z2 = -2 zeta', zz = zeta'^2
-        const double neg = -S3_ESLACK * c.cyy[ts];
-        {
-            const bool lv0 = kv0 && inv_st[kk0] > 0.0, lv1 = kv1 && inv_st[kk1] > 0.0;
-            const double b0 = c.bhat[kk0 * TP + ts], b1 = c.bhat[kk1 * TP + ts];
+// A unit's G (one tile, 32 KB) to LDS by the workgroup.  Odd rows are turned by
+// 16 columns: a wave's read of four rows by sixteen columns then covers every
+// bank once per pass.
+__device__ __forceinline__ void bound_load(double *__restrict__ s_g, const double *__restrict__ G1, int64_t nt,
+                                           const S3Tile &tl) {
+    const double2 *__restrict__ src =
+        reinterpret_cast<const double2 *>(G1 + (((tl.j0 >> 6) * nt + (tl.kb >> 6)) << 12));
 #pragma unroll
-            for (int q = 0; q < S3_GP; ++q) {
-                CDouble *f = cptr(gfac) + (S3_GP * h + q) * S3_GFAC;
-                double x0[S3_NR], x1[S3_NR];
+    for (int it = 0; it < BU * BU / 2 / 256; ++it) {
+        const int e = (int)threadIdx.x + 256 * it, row = e >> 5, c = 2 * (e & 31);
+        *reinterpret_cast<double2 *>(s_g + row * BU + (c ^ ((row & 1) << 4))) = src[e];
+    }
+}
+
+// The bound of one unit for one base of K = 4 NK features (its table: columns
+// from x0, len of them; its rows with a tuple from j0 + lo).  A pair (j, k)
+// passes unless
+//   x = zeta^2 - (p - theta) d < -eps, as a polynomial in u = g - v.w:
+//   q + u (A u - 2 zeta' zs), A = zs^2 + (p - theta) alpha, q = zeta'^2 - (p - theta) d'
+// (eps a slack above the rounding of the terms, which cancel): a NaN passes,
+// and so does any pair when p is at or below theta.
+// u is a matrix product (rows x K by K x columns, G the addend), so it runs in
+// 16 x 16 blocks on the FP64 matrix cores; the rest is 4 FMAs and a comparison
+// per (j, k).  (The matrix cores multiply FP64 at the vector units' rate; what
+// the blocks save is the rows' operands: read by scalar loads, 96 bytes a row
+// and wave, they held a vector form of this loop at 530 us for n = 2000, S =
+// 600, D = 4 (422 here) and at 56 us for S = 1000, D = 3 (45).)  Operands of v_mfma_f64_16x16x4f64: A[i][f] in lane i + 16 f,
+// B[f][c] in lane c + 16 f, D[i][c] in lane c + 16 (i % 4), register i / 4.
+// Passing pairs: `lanes` of them; lane e = 16 rb + 4 cb + i returns those of
+// the 16 x 16 block (rb, cb)'s rows 4 i .. 4 i + 3 in m, bit 16 h + c for row 16
+// rb + 4 i + h and column 16 cb + c.
+typedef double double4_t __attribute__((ext_vector_type(4)));
+template <int NK>
+__device__ __forceinline__ void bound_unit(const double *__restrict__ s_g, int64_t S, const S3Tile &tl,
+                                           const double *__restrict__ tab, int64_t x0, int64_t len, int lo,
+                                           double theta_s, double neg, double (*par)[BU],
+                                           unsigned long long &mine, int &lanes) {
+    constexpr int K = 4 * NK;
+    const int lane = threadIdx.x & 63, col = lane & 15, h = lane >> 4;
+    const int nrow = (int)(tl.jhi - tl.j0) + 1;
+    bool some = false;
+    mine = 0;
+    // field f of column x (a table has less than 4 GB: 32-bit offsets)
+    const uint32_t ln = (uint32_t)len;
+    auto at = [&](uint32_t f, uint32_t x) {
+        return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(tab) + (f * ln + x) * 8u);
+    };
+    auto colx = [&](int x) {  // column j0 or kb + .., kept inside the table
+        const int y = x < (int)S ? x : (int)S - 1;
+        return (uint32_t)(y > (int)x0 ? y - (int)x0 : 0);
+    };
+    // the rows' terms (a lane per row)
+    {
+        const uint32_t j = colx((int)tl.j0 + lane);
+        const double al = at(K + BF_AL, j), zs = at(K + BF_ZS, j);
+        const double pi = fmax(at(K + BF_P, j) - theta_s, 0.0);
+        par[0][lane] = fma(pi, al, zs * zs);
+        par[1][lane] = zs;
+        par[2][lane] = pi;
+    }
+    // the columns' terms
+    const int ncb = S - tl.kb >= BU ? 4 : (int)((S - tl.kb + 15) >> 4);
+    double w[4][NK], dq[4], z2[4], zz[4];  // z2 = -2 zeta', zz = zeta'^2
 #pragma unroll
-                for (int l = 0; l < S3_NR; ++l) {
-                    int64_t i = S3_NR * (S3_GP * h + q) + l;
-                    i = i < S ? i : S - 1;  // past S: the factor's row is zero
-                    x0[l] = Gb[gidx(i, kk0, nt, 1, 0)];
-                    x1[l] = Gb[gidx(i, kk1, nt, 1, 0)];
-                }
-                double d0 = 1.0 - S3_DSLACK, d1 = 1.0 - S3_DSLACK, e0 = b0, e1 = b1;
+    for (int cb = 0; cb < 4; ++cb) {
+        const uint32_t k = colx((int)tl.kb + 16 * cb + col);
 #pragma unroll
-                for (int m = 0; m < S3_NR; ++m) {
-                    double s0 = 0.0, s1 = 0.0;
+        for (int s = 0; s < NK; ++s) w[cb][s] = at(4 * s + h, k);
+        const double e = at(K + BF_E, k);
+        dq[cb] = at(K + BF_D, k) - S3_DSLACK;
+        z2[cb] = -2.0 * e;
+        zz[cb] = e * e;
+    }
+    const bool diag = tl.kcx == 0;
+    auto rowv = [&](double (&v)[NK], int rb) {
+        const uint32_t j = colx((int)tl.j0 + 16 * rb + col);
 #pragma unroll
-                    for (int l = 0; l <= m; ++l) {
-                        s0 = fma(f[m * (m + 1) / 2 + l], x0[l], s0);
-                        s1 = fma(f[m * (m + 1) / 2 + l], x1[l], s1);
-                    }
-                    w[q][m][0] = s0;
-                    w[q][m][1] = s1;
-                    d0 = fma(-s0, s0, d0);
-                    d1 = fma(-s1, s1, d1);
-                    e0 = fma(-s0, f[10 + m], e0);
-                    e1 = fma(-s1, f[10 + m], e1);
-                }
-                // a lane past S or on a constant column never passes
-                dq[q][0] = lv0 ? d0 : S3_NEVER;
-                dq[q][1] = lv1 ? d1 : S3_NEVER;
-                z2[q][0] = -2.0 * e0;
-                z2[q][1] = -2.0 * e1;
-                zz[q][0] = e0 * e0;
-                zz[q][1] = e1 * e1;
-            }
+        for (int s = 0; s < NK; ++s) v[s] = -at(4 * s + h, j);
+    };
+    double v[NK], vn[NK];
+    const int rb0 = lo >> 4;
+    rowv(vn, rb0);
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+    for (int rb = rb0; rb < 4 && 16 * rb < nrow; ++rb) {
+#pragma unroll
+        for (int s = 0; s < NK; ++s) v[s] = vn[s];
+        rowv(vn, rb < 3 ? rb + 1 : 3);
+        double A[4], zs[4], pi[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            A[i] = par[0][16 * rb + 4 * i + h];
+            zs[i] = par[1][16 * rb + 4 * i + h];
+            pi[i] = par[2][16 * rb + 4 * i + h];
         }
-        // G[j][k] for the block's rows: j >> 6 is the same for the whole block
-        // (S3_JR divides 64), so one uniform tile-row base plus 32-bit per-lane
-        // byte offsets (column part + row j & 63) address every step
-        const char *__restrict__ gtile = reinterpret_cast<const char *>(Gb + (((tl.j0 >> 6) * nt) << 12));
-        const uint32_t voff0 = (uint32_t)((((kk0 >> 6) << 12) + (kk0 & 63) + ((jlo & 63) << 6)) * 8);
-        const uint32_t voff1 = (uint32_t)((((kk1 >> 6) << 12) + (kk1 & 63) + ((jlo & 63) << 6)) * 8);
-        // records of row jlo + x are 128 bytes at recj + 128 x (uniform)
-        CChar *recj =
-            (CChar *)(cptr(recg) + (size_t)(s3g_rowoff(S, h) + jlo - S3_NR * S3_GP * h - 1) * (S3_GP * S3_GREC));
-        auto sweep = [&](auto diagc, auto halfc) {
-            constexpr bool DIAG = decltype(diagc)::value;
-            constexpr bool HALF = decltype(halfc)::value;
-            constexpr int JG = S3_JG;
-            unsigned long long rw[S3_GP] = {0, 0};
-            int ln[S3_GP] = {0, 0};
-            double2 ga[JG], gb[JG];  // g(j, k0), g(j, k1)
-            auto fetch = [&](double2 (&dst)[JG], int jg) {
+        const double *__restrict__ grow = s_g + (16 * rb + h) * BU + col;
+        // two blocks at a time (their products and tests overlap), but those
+        // past S or all below the diagonal
 #pragma unroll
-                for (int x = 0; x < JG; ++x) {
-                    const uint32_t jr = (uint32_t)(jg + x < nrow ? jg + x : nrow);
-                    dst[x].x = *reinterpret_cast<const double *>(gtile + (voff0 + jr * 512u));
-                    dst[x].y = HALF ? 0.0 : *reinterpret_cast<const double *>(gtile + (voff1 + jr * 512u));
-                }
-            };
-            // the two groups' records of one step are two halves of 64 bytes,
-            // each loaded while the other is scored (scalar loads may return
-            // out of order, so the half in flight is waited for before the
-            // next one is issued)
-            auto load_half = [&](double (&rv)[S3_GREC], int jr, int q) {
-                CDouble *rp = (CDouble *)(recj + (size_t)jr * 128 + q * 64);
+        for (int cp = 0; cp < 4; cp += 2) {
+            if (cp >= ncb || (diag && cp + 1 < rb)) continue;
+            double4_t u[2];
+            unsigned long long m[2][4], any = 0;
 #pragma unroll
-                for (int e = 0; e < S3_GREC; ++e) rv[e] = rp[e];
-            };
-            // z^2 - (p - theta) d as a polynomial in u, with A = zs^2 + (p -
-            // theta) alpha per step: q + u (A u - 2 zeta' zs), q = zeta'^2 -
-            // (p - theta) d'.  A lane passes unless that is below -eps (a
-            // slack above the rounding of the terms, which cancel): a NaN
-            // passes, and so does any lane when p is at or below theta
-            auto score_half = [&](const double (&rv)[S3_GREC], const double2 gv, int q, int jr) {
-                const double pi = fmax(rv[6] - theta_s, 0.0);
-                const double A = fma(pi, rv[4], rv[7]);
-                unsigned long long m0, m1 = 0;
-                {
-                    double u = gv.x;
+            for (int e = 0; e < 2; ++e)
 #pragma unroll
-                    for (int e = 0; e < S3_NR; ++e) u = fma(-rv[e], w[q][e][0], u);
-                    const double x = fma(u, fma(A, u, rv[5] * z2[q][0]), fma(-pi, dq[q][0], zz[q][0]));
-                    m0 = __ballot(!(x < neg));
-                    if (DIAG) m0 &= __ballot(k0 > jlo + jr);  // k1 > j0 + 64 > j
-                }
-                if (!HALF) {
-                    double u = gv.y;
+                for (int i = 0; i < 4; ++i) u[e][i] = grow[4 * i * BU + 16 * ((cp + e) ^ (h & 1))];
 #pragma unroll
-                    for (int e = 0; e < S3_NR; ++e) u = fma(-rv[e], w[q][e][1], u);
-                    const double x = fma(u, fma(A, u, rv[5] * z2[q][1]), fma(-pi, dq[q][1], zz[q][1]));
-                    m1 = __ballot(!(x < neg));
-                }
-                if ((m0 | m1) && jr <= nrow && jr >= lo1[q]) {
-                    m0 &= __ballot(kv0);
-                    m1 &= __ballot(kv1);
-                    if (lane == 0) {
-                        mask[x0 + jr][q][0] = m0;
-                        mask[x0 + jr][q][1] = m1;
-                    }
-                    rw[q] |= 1ull << (x0 + jr);
-                    ln[q] += __popcll(m0) + __popcll(m1);
-                }
-            };
-            double ra[S3_GREC], rb[S3_GREC];
-            load_half(ra, 0, 0);
-            auto score = [&](const double2 (&src)[JG], int jg) {
+            for (int s = 0; s < NK; ++s)
 #pragma unroll
-                for (int x = 0; x < JG; ++x) {
-                    const int jr = jg + x;
-                    const int jc = jr <= nrow ? jr : nrow;
-                    __builtin_amdgcn_s_waitcnt(0xC07F);
-                    load_half(rb, jc, 1);
-                    __builtin_amdgcn_sched_barrier(0);
-                    score_half(ra, src[x], 0, jr);
-                    __builtin_amdgcn_s_waitcnt(0xC07F);
-                    load_half(ra, jr + 1 <= nrow ? jr + 1 : nrow, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    score_half(rb, src[x], 1, jr);
+                for (int e = 0; e < 2; ++e)
+                    u[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[s], w[cp + e][s], u[e], 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const double x = fma(u[e][i], fma(A[i], u[e][i], zs[i] * z2[cp + e]),
+                                         fma(-pi[i], dq[cp + e], zz[cp + e]));
+                    m[e][i] = __ballot(!(x < neg));
+                    any |= m[e][i];
                 }
-            };
-            __builtin_amdgcn_s_waitcnt(0x0F70);
-            fetch(ga, 0);
-            for (int jg = 0;; jg += 2 * JG) {
-                fetch(gb, jg + JG);
-                score(ga, jg);
-                fetch(ga, jg + 2 * JG);
-                score(gb, jg + JG);
-                if (jg + 2 * JG > nrow) break;
+            if (any) {
+                some = true;
+                unsigned long long f = 0;
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if ((lane & 7) == 4 * e + i) f = m[e][i];
+                if ((lane >> 3) == 2 * rb + (cp >> 1)) mine = f;
             }
-#pragma unroll
-            for (int q = 0; q < S3_GP; ++q) {
-                rows[q] = rw[q];
-                lanes[q] = ln[q];
-            }
-        };
-        if (diag) {
-            if (half) sweep(std::true_type{}, std::true_type{});
-            else sweep(std::true_type{}, std::false_type{});
-        } else {
-            if (half) sweep(std::false_type{}, std::true_type{});
-            else sweep(std::false_type{}, std::false_type{});
-        }
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        __builtin_amdgcn_wave_barrier();
-        if (lanes[0] > limit && lanes[1] > limit) {
-            skip.fails = skip.fails < 5 ? skip.fails + 1 : 5;
-            skip.left = (1 << skip.fails) - 1;
-        } else {
-            skip.fails = 0;
         }
     }
-    // rows without a tuple of the group are left out
+    lanes = 0;
+    if (some) {
+        // those with a tuple: lo <= row < nrow, column < S, k > j
+        const int x = 16 * (lane >> 4) + 4 * (lane & 3), c0 = 16 * ((lane >> 2) & 3);
+        const int64_t left = S - tl.kb - c0;  // columns of the block
+        const unsigned cols = left >= 16 ? 0xffffu : left > 0 ? (1u << left) - 1u : 0u;
+        unsigned long long ok = 0;
 #pragma unroll
-    for (int q = 0; q < S3_GP; ++q) {
-        const int64_t g = S3_GP * h + q;
-        const int64_t gl = tl.j0 > S3_NR * g + 1 ? tl.j0 : S3_NR * g + 1;  // the group's own first row
-        const int lo = (int)(gl - tl.j0), n = (int)(tl.jhi - tl.j0);
-        rows[q] = lo > n ? 0 : rows[q] & (~0ull >> (63 - n)) & (~0ull << lo);
-        if (!rows[q]) lanes[q] = 0;
+        for (int r = 0; r < 4; ++r) {
+            const int first = diag ? x + r - c0 + 1 : 0;  // first column with k > j
+            const unsigned f = first >= 16 ? 0u : first > 0 ? cols & (0xffffu << first) : cols;
+            if (x + r >= lo && x + r < nrow) ok |= (unsigned long long)(f & 0xffffu) << (16 * r);
+        }
+        mine &= ok;
+        int n = __popcll(mine);
+        for (int o = 1; o < 64; o <<= 1) n += __shfl_xor(n, o);
+        lanes = __builtin_amdgcn_readfirstlane(n);
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Calls put(place, row, column) for every passing pair: places count from 0.
+template <class Put>
+__device__ __forceinline__ void bound_each(unsigned long long mine, Put put) {
+    const int lane = threadIdx.x & 63;
+    const int n = __popcll(mine);
+    int at = n;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(at, o);
+        if (lane >= o) at += y;
+    }
+    at -= n;
+    while (mine) {
+        const int b = __builtin_ctzll(mine);
+        mine &= mine - 1;
+        put(at++, 16 * (lane >> 4) + 4 * (lane & 3) + (b >> 4), 16 * ((lane >> 2) & 3) + (b & 15));
+    }
+}
+// bit x: some pair of row x passes
+__device__ __forceinline__ unsigned long long bound_rows(unsigned long long mine) {
+    const int lane = threadIdx.x & 63;
+    unsigned f = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if ((mine >> (16 * r)) & 0xffffull) f |= 1u << r;
+    unsigned long long rows = (unsigned long long)f << (16 * (lane >> 4) + 4 * (lane & 3));
+    for (int o = 1; o < 64; o <<= 1) rows |= (unsigned long long)__shfl_xor((long long)rows, o);
+    return uni((uint64_t)rows);
+}
+
+// Group g's bound over a unit (threshold th): the pairs that pass, as
+// bound_unit returns them.  Without a bound (th infinite, or left out) all
+// rows with a tuple are set in rows, and lanes is more than any limit; else
+// rows is set when there are more than limit.
+template <class CtxT>
+__device__ __forceinline__ void s3_bound(const CtxT &c, const double *__restrict__ recg, const double *__restrict__ s_g,
+                                         const S3Tile &tl, int64_t g, double th, S3Skip &skip, int limit,
+                                         double (*par)[BU], unsigned long long &mine,
+                                         unsigned long long &rows, int &lanes) {
+    const int64_t S = c.S;
+    const int64_t first = S3_NR * g + 1;  // the group's first row
+    const int lo = first > tl.j0 ? (int)(first - tl.j0) : 0, n = (int)(tl.jhi - tl.j0);
+    if (!skip.skip() && th < INF) {
+        const double ctot = c.cyy[c.tstar[0]];
+        bound_unit<1>(s_g, S, tl, recg + s3g_off(S, g) * S3_FIELDS, S3_NR * g, S - S3_NR * g, lo,
+                      th * (1.0 + THETA_SLACK) + S3_TSLACK * ctot, -S3_ESLACK * ctot, par, mine, lanes);
+        skip.result(lanes > limit);
+        rows = lanes > limit ? bound_rows(mine) : 0;
+    } else {
+        rows = (~0ull >> (63 - n)) & (~0ull << lo);
+        lanes = 1 << 30;
     }
 }
 
@@ -2260,52 +2248,54 @@ __device__ inline uint64_t s3_cand(int64_t g, int64_t j, int64_t k) {
 
 // The bound pass of the single search.  What it flags goes to the workgroup's
 // own segments of two pools (no shared counter: same-address atomics
-// serialise): the (group, row, column) pairs of a tile's group one by one
-// while there are at most `limit`, else the group's flagged rows, eight to an
-// item.  The groups of the best features are flagged on most rows, so the
-// pools are scored by a kernel of their own, spread evenly: scored where they
-// were found they left a few waves running long after the rest (n = 2000, S =
-// 1000: 145 us against 105 without the bound).
+// serialise): the (group, row, column) candidates of a unit one by one while
+// there are at most `limit`, else the unit's flagged rows, eight to an item.
+// The groups of the best features are flagged on most rows, so the pools are
+// scored by a kernel of their own, spread evenly: scored where they were found
+// they left a few waves running long after the rest (n = 2000, S = 1000: 145
+// us against 105 without the bound).
 __device__ inline uint64_t s3_row_item(int64_t octet, int64_t g, int64_t kcx, unsigned mask) {
     return ((uint64_t)octet << 42) | ((uint64_t)g << 22) | ((uint64_t)kcx << 8) | mask;
 }
+// Items t0 .. t1 - 1 are dealt to the workgroups in turn (their costs are
+// nearly equal; a shared counter would serialise on one address), XCD-aware:
+// workgroup b runs on XCD b mod 8, and each round's items go to the XCDs in
+// eight runs, whose G and tables meet in one L2.
+__device__ inline uint64_t bound_first(uint64_t t0) {
+    const uint64_t b = blockIdx.x, n = gridDim.x;
+    return t0 + (n % S3_XCDS == 0 ? b % S3_XCDS * (n / S3_XCDS) + b / S3_XCDS : b);
+}
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) void search3_kernel(
-    Ctx c, const double *__restrict__ recg, const double *__restrict__ gfac, const uint64_t *__restrict__ tcum,
-    uint64_t t0, uint64_t t1, uint32_t wg_tiles, int limit) {
-    __shared__ unsigned long long s_m[SEARCH_WAVES][S3_JR][S3_GP][2];
+    Ctx c, const double *__restrict__ recg, const uint64_t *__restrict__ cum, uint64_t t0, uint64_t t1,
+    uint32_t wg_units, int limit, int run, int glo, int ghi) {
+    __shared__ double s_g[BU * BU];
+    __shared__ double s_par[SEARCH_WAVES][3][BU];
     __shared__ unsigned s_n[2];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    uint64_t *__restrict__ cands = c.s3_cands + (size_t)blockIdx.x * wg_tiles * S3_GP * limit;
-    uint64_t *__restrict__ items = c.s3_rows + (size_t)blockIdx.x * wg_tiles * S3_GP * (S3_JR / 8);
+    uint64_t *__restrict__ cands = c.s3_cands + (size_t)blockIdx.x * wg_units * limit;
+    uint64_t *__restrict__ items = c.s3_rows + (size_t)blockIdx.x * wg_units * (BU / 8);
     if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
-    __syncthreads();
+    const int64_t S = c.S;
     const double th = fmin(theta0_of(c), theta_load(c.theta_bits));
     S3Skip skip;
-    // Tiles t0 .. t1 - 1 are dealt round-robin over the waves (their costs are nearly
-    // equal; a shared counter would serialise on one address), XCD-aware:
-    // workgroups are placed on the eight XCDs in turn (workgroup b on XCD
-    // b mod 8), and runs of S3_XCD_RUN consecutive tiles, which share blocks
-    // of G, go to the waves of one XCD and its L2.
-    const bool xa = (gridDim.x % S3_XCDS) == 0;
-    const uint64_t xcd = xa ? blockIdx.x % S3_XCDS : 0;
-    const uint64_t nx = xa ? S3_XCDS : 1;
-    const uint64_t U = (uint64_t)gridDim.x / nx * SEARCH_WAVES;      // waves per XCD
-    const uint64_t u0 = (uint64_t)blockIdx.x / nx * SEARCH_WAVES + wave;
-    for (uint64_t sx = u0;; sx += U) {
-        const uint64_t t = t0 + ((sx / S3_XCD_RUN) * nx + xcd) * S3_XCD_RUN + sx % S3_XCD_RUN;
-        if (t >= t1) break;
+    for (uint64_t t = bound_first(t0); t < t1; t += gridDim.x) {
         S3Tile tl;
-        const int64_t h = s3_locate(c.S, tcum, t, tl);
-        unsigned long long rows[S3_GP];
-        int lanes[S3_GP];
-        s3_bound<Ctx>(c, recg, gfac, tl, h, th, skip, limit, s_m[wave], rows, lanes);
-#pragma unroll
-        for (int q = 0; q < S3_GP; ++q) {
-            if (!rows[q]) continue;
-            const int64_t g = S3_GP * h + q;
-            if (lanes[q] > limit) {
-                const unsigned m = lane < 8 ? (unsigned)(rows[q] >> (8 * lane)) & 0xffu : 0u;  // rows 8 lane ..
+        int64_t b0, b1;
+        bound_locate<S3Groups>(S, cum, t, run, tl, b0, b1);
+        b0 = b0 > glo ? b0 : glo;
+        b1 = b1 <= ghi ? b1 : (int64_t)ghi + 1;
+        if (b0 >= b1) continue;
+        __syncthreads();  // the waves have left the previous item's G
+        bound_load(s_g, c.G1, c.Gnt, tl);
+        __syncthreads();
+        for (int64_t g = b0 + wave; g < b1; g += SEARCH_WAVES) {
+            unsigned long long mine = 0, rows;
+            int lanes;
+            s3_bound<Ctx>(c, recg, s_g, tl, g, th, skip, limit, s_par[wave], mine, rows, lanes);
+            if (!lanes) continue;
+            if (lanes > limit) {
+                const unsigned m = lane < 8 ? (unsigned)(rows >> (8 * lane)) & 0xffu : 0u;  // rows 8 lane ..
                 const unsigned long long b = __ballot(m != 0);
                 unsigned at = 0;
                 if (lane == 0) at = atomicAdd(&s_n[1], (unsigned)__popcll(b));
@@ -2315,43 +2305,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) v
                 continue;
             }
             unsigned at = 0;
-            if (lane == 0) at = atomicAdd(&s_n[0], (unsigned)lanes[q]);
+            if (lane == 0) at = atomicAdd(&s_n[0], (unsigned)lanes);
             at = (unsigned)__shfl((int)at, 0);
-            unsigned long long r = rows[q];
-            while (r) {
-                const int x = __builtin_ctzll(r);
-                r &= r - 1;
-#pragma unroll
-                for (int sl = 0; sl < 2; ++sl) {
-                    const unsigned long long m = s_m[wave][x][q][sl];
-                    if ((m >> lane) & 1ull)
-                        cands[at + __popcll(m & ((1ull << lane) - 1ull))] =
-                            s3_cand(g, tl.j0 + x, tl.kb + 64 * sl + lane);
-                    at += (unsigned)__popcll(m);
-                }
-            }
+            bound_each(mine, [&](int p, int x, int k) { cands[at + p] = s3_cand(g, tl.j0 + x, tl.kb + k); });
         }
     }
     __syncthreads();
     if (threadIdx.x < 2) c.s3_count[2 * blockIdx.x + threadIdx.x] = s_n[threadIdx.x];
 }
 
-// tiles a workgroup of a launch of wgs takes at most
-static uint64_t s3_wg_tiles(uint64_t ntiles, int wgs) {
-    const uint64_t nx = wgs % S3_XCDS == 0 ? S3_XCDS : 1;
-    const uint64_t U = (uint64_t)wgs / nx * SEARCH_WAVES;
-    const uint64_t pos = (ntiles + S3_XCD_RUN * nx - 1) / (S3_XCD_RUN * nx) * S3_XCD_RUN;  // positions of an XCD
-    return (pos + U - 1) / U * SEARCH_WAVES;
+// A large search runs in passes of S3_PASS units (bound, then scoring), which
+// bounds the pools (0.7 GB with one task, 2.3 GB with several; S = 5000 is one
+// pass).  Units that the segments hold: each workgroup takes at most one item
+// more than its share.
+constexpr uint64_t S3_PASS = 1ull << 21;
+static size_t pool_units(uint64_t items, int run, uint64_t pass) {
+    return (size_t)(((items < pass / run ? items : pass / run) + BU_WGS) * run);
 }
-// A large search runs in passes of S3_PASS tiles (bound, then scoring), which
-// bounds the pools (1.2 GB with one task, 4.3 GB with several; S = 5000 is one
-// pass).  Tiles that the segments of every grid of up to SEARCH_WGS_MAX
-// workgroups cover: all positions, and one tile more per wave.
-constexpr uint64_t S3_PASS = 1ull << 20;
-size_t s3_pool_tiles(int64_t S) {
-    const uint64_t n = s3_tiles_host(S);
-    return (size_t)((n < S3_PASS ? n : S3_PASS) + (uint64_t)S3_XCD_RUN * S3_XCDS + (uint64_t)SEARCH_WGS_MAX * SEARCH_WAVES);
-}
+size_t s3_pool_units(int64_t S) { return pool_units(s3_items_host(S), bound_run(bound_units<S3Groups>(S)), S3_PASS); }
 int s3_lanes(int T) { return T > 1 ? S3_LANES_MT : S3_LANES; }
 
 // first[p][s] = items of pool p in the segments before s, first[p][nseg] = all
@@ -2406,10 +2377,10 @@ __device__ inline uint32_t pool_segment(const uint64_t *first, uint32_t nseg, ui
 // scans the segments' counts itself (a scan kernel in between cost 7 us).
 // resume: the waves' lists of the previous pass are carried on.
 template <bool MT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) void s3_eval_kernel(
-    Ctx c, SearchArgs a, const double *__restrict__ rec, uint32_t nseg, uint32_t wg_tiles, int limit, int resume) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void s3_eval_kernel(
+    Ctx c, SearchArgs a, const double *__restrict__ rec, uint32_t nseg, uint32_t wg_units, int limit, int resume) {
     extern __shared__ double smem[];
-    __shared__ unsigned long long s_q[SEARCH_WAVES][S3_JR][2];
+    __shared__ unsigned long long s_q[SEARCH_WAVES][S3_JR];
     __shared__ int s_qj[SEARCH_WAVES][S3_JR];
     __shared__ uint64_t s_bk[MT ? SEARCH_WAVES : 1][MT ? MT_BUF : 1];
     __shared__ double s_be[MT ? SEARCH_WAVES : 1][MT ? MT_BUF : 1];
@@ -2448,7 +2419,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) v
         uint64_t key = 0;
         if (in) {
             const uint32_t s = segment(0, e);
-            key = c.s3_cands[(size_t)s * wg_tiles * S3_GP * limit + (e - first[0][s])];
+            key = c.s3_cands[(size_t)s * wg_units * limit + (e - first[0][s])];
         }
         s3_candidates<MT, Ctx>(c, a, rec, in, key, Ls, Lr, theta0, theta_pub, offered, mb);
     }
@@ -2459,7 +2430,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) v
         uint32_t s = segment(1, e);
         auto item = [&]() {
             while (first[1][s + 1] <= e) ++s;
-            return uni(c.s3_rows[(size_t)s * wg_tiles * S3_GP * (S3_JR / 8) + (e - first[1][s])]);
+            return uni(c.s3_rows[(size_t)s * wg_units * (BU / 8) + (e - first[1][s])]);
         };
         constexpr uint64_t OCTET = 7ull << 42;  // the rows' place in their block
         uint64_t it = item();
@@ -2468,7 +2439,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) v
             S3Tile tl;
             tl.kcx = (int64_t)((it >> 8) & 0x3FFF);
             tl.j0 = (int64_t)(it >> 42) * 8 / S3_JR * S3_JR;
-            tl.kb = tl.j0 + 1 + tl.kcx * S3_KC;
+            tl.kb = tl.j0 + tl.kcx * BU;
             const uint64_t same = (it & ~OCTET) >> 8;  // group, column chunk, row block
             unsigned long long rows = 0;
             bool more = true;
@@ -2504,22 +2475,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3_WPE))) v
 #endif
 // Several independent one-task problems searched by one launch: the record
 // tables and pre-pass bounds of every problem are built first (each problem
-// on its own), then the waves of one persistent grid pull work items from a
-// device queue -- item = a run of S3B_RUN consecutive tiles of one problem,
-// problems ordered by decreasing tile count, so the largest start first and
+// on its own), then the workgroups of one persistent grid pull entries from a
+// device queue -- entry = a run of S3B_RUN consecutive items of one problem,
+// problems ordered by decreasing item count, so the largest start first and
 // the small ones fill the tail.  A wave keeps one list per problem it works
-// on: when its next item belongs to another problem it writes the list to
+// on: when its next entry belongs to another problem it writes the list to
 // that problem's next free list slot (a wave never returns to a problem, as
-// items are taken in queue order) and starts an empty one.  Each problem's
+// entries are taken in queue order) and starts an empty one.  Each problem's
 // merge then reads the lists its waves wrote; the rest is the one-problem
 // path, so the results equal those of separate searches bitwise.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3B_WPE))) void search3_batch_kernel(
     BatchSearchArgs b) {
     extern __shared__ double smem[];
-    __shared__ unsigned long long s_q[SEARCH_WAVES][S3_JR][2];
-    __shared__ int s_qj[SEARCH_WAVES][S3_JR];
-    __shared__ unsigned long long s_m[SEARCH_WAVES][S3_JR][S3_GP][2];
+    __shared__ double s_g[BU * BU];
+    __shared__ double s_par[SEARCH_WAVES][3][BU];
+    __shared__ unsigned long long s_q[SEARCH_WAVES][BU];
+    __shared__ int s_qj[SEARCH_WAVES][BU];
     __shared__ uint64_t s_k[SEARCH_WAVES][S3_LANES];
+    __shared__ uint32_t s_it;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     double *Ls = smem + (size_t)wave * b.KPmax * 2;
@@ -2532,6 +2505,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3B_WPE))) 
     const Ctx *cur_ctx = nullptr;
     double theta0 = INF, theta_pub = INF;
     unsigned offered = 0;
+    int run = 0;
     SearchArgs a{};
     a.D = 3;
     auto flush = [&](const Ctx &c) {
@@ -2542,11 +2516,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3B_WPE))) 
         if (slot < (uint32_t)c.nwaves)
             list_store(c.list_sse + (int64_t)slot * a.KP, c.list_rank + (int64_t)slot * a.KP, Ls, Lr, a.KP);
     };
+    uint32_t nxt = 0;  // thread 0: the entry after this one (taken ahead)
+    if (threadIdx.x == 0) nxt = atomicAdd(queue, 1u);
     for (;;) {
-        uint32_t it = 0;
-        if (lane == 0) it = atomicAdd(queue, 1u);
-        it = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)__shfl((int)it, 0));
+        __syncthreads();
+        if (threadIdx.x == 0) s_it = nxt;
+        __syncthreads();
+        const uint32_t it = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_it);
         if (it >= nitems) break;
+        if (threadIdx.x == 0) nxt = atomicAdd(queue, 1u);
         typedef const __attribute__((address_space(4))) uint32_t CU32;
         typedef const __attribute__((address_space(4))) uint64_t CU64;
         CU32 *ie = (CU32 *)(uintptr_t)b.item_end;
@@ -2557,6 +2535,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3B_WPE))) 
         const Ctx *cp = (const Ctx *)(uintptr_t)((CU64 *)(uintptr_t)b.ctx)[p];
         typedef const __attribute__((address_space(4))) Ctx CCtx;
         CCtx &c = *(CCtx *)(uintptr_t)cp;
+        const int64_t S = c.S;
         if (p != cur) {
             if (cur >= 0) flush(*cur_ctx);
             cur_ctx = cp;
@@ -2572,44 +2551,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3B_WPE))) 
             theta_pub = INF;
             offered = 0;
             skip = S3Skip{};
+            run = bound_run(bound_units<S3Groups>(S));
         }
-        const uint64_t ntiles = c.cum[s3_nblocks(c.S)];
+        const uint64_t n = c.cum[s3_nblocks(S)];
         const uint64_t t0 = (uint64_t)(it - first) * S3B_RUN;
-        const uint64_t t1 = t0 + S3B_RUN < ntiles ? t0 + S3B_RUN : ntiles;
-        for (uint64_t t = t0; t < t1; ++t)
-        {
+        const uint64_t t1 = t0 + S3B_RUN < n ? t0 + S3B_RUN : n;
+        for (uint64_t t = t0; t < t1; ++t) {
             S3Tile tl;
-            const int64_t h = s3_locate(c.S, c.cum, t, tl);
-            unsigned long long rows[S3_GP];
-            int lanes[S3_GP];
-            s3_bound<CCtx>(c, c.recg, c.gfac, tl, h, fmin(fmin(theta0, theta_load(c.theta_bits)), Ls[a.KP - 1]), skip, S3_LANES,
-                           s_m[wave], rows, lanes);
-#pragma unroll 1
-            for (int q = 0; q < S3_GP; ++q) {
-                const int64_t g = S3_GP * h + q;
-                unsigned long long r = q ? rows[1] : rows[0];
-                const int n = q ? lanes[1] : lanes[0];
-                if (!r) continue;
-                if (n > S3_LANES) {
-                    const int x0 = __builtin_ctzll(r), x1 = 63 - __builtin_clzll(r);
+            int64_t b0, b1;
+            bound_locate<S3Groups>(S, c.cum, t, run, tl, b0, b1);
+            __syncthreads();
+            bound_load(s_g, c.G1, c.Gnt, tl);
+            __syncthreads();
+            for (int64_t g = b0 + wave; g < b1; g += SEARCH_WAVES) {
+                unsigned long long mine = 0, rows;
+                int lanes;
+                s3_bound<CCtx>(c, c.recg, s_g, tl, g, fmin(fmin(theta0, theta_load(c.theta_bits)), Ls[a.KP - 1]), skip,
+                               S3_LANES, s_par[wave], mine, rows, lanes);
+                if (!lanes) continue;
+                if (lanes > S3_LANES) {
+                    const int x0 = __builtin_ctzll(rows), x1 = 63 - __builtin_clzll(rows);
                     s3_group<false, CCtx>(c, a, c.rec3, tl, g, tl.j0 + x0, tl.j0 + x1, Ls, Lr, theta0, theta_pub,
                                           offered, mb, s_q[wave], s_qj[wave]);
                     continue;
                 }
-                // at most 64 pairs: one per lane
-                int cnt = 0;
-                while (r) {
-                    const int x = __builtin_ctzll(r);
-                    r &= r - 1;
-#pragma unroll
-                    for (int sl = 0; sl < 2; ++sl) {
-                        const unsigned long long m = s_m[wave][x][q][sl];
-                        if ((m >> lane) & 1ull)
-                            s_k[wave][cnt + __popcll(m & ((1ull << lane) - 1ull))] =
-                                s3_cand(g, tl.j0 + x, tl.kb + 64 * sl + lane);
-                        cnt += __popcll(m);
-                    }
-                }
+                // at most S3_LANES candidates: one per lane
+                const int cnt = lanes;
+                bound_each(mine, [&](int p, int x, int k) { s_k[wave][p] = s3_cand(g, tl.j0 + x, tl.kb + k); });
                 __atomic_signal_fence(__ATOMIC_SEQ_CST);
                 __builtin_amdgcn_wave_barrier();
                 const uint64_t key = lane < cnt ? s_k[wave][lane] : 0;
@@ -2627,44 +2595,44 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3B_WPE))) 
 // into groups of four; per pair of groups (g1 <= g2) and j the Cholesky row of
 // j against the pair's eight columns is built once per search (rec4_kernel).
 // The sweep tests, per (pair, j, k), the fit on all ten features {g1, g2, j,
-// k}: 13 FP64 instructions for sixteen tuples i1 in g1, i2 in g2, against 144
-// for testing the tuples one by one.  A tuple's SSE is at least that of any
-// superset, so only where that bound is at or below the threshold are the
-// sixteen tuples tested themselves (on operator-tree columns, n = 2000, S =
-// 600: 0.4 in 1000).  A work tile is (pair, S3_JR rows j from j0, S3_KC columns k
-// from j0 + 1 + S3_KC c), its lanes as in search3_kernel; what a tile flags
-// goes to its workgroup's segments of two pools, which s4_eval_kernel scores:
-// the candidates (g1, g2, j, k) one per lane while there are at most S4_LANES
-// of them, else (also without a threshold) the whole tile, one item per i2.
-// Bound by FP64 issue.  n = 2000, S = 600: @@
+// k}: a product with eight terms and 5 FP64 instructions for sixteen tuples i1
+// in g1, i2 in g2, against 144 for testing the tuples one by one.  A tuple's
+// SSE is at least that of any superset, so only where that bound is at or
+// below the threshold are the sixteen tuples tested themselves (2 in 1000
+// ten-feature fits on operator-tree columns, n = 2000, S = 600; three in four
+// of those are rows in the span of their pair, whose bound is not tried).
+// Units and items are those of D = 3, over pairs; what a unit flags goes to
+// its workgroup's segments of two pools, which s4_eval_kernel scores: the
+// candidates (g1, g2, j, k) one per lane while there are at most S4_LANES of
+// them, else (also without a threshold) the whole unit, in items of one i2 and
+// S4_DR rows.  n = 2000, S = 600: tables 50 us, bound 420 us, scoring 150 us,
+// against 0.5 ms for a table of all triples and 5.3 ms for the tuples' own
+// tests.  The bound is limited by FP64 issue (vector and matrix, 60 per cent of
+// the cycles); tables and blocks of G take the rest.
 #ifndef S4_WPE
 #define S4_WPE 4                      // waves per SIMD the register budget is sized for
 #endif
 constexpr int S4_NR = 4;              // indices per group
-constexpr int S4_REC = 12;            // doubles per record: v0..v7, 1/d, zs, p, zs^2 (as in the D = 3 group records)
+constexpr int S4_DR = 16;             // rows of a dense item (of a unit taken whole)
+constexpr int S4_ITEMS = S4_NR * S3_JR / S4_DR;  // dense items of a unit
+constexpr int S4_FIELDS = 2 * S4_NR + BF_N;
 constexpr int S4_FAC = 48;            // doubles per factor: R^-1 (36), z (8), SSE of the pair, dependent columns
 constexpr double S4_NORM = 1e6;       // largest squared Frobenius norm of R^-1 the slacks cover
-// A large search runs in passes of S4_PASS tiles (bound, then scoring), which
+// A large search runs in passes of S4_PASS units (bound, then scoring), which
 // bounds the candidate pool at 1.1 GB.
-constexpr uint64_t S4_PASS = 1ull << 17;
+constexpr uint64_t S4_PASS = 1ull << 18;
 
 // groups with a tuple (i2 in the group, j = i2 + 1 <= S - 2)
 __host__ __device__ inline int64_t s4_groups(int64_t S) { return S >= 4 ? (S - 3) / S4_NR + 1 : 0; }
 __host__ __device__ inline int64_t s4_pairs_below(int64_t g) { return g * (g + 1) / 2; }  // pairs with g2 < g
-// Record rows of pair (g1, g2): j = 4 g2 + 1 .. S - 2, from row
-// sum over g < g2 of (g + 1) (S - 2 - 4 g), and g1 (S - 2 - 4 g2) more
-__host__ __device__ inline int64_t s4_rowoff(int64_t S, int64_t g1, int64_t g2) {
-    return (S - 2) * s4_pairs_below(g2) - S4_NR * ((g2 - 1) * g2 * (g2 + 1) / 3) + g1 * (S - 2 - S4_NR * g2);
+// columns of the pairs before (g1, g2), S - 4 g2 each (x = 4 g2 .. S - 1):
+// sum over g < g2 of (g + 1) (S - 4 g), and g1 (S - 4 g2) more
+__host__ __device__ inline int64_t s4_off(int64_t S, int64_t g1, int64_t g2) {
+    return S * s4_pairs_below(g2) - S4_NR * ((g2 - 1) * g2 * (g2 + 1) / 3) + g1 * (S - S4_NR * g2);
 }
-// pairs with rows in row block jb
-__host__ __device__ inline int64_t s4_block_pairs(int64_t S, int64_t jb) {
-    int64_t jmax = jb * S3_JR + S3_JR - 1;
-    if (jmax > S - 2) jmax = S - 2;
-    return jmax >= 1 ? s4_pairs_below((jmax - 1) / S4_NR + 1) : 0;
-}
-__host__ __device__ inline int64_t s4_block_chunks(int64_t S, int64_t jb) {
-    return (S - jb * S3_JR - 1 + S3_KC - 1) / S3_KC;
-}
+struct S4Pairs {
+    static __host__ __device__ int64_t below(int64_t S, int64_t q) { return s4_pairs_below(s3_groups_to(S, q - 1)); }
+};
 __device__ inline void s4_pair(int64_t p, int64_t &g1, int64_t &g2) {
     g2 = (int64_t)((sqrt(8.0 * (double)p + 1.0) - 1.0) * 0.5);
     while (s4_pairs_below(g2) > p) --g2;
@@ -2672,29 +2640,13 @@ __device__ inline void s4_pair(int64_t p, int64_t &g1, int64_t &g2) {
     g1 = p - s4_pairs_below(g2);
 }
 
-int64_t s4_rows_host(int64_t S) { return S >= 4 ? s4_rowoff(S, 0, s4_groups(S)) : 0; }
+int64_t s4_doubles_host(int64_t S) { return S >= 4 ? s4_off(S, 0, s4_groups(S)) * S4_FIELDS : 0; }
 int64_t s4_pairs_host(int64_t S) { return s4_pairs_below(s4_groups(S)); }
-uint64_t s4_tiles_host(int64_t S) {
-    uint64_t acc = 0;
-    for (int64_t b = 0; S >= 4 && b < s3_nblocks(S); ++b) acc += (uint64_t)(s4_block_pairs(S, b) * s4_block_chunks(S, b));
-    return acc;
-}
-size_t s4_pool_tiles(int64_t S) {
-    const uint64_t n = s4_tiles_host(S);
-    return (size_t)((n < S4_PASS ? n : S4_PASS) + (uint64_t)S3_XCD_RUN * S3_XCDS + (uint64_t)SEARCH_WGS_MAX * SEARCH_WAVES);
-}
-
-// tcum[jb] = tiles of the blocks before jb
 __device__ void s4_tile_table(const Ctx &c) {
-    const int64_t nb = s3_nblocks(c.S);
-    uint64_t acc = 0;
-    c.cum[0] = 0;
-    for (int64_t b = 0; b < nb; ++b) {
-        acc += (uint64_t)(s4_block_pairs(c.S, b) * s4_block_chunks(c.S, b));
-        c.cum[b + 1] = acc;
-    }
-    c.stats[1] = acc;
+    c.stats[1] = bound_items<S4Pairs>(c.S, bound_run(bound_units<S4Pairs>(c.S)), c.cum);
 }
+uint64_t s4_items_host(int64_t S) { return bound_items<S4Pairs>(S, bound_run(bound_units<S4Pairs>(S)), nullptr); }
+size_t s4_pool_units(int64_t S) { return pool_units(s4_items_host(S), bound_run(bound_units<S4Pairs>(S)), S4_PASS); }
 
 // The factor of pair e = (g1, g2): of its live columns in index order, G =
 // R^T R, {R^-1 by rows, z = R^-T b, c - |z|^2, and whether a column is too close to
@@ -2758,95 +2710,60 @@ __global__ __launch_bounds__(64) void s4_init_kernel(Ctx c) {
     if (e < s4_pairs_below(s4_groups(c.S))) s4_factor(c, e);
 }
 
-// One wave per (row block, pair), one lane per j.  The records are staged in
-// LDS and written out as consecutive doubles (full cache lines).  Bound by the
-// writes: @@
-__global__ __launch_bounds__(256) void rec4_kernel(Ctx c, int64_t nitem) {
-    __shared__ double stage[SEARCH_WAVES][64 * S4_REC];
-    static_assert(S3_JR == 64, "a lane per row");
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int64_t it = (int64_t)blockIdx.x * SEARCH_WAVES + wave;
-    if (it >= nitem) return;
+// One workgroup per pair, a thread per column.  Bound by the writes: 240 MB in
+// 50 us at S = 600.
+__global__ __launch_bounds__(256) void rec4_kernel(Ctx c) {
     const int64_t S = c.S, nt = c.Gnt;
-    int64_t jb = 0;
-    for (;; ++jb) {
-        const int64_t n = s4_block_pairs(S, jb);
-        if (it < n) break;
-        it -= n;
-    }
     int64_t g1, g2;
-    s4_pair(it, g1, g2);
+    s4_pair(blockIdx.x, g1, g2);
     g1 = uni(g1);
     g2 = uni(g2);
     const double *__restrict__ G1 = c.G1;
     CDouble *f = cptr(c.fac4) + (s4_pairs_below(g2) + g1) * S4_FAC;
-    const int64_t j0 = jb * S3_JR, jlo = j0 > S4_NR * g2 + 1 ? j0 : S4_NR * g2 + 1;
-    const int64_t jhi = j0 + S3_JR - 1 < S - 2 ? j0 + S3_JR - 1 : S - 2;
-    const int64_t j = jlo + lane <= jhi ? jlo + lane : jhi;
     constexpr int N = 2 * S4_NR;
-    double x[N], v[N], al = 0.0, zs = 0.0, p = f[44];
-#pragma unroll
-    for (int m = 0; m < N; ++m) {
-        const int64_t i = S4_NR * (m < S4_NR ? g1 : g2) + m % S4_NR;
-        x[m] = G1[gidx(i < S ? i : S - 1, j, nt, 1, 0)];
-        v[m] = 0.0;
-    }
-    if (!(c.inv_s[j] > 0.0)) {
-        p = S3_NEVER;
-    } else if (f[45] != 0.0) {
-        p = 0.0;
-    } else if (j >= S4_NR * (g2 + 1)) {  // (a j of g2 itself leaves the pair alone)
-        double d = 1.0, e = c.bhat[j];
+    const int64_t x0 = S4_NR * g2, len = S - x0;
+    for (int64_t j = x0 + threadIdx.x; j < S; j += 256) {
+        double x[N], v[N], al = 0.0, zs = 0.0, p = f[44], d = 0.0, e = 0.0;
 #pragma unroll
         for (int m = 0; m < N; ++m) {
-            double s = 0.0;
-#pragma unroll
-            for (int l = 0; l <= m; ++l) s += f[m * (m + 1) / 2 + l] * x[l];
-            v[m] = s;
-            d -= s * s;
-            e -= s * f[36 + m];
+            const int64_t i = S4_NR * (m < S4_NR ? g1 : g2) + m % S4_NR;
+            x[m] = G1[gidx(i < S ? i : S - 1, j, nt, 1, 0)];
+            v[m] = 0.0;
         }
-        if (d > S3_TAU) {
-            al = 1.0 / d;
-            zs = e * al;
-            p = p - e * zs;
-        } else {
+        if (!(c.inv_s[j] > 0.0)) {
+            p = d = S3_NEVER;
+        } else if (f[45] != 0.0) {
             p = 0.0;
-        }
-    }
-    double *o = stage[wave] + lane * S4_REC;
+        } else if (j >= S4_NR * (g2 + 1)) {  // (a column of g2 itself leaves the pair alone)
+            d = 1.0;
+            e = c.bhat[j];
 #pragma unroll
-    for (int m = 0; m < N; ++m) o[m] = v[m];
-    o[8] = al;
-    o[9] = zs;
-    o[10] = p;
-    o[11] = zs * zs;
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_wave_barrier();
-    const int nvals = (int)(jhi - jlo + 1) * S4_REC;
-    double *out = c.rec4 + (s4_rowoff(S, g1, g2) + jlo - S4_NR * g2 - 1) * S4_REC;
-    for (int q = lane; q < nvals; q += 64) out[q] = stage[wave][q];
-}
-
-// tile t: its row block, column chunk and pair of groups (chunk fastest: the
-// waves of a workgroup share the records of a pair)
-__device__ __forceinline__ void s4_locate(int64_t S, const uint64_t *__restrict__ tcum, uint64_t t, S3Tile &tl,
-                                          int64_t &g1, int64_t &g2) {
-    int64_t lo = 0, hi = s3_nblocks(S) - 1;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi + 1) >> 1;
-        if (tcum[mid] <= t) lo = mid; else hi = mid - 1;
+            for (int m = 0; m < N; ++m) {
+                double s = 0.0;
+#pragma unroll
+                for (int l = 0; l <= m; ++l) s += f[m * (m + 1) / 2 + l] * x[l];
+                v[m] = s;
+                d -= s * s;
+                e -= s * f[36 + m];
+            }
+            if (d > S3_TAU) {
+                al = 1.0 / d;
+                zs = e * al;
+                p = p - e * zs;
+            } else {
+                p = 0.0;
+            }
+        }
+        double *o = c.rec4 + s4_off(S, g1, g2) * S4_FIELDS + (j - x0);
+#pragma unroll
+        for (int m = 0; m < N; ++m) o[m * len] = v[m];
+        o += N * len;
+        o[BF_AL * len] = al;
+        o[BF_ZS * len] = zs;
+        o[BF_P * len] = p;
+        o[BF_D * len] = d;
+        o[BF_E * len] = e;
     }
-    const int64_t nkb = s4_block_chunks(S, lo);
-    const int64_t rem = (int64_t)(t - tcum[lo]);
-    tl.kcx = rem % nkb;
-    tl.j0 = lo * S3_JR;
-    tl.jhi = (tl.j0 + S3_JR - 1 < S - 2) ? tl.j0 + S3_JR - 1 : S - 2;
-    tl.kb = tl.j0 + 1 + tl.kcx * S3_KC;
-    s4_pair(rem / nkb, g1, g2);
-    g1 = uni(g1);
-    g2 = uni(g2);
 }
 
 __device__ inline uint64_t s4_cand(int64_t g1, int64_t g2, int64_t j, int64_t k) {
@@ -2854,213 +2771,60 @@ __device__ inline uint64_t s4_cand(int64_t g1, int64_t g2, int64_t j, int64_t k)
 }
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S4_WPE))) void search4_kernel(
-    Ctx c, const double *__restrict__ rec, const double *__restrict__ fac, const uint64_t *__restrict__ tcum,
-    uint64_t t0, uint64_t t1, uint32_t wg_tiles) {
-    __shared__ unsigned long long s_m[SEARCH_WAVES][S3_JR][2];
+    Ctx c, const double *__restrict__ rec, const double *__restrict__ fac, const uint64_t *__restrict__ cum,
+    uint64_t t0, uint64_t t1, uint32_t wg_units, int run, int glo, int ghi) {
+    __shared__ double s_g[BU * BU];
+    __shared__ double s_par[SEARCH_WAVES][3][BU];
     __shared__ unsigned s_n[2];
-    constexpr int N = 2 * S4_NR;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    uint64_t *__restrict__ cands = c.s3_cands + (size_t)blockIdx.x * wg_tiles * S4_LANES;
-    uint64_t *__restrict__ items = c.s3_rows + (size_t)blockIdx.x * wg_tiles * S4_NR;
+    uint64_t *__restrict__ cands = c.s3_cands + (size_t)blockIdx.x * wg_units * S4_LANES;
+    uint64_t *__restrict__ items = c.s3_rows + (size_t)blockIdx.x * wg_units * S4_ITEMS;
     if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t S = c.S, nt = c.Gnt;
-    const double *__restrict__ Gb = c.G1;
-    const double *__restrict__ inv_s = c.inv_s;
-    const double *__restrict__ bhat = c.bhat;
-    const double th = fmin(theta0_of(c), theta_load(c.theta_bits));
-    const double ctot = c.cyy[0];
+    const int64_t S = c.S;
+    const double th = fmin(theta0_of(c), theta_load(c.theta_bits)), ctot = c.cyy[0];
     const double theta_s = th * (1.0 + THETA_SLACK) + S3_TSLACK * ctot, neg = -S3_ESLACK * ctot;
     S3Skip skip;
-    // tiles dealt round-robin, XCD-aware, as in search3_kernel
-    const bool xa = (gridDim.x % S3_XCDS) == 0;
-    const uint64_t xcd = xa ? blockIdx.x % S3_XCDS : 0;
-    const uint64_t nx = xa ? S3_XCDS : 1;
-    const uint64_t U = (uint64_t)gridDim.x / nx * SEARCH_WAVES;
-    const uint64_t u0 = (uint64_t)blockIdx.x / nx * SEARCH_WAVES + wave;
-    for (uint64_t sx = u0;; sx += U) {
-        const uint64_t t = t0 + ((sx / S3_XCD_RUN) * nx + xcd) * S3_XCD_RUN + sx % S3_XCD_RUN;
-        if (t >= t1) break;
+    for (uint64_t t = bound_first(t0); t < t1; t += gridDim.x) {
         S3Tile tl;
-        int64_t g1, g2;
-        s4_locate(S, tcum, t, tl, g1, g2);
-        const int64_t jlo = tl.j0 > S4_NR * g2 + 1 ? tl.j0 : S4_NR * g2 + 1;
-        const int nrow = (int)(tl.jhi - jlo);  // steps 0..nrow
-        CDouble *f = cptr(fac) + (s4_pairs_below(g2) + g1) * S4_FAC;
-        unsigned long long rows = 0;
-        int lanes = 1 << 30;
-        if (skip.left > 0) {
-            --skip.left;
-        } else if (th < INF && f[45] == 0.0) {
-            CChar *recj = (CChar *)(cptr(rec) + (size_t)(s4_rowoff(S, g1, g2) + jlo - S4_NR * g2 - 1) * S4_REC);
-            // touch the 128-byte lines of the tile's records, so that the
-            // scalar loads below find them in L2
-            double pf = 0.0;
-            if (lane * 128 < (nrow + 1) * S4_REC * 8)
-                pf = rec[(size_t)(s4_rowoff(S, g1, g2) + jlo - S4_NR * g2 - 1) * S4_REC + lane * 16];
-            const int64_t k0 = tl.kb + lane, k1 = tl.kb + 64 + lane;
-            const bool kv0 = k0 < S, kv1 = k1 < S;
-            // columns read for lanes past S: any valid one (masked below)
-            const int64_t kk0 = kv0 ? k0 : S - 1, kk1 = kv1 ? k1 : S - 1;
-            const bool diag = tl.kcx == 0, half = S - tl.kb <= 64;
-            // k-dependent part of the pair's solve, for both columns of the lane
-            double w[N][2], dq[2], z2[2], zz[2];  // z2 = -2 zeta', zz = zeta'^2
-            {
-                double x0[N], x1[N];
-#pragma unroll
-                for (int m = 0; m < N; ++m) {
-                    int64_t i = S4_NR * (m < S4_NR ? g1 : g2) + m % S4_NR;
-                    i = i < S ? i : S - 1;  // past S: the factor's row is zero
-                    x0[m] = Gb[gidx(i, kk0, nt, 1, 0)];
-                    x1[m] = Gb[gidx(i, kk1, nt, 1, 0)];
-                }
-                double d0 = 1.0 - S3_DSLACK, d1 = 1.0 - S3_DSLACK, e0 = bhat[kk0], e1 = bhat[kk1];
-#pragma unroll
-                for (int m = 0; m < N; ++m) {
-                    double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-                    for (int l = 0; l <= m; ++l) {
-                        s0 = fma(f[m * (m + 1) / 2 + l], x0[l], s0);
-                        s1 = fma(f[m * (m + 1) / 2 + l], x1[l], s1);
-                    }
-                    w[m][0] = s0;
-                    w[m][1] = s1;
-                    d0 = fma(-s0, s0, d0);
-                    d1 = fma(-s1, s1, d1);
-                    e0 = fma(-s0, f[36 + m], e0);
-                    e1 = fma(-s1, f[36 + m], e1);
-                }
-                // a lane past S or on a constant column never passes
-                dq[0] = kv0 && inv_s[kk0] > 0.0 ? d0 : S3_NEVER;
-                dq[1] = kv1 && inv_s[kk1] > 0.0 ? d1 : S3_NEVER;
-                z2[0] = -2.0 * e0;
-                z2[1] = -2.0 * e1;
-                zz[0] = e0 * e0;
-                zz[1] = e1 * e1;
+        int64_t b0, b1, g1, g2;
+        bound_locate<S4Pairs>(S, cum, t, run, tl, b0, b1);
+        s4_pair(b0, g1, g2);
+        g1 = uni(g1) + wave;
+        g2 = uni(g2);
+        __syncthreads();  // the waves have left the previous item's G
+        bound_load(s_g, c.G1, c.Gnt, tl);
+        __syncthreads();
+        for (int64_t b = b0 + wave; b < b1; b += SEARCH_WAVES, g1 += SEARCH_WAVES) {
+            while (g1 > g2) g1 -= ++g2;
+            if (g1 < glo || g1 > ghi) continue;
+            unsigned long long mine = 0;
+            int lanes = 1 << 30;
+            if (!skip.skip() && th < INF && cptr(fac)[b * S4_FAC + 45] == 0.0) {
+                const int lo = S4_NR * g2 + 1 > tl.j0 ? (int)(S4_NR * g2 + 1 - tl.j0) : 0;
+                bound_unit<2>(s_g, S, tl, rec + s4_off(S, g1, g2) * S4_FIELDS, S4_NR * g2, S - S4_NR * g2, lo, theta_s,
+                              neg, s_par[wave], mine, lanes);
+                skip.result(lanes > S4_LANES);
             }
-            const char *__restrict__ gtile = reinterpret_cast<const char *>(Gb + (((tl.j0 >> 6) * nt) << 12));
-            const uint32_t voff0 = (uint32_t)((((kk0 >> 6) << 12) + (kk0 & 63) + ((jlo & 63) << 6)) * 8);
-            const uint32_t voff1 = (uint32_t)((((kk1 >> 6) << 12) + (kk1 & 63) + ((jlo & 63) << 6)) * 8);
-            lanes = 0;
-            auto sweep = [&](auto diagc, auto halfc) {
-                constexpr bool DIAG = decltype(diagc)::value;
-                constexpr bool HALF = decltype(halfc)::value;
-                constexpr int JG = S3_JG;
-                static_assert(JG % 2 == 0, "the record buffers alternate by row");
-                double2 ga[JG], gb[JG];  // g(j, k0), g(j, k1)
-                auto fetch = [&](double2 (&dst)[JG], int jg) {
-#pragma unroll
-                    for (int x = 0; x < JG; ++x) {
-                        const uint32_t jr = (uint32_t)(jg + x < nrow ? jg + x : nrow);
-                        dst[x].x = *reinterpret_cast<const double *>(gtile + (voff0 + jr * 512u));
-                        dst[x].y = HALF ? 0.0 : *reinterpret_cast<const double *>(gtile + (voff1 + jr * 512u));
-                    }
-                };
-                // a step's record is loaded while the step before is scored
-                auto load = [&](double (&rv)[S4_REC], int jr) {
-                    CDouble *rp = (CDouble *)(recj + (size_t)(jr < nrow ? jr : nrow) * (S4_REC * 8));
-#pragma unroll
-                    for (int e = 0; e < S4_REC; ++e) rv[e] = rp[e];
-                };
-                // the bound as a polynomial in u, as in s3_bound
-                auto step = [&](const double (&rv)[S4_REC], const double2 gv, int jr) {
-                    const double pi = fmax(rv[10] - theta_s, 0.0);
-                    const double A = fma(pi, rv[8], rv[11]);
-                    unsigned long long m0, m1 = 0;
-                    {
-                        double u = gv.x;
-#pragma unroll
-                        for (int e = 0; e < N; ++e) u = fma(-rv[e], w[e][0], u);
-                        const double x = fma(u, fma(A, u, rv[9] * z2[0]), fma(-pi, dq[0], zz[0]));
-                        m0 = __ballot(!(x < neg));
-                        if (DIAG) m0 &= __ballot(k0 > jlo + jr);  // k1 > j0 + 64 > j
-                    }
-                    if (!HALF) {
-                        double u = gv.y;
-#pragma unroll
-                        for (int e = 0; e < N; ++e) u = fma(-rv[e], w[e][1], u);
-                        const double x = fma(u, fma(A, u, rv[9] * z2[1]), fma(-pi, dq[1], zz[1]));
-                        m1 = __ballot(!(x < neg));
-                    }
-                    if ((m0 | m1) && jr <= nrow) {
-                        m0 &= __ballot(kv0);
-                        m1 &= __ballot(kv1);
-                        if (lane == 0) {
-                            s_m[wave][jr][0] = m0;
-                            s_m[wave][jr][1] = m1;
-                        }
-                        rows |= 1ull << jr;
-                        lanes += __popcll(m0) + __popcll(m1);
-                    }
-                };
-                double ra[S4_REC], rb[S4_REC];
-                load(ra, 0);
-                auto score = [&](const double2 (&src)[JG], int jg) {
-#pragma unroll
-                    for (int x = 0; x < JG; x += 2) {
-                        __builtin_amdgcn_s_waitcnt(0xC07F);
-                        load(rb, jg + x + 1);
-                        __builtin_amdgcn_sched_barrier(0);
-                        step(ra, src[x], jg + x);
-                        __builtin_amdgcn_s_waitcnt(0xC07F);
-                        load(ra, jg + x + 2);
-                        __builtin_amdgcn_sched_barrier(0);
-                        step(rb, src[x + 1], jg + x + 1);
-                    }
-                };
-                __builtin_amdgcn_s_waitcnt(0x0F70);
-                fetch(ga, 0);
-                for (int jg = 0;; jg += 2 * JG) {
-                    fetch(gb, jg + JG);
-                    score(ga, jg);
-                    fetch(ga, jg + 2 * JG);
-                    score(gb, jg + JG);
-                    if (jg + 2 * JG > nrow) break;
-                }
-            };
-            if (diag) {
-                if (half) sweep(std::true_type{}, std::true_type{});
-                else sweep(std::true_type{}, std::false_type{});
-            } else {
-                if (half) sweep(std::false_type{}, std::true_type{});
-                else sweep(std::false_type{}, std::false_type{});
-            }
-            asm volatile("; touched %0" ::"v"(pf));  // the load stays (its value is not needed)
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);
-            __builtin_amdgcn_wave_barrier();
             if (lanes > S4_LANES) {
-                skip.fails = skip.fails < 5 ? skip.fails + 1 : 5;
-                skip.left = (1 << skip.fails) - 1;
-            } else {
-                skip.fails = 0;
+                // the whole unit, an item per i2 and S4_DR rows with a tuple in it
+                const int64_t i2 = S4_NR * g2 + lane % S4_NR, jr = tl.j0 + lane / S4_NR * S4_DR;
+                const bool in = lane < S4_ITEMS && i2 > S4_NR * g1 && jr <= tl.jhi && i2 < jr + S4_DR - 1 &&
+                                i2 < tl.jhi && c.inv_s[i2 < S ? i2 : S - 1] > 0.0;
+                const unsigned long long m = __ballot(in);
+                unsigned at = 0;
+                if (lane == 0) at = atomicAdd(&s_n[1], (unsigned)__popcll(m));
+                at = (unsigned)__shfl((int)at, 0);
+                // (group g1, i2, first row / S4_DR, column chunk)
+                if (in)
+                    items[at + __popcll(m & ((1ull << lane) - 1ull))] = s4_cand(g1, i2, jr / S4_DR, tl.kcx);
+                continue;
             }
-        }
-        if (lanes > S4_LANES) {
-            // the whole tile, an item per i2 with a tuple in it
-            const int64_t i2 = S4_NR * g2 + lane;
-            const bool in = lane < S4_NR && i2 > S4_NR * g1 && i2 < tl.jhi && inv_s[i2 < S ? i2 : S - 1] > 0.0;
-            const unsigned long long b = __ballot(in);
+            if (!lanes) continue;
             unsigned at = 0;
-            if (lane == 0) at = atomicAdd(&s_n[1], (unsigned)__popcll(b));
+            if (lane == 0) at = atomicAdd(&s_n[0], (unsigned)lanes);
             at = (unsigned)__shfl((int)at, 0);
-            if (in) items[at + __popcll(b & ((1ull << lane) - 1ull))] = t * S4_NR + lane;
-            continue;
-        }
-        if (!lanes) continue;
-        unsigned at = 0;
-        if (lane == 0) at = atomicAdd(&s_n[0], (unsigned)lanes);
-        at = (unsigned)__shfl((int)at, 0);
-        while (rows) {
-            const int x = __builtin_ctzll(rows);
-            rows &= rows - 1;
-#pragma unroll
-            for (int sl = 0; sl < 2; ++sl) {
-                const unsigned long long m = s_m[wave][x][sl];
-                if ((m >> lane) & 1ull)
-                    cands[at + __popcll(m & ((1ull << lane) - 1ull))] = s4_cand(g1, g2, jlo + x, tl.kb + 64 * sl + lane);
-                at += (unsigned)__popcll(m);
-            }
+            bound_each(mine, [&](int p, int x, int k) { cands[at + p] = s4_cand(g1, g2, tl.j0 + x, tl.kb + k); });
         }
     }
     __syncthreads();
@@ -3158,50 +2922,43 @@ __device__ __forceinline__ void s4_candidates(const Ctx &c, const SearchArgs &a,
     }
 }
 
-constexpr int S4_DR = 16;  // rows of a dense item swept at a time (their records lie in LDS)
-
-// All tuples of a tile with second index i2 and first index in group g1, by
-// the wave: S4_DR rows at a time, whose records are built in LDS and read by
-// all lanes at one address.
-__device__ __forceinline__ void s4_dense(const Ctx &c, const SearchArgs &a, const S3Tile &tl, int64_t g1, int64_t i2,
-                                         double *Ls, uint64_t *Lr, double theta0, double &theta_pub, unsigned &offered,
-                                         double (*s_r)[S4_NR][6], unsigned long long (*s_q)[2]) {
+// A dense item: all tuples of S4_DR rows of a tile with second index i2 and
+// first index in group g1.  The rows' records are built in LDS and read by all
+// lanes at one address.
+__device__ __forceinline__ void s4_dense(const Ctx &c, const SearchArgs &a, uint64_t item, double *Ls, uint64_t *Lr,
+                                         double theta0, double &theta_pub, unsigned &offered,
+                                         double (*s_r)[S4_NR][6], unsigned long long *s_q) {
     const int KP = a.KP;
     const int lane = threadIdx.x & 63;
     const int64_t S = c.S, nt = c.Gnt;
+    const int64_t g1 = (int64_t)(item >> 48), i2 = (int64_t)((item >> 32) & 0xFFFF);
+    const int64_t jr = (int64_t)((item >> 16) & 0xFFFF) * S4_DR, kcx = (int64_t)(item & 0xFFFF);
     const double *__restrict__ Gb = c.G1;
     const double *__restrict__ inv_s = c.inv_s;
     const double ctot = c.cyy[0];
-    const int64_t k0 = tl.kb + lane, k1 = tl.kb + 64 + lane;
-    const bool kv0 = k0 < S, kv1 = k1 < S;
-    const int64_t kk0 = kv0 ? k0 : S - 1, kk1 = kv1 ? k1 : S - 1;
-    // k-dependent part of each pair's solve, for both columns of the lane
-    double w0[S4_NR][2], w1[S4_NR][2], dq[S4_NR][2], zq[S4_NR][2];
+    const int64_t k = jr / BU * BU + kcx * BU + lane, kk = k < S ? k : S - 1;
+    // k-dependent part of each pair's solve
+    double w0[S4_NR], w1[S4_NR], dq[S4_NR], zq[S4_NR];
     {
-        const bool lk0 = kv0 && inv_s[kk0] > 0.0, lk1 = kv1 && inv_s[kk1] > 0.0;
-        const double b0 = c.bhat[kk0], b1 = c.bhat[kk1];
-        const double x2 = Gb[gidx(i2, kk0, nt, 1, 0)], y2 = Gb[gidx(i2, kk1, nt, 1, 0)];
+        const bool lk = k < S && inv_s[kk] > 0.0;
+        const double bk = c.bhat[kk], x2 = Gb[gidx(i2, kk, nt, 1, 0)];
 #pragma unroll
         for (int r = 0; r < S4_NR; ++r) {
             const bool pin = S4_NR * g1 + r < i2;
             const int64_t i1 = pin ? S4_NR * g1 + r : i2;  // a void pair reads valid memory and never passes
             const S4Pair q(Gb[gidx(i1, i2, nt, 1, 0)], c.bhat[i1], c.bhat[i2], pin && inv_s[i1] > 0.0);
-            const double a0 = Gb[gidx(i1, kk0, nt, 1, 0)], a1 = Gb[gidx(i1, kk1, nt, 1, 0)];
-            const double c0 = (x2 - q.r * a0) * q.is, c1 = (y2 - q.r * a1) * q.is;
-            w0[r][0] = a0;
-            w0[r][1] = a1;
-            w1[r][0] = c0;
-            w1[r][1] = c1;
+            const double a0 = Gb[gidx(i1, kk, nt, 1, 0)], c0 = (x2 - q.r * a0) * q.is;
+            w0[r] = a0;
+            w1[r] = c0;
             // a lane past S, a constant column or a void pair never passes
-            dq[r][0] = q.is > 0.0 && lk0 ? 1.0 - a0 * a0 - c0 * c0 : __builtin_nan("");
-            dq[r][1] = q.is > 0.0 && lk1 ? 1.0 - a1 * a1 - c1 * c1 : __builtin_nan("");
-            zq[r][0] = b0 - a0 * q.z0 - c0 * q.z1;
-            zq[r][1] = b1 - a1 * q.z0 - c1 * q.z1;
+            dq[r] = q.is > 0.0 && lk ? 1.0 - a0 * a0 - c0 * c0 : __builtin_nan("");
+            zq[r] = bk - a0 * q.z0 - c0 * q.z1;
         }
     }
-    const int64_t jfirst = tl.j0 > i2 + 1 ? tl.j0 : i2 + 1;
-    for (int64_t jlo = jfirst; jlo <= tl.jhi; jlo += S4_DR) {
-        const int nr = (int)(tl.jhi - jlo + 1 < S4_DR ? tl.jhi - jlo + 1 : S4_DR);
+    {
+        const int64_t jhi = jr + S4_DR - 1 < S - 2 ? jr + S4_DR - 1 : S - 2;
+        const int64_t jlo = jr > i2 + 1 ? jr : i2 + 1;
+        const int nr = (int)(jhi - jlo + 1);
         double th = fmin(theta0, theta_load(c.theta_bits));
         th = fmin(th, Ls[KP - 1]);
         const double theta_f = th < INF ? th * (1.0 + THETA_SLACK) : INF;
@@ -3224,31 +2981,20 @@ __device__ __forceinline__ void s4_dense(const Ctx &c, const SearchArgs &a, cons
         unsigned rows = 0;
         for (int x = 0; x < nr; ++x) {
             const int64_t j = jlo + x;
-            const double gx = Gb[gidx(j, kk0, nt, 1, 0)], gy = Gb[gidx(j, kk1, nt, 1, 0)];
-            unsigned long long m0 = 0, m1 = 0;
+            const double gx = Gb[gidx(j, kk, nt, 1, 0)];
+            unsigned long long m = 0;
 #pragma unroll
             for (int r = 0; r < S4_NR; ++r) {
                 const double v0 = s_r[x][r][0], v1 = s_r[x][r][1], al = s_r[x][r][2], zs = s_r[x][r][3];
                 const double pi = s_r[x][r][4] - theta_f;
-                {
-                    const double u = fma(-v1, w1[r][0], fma(-v0, w0[r][0], gx));
-                    const double d = fma(-al, u * u, dq[r][0]);
-                    const double z = fma(-zs, u, zq[r][0]);
-                    m0 |= __ballot(z * z >= pi * d);
-                }
-                {
-                    const double u = fma(-v1, w1[r][1], fma(-v0, w0[r][1], gy));
-                    const double d = fma(-al, u * u, dq[r][1]);
-                    const double z = fma(-zs, u, zq[r][1]);
-                    m1 |= __ballot(z * z >= pi * d);
-                }
+                const double u = fma(-v1, w1[r], fma(-v0, w0[r], gx));
+                const double d = fma(-al, u * u, dq[r]);
+                const double z = fma(-zs, u, zq[r]);
+                m |= __ballot(z * z >= pi * d);
             }
-            m0 &= __ballot(k0 > j);
-            if (m0 | m1) {
-                if (lane == 0) {
-                    s_q[x][0] = m0;
-                    s_q[x][1] = m1;
-                }
+            m &= __ballot(k > j);
+            if (m) {
+                if (lane == 0) s_q[x] = m;
                 rows |= 1u << x;
             }
         }
@@ -3256,38 +3002,33 @@ __device__ __forceinline__ void s4_dense(const Ctx &c, const SearchArgs &a, cons
         __builtin_amdgcn_wave_barrier();
         // exact scoring of the flagged rows: the same terms, a true division,
         // the rank test and the current bound
-        auto pick = [&](const double (&arr)[S4_NR][2], int r, int sl) {
-            double v = arr[0][0];
+        auto pick = [&](const double (&arr)[S4_NR], int r) {
+            double v = arr[0];
 #pragma unroll
-            for (int q = 0; q < S4_NR; ++q)
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    if (q == r && h == sl) v = arr[q][h];
+            for (int q = 1; q < S4_NR; ++q)
+                if (q == r) v = arr[q];
             return v;
         };
         while (rows) {
             const int x = __builtin_ctz(rows);
             rows &= rows - 1;
             const int64_t j = jlo + x;
-            const unsigned long long fm[2] = {s_q[x][0], s_q[x][1]};
-            const double gx = Gb[gidx(j, kk0, nt, 1, 0)], gy = Gb[gidx(j, kk1, nt, 1, 0)];
+            const unsigned long long fm = s_q[x];
+            const double gx = Gb[gidx(j, kk, nt, 1, 0)];
             for (int r = 0; r < S4_NR; ++r) {
                 const double v0 = s_r[x][r][0], v1 = s_r[x][r][1], al = s_r[x][r][2], zs = s_r[x][r][3];
                 const double p = s_r[x][r][4];
-                for (int sl = 0; sl < 2; ++sl) {
-                    const int64_t k = sl ? k1 : k0;
-                    const double u = fma(-v1, pick(w1, r, sl), fma(-v0, pick(w0, r, sl), sl ? gy : gx));
-                    const double d = fma(-al, u * u, pick(dq, r, sl));
-                    const double z = fma(-zs, u, pick(zq, r, sl));
-                    const int32_t tup[4] = {(int32_t)(S4_NR * g1 + r), (int32_t)i2, (int32_t)j, (int32_t)k};
-                    const double es = (d > RANK_EPS) ? p - z * z / d : INF;
-                    bool take = ((fm[sl] >> lane) & 1ull) && k < S && k > j && es <= fmin(theta_f, Ls[KP - 1]);
-                    if (take && a.ranged) {
-                        const uint64_t lr = lex_rank(BinomTab{c.btab, c.S}, c.S, 4, tup);
-                        if (lr < a.r0 || lr >= a.r1) take = false;
-                    }
-                    list_insert_lanes(Ls, Lr, KP, take, take ? pack_tuple(tup, 4) : 0, es, offered);
+                const double u = fma(-v1, pick(w1, r), fma(-v0, pick(w0, r), gx));
+                const double d = fma(-al, u * u, pick(dq, r));
+                const double z = fma(-zs, u, pick(zq, r));
+                const int32_t tup[4] = {(int32_t)(S4_NR * g1 + r), (int32_t)i2, (int32_t)j, (int32_t)k};
+                const double es = (d > RANK_EPS) ? p - z * z / d : INF;
+                bool take = ((fm >> lane) & 1ull) && k < S && es <= fmin(theta_f, Ls[KP - 1]);
+                if (take && a.ranged) {
+                    const uint64_t lr = lex_rank(BinomTab{c.btab, c.S}, c.S, 4, tup);
+                    if (lr < a.r0 || lr >= a.r1) take = false;
                 }
+                list_insert_lanes(Ls, Lr, KP, take, take ? pack_tuple(tup, 4) : 0, es, offered);
             }
         }
         const double tw = Ls[KP - 1];
@@ -3299,11 +3040,13 @@ __device__ __forceinline__ void s4_dense(const Ctx &c, const SearchArgs &a, cons
 }
 
 // Scores the pools, as s3_eval_kernel does.
-__global__ __launch_bounds__(256) void s4_eval_kernel(Ctx c, SearchArgs a, const uint64_t *__restrict__ tcum,
-                                                      uint32_t nseg, uint32_t wg_tiles, int resume) {
+#ifndef S4E_WPE
+#define S4E_WPE 3
+#endif
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S4E_WPE))) void s4_eval_kernel(Ctx c, SearchArgs a, uint32_t nseg, uint32_t wg_units, int resume) {
     extern __shared__ double smem[];
     __shared__ double s_r[SEARCH_WAVES][S4_DR][S4_NR][6];
-    __shared__ unsigned long long s_q[SEARCH_WAVES][S4_DR][2];
+    __shared__ unsigned long long s_q[SEARCH_WAVES][S4_DR];
     __shared__ unsigned long long s_w[2][SEARCH_WAVES];
     const int KP = a.KP;
     const int lane = threadIdx.x & 63;
@@ -3335,19 +3078,15 @@ __global__ __launch_bounds__(256) void s4_eval_kernel(Ctx c, SearchArgs a, const
         uint64_t key = 0;
         if (in) {
             const uint32_t s = pool_segment(first[0], nseg, e);
-            key = c.s3_cands[(size_t)s * wg_tiles * S4_LANES + (e - first[0][s])];
+            key = c.s3_cands[(size_t)s * wg_units * S4_LANES + (e - first[0][s])];
         }
         s4_candidates(c, a, in, key, Ls, Lr, theta0, theta_pub, offered);
     }
     // the items round-robin: consecutive ones lie on different waves
     for (uint64_t e = (uint64_t)gw; e < nitem; e += nw) {
         const uint32_t s = pool_segment(first[1], nseg, e);
-        const uint64_t it = uni(c.s3_rows[(size_t)s * wg_tiles * S4_NR + (e - first[1][s])]);
-        S3Tile tl;
-        int64_t g1, g2;
-        s4_locate(c.S, tcum, it / S4_NR, tl, g1, g2);
-        s4_dense(c, a, tl, g1, S4_NR * g2 + (int64_t)(it % S4_NR), Ls, Lr, theta0, theta_pub, offered, s_r[wave],
-                 s_q[wave]);
+        const uint64_t it = uni(c.s3_rows[(size_t)s * wg_units * S4_ITEMS + (e - first[1][s])]);
+        s4_dense(c, a, it, Ls, Lr, theta0, theta_pub, offered, s_r[wave], s_q[wave]);
     }
     if (lane == 0 && offered) atomicAdd(c.cand_counter, offered);
     list_store(c.list_sse + gw * KP, c.list_rank + gw * KP, Ls, Lr, KP);
@@ -4282,7 +4021,7 @@ static void launch_merge(const Ctx &c, int nlists, int use_pre, hipStream_t st, 
 // The one-task D = 3 record-table path applies (it also needs the table in
 // the workspace and fewer than 2^31 tiles).
 bool s3_batchable(const Ctx &c, int D) {
-    return D == 3 && c.T == 1 && !c.fp32 && c.rec3 != nullptr && s3_tiles_host(c.S) < (1ull << 31);
+    return D == 3 && c.T == 1 && !c.fp32 && c.rec3 != nullptr && s3_items_host(c.S) < (1ull << 31);
 }
 
 // record table + initialisation + pre-pass selection (one launch), then the
@@ -4315,6 +4054,17 @@ int launch_batch_epilogue(const Ctx &c, const SearchCall &sc, hipStream_t st) {
     launch_merge(c, c.nwaves, 1, st, 0, c.flags + FLAG_NLISTS);
     launch_rescore_final(c, 3, sc.k, st);
     return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// first index of the D-tuple with lexicographic rank r
+static int64_t first_index(int64_t S, int D, uint64_t r) {
+    int64_t i = 0;
+    for (; i < S - D; ++i) {
+        const uint64_t n = binom(S - 1 - i, D - 1);  // tuples that start with i
+        if (r < n) break;
+        r -= n;
+    }
+    return i;
 }
 
 int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
@@ -4351,12 +4101,12 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
         phase_end(c, SISSO_PHASE_MERGE, st);
     } else {
         phase_begin(c, SISSO_PHASE_PREPASS, st);
-        // one task, D = 3: record table + tile sweep (tile count within the 32-bit work counter)
+        // one task, D = 3: record table + sweep of the units
         // D = 3: the record-table sweep, on the filter task's matrix when
         // there are several tasks
-        const bool s3 = D == 3 && !c.fp32 && c.rec3 != nullptr && s3_tiles_host(c.S) < (1ull << 31);
+        const bool s3 = D == 3 && !c.fp32 && c.rec3 != nullptr && s3_items_host(c.S) < (1ull << 31);
         // one task, D = 4: the record table of group pairs (sized at create
-        // only while it stays within S4_TABLE_MAX and 2^31 tiles)
+        // only while it stays within S4_TABLE_MAX)
         const bool s4 = D == 4 && !MT && !c.fp32 && c.rec4 != nullptr;
         if (s4) {
             const int64_t nt = std::max((int64_t)(SISSO_MAX_D + 1) * (c.S + 1), s4_pairs_below(s4_groups(c.S)));
@@ -4381,45 +4131,49 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
         }
         if (s4) {
             // the record table (part of the set-up, like rec3 above)
-            int64_t nitem = 0;
-            for (int64_t jb = 0; jb < s3_nblocks(c.S); ++jb) nitem += s4_block_pairs(c.S, jb);
-            hipLaunchKernelGGL(rec4_kernel, dim3((unsigned)((nitem + SEARCH_WAVES - 1) / SEARCH_WAVES)),
-                               dim3(SEARCH_WG), 0, st, c, nitem);
+            const int64_t nitem = s4_pairs_below(s4_groups(c.S));
+            hipLaunchKernelGGL(rec4_kernel, dim3((unsigned)nitem), dim3(SEARCH_WG), 0, st, c);
         }
         phase_end(c, SISSO_PHASE_PREPASS, st);
         phase_begin(c, SISSO_PHASE_SEARCH, st);
         const size_t nrec = MT ? (size_t)a.JB * c.TP : (size_t)SEARCH_WG;
         const size_t lds = lds_lists + nrec * RECW * sizeof(double) + (size_t)64 * SUBW * sizeof(double);
+        // groups of first indices with a rank in the range
+        int glo = 0, ghi = INT32_MAX;
+        if (sc.ranged && (s3 || s4)) {
+            glo = (int)(first_index(c.S, D, sc.r0) / S3_NR);
+            ghi = (int)(first_index(c.S, D, sc.r1 > sc.r0 ? sc.r1 - 1 : sc.r0) / S3_NR);
+        }
         if (s4) {
-            const uint64_t ntiles = s4_tiles_host(c.S);
-            const uint32_t nseg = (uint32_t)c.search_wgs;
+            const int run = bound_run(bound_units<S4Pairs>(c.S));
+            const uint64_t n = s4_items_host(c.S), pass = S4_PASS / run;
+            const uint32_t nseg = (uint32_t)(c.search_wgs < BU_WGS ? c.search_wgs : BU_WGS);
             const size_t lds4 = lds_lists + (size_t)2 * (nseg + 1) * sizeof(uint64_t);
-            for (uint64_t t0 = 0; t0 < ntiles; t0 += S4_PASS) {
-                const uint64_t t1 = t0 + S4_PASS < ntiles ? t0 + S4_PASS : ntiles;
-                const uint32_t tiles = (uint32_t)s3_wg_tiles(t1 - t0, c.search_wgs);
-                hipLaunchKernelGGL(search4_kernel, dim3(c.search_wgs), dim3(SEARCH_WG), 0, st, c,
-                                   (const double *)c.rec4, (const double *)c.fac4, (const uint64_t *)c.cum, t0, t1,
-                                   tiles);
-                hipLaunchKernelGGL(s4_eval_kernel, dim3(c.search_wgs), dim3(SEARCH_WG), lds4, st, c, a,
-                                   (const uint64_t *)c.cum, nseg, tiles, t0 > 0);
+            for (uint64_t t0 = 0; t0 < n; t0 += pass) {
+                const uint64_t t1 = t0 + pass < n ? t0 + pass : n;
+                const uint32_t wu = (uint32_t)((t1 - t0 + nseg - 1) / nseg * run);
+                hipLaunchKernelGGL(search4_kernel, dim3(nseg), dim3(SEARCH_WG), 0, st, c, (const double *)c.rec4,
+                                   (const double *)c.fac4, (const uint64_t *)c.cum, t0, t1, wu, run, glo, ghi);
+                hipLaunchKernelGGL(s4_eval_kernel, dim3(c.search_wgs), dim3(SEARCH_WG), lds4, st, c, a, nseg, wu,
+                                   t0 > 0);
             }
         } else if (s3) {
-            const uint64_t ntiles = s3_tiles_host(c.S);
-            const uint32_t nseg = (uint32_t)c.search_wgs;
+            const int run = bound_run(bound_units<S3Groups>(c.S));
+            const uint64_t n = s3_items_host(c.S), pass = S3_PASS / run;
+            const uint32_t nseg = (uint32_t)(c.search_wgs < BU_WGS ? c.search_wgs : BU_WGS);
             const int limit = s3_lanes(c.T);
             const size_t lds3 = lds_lists + (size_t)2 * (nseg + 1) * sizeof(uint64_t);
-            for (uint64_t t0 = 0; t0 < ntiles; t0 += S3_PASS) {
-                const uint64_t t1 = t0 + S3_PASS < ntiles ? t0 + S3_PASS : ntiles;
-                const uint32_t tiles = (uint32_t)s3_wg_tiles(t1 - t0, c.search_wgs);
-                hipLaunchKernelGGL(search3_kernel, dim3(c.search_wgs), dim3(SEARCH_WG), 0, st, c,
-                                   (const double *)c.recg, (const double *)c.gfac, (const uint64_t *)c.cum, t0, t1,
-                                   tiles, limit);
+            for (uint64_t t0 = 0; t0 < n; t0 += pass) {
+                const uint64_t t1 = t0 + pass < n ? t0 + pass : n;
+                const uint32_t wu = (uint32_t)((t1 - t0 + nseg - 1) / nseg * run);
+                hipLaunchKernelGGL(search3_kernel, dim3(nseg), dim3(SEARCH_WG), 0, st, c, (const double *)c.recg,
+                                   (const uint64_t *)c.cum, t0, t1, wu, limit, run, glo, ghi);
                 if (MT)
                     hipLaunchKernelGGL(s3_eval_kernel<true>, dim3(c.search_wgs), dim3(SEARCH_WG), lds3, st, c, a,
-                                       (const double *)c.rec3, nseg, tiles, limit, t0 > 0);
+                                       (const double *)c.rec3, nseg, wu, limit, t0 > 0);
                 else
                     hipLaunchKernelGGL(s3_eval_kernel<false>, dim3(c.search_wgs), dim3(SEARCH_WG), lds3, st, c, a,
-                                       (const double *)c.rec3, nseg, tiles, limit, t0 > 0);
+                                       (const double *)c.rec3, nseg, wu, limit, t0 > 0);
             }
         }
         else switch (D) {

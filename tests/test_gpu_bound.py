@@ -1,7 +1,7 @@
 """The record-table searches' superset bound: a group of four first indices is
 tested together (the fit on the group, j and k bounds its tuples' fits), and
 only what passes is scored tuple by tuple.  Against the oracle's exhaustive
-top-k over the edges of tiles (64 rows, 128 columns, groups of 4 and 8), one
+top-k over the edges of units (64 rows, 64 columns) and groups of 4, one
 and several tasks, rank ranges, every pool distribution (search grids), and
 inputs on which the bound is weak or cannot be used: noise targets, groups
 with dependent or constant columns, columns in the span of others."""
@@ -81,7 +81,7 @@ def test_d3_grids_and_ranges(kind, T):
 
 @pytest.mark.parametrize("T", [1, 2])
 def test_search_in_several_passes(T):
-    """S = 7200 takes two passes over the tiles (one holds 2^20).  Two of three
+    """S = 7200 takes two passes over the units (one holds 2^21).  Two of three
     columns are constant, so the result is that of the 2400 live columns
     alone, which take one pass."""
     p = tiny_problem(41 + T, S=2400, n=64 * T, T=T, D=3, k=30, sigma=0.3)
@@ -112,7 +112,7 @@ def test_d4(kind, S):
 def test_d4_grids_and_ranges(kind):
     """Every search grid gives the same result bit for bit; a range of ranks
     gives the oracle's list of that range, also one with fewer tuples than the
-    list holds (no threshold: every tile is scored whole)."""
+    list holds (no threshold: every unit is scored whole)."""
     S, k = 68, 15
     p = problem(kind, S, 1, 4, 91)
     ref = search(p, 4, k)
@@ -133,7 +133,7 @@ def test_d4_grids_and_ranges(kind):
 
 
 def test_d4_search_in_several_passes():
-    """S = 760 takes two passes over the tiles (one holds 2^17).  Three of four
+    """S = 760 takes two passes over the units (one holds 2^18).  Three of four
     columns are constant, so the result is that of the 190 live columns alone."""
     p = tiny_problem(45, S=190, n=80, D=4, k=30, sigma=0.3)
     ref = search(p, 4, 30)
