@@ -3182,6 +3182,128 @@ __global__ __launch_bounds__(256) void prefix_best_kernel(Ctx c, const int32_t *
     }
 }
 
+// Initialisation of a prefix-list search: the per-search state, and an empty
+// pool without a bound.
+__global__ __launch_bounds__(256) void list_init_kernel(Ctx c) {
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    search_init_body(c, e, e == 0, 2, 1, JBLK, 0);
+    if (e < PRE_BINS) c.pre->hist[e] = 0;
+    if (e == 0) {
+        c.pre->done[0] = 0;
+        c.pre->theta0 = INF;
+    }
+}
+
+// One task: an upper bound of the KP-th best SSE over the list's extensions,
+// from the pool of tuples P + {k} with k behind P's last index, P among the
+// first LIST_POOL rows and not a repeat of an earlier one (so the pool's
+// tuples are distinct).  A tuple counts if the product of its pivots clears
+// RANK_EPS (a pivot is at most 1, so that is the full-rank test in any order
+// of the columns), at its incremental SSE plus the slack of list_search_kernel's
+// filter.  Without the bound every wave filled a list of its own first: at 895
+// prefixes, S = 600 the search took 198 us and the merge of its lists 267 us.
+constexpr int LIST_POOL = 4096;
+template <int M>
+__global__ __launch_bounds__(256) void list_pool_kernel(Ctx c, const int32_t *__restrict__ pre, int64_t n) {
+    constexpr int BPT = PRE_BINS / 256;
+    __shared__ unsigned h[PRE_BINS];
+    __shared__ unsigned wsum[4];
+    __shared__ int s_last;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t p = (int64_t)blockIdx.x * 4 + wave;
+    const int64_t base = pool_base(c.cyy[0]);
+    for (int b = tid; b < PRE_BINS; b += 256) h[b] = 0;
+    __syncthreads();
+    int32_t P[M];
+    if (p < n && load_prefix<M>(c, pre, p, P)) {
+        bool fresh = true;
+        for (int64_t o = lane; o < p; o += 64) {
+            bool same = true;
+#pragma unroll
+            for (int m = 0; m < M; ++m) same &= pre[o * M + m] == P[m];
+            fresh &= !same;
+        }
+        double L[M][M], z[M], pp = c.cyy[0], det = 1.0;
+#pragma unroll
+        for (int a = 0; a < M; ++a) {
+#pragma unroll
+            for (int b2 = 0; b2 < a; ++b2) {
+                double v = Gat(c, P[a], P[b2], 0);
+#pragma unroll
+                for (int l = 0; l < b2; ++l) v -= L[a][l] * L[b2][l];
+                L[a][b2] = v / L[b2][b2];
+            }
+            double d = Gat(c, P[a], P[a], 0);
+#pragma unroll
+            for (int l = 0; l < a; ++l) d -= L[a][l] * L[a][l];
+            det *= d;
+            L[a][a] = sqrt(fmax(d, RANK_EPS));
+            double zz = c.bhat[(int64_t)P[a] * c.TP];
+#pragma unroll
+            for (int l = 0; l < a; ++l) zz -= L[a][l] * z[l];
+            z[a] = zz / L[a][a];
+            pp -= z[a] * z[a];
+        }
+        if (!__any(!fresh) && det > 10.0 * RANK_EPS)
+            for (int64_t k = P[M - 1] + 1 + lane; k < c.S; k += 64) {
+                double w[M], d = Gat(c, k, k, 0), zeta = c.bhat[k * c.TP];
+#pragma unroll
+                for (int a = 0; a < M; ++a) {
+                    double v = Gat(c, P[a], k, 0);
+#pragma unroll
+                    for (int l = 0; l < a; ++l) v -= L[a][l] * w[l];
+                    w[a] = v / L[a][a];
+                    d -= w[a] * w[a];
+                    zeta -= w[a] * z[a];
+                }
+                if (!(det * d > 10.0 * RANK_EPS)) continue;
+                const double s = fmax(pp - zeta * zeta / d, 0.0) * (1.0 + 1e-8) + 1e-12 * c.cyy[0];
+                atomicAdd(&h[pool_bin(s, base)], 1u);
+            }
+    }
+    __syncthreads();
+    auto scan = [&](const unsigned (&v)[BPT]) {
+        unsigned own = 0;
+#pragma unroll
+        for (int b = 0; b < BPT; ++b) own += v[b];
+        unsigned incl = own;
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned y = __shfl_up(incl, o);
+            if (lane >= o) incl += y;
+        }
+        if (lane == 63) wsum[wave] = incl;
+        __syncthreads();
+        unsigned before = incl - own;
+        for (int w = 0; w < wave; ++w) before += wsum[w];
+        return before;
+    };
+    // bins past the workgroup's own KP smallest cannot hold the pool's KP-th
+    unsigned v[BPT];
+#pragma unroll
+    for (int b = 0; b < BPT; ++b) v[b] = h[tid * BPT + b];
+    unsigned before = scan(v);
+#pragma unroll
+    for (int b = 0; b < BPT; ++b) {
+        if (v[b] && before < (unsigned)c.KP) atomicAdd(&c.pre->hist[tid * BPT + b], v[b]);
+        before += v[b];
+    }
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) s_last = atomicAdd(&c.pre->done[0], 1u) == gridDim.x - 1u;
+    __syncthreads();
+    if (!s_last) return;
+    __threadfence();
+#pragma unroll
+    for (int b = 0; b < BPT; ++b)
+        v[b] = __hip_atomic_load(&c.pre->hist[tid * BPT + b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    before = scan(v);
+#pragma unroll
+    for (int b = 0; b < BPT; ++b) {
+        if (before < (unsigned)c.KP && before + v[b] >= (unsigned)c.KP) c.pre->theta0 = pool_edge(tid * BPT + b, base);
+        before += v[b];
+    }
+}
+
 // Top-k candidates over the extensions of a prefix list: persistent waves
 // take prefixes in turn, lanes run over k, and each wave keeps its sorted
 // list as in the exhaustive search (bound: own KP-th entry and the
@@ -3244,7 +3366,7 @@ __global__ __launch_bounds__(256) void list_search_kernel(Ctx c, const int32_t *
             }
         }
         // the device-wide bound is read once per prefix (a memory round trip)
-        const double th_dev = theta_load(c.theta_bits);
+        const double th_dev = fmin(theta_load(c.theta_bits), theta0_of(c));
         for (int64_t kb = 0; kb < c.S; kb += 64) {
             const int64_t k = kb + lane;
             double sse = INF;
@@ -3546,20 +3668,39 @@ __global__ __launch_bounds__(MERGE_THREADS) void merge_select_kernel(Ctx c, int 
         c.stats[3] = (uint64_t)__double_as_longlong(theta_load(c.theta_bits));
     }
     // Few candidates (the usual case once the pre-pass bound is tight): the
-    // KP smallest by rank counting, with no sort.  Without dedupe the keys are
-    // distinct, so the ranks (candidates ordered before each one) are too,
+    // KP smallest by rank counting, with no sort.  Once the later copies of a
+    // tuple are empty (dedupe; otherwise there are none) the keys are distinct,
+    // so the ranks (candidates ordered before each one) are too,
     // and writing candidate x at position rank(x) < KP gives the sorted
     // prefix the sorting path below returns (the candidates are finite:
     // merge_compact appends only entries below INF); positions past the
     // candidates are empty (INF, ~0) as there.
-    if (!dedupe && total <= MERGE_THREADS) {
+    if (total <= MERGE_THREADS) {
         const int n = (int)total;
-        if (tid < n) {
+        bool mine = tid < n;
+        if (mine) {
             ks[tid] = c.cand_sse[tid];
             kr[tid] = c.cand_rank[tid];
         }
         __syncthreads();
-        if (tid < n) {
+        int kept = n;
+        if (dedupe) {
+            if (mine) {
+                const double v = ks[tid];
+                const uint64_t r = kr[tid];
+                int copy = 0;
+#pragma unroll 8
+                for (int i = 0; i < tid; ++i) copy |= (int)((ks[i] == v) & (kr[i] == r));
+                mine = !copy;
+            }
+            kept = __syncthreads_count(mine);
+            if (tid < n && !mine) {
+                ks[tid] = INF;
+                kr[tid] = ~0ull;
+            }
+            __syncthreads();
+        }
+        if (mine) {
             const double v = ks[tid];
             const uint64_t r = kr[tid];
             // (SSE, key) order written without short-circuit evaluation, so
@@ -3580,7 +3721,7 @@ __global__ __launch_bounds__(MERGE_THREADS) void merge_select_kernel(Ctx c, int 
                 c.merged_rank[rank] = r;
             }
         }
-        for (int i = n + tid; i < KP; i += MERGE_THREADS) {
+        for (int i = kept + tid; i < KP; i += MERGE_THREADS) {
             c.merged_sse[i] = INF;
             c.merged_rank[i] = ~0ull;
         }
@@ -4294,7 +4435,18 @@ int launch_prefix_features_range(const Ctx &c, int M, uint64_t r0, int64_t n, fl
 int launch_list_search(const Ctx &c, int D, int k, const int32_t *pre, int64_t n, hipStream_t st) {
     const unsigned init_blocks = (unsigned)(((SISSO_MAX_D + 1) * (c.S + 1) + 255) / 256);
     phase_begin(c, SISSO_PHASE_PREPASS, st);
-    hipLaunchKernelGGL(search_init_kernel, dim3(init_blocks), dim3(256), 0, st, c, 2, 1, JBLK, 0);
+    hipLaunchKernelGGL(list_init_kernel, dim3(init_blocks > PRE_BINS / 256 ? init_blocks : PRE_BINS / 256), dim3(256),
+                       0, st, c);
+    if (c.T == 1) {
+        const int64_t np = n < LIST_POOL ? n : LIST_POOL;
+        const dim3 grid((unsigned)((np + 3) / 4));
+        switch (D - 1) {
+            case 1: hipLaunchKernelGGL((list_pool_kernel<1>), grid, dim3(256), 0, st, c, pre, np); break;
+            case 2: hipLaunchKernelGGL((list_pool_kernel<2>), grid, dim3(256), 0, st, c, pre, np); break;
+            case 3: hipLaunchKernelGGL((list_pool_kernel<3>), grid, dim3(256), 0, st, c, pre, np); break;
+            default: return -1;
+        }
+    }
     phase_end(c, SISSO_PHASE_PREPASS, st);
     int64_t wgs = (n + SEARCH_WAVES - 1) / SEARCH_WAVES;
     if (wgs > c.search_wgs) wgs = c.search_wgs;
@@ -4309,7 +4461,7 @@ int launch_list_search(const Ctx &c, int D, int k, const int32_t *pre, int64_t n
     }
     phase_end(c, SISSO_PHASE_SEARCH, st);
     phase_begin(c, SISSO_PHASE_MERGE, st);
-    launch_merge(c, (int)wgs * SEARCH_WAVES, 0, st, 1);
+    launch_merge(c, (int)wgs * SEARCH_WAVES, 1, st, 1);
     phase_end(c, SISSO_PHASE_MERGE, st);
     launch_rescore_final(c, D, k, st);
     return hipGetLastError() == hipSuccess ? 0 : -1;

@@ -1,0 +1,85 @@
+"""Prefix-list search and score selection: the list's pooled bound (repeated,
+malformed and rank-deficient rows, lists longer than the pool takes) against
+the oracle's exhaustive top-k, and the selection's cut over the histogram's
+edges against the sorted scores."""
+import itertools
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+from synth.problems import tiny_problem
+from tests.parity import compare_topk
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T", [1, 2])
+@pytest.mark.parametrize("S,D,kind", [(40, 2, "plain"), (30, 3, "plain"), (96, 3, "plain"), (14, 4, "plain"),
+                                      (30, 3, "repeated"), (14, 4, "repeated"), (30, 3, "dependent"),
+                                      (14, 4, "dependent")])
+def test_list_of_all_prefixes(S, D, kind, T):
+    """Every (D-1)-prefix in the list (S = 96, D = 3: 4560 rows): the result
+    is the exhaustive one, whatever repeats and invalid rows are among them."""
+    import torch
+    from paper_2502_20072_amd import L0Search
+    from paper_2502_20072_amd import _binding as B
+    p = tiny_problem(6100 + S + D + T, S=S, n=45 * T, T=T, D=D, sigma=0.3)
+    if kind == "dependent":
+        for j in range(3, S, 5):
+            p.F[j] = 2.0 * p.F[j - 1]
+        p.F[S - 2] = 0.5
+    pre = np.array(list(itertools.combinations(range(S), D - 1)), dtype=np.int32)
+    rng = np.random.default_rng(S)
+    if kind == "repeated":
+        bad = np.full((5, D - 1), S, dtype=np.int32)
+        bad[1:3] = -1
+        pre = np.concatenate([np.repeat(pre, 3, axis=0), bad])
+    pre = pre[rng.permutation(len(pre))]
+    k = min(25, math.comb(S, D) // 3)
+    s = L0Search(p.F, p.y, p.task_offsets, D_max=D, k_max=k)
+    s.gram()
+    B.sisso_l0_search_list(s.handle, D, k, torch.from_numpy(pre).to("cuda"))
+    s.last_D, s.last_k = D, k
+    gi, gs, _ = s.topk()
+    s.close()
+    oi, os_, _ = oracle.topk(p.F, p.y, D, k, p.task_offsets)
+    compare_topk(p, D, k, gi, gs, oi, os_)
+
+
+@pytest.mark.parametrize("n,K", [(1, 1), (5, 3), (1024, 1024), (5000, 1), (5000, 4999), (100003, 700)])
+@pytest.mark.parametrize("kind", ["normal", "equal", "negative", "nan", "infinite"])
+def test_selection_cut(n, K, kind):
+    """The K largest scores are all selected, and nothing below the K-th by
+    more than 2^8 steps of the key."""
+    import torch
+    from paper_2502_20072_amd import _binding as B
+    rng = np.random.default_rng(n + K)
+    sc = rng.standard_normal(n).astype(np.float32)
+    if kind == "equal":
+        sc[:] = 0.25
+    elif kind == "negative":
+        sc = -np.abs(sc) - 1e-3
+    elif kind == "nan":
+        sc[rng.random(n) < 0.3] = np.nan
+    elif kind == "infinite":
+        sc[rng.random(n) < 0.2] = -np.inf
+        sc[rng.random(n) < 0.1] = np.inf
+    t = torch.from_numpy(sc).to("cuda")
+    out = torch.empty(n, dtype=torch.int64, device="cuda")
+    ws = torch.empty(B.sisso_select_workspace_bytes(), dtype=torch.uint8, device="cuda")
+    cnt = B.sisso_select_top(t, K, out, ws, torch.cuda.current_stream().cuda_stream)
+    got = np.sort(out[:cnt].cpu().numpy())
+    u = sc.view(np.uint32).astype(np.int64)
+    key = np.where(u & 0x80000000, 0xFFFFFFFF - u, u | 0x80000000)
+    key[np.isnan(sc)] = -1
+    order = np.sort(key[key >= 0])[::-1]
+    if len(order) < K:                 # fewer numbers than K: all of them
+        want = np.flatnonzero(key >= 0)
+        assert np.array_equal(got, want)
+        return
+    kth = order[K - 1]
+    assert len(np.unique(got)) == cnt >= K
+    assert set(np.flatnonzero(key >= kth)) <= set(got.tolist())
+    assert key[got].min() >= kth - 256
