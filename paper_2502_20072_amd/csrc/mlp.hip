@@ -20,7 +20,7 @@ constexpr int NP = SISSO_MLP_NPARAM;
 constexpr int OW1 = 0, OB1 = IN * H, OW2 = OB1 + H, OB2 = OW2 + H * H, OW3 = OB2 + H, OB3 = OW3 + H;
 static_assert(OB3 + 1 == NP, "parameter layout");
 constexpr int FB = 16;  // samples per forward / hidden-gradient block
-constexpr int GB = 64;  // samples per weight-gradient block (one partial row each)
+constexpr int GB = 32;  // samples per weight-gradient block (one partial row of 71 KB each)
 
 inline size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -51,124 +51,199 @@ size_t ws_bytes(int64_t n) {
     return al((size_t)n * H * 4) * 4 + al((size_t)n * 4) * 2 + al((size_t)((n + GB - 1) / GB) * (NP + 1) * 4) + 256;
 }
 
+// W2 in LDS, rows of WL floats: a wave's read of 64 consecutive columns of a
+// row (forward) and of one column of 64 rows (backward) both cover the banks.
+constexpr int WL = H + 1;
+__device__ inline void stage_w2(const float *__restrict__ P, float (*w2)[WL]) {
+#pragma unroll 8
+    for (int e = threadIdx.x; e < H * H; e += 256) w2[e / H][e % H] = P[OW2 + e];
+}
+constexpr int HS = FB / 2;  // samples a thread takes
+
 // ------------------------------------------------------------- forward
-// Block: FB samples; thread (s, g) owns hidden units 8g..8g+7 of sample s.
+// Block: FB samples; thread (j, half) owns hidden unit j of HS samples, so one
+// read of W2 serves HS products (and the samples' values, [k][sample], come as
+// wide broadcast reads).  With a thread per sample and eight units, W2 was read
+// from L1 once a product.  Bound by latency at the training batch sizes.
 __global__ __launch_bounds__(256) void mlp_forward_kernel(const float *__restrict__ P, const float *__restrict__ x,
                                                           int64_t n, float *__restrict__ h1g, float *__restrict__ h2g,
-                                                          float *__restrict__ out) {
-    __shared__ float h1s[FB][H];
-    const int tid = threadIdx.x, s = tid >> 4, g = tid & 15;
-    const int64_t i = (int64_t)blockIdx.x * FB + s;
-    const bool live = i < n;
-    float xi[IN];
+                                                          float *__restrict__ o1, float *__restrict__ out) {
+    __shared__ float w2[H][WL];
+    __shared__ __attribute__((aligned(16))) float hs[H][FB + 4];
+    __shared__ float xs[FB][IN];
+    __shared__ float os[4][HS];
+    const int tid = threadIdx.x, j = tid & (H - 1), half = tid >> 7;
+    const int64_t i0 = (int64_t)blockIdx.x * FB;
+    const int cnt = (int)(n - i0 < FB ? n - i0 : FB);
+    if (tid < FB * IN) xs[tid / IN][tid % IN] = tid < cnt * IN ? x[i0 * IN + tid] : 0.f;
+    stage_w2(P, w2);
+    float w1[IN];
 #pragma unroll
-    for (int a = 0; a < IN; ++a) xi[a] = live ? x[i * IN + a] : 0.f;
+    for (int a = 0; a < IN; ++a) w1[a] = P[OW1 + a * H + j];
+    const float b1 = P[OB1 + j], b2 = P[OB2 + j], w3 = P[OW3 + j];
+    __syncthreads();
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int j = 8 * g + u;
-        float z = P[OB1 + j];
+    for (int q = 0; q < HS; ++q) {
+        const int s = half * HS + q;
+        float z = b1;
 #pragma unroll
-        for (int a = 0; a < IN; ++a) z = fmaf(xi[a], P[OW1 + a * H + j], z);
+        for (int a = 0; a < IN; ++a) z = fmaf(xs[s][a], w1[a], z);
         z = fmaxf(z, 0.f);
-        h1s[s][j] = z;
-        if (live) h1g[i * H + j] = z;
+        hs[j][s] = z;
+        if (s < cnt) h1g[(i0 + s) * H + j] = z;
     }
     __syncthreads();
-    float o = 0.f;
+    float z[HS];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int j = 8 * g + u;
-        float z = P[OB2 + j];
-        for (int k = 0; k < H; ++k) z = fmaf(h1s[s][k], P[OW2 + k * H + j], z);
-        z = fmaxf(z, 0.f);
-        if (live) h2g[i * H + j] = z;
-        o = fmaf(z, P[OW3 + j], o);
+    for (int q = 0; q < HS; ++q) z[q] = b2;
+#pragma unroll 4
+    for (int k = 0; k < H; ++k) {
+        const float w = w2[k][j];
+#pragma unroll
+        for (int q = 0; q < HS; ++q) z[q] = fmaf(hs[k][half * HS + q], w, z[q]);
     }
-    for (int m = 8; m >= 1; m >>= 1) o += __shfl_xor(o, m);  // the 16 threads of sample s
-    if (g == 0 && live) out[i] = o + P[OB3];
+#pragma unroll
+    for (int q = 0; q < HS; ++q) {
+        const int s = half * HS + q;
+        const float h2 = fmaxf(z[q], 0.f);
+        if (s < cnt) h2g[(i0 + s) * H + j] = h2;
+        z[q] = h2 * w3;
+        for (int m = 32; m >= 1; m >>= 1) z[q] += __shfl_xor(z[q], m);  // the wave's 64 units
+        if ((tid & 63) == 0) os[tid >> 6][q] = z[q];
+    }
+    __syncthreads();
+    if (tid < cnt) {
+        const int hv = tid / HS, q = tid % HS;
+        const float o = os[2 * hv][q] + os[2 * hv + 1][q] + P[OB3];
+        o1[i0 + tid] = o;
+        out[i0 + tid] = o;
+    }
 }
 
 // ------------------------------------------------------------ backward
-__global__ void mlp_dout_kernel(const float *__restrict__ o, const float *__restrict__ y, int64_t n,
-                                float *__restrict__ dout) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dout[i] = 2.f * (o[i] - y[i]) / (float)n;
-}
-
-// dz2[i][j] = dout[i] W3[j] [h2 > 0]
-__global__ void mlp_dz2_kernel(const float *__restrict__ P, const float *__restrict__ h2, const float *__restrict__ dout,
-                               int64_t n, float *__restrict__ dz2) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n * H) return;
-    const int64_t i = e / H;
-    const int j = (int)(e % H);
-    dz2[e] = h2[e] > 0.f ? dout[i] * P[OW3 + j] : 0.f;
-}
-
-// dz1[i][k] = (sum_j dz2[i][j] W2[k][j]) [h1 > 0]; block of FB samples
-__global__ __launch_bounds__(256) void mlp_dz1_kernel(const float *__restrict__ P, const float *__restrict__ h1,
-                                                      const float *__restrict__ dz2, int64_t n, float *__restrict__ dz1) {
-    __shared__ float d2[FB][H];
-    const int tid = threadIdx.x, s = tid >> 4, g = tid & 15;
-    const int64_t i = (int64_t)blockIdx.x * FB + s;
-    const bool live = i < n;
+// dout[i] = 2 (o - y) / n, dz2[i][j] = dout[i] W3[j] [h2 > 0], dz1[i][k] =
+// (sum_j dz2[i][j] W2[k][j]) [h1 > 0]; block and threads as in the forward
+// pass, thread (k, half).
+__global__ __launch_bounds__(256) void mlp_dz_kernel(const float *__restrict__ P, const float *__restrict__ h1,
+                                                     const float *__restrict__ h2, const float *__restrict__ o,
+                                                     const float *__restrict__ y, int64_t n, float *__restrict__ dout,
+                                                     float *__restrict__ dz2, float *__restrict__ dz1) {
+    __shared__ float w2[H][WL];
+    __shared__ __attribute__((aligned(16))) float ds[H][FB + 4];
+    const int tid = threadIdx.x, k = tid & (H - 1), half = tid >> 7;
+    const int64_t i0 = (int64_t)blockIdx.x * FB;
+    const int cnt = (int)(n - i0 < FB ? n - i0 : FB);
+    stage_w2(P, w2);
+    const float w3 = P[OW3 + k];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) d2[s][8 * g + u] = live ? dz2[i * H + 8 * g + u] : 0.f;
+    for (int q = 0; q < HS; ++q) {
+        const int s = half * HS + q;
+        const int64_t i = i0 + (s < cnt ? s : 0);
+        const float d = 2.f * (o[i] - y[i]) / (float)n;
+        const float z = s < cnt && h2[i * H + k] > 0.f ? d * w3 : 0.f;
+        ds[k][s] = z;
+        if (s < cnt) {
+            dz2[i * H + k] = z;
+            if (k == 0) dout[i] = d;
+        }
+    }
     __syncthreads();
-    if (!live) return;
+    float z[HS];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int k = 8 * g + u;
-        float z = 0.f;
-        for (int j = 0; j < H; ++j) z = fmaf(d2[s][j], P[OW2 + k * H + j], z);
-        dz1[i * H + k] = h1[i * H + k] > 0.f ? z : 0.f;
+    for (int q = 0; q < HS; ++q) z[q] = 0.f;
+#pragma unroll 4
+    for (int j = 0; j < H; ++j) {
+        const float w = w2[k][j];
+#pragma unroll
+        for (int q = 0; q < HS; ++q) z[q] = fmaf(ds[j][half * HS + q], w, z[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < HS; ++q) {
+        const int s = half * HS + q;
+        const int64_t i = i0 + s;
+        if (s < cnt) dz1[i * H + k] = h1[i * H + k] > 0.f ? z[q] : 0.f;
     }
 }
 
 // Per-block partial sums over GB samples (fixed order) of every parameter
-// gradient and of the squared error; row b of part has NP + 1 entries.
+// gradient and of the squared error; row b of part has NP + 1 entries.  The
+// W2 gradient is a product over the samples: thread (a, b) holds an 8 x 8 tile
+// of it in registers, 16 LDS values for 64 products a sample (one value of
+// each matrix per product before: 127 us at n = 4096, now 26; with 16
+// samples a block 17, for twice the partial rows).
 __global__ __launch_bounds__(256) void mlp_grad_partial_kernel(const float *__restrict__ x, const float *__restrict__ h1,
                                                                const float *__restrict__ h2, const float *__restrict__ o,
                                                                const float *__restrict__ y, const float *__restrict__ dz1,
                                                                const float *__restrict__ dz2, const float *__restrict__ dout,
                                                                int64_t n, float *__restrict__ part) {
-    __shared__ float sh1[GB][H + 1], sd2[GB][H + 1];
+    __shared__ __attribute__((aligned(16))) float sh1[GB][H], sd2[GB][H];
+    __shared__ float sx[GB][IN], sdo[GB], se[GB];
     const int tid = threadIdx.x;
     const int64_t i0 = (int64_t)blockIdx.x * GB;
     const int cnt = (int)(n - i0 < GB ? n - i0 : GB);
+#pragma unroll 8
     for (int e = tid; e < GB * H; e += 256) {
         const int s = e / H, k = e % H;
-        sh1[s][k] = s < cnt ? h1[(i0 + s) * H + k] : 0.f;
-        sd2[s][k] = s < cnt ? dz2[(i0 + s) * H + k] : 0.f;
+        sh1[s][k] = s < cnt ? h1[i0 * H + e] : 0.f;
+        sd2[s][k] = s < cnt ? dz2[i0 * H + e] : 0.f;
+    }
+    for (int e = tid; e < GB * IN; e += 256) sx[e / IN][e % IN] = e < cnt * IN ? x[i0 * IN + e] : 0.f;
+    if (tid < GB) {
+        sdo[tid] = tid < cnt ? dout[i0 + tid] : 0.f;
+        se[tid] = tid < cnt ? o[i0 + tid] - y[i0 + tid] : 0.f;
     }
     __syncthreads();
     float *row = part + (int64_t)blockIdx.x * (NP + 1);
-    for (int p = tid; p < NP + 1; p += 256) {
-        float acc = 0.f;
-        if (p < OB1) {  // W1[a][k]: x[a] dz1[k]
-            const int a = p / H, k = p % H;
-            for (int s = 0; s < cnt; ++s) acc = fmaf(x[(i0 + s) * IN + a], dz1[(i0 + s) * H + k], acc);
-        } else if (p < OW2) {  // b1[k]
-            const int k = p - OB1;
-            for (int s = 0; s < cnt; ++s) acc += dz1[(i0 + s) * H + k];
-        } else if (p < OB2) {  // W2[k][j]: h1[k] dz2[j]
-            const int k = (p - OW2) / H, j = (p - OW2) % H;
-            for (int s = 0; s < cnt; ++s) acc = fmaf(sh1[s][k], sd2[s][j], acc);
-        } else if (p < OW3) {  // b2[j]
-            const int j = p - OB2;
-            for (int s = 0; s < cnt; ++s) acc += sd2[s][j];
-        } else if (p < OB3) {  // W3[j]: h2[j] dout
-            const int j = p - OW3;
-            for (int s = 0; s < cnt; ++s) acc = fmaf(h2[(i0 + s) * H + j], dout[i0 + s], acc);
-        } else if (p == OB3) {
-            for (int s = 0; s < cnt; ++s) acc += dout[i0 + s];
-        } else {  // squared error
-            for (int s = 0; s < cnt; ++s) {
-                const float d = o[i0 + s] - y[i0 + s];
-                acc = fmaf(d, d, acc);
-            }
+    {
+        const int a = tid >> 4, b = tid & 15;  // rows 8 a .., columns 4 b .. and 64 + 4 b ..
+        float acc[8][8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int v = 0; v < 8; ++v) acc[u][v] = 0.f;
+        for (int s = 0; s < GB; ++s) {
+            const float4 ha = *reinterpret_cast<const float4 *>(&sh1[s][8 * a]);
+            const float4 hb = *reinterpret_cast<const float4 *>(&sh1[s][8 * a + 4]);
+            const float4 da = *reinterpret_cast<const float4 *>(&sd2[s][4 * b]);
+            const float4 db = *reinterpret_cast<const float4 *>(&sd2[s][64 + 4 * b]);
+            const float hv[8] = {ha.x, ha.y, ha.z, ha.w, hb.x, hb.y, hb.z, hb.w};
+            const float dv[8] = {da.x, da.y, da.z, da.w, db.x, db.y, db.z, db.w};
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int v = 0; v < 8; ++v) acc[u][v] = fmaf(hv[u], dv[v], acc[u][v]);
         }
-        row[p] = acc;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int v = 0; v < 8; ++v)
+                row[OW2 + (8 * a + u) * H + (v < 4 ? 4 * b + v : 60 + 4 * b + v)] = acc[u][v];
+    }
+    // the rest: thread (k, half) takes b1, four of the inputs' W1 (half 0: the
+    // first) and one of b2 and W3
+    {
+        const int k = tid & (H - 1), half = tid >> 7;
+        float w[IN / 2], g1 = 0.f, g2 = 0.f;
+#pragma unroll
+        for (int a = 0; a < IN / 2; ++a) w[a] = 0.f;
+#pragma unroll 4
+        for (int s = 0; s < cnt; ++s) {
+            const float d1 = dz1[(i0 + s) * H + k];
+#pragma unroll
+            for (int a = 0; a < IN / 2; ++a) w[a] = fmaf(sx[s][half * (IN / 2) + a], d1, w[a]);
+            g1 += d1;
+            if (half) g2 = fmaf(h2[(i0 + s) * H + k], sdo[s], g2);
+            else g2 += sd2[s][k];
+        }
+#pragma unroll
+        for (int a = 0; a < IN / 2; ++a) row[OW1 + (half * (IN / 2) + a) * H + k] = w[a];
+        if (!half) row[OB1 + k] = g1;
+        row[(half ? OW3 : OB2) + k] = g2;
+    }
+    if (tid < 2) {
+        float acc = 0.f;
+        for (int s = 0; s < cnt; ++s) acc = tid ? fmaf(se[s], se[s], acc) : acc + sdo[s];
+        row[OB3 + tid] = acc;  // b3, then the squared error
     }
 }
 
@@ -177,6 +252,7 @@ __global__ void mlp_reduce_kernel(const float *__restrict__ part, int nb, int64_
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p > NP) return;
     float acc = 0.f;
+#pragma unroll 16
     for (int b = 0; b < nb; ++b) acc += part[(int64_t)b * (NP + 1) + p];
     if (p < NP) grad[p] = acc;
     else loss[0] = acc / (float)n;
@@ -452,8 +528,7 @@ extern "C" int32_t sisso_mlp_forward(const float *params, const float *x, int64_
     const Ws w = carve(workspace, n);
     hipStream_t st = (hipStream_t)stream;
     hipLaunchKernelGGL(mlp_forward_kernel, dim3((unsigned)((n + FB - 1) / FB)), dim3(256), 0, st, params, x, n, w.h1,
-                       w.h2, w.o);
-    if (hipMemcpyAsync(out, w.o, (size_t)n * 4, hipMemcpyDeviceToDevice, st) != hipSuccess) return SISSO_EDEVICE;
+                       w.h2, w.o, out);
     return launched();
 }
 
@@ -464,14 +539,11 @@ extern "C" int32_t sisso_mlp_backward(const float *params, const float *x, const
     const Ws w = carve(workspace, n);
     hipStream_t st = (hipStream_t)stream;
     const int nb = (int)((n + GB - 1) / GB);
-    hipLaunchKernelGGL(mlp_dout_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, w.o, target, n, w.dout);
-    hipLaunchKernelGGL(mlp_dz2_kernel, dim3((unsigned)((n * H + 255) / 256)), dim3(256), 0, st, params, w.h2, w.dout, n,
-                       w.dz2);
-    hipLaunchKernelGGL(mlp_dz1_kernel, dim3((unsigned)((n + FB - 1) / FB)), dim3(256), 0, st, params, w.h1, w.dz2, n,
-                       w.dz1);
+    hipLaunchKernelGGL(mlp_dz_kernel, dim3((unsigned)((n + FB - 1) / FB)), dim3(256), 0, st, params, w.h1, w.h2, w.o,
+                       target, n, w.dout, w.dz2, w.dz1);
     hipLaunchKernelGGL(mlp_grad_partial_kernel, dim3((unsigned)nb), dim3(256), 0, st, x, w.h1, w.h2, w.o, target, w.dz1,
                        w.dz2, w.dout, n, w.part);
-    hipLaunchKernelGGL(mlp_reduce_kernel, dim3((NP + 1 + 255) / 256), dim3(256), 0, st, w.part, nb, n, grad, loss);
+    hipLaunchKernelGGL(mlp_reduce_kernel, dim3((NP + 1 + 63) / 64), dim3(64), 0, st, w.part, nb, n, grad, loss);
     return launched();
 }
 
