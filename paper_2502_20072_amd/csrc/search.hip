@@ -345,8 +345,8 @@ __device__ void s3_tile_table(const Ctx &c);
 
 __device__ void s4_tile_table(const Ctx &c);
 
-// s3: 0 = work-item table of the general kernel, 4 = the D = 4 record-table
-// tiles, other = the D = 3 record-table tiles
+// s3: 0 = work-item table of the general kernel, 2 = none (D = 2, one task), 4 =
+// the D = 4 record-table items, other = the D = 3 record-table items
 __device__ void search_init_body(const Ctx &c, int64_t e, bool leader, int D, int R, int JB, int s3) {
     if (e < (int64_t)(SISSO_MAX_D + 1) * (c.S + 1)) {
         const int r = (int)(e / (c.S + 1));
@@ -361,6 +361,11 @@ __device__ void search_init_body(const Ctx &c, int64_t e, bool leader, int D, in
         c.flags[FLAG_BATCHQ] = 0;
         c.flags[FLAG_NLISTS] = 0;
         c.stats[1] = 0;
+        if (s3 == 2) {
+            const int64_t q = (c.S + 63) / 64;
+            c.stats[1] = (uint64_t)(q * (q + 1) / 2);
+            return;
+        }
         if (s3 == 4) {
             s4_tile_table(c);
             return;
@@ -3092,6 +3097,78 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S4E_WPE))) 
     list_store(c.list_sse + gw * KP, c.list_rank + gw * KP, Ls, Lr, KP);
 }
 
+// ------------------------------------------------------- D = 2, one task
+// A tuple (j, k) costs one element of G and six FP64 instructions: z = b_k -
+// g b_j, d = 1 - g^2, pass iff z^2 >= (p_j - theta) d, p_j = c - b_j^2 (the
+// arithmetic of search_kernel).  A workgroup takes one 64 x 64 tile of G at a
+// time, a wave 16 of its rows, a lane a column: the upper triangle is read
+// once, in whole lines, 8 KB in flight a wave.  Bound by HBM once G leaves
+// the caches (10 GB at S = 50,000: 2570 us, now 1890), by latency below (S = 200:
+// 42 us, now 13; S = 4096: 171, now 21): search_kernel has S / 64 work items at
+// D = 2, each a row
+// block against all columns, and a quarter of its registers in use.
+constexpr int S2_ROWS = 16;
+__global__ __launch_bounds__(256) void search2_kernel(Ctx c, SearchArgs a, int64_t ntiles) {
+    extern __shared__ double smem[];
+    const int KP = a.KP;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double *Ls = smem + (size_t)wave * KP * 2;
+    uint64_t *Lr = reinterpret_cast<uint64_t *>(Ls + KP);
+    for (int m = lane; m < KP; m += 64) {
+        Ls[m] = INF;
+        Lr[m] = ~0ull;
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_wave_barrier();
+    const int64_t S = c.S, nt = c.Gnt;
+    const double theta0 = theta0_of(c), ctot = c.cyy[0];
+    double theta_pub = INF;
+    unsigned offered = 0;
+    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        int64_t ta, tb;  // tile (ta, tb), ta <= tb
+        s4_pair(t, ta, tb);
+        ta = uni(ta);
+        tb = uni(tb);
+        const int64_t j0 = ta * 64 + wave * S2_ROWS, k = tb * 64 + lane;
+        if (j0 >= S) continue;
+        const double *__restrict__ G = c.G + ((ta * nt + tb) << 12) + wave * S2_ROWS * 64 + lane;
+        double g[S2_ROWS];
+#pragma unroll
+        for (int x = 0; x < S2_ROWS; ++x) g[x] = G[x * 64];
+        const int64_t kk = k < S ? k : S - 1;
+        const bool kv = k < S && c.inv_s[kk] > 0.0;
+        const double bk = c.bhat[kk];
+        const double th = fmin(fmin(theta0, theta_load(c.theta_bits)), Ls[KP - 1]);
+        const double theta_f = th < INF ? th * (1.0 + THETA_SLACK) : INF;
+#pragma unroll
+        for (int x = 0; x < S2_ROWS; ++x) {
+            const int64_t j = j0 + x, jj = j < S ? j : S - 1;
+            const double bj = cptr(c.bhat)[jj];
+            const bool jv = j < S && cptr(c.inv_s)[jj] > 0.0;
+            const double p = ctot - bj * bj;
+            const double d = 1.0 - g[x] * g[x], z = fma(-bj, g[x], bk);
+            if (!__ballot(jv && kv && k > j && z * z >= (p - theta_f) * d)) continue;
+            const int32_t tup[2] = {(int32_t)j, (int32_t)k};
+            const double es = (d > RANK_EPS) ? p - (z * z) / d : INF;
+            bool take = jv && kv && k > j && z * z >= (p - theta_f) * d && es <= fmin(theta_f, Ls[KP - 1]);
+            if (take && a.ranged) {
+                const uint64_t lr = lex_rank(BinomTab{c.btab, c.S}, c.S, 2, tup);
+                if (lr < a.r0 || lr >= a.r1) take = false;
+            }
+            list_insert_lanes(Ls, Lr, KP, take, take ? pack_tuple(tup, 2) : 0, es, offered);
+        }
+        const double tw = Ls[KP - 1];
+        if (tw < theta_pub) {
+            theta_pub = tw;
+            if (lane == 0) theta_publish(c.theta_bits, tw);
+        }
+    }
+    if (lane == 0 && offered) atomicAdd(c.cand_counter, offered);
+    const int64_t gw = (int64_t)blockIdx.x * SEARCH_WAVES + wave;
+    list_store(c.list_sse + gw * KP, c.list_rank + gw * KP, Ls, Lr, KP);
+}
+
 // D = 1: every feature is a tuple; SSE = sum_t (c_t - b_t^2) over full-rank columns.
 __global__ __launch_bounds__(256) void search_d1_kernel(Ctx c, SearchArgs a) {
     extern __shared__ double smem[];
@@ -4249,6 +4326,9 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
         // one task, D = 4: the record table of group pairs (sized at create
         // only while it stays within S4_TABLE_MAX)
         const bool s4 = D == 4 && !MT && !c.fp32 && c.rec4 != nullptr;
+        const bool s2 = D == 2 && !MT && !c.fp32;
+        const int64_t ntiles2 = ((c.S + 63) / 64) * ((c.S + 63) / 64 + 1) / 2;
+        const int wgs = s2 && ntiles2 < c.search_wgs ? (int)ntiles2 : c.search_wgs;
         if (s4) {
             const int64_t nt = std::max((int64_t)(SISSO_MAX_D + 1) * (c.S + 1), s4_pairs_below(s4_groups(c.S)));
             hipLaunchKernelGGL(s4_init_kernel, dim3((unsigned)((nt + 63) / 64)), dim3(64), 0, st, c);
@@ -4263,7 +4343,8 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
             // one more column: its first workgroup runs the pre-pass selection
             hipLaunchKernelGGL(rec3_kernel, dim3((unsigned)(bx + 1), (unsigned)ngr, 2), dim3(PRE_WG), 0, st, c, c.rec3);
         } else {
-            hipLaunchKernelGGL(search_init_kernel, dim3(init_blocks), dim3(256), 0, st, c, D, a.R, a.JB, 0);
+            hipLaunchKernelGGL(search_init_kernel, dim3(init_blocks), dim3(256), 0, st, c, D, a.R, a.JB,
+                               s2 ? 2 : 0);
         }
         switch (D) {
             case 2: launch_prepass<2>(c, sc, st); break;
@@ -4285,7 +4366,9 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
             glo = (int)(first_index(c.S, D, sc.r0) / S3_NR);
             ghi = (int)(first_index(c.S, D, sc.r1 > sc.r0 ? sc.r1 - 1 : sc.r0) / S3_NR);
         }
-        if (s4) {
+        if (s2) {
+            hipLaunchKernelGGL(search2_kernel, dim3(wgs), dim3(SEARCH_WG), lds_lists, st, c, a, ntiles2);
+        } else if (s4) {
             const int run = bound_run(bound_units<S4Pairs>(c.S));
             const uint64_t n = s4_items_host(c.S), pass = S4_PASS / run;
             const uint32_t nseg = (uint32_t)(c.search_wgs < BU_WGS ? c.search_wgs : BU_WGS);
@@ -4325,7 +4408,7 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
         }
         phase_end(c, SISSO_PHASE_SEARCH, st);
         phase_begin(c, SISSO_PHASE_MERGE, st);
-        launch_merge(c, c.search_wgs * SEARCH_WAVES, 1, st);
+        launch_merge(c, wgs * SEARCH_WAVES, 1, st);
         phase_end(c, SISSO_PHASE_MERGE, st);
     }
     launch_rescore_final(c, D, sc.k, st);
