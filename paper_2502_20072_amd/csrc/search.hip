@@ -4401,7 +4401,11 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
             }
         }
         else switch (D) {
-            case 2: MT ? launch_one<2, true>(c, a, lds, st) : launch_one<2, false>(c, a, lds, st); break;
+            // (one task, D = 2 comes here in the FP32 solve form only)
+            case 2:
+                if (MT) launch_one<2, true>(c, a, lds, st);
+                else hipLaunchKernelGGL((search_kernel<2, false, float>), dim3(c.search_wgs), dim3(SEARCH_WG), lds, st, c, a);
+                break;
             case 3: MT ? launch_one<3, true>(c, a, lds, st) : launch_one<3, false>(c, a, lds, st); break;
             case 4: MT ? launch_one<4, true>(c, a, lds, st) : launch_one<4, false>(c, a, lds, st); break;
             default: return -1;
