@@ -40,38 +40,44 @@ def search_flop_per_tuple(D: int, T: int) -> float:
     return float(ALG_FLOP[D] * T)
 
 
-def issued_flop_per_tuple(D: int, T: int) -> float:
-    """FP64 operations the search kernel actually issues per tuple.
+def bounded(D: int, T: int) -> int:
+    """Tuples that the FP64 search's superset bound tests together: 4 at D = 3
+    (a group of four first indices; several tasks on the task of largest
+    |y_t - mean|^2), 16 at D = 4 with one task (two groups of four); 1 where
+    every tuple is tested itself."""
+    return 4 if D == 3 else 16 if D == 4 and T == 1 else 1
 
-    Per task, with the prefix's Cholesky row and the k-dependent part of the
-    sub-prefix solve hoisted out of the sweep: u = g - v.w (D-2 FMA),
-    d = d' - alpha u^2 (1 MUL + 1 FMA), zeta = zeta' - zs u (1 FMA), and the
-    division-free test zeta^2 >= pi d (2 MUL).  FMA counts 2.
-    Single task: 2(D-2) + 3 + 2 + 2.
+
+def issued_flop_per_tuple(D: int, T: int, f32: bool = False) -> float:
+    """FP64 operations the search issues per tuple (FMA counts 2).
+
+    With a superset bound over K = 4 (D = 3) or 8 (D = 4) features: u = g - v.w
+    (K FMA), and the test as a polynomial in u (3 FMA, 1 MUL), once for all the
+    tuples it covers; the few that it lets through are not counted.  Otherwise,
+    with the prefix's Cholesky row and the k-dependent part of the sub-prefix
+    solve hoisted out of the sweep: u = g - v.w (D-2 FMA), d = d' - alpha u^2 (1
+    MUL + 1 FMA), zeta = zeta' - zs u (1 FMA), and the division-free test
+    zeta^2 >= pi d (2 MUL): 2(D-2) + 3 + 2 + 2 (one less at D = 2, alpha = 1).
     """
-    per_task = 2 * (D - 2) + 3 + 2 + 2
-    if T == 1 or D == 3:
-        # D = 3 with several tasks sweeps with the one-task test on the task of
-        # largest |y_t - mean|^2 (its SSE bounds the sum from below); only the
-        # few tuples it passes are scored over every task
-        return float(per_task)
+    if bounded(D, T) > 1 and not f32:
+        return (2 * 4 * (D - 2) + 7) / bounded(D, T)
+    if T == 1:
+        return float(2 * (D - 2) + 3 + 2 + 2 - (D == 2 and not f32))
     # many tasks: the test becomes p - zeta^2 r with r a Newton-refined
     # reciprocal (1 RCP + 2 FMA + 1 MUL + 1 FMA) and a sum over tasks (1 ADD)
     return float(T * (2 * (D - 2) + 3 + 2 + 1 + 1 + 2 * 2 + 2 + 1))
 
 
 def performed_flop(D: int, T: int, ntup: int) -> tuple:
-    """(FLOP, pruned) of the work one search performs.
+    """(FLOP, pruned) of the work one FP64 search performs.
 
-    One task, or several tasks at D != 3: every tuple is solved in every task,
-    ALG_FLOP[D] * T per tuple.  Several tasks at D = 3: the sweep solves every
-    tuple in one task only (its SSE is a lower bound of the sum over tasks, so
-    the tuples it rejects are pruned exactly) and only the survivors are solved
-    in every task; the work performed is the one-task sweep, ALG_FLOP[3] per
-    tuple, and the few survivors' solves are not counted.
+    Where a superset's fit bounds several tuples together (its SSE is a lower
+    bound of theirs, so the tuples it rejects are pruned exactly), the work is
+    that of the bounds, and the few survivors' solves are not counted; else
+    every tuple is solved in every task, ALG_FLOP[D] * T per tuple.
     """
-    if T > 1 and D == 3:
-        return float(ALG_FLOP[3]) * ntup, True
+    if bounded(D, T) > 1:
+        return issued_flop_per_tuple(D, T) * ntup, True
     return search_flop_per_tuple(D, T) * ntup, False
 
 
@@ -97,10 +103,10 @@ def measured_traffic(kernel: str, workload: str):
     return float(fields["bytes per launch"])
 
 
-# MFMA products per Gram K-step: FP64 one, the BF16 form's three slices six
-# (s + u <= 2), the FP16 form's two slices three
-GRAM_PRODUCTS = {"fp64": 1, "bf16": 6, "fp16": 3, "fp32": 1}
-MFMA_PEAK = {"fp64": 78.6e12, "bf16": 2.5e15, "fp16": 2.5e15, "fp32": 78.6e12}
+# MFMA products per Gram K-step: FP64 fifteen residues in INT8, the BF16 form's
+# three slices six (s + u <= 2), the FP16 form's two slices three
+GRAM_PRODUCTS = {"fp64": 15, "bf16": 6, "fp16": 3, "fp32": 15}
+MFMA_PEAK = {"fp64": 5.0e15, "bf16": 2.5e15, "fp16": 2.5e15, "fp32": 5.0e15}
 
 
 def gram_roofline(p, name: str, prec: int, gram_ms: float) -> dict:
@@ -112,13 +118,13 @@ def gram_roofline(p, name: str, prec: int, gram_ms: float) -> dict:
     form = {B.SISSO_PREC_FP64: "fp64", B.SISSO_PREC_BF16_COMP: "bf16", B.SISSO_PREC_FP16_COMP: "fp16",
             B.SISSO_PREC_FP32_SOLVE: "fp32"}[prec]
     alg = float(p.n) * (p.S * (p.S + 1) + 2 * p.S)
-    kern = "gram_lp_kernel" if form in ("bf16", "fp16") else "gram_kernel"
+    kern = "gram_lp_kernel" if form in ("bf16", "fp16") else "gram_mod_kernel"
     achieved = alg * GRAM_PRODUCTS[form] / (gram_ms * 1e-3)
-    return dict(bound="mfma", kernel=kern, achieved=achieved / 1e12, peak=MFMA_PEAK[form] / 1e12, unit="TFLOP/s",
-                frac=achieved / MFMA_PEAK[form], traffic=measured_traffic(kern, name), algorithmic_flop=alg,
+    return dict(bound="mfma", kernel=kern, achieved=achieved / 1e12, peak=MFMA_PEAK[form] / 1e12,
+                unit="TFLOP/s" if form in ("bf16", "fp16") else "TOP/s", frac=achieved / MFMA_PEAK[form], traffic=measured_traffic(kern, name), algorithmic_flop=alg,
                 mfma_products=GRAM_PRODUCTS[form], gram_ms=gram_ms,
-                note="phase time: the Gram launch and its finishing pass (the partial sums summed, "
-                     "scaled and tiled)")
+                note="phase time: the Gram launches (FP64: residues and their products) and the "
+                     "finishing pass")
 
 
 def cpu_baseline(p, D: int, k: int, target_s: float = 15.0):
@@ -324,19 +330,19 @@ def bench_exhaustive(args, p, name: str, prec: int, steps: int, warmup: int, sea
     # sweep, no filter task) solves every tuple in every task
     flop, pruned = (ALG_FLOP[D] * p.T * ntup, False) if f32 else performed_flop(D, p.T, ntup)
     achieved = flop / search_s
-    kname = "search_kernel" if f32 else {3: "search3_kernel",
+    kname = "search_kernel" if f32 else {2: "search2_kernel" if p.T == 1 else "search_kernel", 3: "search3_kernel",
                                          4: "search4_kernel" if p.T == 1 else "search_kernel"}.get(D, "search_kernel")
     roofline = dict(bound="alu", kernel=kname, achieved=achieved / 1e12, peak=FP64_PEAK / 1e12,
                     unit="TFLOP/s", frac=achieved / FP64_PEAK, traffic=measured_traffic(kname, name),
-                    flop_per_tuple=flop / ntup, issued_flop_per_tuple=issued_flop_per_tuple(D, p.T),
+                    flop_per_tuple=flop / ntup, issued_flop_per_tuple=issued_flop_per_tuple(D, p.T, f32),
                     search_ms=acc["search"], search_tuples_per_s=ntup / search_s)
     if f32:
         roofline["note"] = ("FP32 solves without packed FP32 instructions (the build disables them): "
                             "the vector FP32 rate equals the FP64 one, 256 CU x 64 lanes x 2 x 2.4 GHz")
     if pruned:
-        roofline["pruned"] = ("several tasks at D=3: the sweep solves every tuple in the task of largest "
-                              "|y_t - mean|^2 only (an exact lower bound of the sum); the survivors' "
-                              "all-task solves are not counted")
+        roofline["pruned"] = (f"the fit on a superset bounds {bounded(D, p.T)} tuples together"
+                              + (" in the task of largest |y_t - mean|^2" if p.T > 1 else "")
+                              + "; the work counted is the bounds', the time includes the survivors' scoring")
     search_roofline = None
     if acc["gram"] > acc["search"]:
         # the Gram dominates the step: its roofline is the line's, the

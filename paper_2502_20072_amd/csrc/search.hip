@@ -13,7 +13,11 @@
 // rank test.  For a single task the comparison SSE <= theta needs no
 // division: zeta^2 >= (p_P - theta) d.
 //
-// Work decomposition.  A tuple is (P', j, k): a sub-prefix P' of D-2
+// D = 2 with one task, D = 3 and D = 4 with one task run kernels of their own
+// (search2_kernel; search3_kernel and search4_kernel, which bound several
+// tuples by the fit on a superset); search_kernel serves the rest.
+//
+// Work decomposition of search_kernel.  A tuple is (P', j, k): a sub-prefix P' of D-2
 // indices, the (D-1)-th index j and the last index k.  A work item is a
 // block of 64 consecutive j values together with a group of sub-prefixes
 // (SUBP of them for one task, one when lanes are split over tasks).  The
@@ -21,8 +25,8 @@
 // parallel (one thread each) into LDS; then each wave sweeps chunks of 64
 // consecutive k (one per lane), keeps the k-dependent part of the
 // sub-prefix solve in registers, and for every j loads one G[j][k] that
-// serves all sub-prefixes of the item.  Items are handed out through an
-// atomic counter in order of increasing j, i.e. largest first; sub-prefix
+// serves all sub-prefixes of the item.  Items are dealt round-robin in order
+// of increasing j, i.e. largest first; sub-prefix
 // groups are addressed by colexicographic rank (combinatorial number
 // system), so item -> (j-block, sub-prefixes) is a bisection, not a table.
 //
@@ -2927,7 +2931,7 @@ __device__ __forceinline__ void s4_candidates(const Ctx &c, const SearchArgs &a,
     }
 }
 
-// A dense item: all tuples of S4_DR rows of a tile with second index i2 and
+// A dense item: all tuples of S4_DR rows of a unit with second index i2 and
 // first index in group g1.  The rows' records are built in LDS and read by all
 // lanes at one address.
 __device__ __forceinline__ void s4_dense(const Ctx &c, const SearchArgs &a, uint64_t item, double *Ls, uint64_t *Lr,
@@ -4237,7 +4241,7 @@ static void launch_merge(const Ctx &c, int nlists, int use_pre, hipStream_t st, 
 }
 
 // The one-task D = 3 record-table path applies (it also needs the table in
-// the workspace and fewer than 2^31 tiles).
+// the workspace and fewer than 2^31 items).
 bool s3_batchable(const Ctx &c, int D) {
     return D == 3 && c.T == 1 && !c.fp32 && c.rec3 != nullptr && s3_items_host(c.S) < (1ull << 31);
 }

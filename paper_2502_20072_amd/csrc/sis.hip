@@ -173,6 +173,10 @@ __host__ __device__ constexpr int nr_pad(int nres) {
 // A full tile's columns in registers: lane l holds samples s, s + 1, s = 2 (l &
 // 7), of slots (l >> 3) + 8 q.  (Columns start at any multiple of 8 bytes.)
 typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+// Most residuals that are loaded a tile ahead (8: 957 -> 625 us for two passes
+// over 79,800 pairs, n = 1500, 5 residuals; ten would cost registers, one
+// gains nothing).
+constexpr int SC_AHEAD = 8;
 constexpr int SC_Q = 8;
 template <int OP>
 struct ScreenCols {
@@ -346,13 +350,24 @@ __device__ inline void screen_pass(const double *__restrict__ X, const int64_t *
     int64_t s0 = r0;
     if (!is_binary(OP) || ua >= 0) {
         ScreenCols<OP> next(X, ca, cb, ua, r0, lane);
-        if (r1 - r0 >= SC_TS) next.fetch(r1 - r0 >= 2 * SC_TS ? SC_TS : 0);
+        constexpr bool AHEAD = NR > 1 && NR <= SC_AHEAD;
+        double rn[NR];
+        if (r1 - r0 >= SC_TS) {
+            next.fetch(r1 - r0 >= 2 * SC_TS ? SC_TS : 0);
+            if (AHEAD) residuals(rn, r0);
+        }
         for (; r1 - s0 >= SC_TS; s0 += SC_TS) {
             double rv[NR];
-            residuals(rv, s0);
+            if (AHEAD) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) rv[r] = rn[r];
+            } else {
+                residuals(rv, s0);
+            }
             next.store(tile, lane);
             // (a task's last tile is fetched again rather than passed)
             next.fetch(r1 - s0 >= 3 * SC_TS ? SC_TS : 0);
+            if (AHEAD) residuals(rn, r1 - s0 >= 2 * SC_TS ? s0 + SC_TS : s0);
             wave_lds_sync();
             if (FIRST && s0 == r0) K = tile[lane * SC_LD];
             screen_tile<NR, RULES, true>(tile, lane, rv, SC_TS, K, A, vmin, vmax);
@@ -371,11 +386,8 @@ __device__ inline void screen_pass(const double *__restrict__ X, const int64_t *
     }
 }
 
-#ifndef SC_WPE
-#define SC_WPE 3                      // waves per SIMD the register budget is sized for
-#endif
 template <int OP, int NR>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SC_WPE))) void screen_kernel(const double *__restrict__ X, int64_t n, int64_t Mc,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void screen_kernel(const double *__restrict__ X, int64_t n, int64_t Mc,
                                                      const int32_t *__restrict__ pairs, int64_t P,
                                                      const int64_t *__restrict__ off, int T,
                                                      const double *__restrict__ Rc, int64_t ldr,
