@@ -222,12 +222,15 @@ struct ScreenCols {
 
 // The tile of samples [s0, s0 + cnt) without that (a task's last samples, or
 // a group with several first children).
-template <int OP>
+template <int OP, int NR>
 __device__ inline void screen_load(const double *__restrict__ X, const int64_t *__restrict__ ca,
                                    const int64_t *__restrict__ cb, int64_t s0, int cnt, double *tile, int lane) {
     const int s = lane & (SC_TS - 1);
     if (s >= cnt) return;
-#pragma unroll 4
+    // all loads in flight where the registers allow it (one residual: five
+    // passes over 79,800 pairs, n = 1500: 1371 -> 1093 us)
+    constexpr int UN = NR == 1 ? 16 : 4;
+#pragma unroll UN
     for (int q = 0; q < 16; ++q) {
         const int slot = (lane >> 4) + 4 * q;
         const double a = X[ca[slot] + s0 + s];
@@ -378,7 +381,7 @@ __device__ inline void screen_pass(const double *__restrict__ X, const int64_t *
         const int cnt = (int)(r1 - s0 < SC_TS ? r1 - s0 : SC_TS);
         double rv[NR];
         residuals(rv, s0);
-        screen_load<OP>(X, ca, cb, s0, cnt, tile, lane);
+        screen_load<OP, NR>(X, ca, cb, s0, cnt, tile, lane);
         wave_lds_sync();
         if (FIRST && s0 == r0) K = tile[lane * SC_LD];
         screen_tile<NR, RULES, false>(tile, lane, rv, cnt, K, A, vmin, vmax);
