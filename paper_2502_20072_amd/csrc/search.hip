@@ -1449,13 +1449,33 @@ __host__ __device__ inline int64_t s3_rows(int64_t S) {
 // G[g, x].  Columns x = 4 g .. S - 1, field by field (columns consecutive):
 //   v0..v3, alpha = 1/d, zs = e/d, p, d, e with e = b_x - v.z, d = 1 - |v|^2,
 //   z = R^-T b_g, p = c - |z|^2 - e^2/d (the SSE of the group and x).
-// A tuple's j reads alpha, zs, p, its k reads d and e.  The bound is computed
-// with group pivots above S3_TAU only and compared with slacks (S3_DSLACK on
-// d, S3_TSLACK c on theta) above the rounding that leaves: p = 0 marks a j
-// whose group or column is too close to dependent (it always passes), p =
-// S3_NEVER one without a tuple (a constant column), d = S3_NEVER a constant k.
-// A column of the group itself leaves the group alone (v = 0, alpha = 0).
-constexpr double S3_TAU = 1e-5, S3_DSLACK = 1e-7, S3_TSLACK = 1e-7, S3_ESLACK = 1e-13, S3_NEVER = 1e300;
+// A tuple's j reads alpha, zs, p, its k reads d and e.  p = 0 marks a j whose
+// group or column is too close to dependent for the bound (it always passes), p
+// = S3_NEVER one without a tuple (a constant column), d = S3_NEVER a constant
+// k.  A column of the group itself leaves the group alone (v = 0, alpha = 0).
+//
+// The bound is compared with a slack, S3_SLACK on d and S3_SLACK c on theta,
+// so it has to be known to that.  A factor of K columns is the exact one of a G
+// changed by at most (K + 1) 2^-53 per entry (Cholesky's backward error; as
+// much again is allowed for the explicit inverse), which changes d, zeta /
+// sqrt(c) and p / c of the pair (j, k) by at most
+//   e = 2 K (K + 1) 2^-53 |R^-1|^2 (1 + 1 / sqrt(d_j))^2
+// (|.| the Frobenius norm, d_j the pivot of j).  With a = S3_SLACK - e and P =
+// (p - theta) / c, a fit at or below theta has zeta^2 >= P d c, and it passes if
+// (sqrt(P d) - e)^2 >= (P - a) (d - a), which holds for e <= S3_SLACK / 2.
+// bound_tau gives the smallest d_j with that.  (Pivots above S3_TAU alone are
+// not enough: in a group of columns each close to the span of the ones before
+// it |R^-1|^2 reaches 1e15, and the fit came out up to c too high.)
+constexpr double S3_TAU = 1e-5;       // smallest pivot of a group
+constexpr double S3_SLACK = 1e-6;
+constexpr double S3_ESLACK = 1e-13;   // slack above the rounding of the test itself, times c
+constexpr double S3_NEVER = 1e300;
+// smallest pivot of a column j that is tried with a group of K columns, norm = |R^-1|^2 (above 1: none)
+template <int K>
+__device__ inline double bound_tau(double norm) {
+    const double t = sqrt(S3_SLACK / (4.0 * K * (K + 1) * 0x1p-53 * norm)) - 1.0;
+    return t >= 1.0 ? fmax(S3_TAU, 1.0 / (t * t)) : 2.0;
+}
 // fields of a table over K features
 enum { BF_AL, BF_ZS, BF_P, BF_D, BF_E, BF_N };  // after the K entries of v
 constexpr int S3_FIELDS = S3_NR + BF_N;
@@ -1470,7 +1490,7 @@ __device__ void s3_group_record(const Ctx &c, int64_t g, int64_t x) {
     const int ts = c.tstar[0], TP = c.TP;
     const double *__restrict__ G1 = c.G1;
     // the group's factor (the same for every thread of the group)
-    double Li[S3_NR][S3_NR], L[S3_NR][S3_NR], z[S3_NR], pg = c.cyy[ts];
+    double Li[S3_NR][S3_NR], L[S3_NR][S3_NR], z[S3_NR], pg = c.cyy[ts], norm = 0.0;
     bool bad = false;
 #pragma unroll
     for (int m = 0; m < S3_NR; ++m) {
@@ -1494,12 +1514,16 @@ __device__ void s3_group_record(const Ctx &c, int64_t g, int64_t x) {
 #pragma unroll
             for (int q = l; q < m; ++q) s += L[m][q] * Li[q][l];
             Li[m][l] = -Li[m][m] * s;
+            norm += Li[m][l] * Li[m][l];
             zz += Li[m][l] * c.bhat[(S3_NR * g + l < S ? S3_NR * g + l : 0) * TP + ts];
         }
+        norm += Li[m][m] * Li[m][m];
         if (live) zz += Li[m][m] * c.bhat[i * TP + ts];
         z[m] = zz;
         pg -= zz * zz;
     }
+    const double tau = bound_tau<S3_NR>(norm);
+    bad |= tau > 1.0;
     double v[S3_NR] = {0.0, 0.0, 0.0, 0.0}, al = 0.0, zs = 0.0, p = pg, d = 0.0, e = 0.0;
     if (!(G1[gidx(j, j, nt, 1, 0)] > 0.5)) {
         p = d = S3_NEVER;
@@ -1517,7 +1541,7 @@ __device__ void s3_group_record(const Ctx &c, int64_t g, int64_t x) {
             d -= s * s;
             e -= s * z[m];
         }
-        if (d > S3_TAU) {
+        if (d > tau) {
             al = 1.0 / d;
             zs = e * al;
             p = pg - e * zs;
@@ -2111,7 +2135,7 @@ __device__ __forceinline__ void bound_unit(const double *__restrict__ s_g, int64
 #pragma unroll
         for (int s = 0; s < NK; ++s) w[cb][s] = at(4 * s + h, k);
         const double e = at(K + BF_E, k);
-        dq[cb] = at(K + BF_D, k) - S3_DSLACK;
+        dq[cb] = at(K + BF_D, k) - S3_SLACK;
         z2[cb] = -2.0 * e;
         zz[cb] = e * e;
     }
@@ -2242,7 +2266,7 @@ __device__ __forceinline__ void s3_bound(const CtxT &c, const double *__restrict
     if (!skip.skip() && th < INF) {
         const double ctot = c.cyy[c.tstar[0]];
         bound_unit<1>(s_g, S, tl, recg + s3g_off(S, g) * S3_FIELDS, S3_NR * g, S - S3_NR * g, lo,
-                      th * (1.0 + THETA_SLACK) + S3_TSLACK * ctot, -S3_ESLACK * ctot, par, mine, lanes);
+                      th * (1.0 + THETA_SLACK) + S3_SLACK * ctot, -S3_ESLACK * ctot, par, mine, lanes);
         skip.result(lanes > limit);
         rows = lanes > limit ? bound_rows(mine) : 0;
     } else {
@@ -2792,7 +2816,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S4_WPE))) v
     if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
     const int64_t S = c.S;
     const double th = fmin(theta0_of(c), theta_load(c.theta_bits)), ctot = c.cyy[0];
-    const double theta_s = th * (1.0 + THETA_SLACK) + S3_TSLACK * ctot, neg = -S3_ESLACK * ctot;
+    const double theta_s = th * (1.0 + THETA_SLACK) + S3_SLACK * ctot, neg = -S3_ESLACK * ctot;
     S3Skip skip;
     for (uint64_t t = bound_first(t0); t < t1; t += gridDim.x) {
         S3Tile tl;
