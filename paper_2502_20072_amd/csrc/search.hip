@@ -2649,8 +2649,7 @@ constexpr int S4_NR = 4;              // indices per group
 constexpr int S4_DR = 16;             // rows of a dense item (of a unit taken whole)
 constexpr int S4_ITEMS = S4_NR * S3_JR / S4_DR;  // dense items of a unit
 constexpr int S4_FIELDS = 2 * S4_NR + BF_N;
-constexpr int S4_FAC = 48;            // doubles per factor: R^-1 (36), z (8), SSE of the pair, dependent columns
-constexpr double S4_NORM = 1e6;       // largest squared Frobenius norm of R^-1 the slacks cover
+constexpr int S4_FAC = 48;            // doubles per factor: R^-1 (36), z (8), SSE of the pair, bound_tau
 // A large search runs in passes of S4_PASS units (bound, then scoring), which
 // bounds the candidate pool at 1.1 GB.
 constexpr uint64_t S4_PASS = 1ull << 18;
@@ -2682,8 +2681,8 @@ uint64_t s4_items_host(int64_t S) { return bound_items<S4Pairs>(S, bound_run(bou
 size_t s4_pool_units(int64_t S) { return pool_units(s4_items_host(S), bound_run(bound_units<S4Pairs>(S)), S4_PASS); }
 
 // The factor of pair e = (g1, g2): of its live columns in index order, G =
-// R^T R, {R^-1 by rows, z = R^-T b, c - |z|^2, and whether a column is too close to
-// dependent for the bound}.  The columns past S, the constant ones and, with
+// R^T R, {R^-1 by rows, z = R^-T b, c - |z|^2, and the smallest pivot of a j
+// that is tried with it (above 1: none)}.  The columns past S, the constant ones and, with
 // g1 = g2, the second four have zero rows.
 __device__ void s4_factor(const Ctx &c, int64_t e) {
     int64_t g1, g2;
@@ -2733,7 +2732,7 @@ __device__ void s4_factor(const Ctx &c, int64_t e) {
         pg -= zz * zz;
     }
     f[44] = pg;
-    f[45] = bad || !(norm <= S4_NORM) ? 1.0 : 0.0;
+    f[45] = bad ? 2.0 : bound_tau<N>(norm);
     f[46] = f[47] = 0.0;
 }
 
@@ -2765,7 +2764,7 @@ __global__ __launch_bounds__(256) void rec4_kernel(Ctx c) {
         }
         if (!(c.inv_s[j] > 0.0)) {
             p = d = S3_NEVER;
-        } else if (f[45] != 0.0) {
+        } else if (f[45] > 1.0) {
             p = 0.0;
         } else if (j >= S4_NR * (g2 + 1)) {  // (a column of g2 itself leaves the pair alone)
             d = 1.0;
@@ -2779,7 +2778,7 @@ __global__ __launch_bounds__(256) void rec4_kernel(Ctx c) {
                 d -= s * s;
                 e -= s * f[36 + m];
             }
-            if (d > S3_TAU) {
+            if (d > f[45]) {
                 al = 1.0 / d;
                 zs = e * al;
                 p = p - e * zs;
@@ -2833,7 +2832,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S4_WPE))) v
             if (g1 < glo || g1 > ghi) continue;
             unsigned long long mine = 0;
             int lanes = 1 << 30;
-            if (!skip.skip() && th < INF && cptr(fac)[b * S4_FAC + 45] == 0.0) {
+            if (!skip.skip() && th < INF && cptr(fac)[b * S4_FAC + 45] <= 1.0) {
                 const int lo = S4_NR * g2 + 1 > tl.j0 ? (int)(S4_NR * g2 + 1 - tl.j0) : 0;
                 bound_unit<2>(s_g, S, tl, rec + s4_off(S, g1, g2) * S4_FIELDS, S4_NR * g2, S - S4_NR * g2, lo, theta_s,
                               neg, s_par[wave], mine, lanes);

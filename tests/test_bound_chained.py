@@ -60,13 +60,12 @@ def terms(G, b, c, K, dtype):
     v = [np.stack([(Li[:, m, :m + 1] * G[:, :m + 1, x]).sum(1) for m in range(K)], 1) for x in (K, K + 1)]
     d = [1 - (w ** 2).sum(1) for w in v]
     e = [b[:, x] - (w * z).sum(1) for x, w in zip((K, K + 1), v)]
-    with np.errstate(divide="ignore", invalid="ignore", over="ignore"):
-        zs = e[0] / d[0]
-        u = G[:, K, K + 1] - (v[0] * v[1]).sum(1)
-        return low, kappa, d[0], p - e[0] * zs, d[1] - u * u / d[0], e[1] - zs * u
+    zs = e[0] / d[0]
+    u = G[:, K, K + 1] - (v[0] * v[1]).sum(1)
+    return low, kappa, d[0], p - e[0] * zs, d[1] - u * u / d[0], e[1] - zs * u
 
 
-@pytest.mark.parametrize("K", [4])
+@pytest.mark.parametrize("K", [4, 8])
 def test_error_of_the_terms_within_half_the_slack(K):
     tau, slack = constant("S3_TAU"), constant("S3_SLACK")
     rng = np.random.default_rng(K)
@@ -90,8 +89,9 @@ def test_error_of_the_terms_within_half_the_slack(K):
         G[i], b[i], c[i] = x @ x.T, x @ y, y @ y
     at = np.arange(K + 2)
     G[:, at, at] = 1.0
-    low, kappa, dj, p, d, zeta = terms(G, b, c, K, np.float64)
-    ref = terms(G, b, c, K, np.longdouble)
+    with np.errstate(all="ignore"):  # (bases with pivots of zero)
+        low, kappa, dj, p, d, zeta = terms(G, b, c, K, np.float64)
+        ref = terms(G, b, c, K, np.longdouble)
     # the rule of the search: the base's pivots, then a smallest pivot of j
     room = np.sqrt(slack / (4 * K * (K + 1) * 2.0 ** -53 * kappa)) - 1.0
     used = (low > tau) & (room >= 1.0) & (dj > np.maximum(tau, 1.0 / np.maximum(room, 1e-30) ** 2)) & (ref[4] > 0)
@@ -165,6 +165,14 @@ def test_d3(seed, T):
     p = chained_problem(seed, 88, T)
     idx, sse, _ = run(p, 3, 20)
     check(p, 3, 20, idx, sse)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("seed", SEEDS)
+def test_d4(seed):
+    p = chained_problem(seed, 30, 1)
+    idx, sse, _ = run(p, 4, 15)
+    check(p, 4, 15, idx, sse)
 
 
 @pytest.mark.gpu
