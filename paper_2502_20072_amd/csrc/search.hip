@@ -4551,7 +4551,7 @@ int launch_list_search(const Ctx &c, int D, int k, const int32_t *pre, int64_t n
     phase_begin(c, SISSO_PHASE_PREPASS, st);
     hipLaunchKernelGGL(list_init_kernel, dim3(init_blocks > PRE_BINS / 256 ? init_blocks : PRE_BINS / 256), dim3(256),
                        0, st, c);
-    if (c.T == 1) {
+    if (c.T == 1 && n > 0) {
         const int64_t np = n < LIST_POOL ? n : LIST_POOL;
         const dim3 grid((unsigned)((np + 3) / 4));
         switch (D - 1) {

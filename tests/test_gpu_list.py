@@ -48,6 +48,24 @@ def test_list_of_all_prefixes(S, D, kind, T):
     compare_topk(p, D, k, gi, gs, oi, os_)
 
 
+@pytest.mark.parametrize("T", [1, 2])
+@pytest.mark.parametrize("D", [2, 3, 4])
+def test_empty_list(D, T):
+    """A list without rows has no tuples: every result row is marked empty."""
+    import torch
+    from paper_2502_20072_amd import L0Search
+    from paper_2502_20072_amd import _binding as B
+    p = tiny_problem(6200 + D, S=20, n=45 * T, T=T, D=D, sigma=0.3)
+    s = L0Search(p.F, p.y, p.task_offsets, D_max=D, k_max=5)
+    s.gram()
+    B.sisso_l0_search_list(s.handle, D, 5, torch.empty((0, D - 1), dtype=torch.int32, device="cuda"))
+    s.last_D, s.last_k = D, 5
+    gi, gs, gc = s.topk()
+    assert s.scored() == 0
+    s.close()
+    assert (gi == -1).all() and np.isposinf(gs).all() and np.isnan(gc).all()
+
+
 @pytest.mark.parametrize("n,K", [(1, 1), (5, 3), (1024, 1024), (5000, 1), (5000, 4999), (100003, 700)])
 @pytest.mark.parametrize("kind", ["normal", "equal", "negative", "nan", "infinite"])
 def test_selection_cut(n, K, kind):
