@@ -340,6 +340,31 @@ __device__ void wave_sort_list(double *Ls, uint64_t *Lr, int KP) {
         }
 }
 
+// Empties the later copies of equal entries of a sorted list (one tuple reached
+// from several prefixes), sorts again, and returns the number of entries left.
+__device__ int wave_drop_copies(double *Ls, uint64_t *Lr, int KP) {
+    const int lane = threadIdx.x & 63;
+    unsigned copy = 0;
+    int n = 0;
+    for (int m = 0; m < KP; m += 64) {
+        const int e = m + lane;
+        const bool c = e > 0 && Ls[e] < INF && Ls[e] == Ls[e - 1] && Lr[e] == Lr[e - 1];
+        copy |= (unsigned)c << (m >> 6);
+        n += __popcll(__ballot(!c && Ls[e] < INF));
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_wave_barrier();
+    for (int m = 0; m < KP; m += 64)
+        if ((copy >> (m >> 6)) & 1u) {
+            Ls[m + lane] = INF;
+            Lr[m + lane] = ~0ull;
+        }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_wave_barrier();
+    if (__any(copy != 0)) wave_sort_list(Ls, Lr, KP);
+    return n;
+}
+
 // ------------------------------------------------------------ init kernel
 // Resets the per-search device state and tabulates the cumulative number
 // of work items per j-block: block jb covers j in [JB*jb, N_jb) with
@@ -3558,9 +3583,11 @@ __global__ __launch_bounds__(256) void list_search_kernel(Ctx c, const int32_t *
             }
             unsigned long long m = __ballot(sse < INF && sse <= th);
             offered += (unsigned)__popcll(m);
-            if (fill < KP && m) {
+            while (fill < KP && m) {
                 // the list is not full: append (one slot per passing lane), and
-                // sort once it is
+                // sort once it is; copies of one tuple among the entries are
+                // dropped, so a full list holds KP tuples and its last entry
+                // bounds the KP-th best
                 const int rank = __popcll(m & ((1ull << lane) - 1ull));
                 const int nfit = min(__popcll(m), KP - fill);
                 const bool mine = ((m >> lane) & 1ull) && rank < nfit;
@@ -3572,7 +3599,10 @@ __global__ __launch_bounds__(256) void list_search_kernel(Ctx c, const int32_t *
                 __builtin_amdgcn_wave_barrier();
                 m &= ~__ballot(mine);
                 fill += nfit;
-                if (fill == KP) wave_sort_list(Ls, Lr, KP);
+                if (fill == KP) {
+                    wave_sort_list(Ls, Lr, KP);
+                    fill = wave_drop_copies(Ls, Lr, KP);
+                }
             }
             while (m) {
                 const int src = __ffsll((long long)m) - 1;

@@ -48,6 +48,31 @@ def test_list_of_all_prefixes(S, D, kind, T):
     compare_topk(p, D, k, gi, gs, oi, os_)
 
 
+@pytest.mark.parametrize("grid", [1, 3, 1024])
+@pytest.mark.parametrize("T", [1, 2])
+@pytest.mark.parametrize("S,D", [(40, 2), (20, 3), (14, 4)])
+def test_copies_do_not_fill_a_list(S, D, T, grid):
+    """A few rows repeated many times come first: a wave that reaches their
+    tuples again and again still takes the better ones of the rows behind."""
+    import torch
+    from paper_2502_20072_amd import L0Search
+    from paper_2502_20072_amd import _binding as B
+    p = tiny_problem(6300 + S + T, S=S, n=45 * T, T=T, D=D, sigma=0.3)
+    pre = np.array(list(itertools.combinations(range(S), D - 1)), dtype=np.int32)
+    head = pre[np.random.default_rng(S).permutation(len(pre))[:4]]
+    pre = np.concatenate([np.tile(head, (50, 1)), pre])
+    k = 48
+    s = L0Search(p.F, p.y, p.task_offsets, D_max=D, k_max=k)
+    s.set_search_grid(grid)
+    s.gram()
+    B.sisso_l0_search_list(s.handle, D, k, torch.from_numpy(pre).to("cuda"))
+    s.last_D, s.last_k = D, k
+    gi, gs, _ = s.topk()
+    s.close()
+    oi, os_, _ = oracle.topk(p.F, p.y, D, k, p.task_offsets)
+    compare_topk(p, D, k, gi, gs, oi, os_)
+
+
 @pytest.mark.parametrize("T", [1, 2])
 @pytest.mark.parametrize("D", [2, 3, 4])
 def test_empty_list(D, T):
