@@ -2471,9 +2471,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void s
     unsigned offered = 0;
     MtBuf mb{s_bk[MT ? wave : 0], s_be[MT ? wave : 0], 0};
     // the last waves take the first candidates: the first ones get the items
-    for (uint64_t b = nw - 1 - (uint64_t)gw; b * 64 < ncand; b += nw) {
-        const uint64_t e = b * 64 + lane;
-        const bool in = e < ncand;
+    // (several tasks: as few at a time as leave every wave some, see below)
+    const uint64_t fair = (ncand + nw - 1) / nw;
+    const uint32_t per = MT && fair < 64 ? (uint32_t)(fair ? fair : 1) : 64u;
+    for (uint64_t b = nw - 1 - (uint64_t)gw; b * per < ncand; b += nw) {
+        const uint64_t e = b * per + lane;
+        const bool in = lane < (int)per && e < ncand;
         uint64_t key = 0;
         if (in) {
             const uint32_t s = segment(0, e);
@@ -2481,46 +2484,71 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void s
         }
         s3_candidates<MT, Ctx>(c, a, rec, in, key, Ls, Lr, theta0, theta_pub, offered, mb);
     }
-    const uint64_t run = (nitem + nw - 1) / nw;
-    uint64_t e = uni((uint64_t)((uint64_t)gw * run));
-    const uint64_t e1 = uni((uint64_t)(e + run < nitem ? e + run : nitem));
-    if (e < e1) {
-        uint32_t s = segment(1, e);
-        auto item = [&]() {
-            while (first[1][s + 1] <= e) ++s;
-            return uni(c.s3_rows[(size_t)s * wg_units * (BU / 8) + (e - first[1][s])]);
-        };
-        constexpr uint64_t OCTET = 7ull << 42;  // the rows' place in their block
-        uint64_t it = item();
-        for (;;) {
-            const int64_t g = (int64_t)((it >> 22) & 0xFFFFF);
-            S3Tile tl;
-            tl.kcx = (int64_t)((it >> 8) & 0x3FFF);
-            tl.j0 = (int64_t)(it >> 42) * 8 / S3_JR * S3_JR;
-            tl.kb = tl.j0 + tl.kcx * BU;
-            const uint64_t same = (it & ~OCTET) >> 8;  // group, column chunk, row block
-            unsigned long long rows = 0;
-            bool more = true;
-            for (;;) {
-                rows |= (unsigned long long)(it & 0xff) << (8 * ((it >> 42) & 7));
-                if (++e >= e1) {
-                    more = false;
-                    break;
-                }
-                it = item();
-                if ((it & ~OCTET) >> 8 != same) break;
-            }
-            const int x0 = __builtin_ctzll(rows), x1 = 63 - __builtin_clzll(rows);
-            s3_group<MT, Ctx>(c, a, rec, tl, g, tl.j0 + x0, tl.j0 + x1, Ls, Lr, theta0, theta_pub, offered, mb,
-                              s_q[wave], s_qj[wave]);
-            if (!more) break;
-        }
-    }
+    auto place = [](uint64_t it, S3Tile &tl) {
+        tl.kcx = (int64_t)((it >> 8) & 0x3FFF);
+        tl.j0 = (int64_t)(it >> 42) * 8 / S3_JR * S3_JR;
+        tl.kb = tl.j0 + tl.kcx * BU;
+        return (int64_t)((it >> 22) & 0xFFFFF);  // the group
+    };
     if constexpr (MT) {
+        // a tuple that passes the filter task costs a solve per task, mostly one
+        // tuple after another in the wave that found it: the items' rows are
+        // dealt out in turn, 8 at a time while that leaves a wave four shares,
+        // else 4, 2 or 1.  (In runs of whole items a few waves went on long after
+        // the rest: 40 tasks of 12 rows, S = 60: the call 2375 us, now 577; 8 tasks
+        // of 60, S = 500, a noise target: 4625, now 3375.)
+        const uint64_t nrow = nitem * 8;
+        int R = 8;
+        while (R > 1 && nrow < (uint64_t)R * 4 * nw) R >>= 1;
+        for (uint64_t q = (uint64_t)gw * R; q < nrow; q += nw * R) {
+            const uint64_t e = q >> 3;
+            const uint32_t s = pool_segment(first[1], nseg, e);
+            const uint64_t it = uni(c.s3_rows[(size_t)s * wg_units * (BU / 8) + (e - first[1][s])]);
+            const unsigned m = ((unsigned)it & 0xffu) & (((1u << R) - 1u) << (q & 7));
+            if (!m) continue;
+            S3Tile tl;
+            const int64_t g = place(it, tl);
+            const int64_t j = tl.j0 + 8 * (int64_t)((it >> 42) & 7);
+            s3_group<MT, Ctx>(c, a, rec, tl, g, j + __builtin_ctz(m), j + 31 - __builtin_clz(m), Ls, Lr, theta0,
+                              theta_pub, offered, mb, s_q[wave], s_qj[wave]);
+        }
         if (mb.n > 0) {
             const double th = fmin(theta0, theta_load(c.theta_bits));
             const double theta_f = th < INF ? th * (1.0 + THETA_SLACK) : INF;
             offered += mt_flush(c, Ls, Lr, KP, mb.key, mb.sse, mb.n, theta_f);
+        }
+    } else {
+        const uint64_t run = (nitem + nw - 1) / nw;
+        uint64_t e = uni((uint64_t)((uint64_t)gw * run));
+        const uint64_t e1 = uni((uint64_t)(e + run < nitem ? e + run : nitem));
+        if (e < e1) {
+            uint32_t s = segment(1, e);
+            auto item = [&]() {
+                while (first[1][s + 1] <= e) ++s;
+                return uni(c.s3_rows[(size_t)s * wg_units * (BU / 8) + (e - first[1][s])]);
+            };
+            constexpr uint64_t OCTET = 7ull << 42;  // the rows' place in their block
+            uint64_t it = item();
+            for (;;) {
+                S3Tile tl;
+                const int64_t g = place(it, tl);
+                const uint64_t same = (it & ~OCTET) >> 8;  // group, column chunk, row block
+                unsigned long long rows = 0;
+                bool more = true;
+                for (;;) {
+                    rows |= (unsigned long long)(it & 0xff) << (8 * ((it >> 42) & 7));
+                    if (++e >= e1) {
+                        more = false;
+                        break;
+                    }
+                    it = item();
+                    if ((it & ~OCTET) >> 8 != same) break;
+                }
+                const int x0 = __builtin_ctzll(rows), x1 = 63 - __builtin_clzll(rows);
+                s3_group<MT, Ctx>(c, a, rec, tl, g, tl.j0 + x0, tl.j0 + x1, Ls, Lr, theta0, theta_pub, offered, mb,
+                                  s_q[wave], s_qj[wave]);
+                if (!more) break;
+            }
         }
     }
     if (lane == 0 && offered) atomicAdd(c.cand_counter, offered);
