@@ -163,9 +163,10 @@ static Layout compute_layout(int64_t n_total, int64_t S, int T, int D_max, int k
     L.s3_rows = take(std::max(pt3 * 8, pt4 * 16) * sizeof(uint64_t));
     L.s3_count = take(L.rec3_bytes ? (size_t)SEARCH_WGS_MAX * 2 * sizeof(uint32_t) : 0);
     L.lists = take((size_t)nlists * L.KP * 2 * d + (size_t)nlists * L.KP * 2 * d);
-    // FP64 Gram: the residues take the zone above, GM_KC_MIN samples at a time
-    // or as many as fit (more chunks cost a read and a write of the residue
-    // planes each); and a residue plane per modulus over the upper tile pairs.
+    // FP64 Gram: the residues take the zone above, as many samples at a time as
+    // fit (more chunks cost a read and a write of the residue planes each), which
+    // is grown to hold kc; and a residue plane per modulus over the upper tile
+    // pairs.
     // Tile edge: 256-wide tiles run one to a CU at 2.0e15 products/s over whole
     // rounds of the 256 CUs, 128-wide ones three to a CU at 1.45e15 (measured
     // at S = 4096, n = 50,000 and S = 1000, n = 8192); the smaller time wins.
@@ -183,7 +184,11 @@ static Layout compute_layout(int64_t n_total, int64_t S, int T, int D_max, int k
         L.part = take((size_t)L.nsplit * T * S * S * d);
     } else {
         const int64_t kpad = (n_total + GM_BK - 1) / GM_BK * GM_BK + (int64_t)(T - 1) * GM_BK;
-        const size_t least = (size_t)GM_NP * S * std::min(kpad, S < 1024 ? GM_KC_MIN : GM_KC_WIDE);
+        int64_t kc = GM_KC_WIDE;
+        if (S < 1024)
+            kc = std::max(GM_KC_MIN, std::min({(kpad / 4 + GM_BK - 1) / GM_BK * GM_BK,
+                                               GM_RES_MAX / (GM_NP * S) / GM_BK * GM_BK, GM_KC_MAX}));
+        const size_t least = (size_t)GM_NP * S * std::min(kpad, kc);
         if (o - zone < least) o = align256(zone + least);
         L.gm_res = zone;
         L.gm_kc = std::min({(int64_t)((o - zone) / ((size_t)GM_NP * S)) / GM_BK * GM_BK, kpad, GM_KC_MAX});

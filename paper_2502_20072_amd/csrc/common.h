@@ -29,9 +29,14 @@ constexpr int GM_NP = 15;              // FP64 Gram: moduli of the residue produ
 constexpr int GM_BK = 128;             // FP64 Gram: a task's samples are padded to whole K-steps of 128 (256-wide
 constexpr int GM_BK_S = 64;            // tiles) or 64 (128-wide tiles)
 constexpr int64_t GM_KC_MAX = 65536;   // FP64 Gram: most samples per chunk (32-bit sums of byte products: 2^30)
-constexpr int64_t GM_KC_MIN = 4096;    // FP64 Gram: samples per chunk that the workspace holds at least, and from
-constexpr int64_t GM_KC_WIDE = 16384;  // 1024 features on (a chunk's pass over the residue planes costs as much as 425
-                                       // samples' products)
+// FP64 Gram: samples per chunk that the workspace holds at least.  A chunk's
+// pass over the residue planes costs as much as 425 samples' products, so
+// GM_KC_WIDE from 1024 features on; below, where a chunk is mostly its launches
+// and the fill of a few workgroups, GM_KC_MIN and a quarter of all samples, up to
+// GM_RES_MAX bytes (16 tasks of 10,000 rows, S = 100, in chunks of 4096: 896
+// us, in four 351).
+constexpr int64_t GM_KC_WIDE = 16384, GM_KC_MIN = 4096;
+constexpr int64_t GM_RES_MAX = (int64_t)256 << 20;
 constexpr int PROP_NF = 8;             // learned proposal: features per prefix
 
 // ---------------------------------------------------------------- binomials
