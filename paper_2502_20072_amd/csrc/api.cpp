@@ -186,14 +186,21 @@ static Layout compute_layout(int64_t n_total, int64_t S, int T, int D_max, int k
         const int64_t kpad = (n_total + GM_BK - 1) / GM_BK * GM_BK + (int64_t)(T - 1) * GM_BK;
         int64_t kc = GM_KC_WIDE;
         if (S < 1024)
-            kc = std::max(GM_KC_MIN, std::min({(kpad / 4 + GM_BK - 1) / GM_BK * GM_BK,
+            kc = std::max(GM_KC_MIN, std::min({((T > 1 ? kpad : kpad / 4) + GM_BK - 1) / GM_BK * GM_BK,
                                                GM_RES_MAX / (GM_NP * S) / GM_BK * GM_BK, GM_KC_MAX}));
         const size_t least = (size_t)GM_NP * S * std::min(kpad, kc);
         if (o - zone < least) o = align256(zone + least);
         L.gm_res = zone;
         L.gm_kc = std::min({(int64_t)((o - zone) / ((size_t)GM_NP * S)) / GM_BK * GM_BK, kpad, GM_KC_MAX});
         const size_t nt = (size_t)((S + L.gm_tile - 1) / L.gm_tile);
-        const size_t planes = nt * (nt + 1) / 2 * T * GM_NP * L.gm_tile * L.gm_tile;
+        const size_t tiles = nt * (nt + 1) / 2;
+        // parts of a product's samples: about one workgroup of a chunk's tasks
+        // for each of the 256 CUs, while a part has GM_PART steps or more
+        const int64_t rows = std::min(std::max(n_total / T, (int64_t)1), L.gm_kc);
+        const int64_t wgs = (int64_t)tiles * GM_NP * std::min((int64_t)T, std::max(L.gm_kc / rows, (int64_t)1));
+        L.gm_ns = (int)std::max((int64_t)1, std::min({(256 + wgs / 2) / wgs, rows / (L.gm_bk * GM_PART),
+                                                      (int64_t)GM_NS_MAX}));
+        const size_t planes = tiles * L.gm_ns * T * GM_NP * L.gm_tile * L.gm_tile;
         L.part = take(std::max((size_t)S * S * d, planes));
     }
     L.merged = take((size_t)L.KP * 2 * d);
@@ -253,6 +260,7 @@ static void carve(sisso_l0 *h) {
     c.gm_kb = (int64_t *)(base + L.gm_kb);
     c.gm_res = (uint8_t *)(base + L.gm_res);
     c.gm_tile = L.gm_tile;
+    c.gm_ns = L.gm_ns;
     c.gm_kc = L.gm_kc;
     c.lp_cbase = (int32_t *)(base + L.lp_cbase);
     c.lp_exp = (int32_t *)(base + L.lp_exp);

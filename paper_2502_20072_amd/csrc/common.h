@@ -32,11 +32,15 @@ constexpr int64_t GM_KC_MAX = 65536;   // FP64 Gram: most samples per chunk (32-
 // FP64 Gram: samples per chunk that the workspace holds at least.  A chunk's
 // pass over the residue planes costs as much as 425 samples' products, so
 // GM_KC_WIDE from 1024 features on; below, where a chunk is mostly its launches
-// and the fill of a few workgroups, GM_KC_MIN and a quarter of all samples, up to
-// GM_RES_MAX bytes (16 tasks of 10,000 rows, S = 100, in chunks of 4096: 896
-// us, in four 351).
+// and the fill of a few workgroups, GM_KC_MIN and a quarter of the samples of one
+// task or all of several, up to GM_RES_MAX bytes (16 tasks of 10,000 rows, S =
+// 100, in chunks of 4096: 896 us, now 222).
 constexpr int64_t GM_KC_WIDE = 16384, GM_KC_MIN = 4096;
 constexpr int64_t GM_RES_MAX = (int64_t)256 << 20;
+// FP64 Gram: most parts of a product's samples, and the least K-steps of a part
+// (a part costs a pass of the finishing kernel over its plane)
+constexpr int GM_NS_MAX = 8;
+constexpr int64_t GM_PART = 16;
 constexpr int PROP_NF = 8;             // learned proposal: features per prefix
 
 // ---------------------------------------------------------------- binomials
@@ -264,11 +268,12 @@ struct Layout {
     size_t bhat;       // double [S][TP] normalised F_t^T y_t
     size_t G;          // double [S][S][TP] correlation matrices, task fastest
     size_t part;       // precision forms: double [nsplit][T][S][S] raw centred Gram partial sums;
-                       // FP64: residue planes, bytes [T][tile pairs][GM_NP][gm_tile^2]; scratch of
+                       // FP64: residue planes, bytes [gm_ns][T][tile pairs][GM_NP][gm_tile^2]; scratch of
                        // sisso_gram_read (at least S^2 doubles)
     size_t gm_kb;      // FP64 Gram: int64 [T+1] first padded sample of each task
     size_t gm_res;     // FP64 Gram: residues, bytes [GM_NP][S][gm_kc], over G and the regions of the search
     int gm_tile;       // FP64 Gram: tile edge of the products (128 or 256)
+    int gm_ns;         // FP64 Gram: workgroups that share the samples of a product
     int64_t gm_kc;     // FP64 Gram: padded samples per chunk
     int gm_bk;         // FP64 Gram: samples per K-step
     size_t flags;      // uint32 [64] device status words

@@ -134,7 +134,9 @@ __global__ __launch_bounds__(256) void residue_kernel(const double *__restrict__
 // One workgroup per (task, modulus, TM x TM tile pair bi <= bj): the product
 // of two panels of residues over the chunk's samples of the task, reduced
 // modulo p to a byte per entry.  A chunk that does not start the task adds
-// the residue already there.
+// the residue already there.  Where the tiles are few, ns workgroups share the
+// samples of a product, each with a plane of its own (the finishing pass adds
+// them): 4 tasks of 30,000 rows, S = 40: 756 us, now 119.
 //
 // Tiles.  WM x WN waves; a wave owns (16 MB) columns gj times (16 NB) rows
 // gi of G as MB x NB blocks of v_mfma_i32_16x16x64_i8 (A[i][k] in lane
@@ -152,7 +154,7 @@ __global__ __launch_bounds__(256) void residue_kernel(const double *__restrict__
 template <int TM, int WM, int WN, int BK, int PD, int WPE>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void gram_mod_kernel(
     const uint8_t *__restrict__ res, int64_t S, int64_t kc, int64_t c0, const int64_t *__restrict__ kb,
-    const int32_t *__restrict__ torder, int T, int ntile, uint8_t *__restrict__ planes) {
+    const int32_t *__restrict__ torder, int T, int ntile, int ns, uint8_t *__restrict__ planes) {
     constexpr int NT = 64 * WM * WN;          // threads
     constexpr int MB = TM / (16 * WM);        // 16-column blocks per wave
     constexpr int NB = TM / (16 * WN);        // 16-row blocks per wave
@@ -178,7 +180,7 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WP
     };
 
     const uint32_t npair = (uint32_t)((int64_t)ntile * (ntile + 1) / 2);
-    const uint32_t nblk = npair * GM_NP;      // products of a task
+    const uint32_t nblk = npair * GM_NP * (uint32_t)ns;  // workgroups of a task
     uint32_t b = blockIdx.x;
     int t;
     {
@@ -192,17 +194,26 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WP
         b = (b % 8) * q + b / 8;
         if (b >= nblk) return;
     }
-    const int l = (int)(b / npair);
+    const int split = (int)(b / (npair * GM_NP));
+    const int l = (int)(b / npair % GM_NP);
     const uint32_t pair = b % npair;
     int bi, bj;
     gm_tile_pair(pair, ntile, bi, bj);
 
-    // the task's samples inside the chunk [c0, c0 + kc)
-    const int64_t k0 = kb[t] > c0 ? kb[t] - c0 : 0;
+    // the task's samples inside the chunk [c0, c0 + kc), and this workgroup's
+    int64_t k0 = kb[t] > c0 ? kb[t] - c0 : 0;
     const int64_t k1 = kb[t + 1] - c0 < kc ? kb[t + 1] - c0 : kc;
     if (k0 >= k1) return;
     const bool first = kb[t] >= c0;
-    const int steps = (int)((k1 - k0) / BK);
+    const int all = (int)((k1 - k0) / BK), s0 = (int)((int64_t)all * split / ns);
+    const int steps = (int)((int64_t)all * (split + 1) / ns) - s0;
+    k0 += (int64_t)s0 * BK;
+    uint8_t *out = planes + ((((int64_t)split * T + t) * npair + pair) * GM_NP + l) * (TM * TM);
+    if (steps == 0) {  // (a task with fewer steps than parts)
+        if (first)
+            for (int e = threadIdx.x; e < TM * TM / 16; e += NT) reinterpret_cast<int4_t *>(out)[e] = (int4_t){0, 0, 0, 0};
+        return;
+    }
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -298,7 +309,6 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WP
     // residues of the sums: a lane holds row wi + 16 n + lane % 16, columns
     // wj + 4 MB (lane / 16) + 0 .. 4 MB - 1
     const double p = GM_T.p[l], ip = GM_T.ip[l];
-    uint8_t *out = planes + (((int64_t)t * npair + pair) * GM_NP + l) * (TM * TM);
     uint8_t *o0 = out + (wi + (lane & 15)) * TM + wj + 4 * MB * (lane >> 4);
     if (!first) {
 #pragma unroll
@@ -339,20 +349,41 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WP
 // not finite either and carries over to its row and column.
 __device__ inline double mod_scale(double inv) { return inv > 0.0 ? ldexp(inv, -mod_exp(inv)) : 0.0; }
 
-template <int NQ>  // NQ dwords: 4 NQ consecutive entries
-__device__ inline void crt_read(const uint8_t *src, int64_t stride, double (&v)[4 * NQ]) {
-    uint32_t w[GM_NP][NQ];
+// Four consecutive entries; SPLIT: ns parts, `part` bytes apart, are added first.
+template <bool SPLIT>
+__device__ inline void crt_read(const uint8_t *src, int64_t stride, int ns, int64_t part, double (&v)[4]) {
+    uint32_t w[GM_NP];
 #pragma unroll
-    for (int l = 0; l < GM_NP; ++l)
+    for (int l = 0; l < GM_NP; ++l) w[l] = *reinterpret_cast<const uint32_t *>(src + l * stride);
+    if constexpr (!SPLIT) {
 #pragma unroll
-        for (int x = 0; x < NQ; ++x) w[l][x] = reinterpret_cast<const uint32_t *>(src + l * stride)[x];
+        for (int e = 0; e < 4; ++e) {
+            double hi = 0.0, lo = 0.0;
 #pragma unroll
-    for (int e = 0; e < 4 * NQ; ++e) {
-        double hi = 0.0, lo = 0.0;
-#pragma unroll
-        for (int l = 0; l < GM_NP; ++l) crt_add((double)(int)(int8_t)(w[l][e / 4] >> (8 * (e % 4))), l, hi, lo);
-        v[e] = crt_value(hi, lo);
+            for (int l = 0; l < GM_NP; ++l) crt_add((double)(int)(int8_t)(w[l] >> (8 * e)), l, hi, lo);
+            v[e] = crt_value(hi, lo);
+        }
+        return;
     }
+    double hi[4] = {0.0, 0.0, 0.0, 0.0}, lo[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int l = 0; l < GM_NP; ++l) {
+        int r[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = (int)(int8_t)(w[l] >> (8 * e));
+        for (int q = 1; q < ns; ++q) {
+            const uint32_t x = *reinterpret_cast<const uint32_t *>(src + q * part + l * stride);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r[e] += (int)(int8_t)(x >> (8 * e));
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double a = (double)r[e];
+            crt_add(fma(-rint(a * GM_T.ip[l]), GM_T.p[l], a), l, hi[e], lo[e]);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = crt_value(hi[e], lo[e]);
 }
 
 // One task per workgroup: a band of GM_FIN rows of a 64 x 64 tile pair (ti <=
@@ -363,8 +394,9 @@ __device__ inline void crt_read(const uint8_t *src, int64_t stride, double (&v)[
 // (S = 200: 12.7 us with whole tiles).
 // (with several tasks the filter task's tiles also go to G1, bitwise the same)
 constexpr int GM_FIN = 16;
+template <bool SPLIT>
 __global__ __launch_bounds__(256) void gram_mod_finish_kernel(const uint8_t *__restrict__ planes, int64_t S, int T,
-                                                              int TP, int tm, int ntile,
+                                                              int TP, int tm, int ntile, int ns,
                                                               const double *__restrict__ mu,
                                                               const double *__restrict__ inv_s,
                                                               double *__restrict__ G, int64_t nt,
@@ -389,7 +421,7 @@ __global__ __launch_bounds__(256) void gram_mod_finish_kernel(const uint8_t *__r
     const int64_t i = (int64_t)ti * GT + GM_FIN * band + li;
     const double fi = i < S ? mod_scale(ist[i]) : 0.0, mi = i < S ? mt[i] : 0.0;
     double v[4];
-    crt_read<1>(src, (int64_t)tm * tm, v);
+    crt_read<SPLIT>(src, (int64_t)tm * tm, ns, (int64_t)T * npair * GM_NP * tm * tm, v);
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
         const int64_t k = (int64_t)tk * GT + lk + x;
@@ -431,8 +463,9 @@ __global__ __launch_bounds__(256) void gram_mod_finish_kernel(const uint8_t *__r
 // ([task][row][column], one padding double per task), then written row by
 // row to tile (ti, tk) and column by column to tile (tk, ti).
 constexpr int GM_FR = 4;
+template <bool SPLIT>
 __global__ __launch_bounds__(256) void gram_mod_finish_tasks_kernel(const uint8_t *__restrict__ planes, int64_t S,
-                                                                    int T, int TP, int tm, int ntile,
+                                                                    int T, int TP, int tm, int ntile, int ns,
                                                                     const double *__restrict__ mu,
                                                                     const double *__restrict__ inv_s,
                                                                     double *__restrict__ G, int64_t nt,
@@ -455,7 +488,8 @@ __global__ __launch_bounds__(256) void gram_mod_finish_tasks_kernel(const uint8_
             const double *ist = inv_s + (int64_t)t * S, *mt = mu + (int64_t)t * S;
             const int64_t i = (int64_t)ti * GT + GM_FR * band + r;
             const double fi = i < S ? mod_scale(ist[i]) : 0.0, mi = i < S ? mt[i] : 0.0;
-            crt_read<1>(src0 + (int64_t)t * npair * GM_NP * tm * tm + (int64_t)r * tm + 4 * q, (int64_t)tm * tm, v);
+            crt_read<SPLIT>(src0 + (int64_t)t * npair * GM_NP * tm * tm + (int64_t)r * tm + 4 * q, (int64_t)tm * tm, ns,
+                     (int64_t)T * npair * GM_NP * tm * tm, v);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int64_t k = (int64_t)tk * GT + 4 * q + e;
@@ -491,7 +525,7 @@ int launch_gram_mod(const Ctx &c, hipStream_t st) {
     const int tm = c.gm_tile;
     const int ntile = (int)((c.S + tm - 1) / tm);
     const int64_t npair = (int64_t)ntile * (ntile + 1) / 2;
-    const unsigned blocks = (unsigned)((npair * GM_NP + 7) / 8 * 8 * c.T);
+    const unsigned blocks = (unsigned)((npair * GM_NP * c.gm_ns + 7) / 8 * 8 * c.T);
     for (int64_t c0 = 0; c0 < c.gm_kpad; c0 += c.gm_kc) {
         const int64_t kc = c.gm_kpad - c0 < c.gm_kc ? c.gm_kpad - c0 : c.gm_kc;
         const int64_t nseg = (kc + GM_RB - 1) / GM_RB;
@@ -499,21 +533,23 @@ int launch_gram_mod(const Ctx &c, hipStream_t st) {
                            c.off_dev, c.gm_kb, c.T, c.mu, c.inv_s, c0, kc, nseg, c.gm_res);
         if (tm == 256)
             hipLaunchKernelGGL((gram_mod_kernel<256, 2, 4, GM_BK, 1, 2>), dim3(blocks), dim3(512), 0, st, c.gm_res, c.S, kc, c0,
-                               c.gm_kb, c.torder, c.T, ntile, (uint8_t *)c.part);
+                               c.gm_kb, c.torder, c.T, ntile, c.gm_ns, (uint8_t *)c.part);
         else
             hipLaunchKernelGGL((gram_mod_kernel<128, 2, 2, GM_BK_S, 2, 3>), dim3(blocks), dim3(256), 0, st, c.gm_res, c.S, kc, c0,
-                               c.gm_kb, c.torder, c.T, ntile, (uint8_t *)c.part);
+                               c.gm_kb, c.torder, c.T, ntile, c.gm_ns, (uint8_t *)c.part);
     }
     const int64_t npair64 = c.Gnt * (c.Gnt + 1) / 2;
     double *G1 = c.G1 != c.G ? c.G1 : nullptr;
+    const auto *planes = (const uint8_t *)c.part;
     if (c.T > 1 && c.TP <= 16)
-        hipLaunchKernelGGL(gram_mod_finish_tasks_kernel, dim3((unsigned)(npair64 * (GT / GM_FR))), dim3(256),
-                           (size_t)c.TP * (GM_FR * GT + 1) * sizeof(double), st, (const uint8_t *)c.part, c.S, c.T,
-                           c.TP, tm, ntile, c.mu, c.inv_s, c.G, c.Gnt, G1, c.tstar);
+        hipLaunchKernelGGL(c.gm_ns > 1 ? gram_mod_finish_tasks_kernel<true> : gram_mod_finish_tasks_kernel<false>,
+                           dim3((unsigned)(npair64 * (GT / GM_FR))), dim3(256),
+                           (size_t)c.TP * (GM_FR * GT + 1) * sizeof(double), st, planes, c.S, c.T, c.TP, tm, ntile,
+                           c.gm_ns, c.mu, c.inv_s, c.G, c.Gnt, G1, c.tstar);
     else
-        hipLaunchKernelGGL(gram_mod_finish_kernel, dim3((unsigned)(npair64 * c.T * (GT / GM_FIN))), dim3(256), 0, st,
-                           (const uint8_t *)c.part, c.S, c.T, c.TP, tm, ntile, c.mu, c.inv_s, c.G, c.Gnt, G1,
-                           c.tstar);
+        hipLaunchKernelGGL(c.gm_ns > 1 ? gram_mod_finish_kernel<true> : gram_mod_finish_kernel<false>,
+                           dim3((unsigned)(npair64 * c.T * (GT / GM_FIN))), dim3(256), 0, st, planes, c.S, c.T, c.TP,
+                           tm, ntile, c.gm_ns, c.mu, c.inv_s, c.G, c.Gnt, G1, c.tstar);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
