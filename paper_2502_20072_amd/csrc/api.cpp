@@ -60,24 +60,17 @@ static int precision_slices(int32_t precision) {
     }
 }
 
-static Layout compute_layout(int64_t n_total, int64_t S, int T, int D_max, int k_max, int lp_ns, bool fp32) {
-    Layout L{};
-    L.lp_ns = lp_ns > 0 ? lp_ns : 0;
-    L.fp32 = fp32 ? 1 : 0;
-    // chunks of LP_XC samples per task; bounded without reading the offsets
-    L.lp_nchunk = L.lp_ns ? (int)((n_total + LP_XC - 1) / LP_XC + T) : 0;
-    L.TP = next_pow2(T);
+// Row splits of the FP64 products and of the precision forms.  Split the rows
+// of every tile pair into ns parts (>= 256 rows each, at most 8) so that the
+// Gram's workgroups, about equal in cost and one per CU at a time, fill whole
+// rounds of the 256 CUs: the launch takes ceil(blocks ns / 256) rounds of 1/ns
+// of a tile pair's work; a split is taken while it cuts that time by more than
+// 2 % (the finish kernel reads every split's partial matrices).  With several
+// tasks the workgroups' costs follow the tasks' row counts (and are launched
+// largest first), so only a small launch is split, to about 512 workgroups.
+static int gram_splits(int64_t n_total, int64_t S, int T) {
     const int64_t ntile = (S + GRAM_TILE - 1) / GRAM_TILE;
     const int64_t blocks = ntile * (ntile + 1) / 2 * T;
-    // Split the rows of every tile pair into ns parts (>= 256 rows each, at
-    // most 8) so that the Gram's workgroups, about equal in cost and one per
-    // CU at a time, fill whole rounds of the 256 CUs: the launch takes
-    // ceil(blocks ns / 256) rounds of 1/ns of a tile pair's work; a split is
-    // taken while it cuts that time by more than 2 % (the finish kernel reads
-    // every split's partial matrices).
-    // With several tasks the workgroups' costs follow the tasks' row counts
-    // (and are launched largest first), so only a small launch is split, to
-    // about 512 workgroups.
     const int64_t byrows = n_total / 256 > 1 ? n_total / 256 : 1;
     int64_t ns = 1;
     if (T == 1) {
@@ -96,7 +89,76 @@ static Layout compute_layout(int64_t n_total, int64_t S, int T, int D_max, int k
         if (ns > 16) ns = 16;
         if (ns < 1) ns = 1;
     }
-    L.nsplit = (int)ns;
+    return (int)ns;
+}
+
+// Tile edge, K-step and parts of the residue products.  256-wide tiles run one
+// to a CU at 2.0e15 products/s over whole rounds of the 256 CUs, 128-wide ones
+// three to a CU at 1.45e15 (measured at S = 4096, n = 50,000 and S = 1000, n =
+// 8192); the smaller time wins, but tasks of up to 500 rows on average, whose
+// few K-steps leave a lone workgroup waiting, take the narrow ones (16 tasks,
+// S = 1500: 427 against 482 us at 400 rows each, 686 against 682 at 1000).
+// Parts: about one workgroup of a chunk's tasks for each of the 256 CUs, while a
+// part has GM_PART steps or more (kc: samples per chunk).
+static void gram_tiles(int64_t n_total, int64_t S, int T, int &tile, int &bk) {
+    auto pairs = [&](int64_t edge) {
+        const int64_t q = (S + edge - 1) / edge;
+        return (double)(q * (q + 1) / 2) * GM_NP * T;
+    };
+    const double wide = ceil(pairs(256) / 256) * 4;
+    const double narrow = std::max(1.0, pairs(128) / 256) * 1.37;
+    tile = wide < narrow && n_total > 500 * (int64_t)T ? 256 : 128;
+    bk = tile == 256 ? GM_BK : GM_BK_S;
+}
+static int gram_parts(int64_t n_total, int64_t S, int T, int tile, int bk, int64_t kc) {
+    const int64_t q = (S + tile - 1) / tile, rows = std::min(std::max(n_total / T, (int64_t)1), kc);
+    const int64_t wgs = q * (q + 1) / 2 * GM_NP * std::min((int64_t)T, std::max(kc / rows, (int64_t)1));
+    return (int)std::max((int64_t)1, std::min({(256 + wgs / 2) / wgs, rows / (bk * GM_PART), (int64_t)GM_NS_MAX}));
+}
+
+// FP64 Gram on the FP64 matrix cores or by residue products, by the smaller of
+// two estimates (us).  Both are sums of what the phases were measured to take
+// over 3936 shapes of 1 to 64 tasks of 8 to 5000 rows and 30 to 20,000 features:
+// a fixed part, the products' rounds of workgroups, and the bytes of partial
+// sums, planes, residues and results.  Half of the shapes are within 5 % of
+// their estimate; the line lies near 25 rows a task at S = 300, 100 at S = 1000
+// and 150 to 250 above, higher with more than 16 tasks (whose results are
+// written in strides), and at S <= 128 the FP64 products win again where many
+// long tasks fill the chip (64 tasks of 5000 rows: 257 against 517 us).
+static bool gram_f64(int64_t n_total, int64_t S, int T) {
+    const int TP = next_pow2(T);
+    const double rows = (double)n_total / T, MB = 1e-6, out = (double)S * S * TP * 8 * MB;
+    auto tri = [&](int64_t edge) {
+        const int64_t q = (S + edge - 1) / edge;
+        return (double)(q * (q + 1) / 2) * T;
+    };
+    const int ns = gram_splits(n_total, S, T);
+    const double wgs = tri(GRAM_TILE) * ns, f64_rounds = wgs < 1024 ? ceil(wgs / 256) : wgs / 256 + 0.5;
+    // more than 16 tasks: results beyond 500 MB leave the caches half written
+    const double far = std::max(0.0, out - 500.0);
+    const double f64 = 10.3 + 2.53 * f64_rounds * ceil(ceil(rows / GRAM_KC) / ns) +
+                       0.153 * (double)S * S * 4 * T * ns * MB + 0.025 * n_total * S * 8 * MB +
+                       (T > 16 ? 1.4 * out + 0.9 * far : 0.35 * out) +
+                       (T > 1 && T <= 16 ? TP * (0.345 + 0.24 * ns) : 1.6 * ns);
+    int tile, bk;
+    gram_tiles(n_total, S, T, tile, bk);
+    const int parts = gram_parts(n_total, S, T, tile, bk, GM_KC_MAX);
+    const double rounds = std::max(1.0, tri(tile) * GM_NP * parts / (tile == 256 ? 256 : 768));
+    const double steps = ceil(ceil(rows / bk) / parts), planes = tri(tile) * GM_NP * tile * tile * MB;
+    const double res = 16.4 + 15.0 * (n_total / GM_KC_MAX) +
+                       rounds * (tile == 256 ? 1.1 * steps + 2.0 : 0.39 * steps) +
+                       planes * (0.756 + (parts > 1 ? 2.22 * parts : 0.0)) +
+                       (T > 16 ? 1.14 * out + 1.48 * far : 0.103 * out) + 0.359 * n_total * S * 23 * MB;
+    return f64 < res;
+}
+
+static Layout compute_layout(int64_t n_total, int64_t S, int T, int D_max, int k_max, int lp_ns, bool fp32) {
+    Layout L{};
+    L.lp_ns = lp_ns > 0 ? lp_ns : 0;
+    L.fp32 = fp32 ? 1 : 0;
+    // chunks of LP_XC samples per task; bounded without reading the offsets
+    L.lp_nchunk = L.lp_ns ? (int)((n_total + LP_XC - 1) / LP_XC + T) : 0;
+    L.TP = next_pow2(T);
     // candidates re-scored exactly: k + 16 leaves a margin for FP64
     // normal-equation rounding at the k-th position; the precision forms rank
     // by SSEs from an approximate Gram (relative error ~1e-6..1e-5) or from
@@ -163,24 +225,14 @@ static Layout compute_layout(int64_t n_total, int64_t S, int T, int D_max, int k
     L.s3_rows = take(std::max(pt3 * 8, pt4 * 16) * sizeof(uint64_t));
     L.s3_count = take(L.rec3_bytes ? (size_t)SEARCH_WGS_MAX * 2 * sizeof(uint32_t) : 0);
     L.lists = take((size_t)nlists * L.KP * 2 * d + (size_t)nlists * L.KP * 2 * d);
-    // FP64 Gram: the residues take the zone above, as many samples at a time as
-    // fit (more chunks cost a read and a write of the residue planes each), which
-    // is grown to hold kc; and a residue plane per modulus over the upper tile
-    // pairs.
-    // Tile edge: 256-wide tiles run one to a CU at 2.0e15 products/s over whole
-    // rounds of the 256 CUs, 128-wide ones three to a CU at 1.45e15 (measured
-    // at S = 4096, n = 50,000 and S = 1000, n = 8192); the smaller time wins.
-    {
-        auto pairs = [&](int64_t tile) {
-            const int64_t q = (S + tile - 1) / tile;
-            return (double)(q * (q + 1) / 2) * GM_NP * T;
-        };
-        const double wide = ceil(pairs(256) / 256) * 4;
-        const double narrow = std::max(1.0, pairs(128) / 256) * 1.37;
-        L.gm_tile = wide < narrow ? 256 : 128;
-    }
-    L.gm_bk = L.gm_tile == 256 ? GM_BK : GM_BK_S;
-    if (L.lp_ns) {
+    // FP64 Gram by residue products: the residues take the zone above, as many
+    // samples at a time as fit (more chunks cost a read and a write of the residue
+    // planes each), which is grown to hold kc; and a residue plane per modulus
+    // over the upper tile pairs.
+    L.gm_f64 = L.lp_ns == 0 && gram_f64(n_total, S, T);
+    gram_tiles(n_total, S, T, L.gm_tile, L.gm_bk);
+    L.nsplit = L.lp_ns || L.gm_f64 ? gram_splits(n_total, S, T) : 1;
+    if (L.lp_ns || L.gm_f64) {
         L.part = take((size_t)L.nsplit * T * S * S * d);
     } else {
         const int64_t kpad = (n_total + GM_BK - 1) / GM_BK * GM_BK + (int64_t)(T - 1) * GM_BK;
@@ -193,14 +245,8 @@ static Layout compute_layout(int64_t n_total, int64_t S, int T, int D_max, int k
         L.gm_res = zone;
         L.gm_kc = std::min({(int64_t)((o - zone) / ((size_t)GM_NP * S)) / GM_BK * GM_BK, kpad, GM_KC_MAX});
         const size_t nt = (size_t)((S + L.gm_tile - 1) / L.gm_tile);
-        const size_t tiles = nt * (nt + 1) / 2;
-        // parts of a product's samples: about one workgroup of a chunk's tasks
-        // for each of the 256 CUs, while a part has GM_PART steps or more
-        const int64_t rows = std::min(std::max(n_total / T, (int64_t)1), L.gm_kc);
-        const int64_t wgs = (int64_t)tiles * GM_NP * std::min((int64_t)T, std::max(L.gm_kc / rows, (int64_t)1));
-        L.gm_ns = (int)std::max((int64_t)1, std::min({(256 + wgs / 2) / wgs, rows / (L.gm_bk * GM_PART),
-                                                      (int64_t)GM_NS_MAX}));
-        const size_t planes = tiles * L.gm_ns * T * GM_NP * L.gm_tile * L.gm_tile;
+        L.gm_ns = gram_parts(n_total, S, T, L.gm_tile, L.gm_bk, L.gm_kc);
+        const size_t planes = nt * (nt + 1) / 2 * L.gm_ns * T * GM_NP * L.gm_tile * L.gm_tile;
         L.part = take(std::max((size_t)S * S * d, planes));
     }
     L.merged = take((size_t)L.KP * 2 * d);
@@ -259,6 +305,7 @@ static void carve(sisso_l0 *h) {
     c.flags = (uint32_t *)(base + L.flags);
     c.gm_kb = (int64_t *)(base + L.gm_kb);
     c.gm_res = (uint8_t *)(base + L.gm_res);
+    c.gm_f64 = L.gm_f64;
     c.gm_tile = L.gm_tile;
     c.gm_ns = L.gm_ns;
     c.gm_kc = L.gm_kc;

@@ -12,7 +12,8 @@ namespace sl0 {
 constexpr int WAVE = 64;               // CDNA wavefront width
 constexpr double RANK_EPS = 1e-10;     // pivot ratio at or below which a tuple is rank-deficient
 constexpr double RANK_EPS_F32 = 1e-5;  // the same for the FP32 solve form (a few hundred units of 2^-23)
-constexpr int GRAM_TILE = 128;         // precision forms: Gram output tile (rows = cols)
+constexpr int GRAM_TILE = 128;         // FP64 products and precision forms: Gram output tile (rows = cols)
+constexpr int GRAM_KC = 16;            // FP64 products: samples per LDS stage (divides 256)
 constexpr int SEARCH_WG = 256;         // threads per search workgroup (4 waves)
 constexpr int SEARCH_WAVES = SEARCH_WG / WAVE;
 constexpr int SEARCH_WGS_MAX = 2048;   // largest persistent search grid (lists are sized for it)
@@ -267,12 +268,13 @@ struct Layout {
     size_t inv_s;      // double [T][S] 1/|x - mean| (0 for a constant column)
     size_t bhat;       // double [S][TP] normalised F_t^T y_t
     size_t G;          // double [S][S][TP] correlation matrices, task fastest
-    size_t part;       // precision forms: double [nsplit][T][S][S] raw centred Gram partial sums;
-                       // FP64: residue planes, bytes [gm_ns][T][tile pairs][GM_NP][gm_tile^2]; scratch of
+    size_t part;       // FP64 products and precision forms: double [nsplit][T][S][S] raw centred Gram
+                       // partial sums; else residue planes, bytes [gm_ns][T][tile pairs][GM_NP][gm_tile^2]; scratch of
                        // sisso_gram_read (at least S^2 doubles)
     size_t gm_kb;      // FP64 Gram: int64 [T+1] first padded sample of each task
     size_t gm_res;     // FP64 Gram: residues, bytes [GM_NP][S][gm_kc], over G and the regions of the search
     int gm_tile;       // FP64 Gram: tile edge of the products (128 or 256)
+    int gm_f64;        // FP64 Gram: on the FP64 matrix cores (no residues)
     int gm_ns;         // FP64 Gram: workgroups that share the samples of a product
     int64_t gm_kc;     // FP64 Gram: padded samples per chunk
     int gm_bk;         // FP64 Gram: samples per K-step

@@ -1,4 +1,5 @@
-// Per-task column statistics, and the finishing pass of the precision Grams.
+// Per-task column statistics, the FP64 Gram of short tasks on the FP64 matrix
+// cores, and its and the precision Grams' finishing pass.
 //
 // Every least-squares system the l0 step solves is the normal-equation
 // system of [1, x_i1, ..., x_iD] against y on the rows of one task.
@@ -192,7 +193,166 @@ __global__ __launch_bounds__(256) void stats_x_kernel(const double *__restrict__
     }
 }
 
-// ------------------------------------- finishing pass of the precision forms
+// ------------------------------------- a1: FP64 Gram on the FP64 matrix cores
+// For tasks of few rows, where the residue products' passes over the residues
+// and their planes cost more than the products (f64_products in the layout says
+// where).
+//
+// One workgroup (4 waves) computes a GRAM_TILE x GRAM_TILE block (bi <= bj)
+// of the centred Gram of one task over one split of its rows; each wave owns
+// a 64x64 quarter as 4x4 MFMA 16x16 accumulators.  Samples are staged through
+// LDS in chunks of GRAM_KC, centred on load (x - mean).
+//
+// v_mfma_f64_16x16x4f64 operand layout: A[i][k] in lane i + 16k, B[k][j] in
+// lane j + 16k, result D[i][j] in lane j + 16*(i%4), register i/4.
+typedef double double4_t __attribute__((ext_vector_type(4)));
+
+// LDS holds the chunk feature-major, [feature][sample] with a row of KC + 1
+// doubles: the loader's stores (16 consecutive samples of a feature) are
+// contiguous, and the MFMA operand reads (16 features at one sample) fall on
+// distinct banks (row stride 34 dwords).
+constexpr int LDS_STRIDE = GRAM_KC + 1;
+
+// One wave per SIMD is all this launch needs (about one workgroup per CU), so
+// the register budget is the whole file: no spills around the prefetch.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gram_f64_kernel(
+    const double *__restrict__ F, int64_t n_total, int64_t S, const int64_t *__restrict__ off,
+    const int32_t *__restrict__ torder, int T, const double *__restrict__ mu, int ntile, int nsplit,
+    double *__restrict__ part) {
+    __shared__ double As[GRAM_TILE][LDS_STRIDE];
+    __shared__ double Bs[GRAM_TILE][LDS_STRIDE];
+
+    // blockIdx.x -> (split, task rank, tile pair); tile pairs enumerate
+    // bi <= bj row by row; task ranks follow decreasing row counts
+    int64_t b = blockIdx.x;
+    const int npair = ntile * (ntile + 1) / 2;
+    const int split = (int)(b / ((int64_t)T * npair));
+    b -= (int64_t)split * T * npair;
+    const int tr = (int)(b / npair);
+    const int t = torder[tr];
+    int pr = (int)(b - (int64_t)tr * npair);
+    int bi = 0;
+    while (pr >= ntile - bi) {
+        pr -= ntile - bi;
+        ++bi;
+    }
+    const int bj = bi + pr;
+
+    const int64_t r0 = off[t], r1 = off[t + 1];
+    const int64_t nchunk = (r1 - r0 + GRAM_KC - 1) / GRAM_KC;
+    const int64_t per = (nchunk + nsplit - 1) / nsplit;
+    const int64_t c0 = (int64_t)split * per;
+    const int64_t c1 = c0 + per < nchunk ? c0 + per : nchunk;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = (wave >> 1) * 64;  // wave's row offset inside the tile
+    const int wc = (wave & 1) * 64;   // wave's column offset
+    const double *mut = mu + (int64_t)t * S;
+
+    double4_t acc[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[a][c] = (double4_t){0.0, 0.0, 0.0, 0.0};
+
+    // loader mapping: kk = tid % KC (consecutive samples), feature = tid / KC + FPP r
+    constexpr int FPP = 256 / GRAM_KC;          // features per loader pass
+    constexpr int NP = GRAM_TILE / FPP;         // loader passes per operand
+    const int kk = tid % GRAM_KC;
+    const int f0 = tid / GRAM_KC;
+    double muA[NP], muB[NP];
+#pragma unroll
+    for (int r = 0; r < NP; ++r) {
+        const int64_t ga = (int64_t)bi * GRAM_TILE + f0 + FPP * r;
+        const int64_t gb = (int64_t)bj * GRAM_TILE + f0 + FPP * r;
+        muA[r] = ga < S ? mut[ga] : 0.0;
+        muB[r] = gb < S ? mut[gb] : 0.0;
+    }
+
+    // register-staged double buffering: the global loads of chunk c+1 are in
+    // flight while the MFMAs of chunk c run out of LDS.  Loads are
+    // unconditional (row and feature clamped into range); masking and centring
+    // happen at the LDS store, so no load is waited on before the MFMAs.
+    int64_t fa[NP], fb[NP];
+    bool ina[NP], inb[NP];
+#pragma unroll
+    for (int r = 0; r < NP; ++r) {
+        const int64_t ga = (int64_t)bi * GRAM_TILE + f0 + FPP * r;
+        const int64_t gb = (int64_t)bj * GRAM_TILE + f0 + FPP * r;
+        ina[r] = ga < S;
+        inb[r] = gb < S;
+        fa[r] = (ina[r] ? ga : S - 1) * n_total;
+        fb[r] = (inb[r] ? gb : S - 1) * n_total;
+    }
+    double sa[NP], sb[NP];
+    int64_t row = r0 + c0 * GRAM_KC + kk;
+    if (c0 < c1) {
+        const int64_t rowc = row < r1 ? row : r1 - 1;
+#pragma unroll
+        for (int r = 0; r < NP; ++r) {
+            sa[r] = F[fa[r] + rowc];
+            sb[r] = F[fb[r] + rowc];
+        }
+#pragma unroll
+        for (int r = 0; r < NP; ++r) {
+            As[f0 + FPP * r][kk] = (row < r1 && ina[r]) ? sa[r] - muA[r] : 0.0;
+            Bs[f0 + FPP * r][kk] = (row < r1 && inb[r]) ? sb[r] - muB[r] : 0.0;
+        }
+    }
+    __syncthreads();
+    for (int64_t c = c0; c < c1; ++c) {
+        const bool more = c + 1 < c1;
+        row += GRAM_KC;
+        if (more) {
+            const int64_t rowc = row < r1 ? row : r1 - 1;
+#pragma unroll
+            for (int r = 0; r < NP; ++r) {
+                sa[r] = F[fa[r] + rowc];
+                sb[r] = F[fb[r] + rowc];
+            }
+        }
+#pragma unroll
+        for (int ks = 0; ks < GRAM_KC / 4; ++ks) {
+            const int krow = ks * 4 + (lane >> 4);
+            double a[4], bv[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) a[m] = As[wr + m * 16 + (lane & 15)][krow];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) bv[m] = Bs[wc + m * 16 + (lane & 15)][krow];
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int n = 0; n < 4; ++n)
+                    acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m], bv[n], acc[m][n], 0, 0, 0);
+        }
+        __syncthreads();
+        if (more) {
+#pragma unroll
+            for (int r = 0; r < NP; ++r) {
+                As[f0 + FPP * r][kk] = (row < r1 && ina[r]) ? sa[r] - muA[r] : 0.0;
+                Bs[f0 + FPP * r][kk] = (row < r1 && inb[r]) ? sb[r] - muB[r] : 0.0;
+            }
+        }
+        __syncthreads();
+    }
+
+    // store the raw block into part[split][t][i][j]
+    double *P = part + ((int64_t)split * T + t) * S * S;
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int n = 0; n < 4; ++n)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int64_t gi = (int64_t)bi * GRAM_TILE + wr + m * 16 + (lane >> 4) + 4 * r;
+                const int64_t gj = (int64_t)bj * GRAM_TILE + wc + n * 16 + (lane & 15);
+                if (gi < S && gj < S) P[gi * S + gj] = acc[m][n][r];
+            }
+}
+
+// --------------- finishing pass of the FP64 products and of the precision forms
 // Sum the split partials, scale to a correlation matrix and write the tiled
 // layout.  One workgroup per (task, 64x64 output tile pair ti <= tk): it reads
 // every partial of the canonical upper block once (coalesced rows), writes
@@ -373,10 +533,17 @@ int launch_stats(const Ctx &c, hipStream_t st) {
 int launch_gram(const Ctx &c, hipStream_t st) {
     phase_begin(c, SISSO_PHASE_GRAM, st);
     int rc = 0;
-    if (c.lp_ns == 0) {
+    if (c.lp_ns == 0 && !c.gm_f64) {
         rc = launch_gram_mod(c, st);
     } else {
-        rc = launch_gram_lp(c, c.lp_ns, st);
+        if (c.lp_ns > 0) {
+            rc = launch_gram_lp(c, c.lp_ns, st);
+        } else {
+            const int ntile = (int)((c.S + GRAM_TILE - 1) / GRAM_TILE);
+            const int64_t blocks = (int64_t)c.nsplit * c.T * ntile * (ntile + 1) / 2;
+            hipLaunchKernelGGL(gram_f64_kernel, dim3((unsigned)blocks), dim3(256), 0, st, c.F, c.n_total, c.S,
+                               c.off_dev, c.torder, c.T, c.mu, ntile, c.nsplit, c.part);
+        }
         const int64_t npair64 = c.Gnt * (c.Gnt + 1) / 2;
         double *G1 = c.G1 != c.G ? c.G1 : nullptr;
         if (c.T > 1 && c.TP <= 16) {

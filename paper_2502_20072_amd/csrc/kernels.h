@@ -21,6 +21,7 @@ struct Ctx {
     int64_t *gm_kb;                  // FP64 Gram: first padded sample of each task [T+1]
     uint8_t *gm_res;                 // FP64 Gram: residues [GM_NP][S][gm_kc]
     int64_t gm_kpad, gm_kc;          // FP64 Gram: padded samples in all, per chunk
+    int gm_f64;                      // FP64 Gram: on the FP64 matrix cores
     int gm_tile, gm_ns;              // FP64 Gram: tile edge of the products, parts of their samples
     int32_t *lp_cbase;               // precision form: first chunk of each task [T+1]
     int32_t *lp_exp;                 // precision form: chunk exponents [S][lp_nchunk]

@@ -96,6 +96,35 @@ def test_real_columns(kind, S, rows):
         assert np.array_equal(G, G.T)
 
 
+@pytest.mark.parametrize("S,rows", [
+    (1, [4]), (63, [3]), (130, [5]), (300, [16]), (1000, [30]), (1300, [9]),   # few rows: FP64 products
+    (129, [6, 21]), (600, [16, 33, 47]), (130, [5 + t % 3 for t in range(16)]),
+    (70, [4 + t for t in range(17)]), (200, [9] * 64),
+    (64, [600 + t for t in range(64)]),  # many long tasks of few features: FP64 products again
+    (33, [5000] * 4), (200, [3000, 7]),  # parts of the samples, one of the tasks too short for them
+    (260, [260] * 3), (257, [900] * 2),  # 128- and 256-wide tiles
+])
+def test_both_products(S, rows):
+    """Either side of the line between the FP64 products and the residue ones,
+    and the residue products' parts: within the rounding of FP64 sums (n / 2 U
+    with the centring, whatever their order) of 80-bit arithmetic, unit diagonal,
+    bitwise symmetric."""
+    rng = np.random.default_rng(S + len(rows))
+    off = np.concatenate([[0], np.cumsum(rows)])
+    F = rng.standard_normal((S, off[-1])) + rng.standard_normal((S, 1))
+    pick = np.unique(np.concatenate([np.arange(min(S, 20)), rng.integers(0, S, 30), [S - 1]]))
+    for t, G in enumerate(gram(F, off)):
+        x = F[:, off[t]:off[t + 1]].astype(np.longdouble)[pick]
+        x = x - x.mean(1, keepdims=True)
+        x /= np.sqrt((x * x).sum(1, keepdims=True))
+        ref = (x @ x.T).astype(float)
+        # x - mean carries U |x|; a task's columns of a few rows can be close to constant
+        raw = F[pick, off[t]:off[t + 1]]
+        amp = np.max(np.linalg.norm(raw, axis=1) / np.linalg.norm(raw - raw.mean(1, keepdims=True), axis=1))
+        assert np.abs(G[np.ix_(pick, pick)] - ref).max() <= (rows[t] / 2 + 30) * amp * U
+        assert np.all(np.diag(G) == 1.0) and np.array_equal(G, G.T)
+
+
 def test_dead_and_non_finite_columns():
     """A constant column's row, column and diagonal are zero; a non-finite one
     is reported by the readout of a search."""
