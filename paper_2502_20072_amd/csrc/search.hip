@@ -340,29 +340,41 @@ __device__ void wave_sort_list(double *Ls, uint64_t *Lr, int KP) {
         }
 }
 
-// Empties the later copies of equal entries of a sorted list (one tuple reached
-// from several prefixes), sorts again, and returns the number of entries left.
-__device__ int wave_drop_copies(double *Ls, uint64_t *Lr, int KP) {
+// Drops the later copies of equal entries of a sorted, full list (one tuple
+// reached from several prefixes); the places behind the others are empty.
+__device__ void wave_drop_copies(double *Ls, uint64_t *Lr, int KP) {
     const int lane = threadIdx.x & 63;
-    unsigned copy = 0;
     int n = 0;
+    double ps = INF;  // the entry before the chunk
+    uint64_t pr = ~0ull;
     for (int m = 0; m < KP; m += 64) {
-        const int e = m + lane;
-        const bool c = e > 0 && Ls[e] < INF && Ls[e] == Ls[e - 1] && Lr[e] == Lr[e - 1];
-        copy |= (unsigned)c << (m >> 6);
-        n += __popcll(__ballot(!c && Ls[e] < INF));
-    }
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_wave_barrier();
-    for (int m = 0; m < KP; m += 64)
-        if ((copy >> (m >> 6)) & 1u) {
-            Ls[m + lane] = INF;
-            Lr[m + lane] = ~0ull;
+        const double v = Ls[m + lane];
+        const uint64_t r = Lr[m + lane];
+        double vb = __shfl_up(v, 1);
+        uint64_t rb = (uint64_t)__shfl_up((long long)r, 1);
+        if (lane == 0) {
+            vb = ps;
+            rb = pr;
         }
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_wave_barrier();
-    if (__any(copy != 0)) wave_sort_list(Ls, Lr, KP);
-    return n;
+        ps = __shfl(v, 63);
+        pr = (uint64_t)__shfl((long long)r, 63);
+        const bool keep = v < INF && !(v == vb && r == rb);
+        const unsigned long long b = __ballot(keep);
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_wave_barrier();
+        Ls[m + lane] = INF;
+        Lr[m + lane] = ~0ull;
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_wave_barrier();
+        if (keep) {
+            const int to = n + __popcll(b & ((1ull << lane) - 1ull));
+            Ls[to] = v;
+            Lr[to] = r;
+        }
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_wave_barrier();
+        n += __popcll(b);
+    }
 }
 
 // ------------------------------------------------------------ init kernel
@@ -3466,8 +3478,10 @@ __global__ __launch_bounds__(256) void list_pool_kernel(Ctx c, const int32_t *__
 // list as in the exhaustive search (bound: own KP-th entry and the
 // device-wide bound).  The lists feed the same merge, re-score and final
 // ordering (merge removes tuples that several prefixes produced).
+// (M = 3: registers for three waves per SIMD, n = 60,000: 577 us at two, 521 at three)
 template <int M>
-__global__ __launch_bounds__(256) void list_search_kernel(Ctx c, const int32_t *__restrict__ pre, int64_t n) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(M == 3 ? 3 : 1))) void list_search_kernel(
+    Ctx c, const int32_t *__restrict__ pre, int64_t n) {
     extern __shared__ double smem[];
     const int KP = c.KP;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -3478,7 +3492,7 @@ __global__ __launch_bounds__(256) void list_search_kernel(Ctx c, const int32_t *
         Lr[m] = ~0ull;
     }
     double theta_pub = INF;
-    int fill = 0;  // entries appended while the list is filling (sorted once full)
+    int fill = 0;  // entries appended (KP: the list is sorted)
     unsigned offered = 0;  // tuples offered to the list (diagnostics; one atomic per wave)
     const int64_t gw = (int64_t)blockIdx.x * SEARCH_WAVES + wave;
     const int64_t nw = (int64_t)gridDim.x * SEARCH_WAVES;
@@ -3611,11 +3625,11 @@ __global__ __launch_bounds__(256) void list_search_kernel(Ctx c, const int32_t *
             }
             unsigned long long m = __ballot(sse < INF && sse <= th);
             offered += (unsigned)__popcll(m);
-            while (fill < KP && m) {
+            if (fill < KP && m) {
                 // the list is not full: append (one slot per passing lane), and
-                // sort once it is; copies of one tuple among the entries are
-                // dropped, so a full list holds KP tuples and its last entry
-                // bounds the KP-th best
+                // sort once it is and drop the copies of a tuple, so that a full
+                // list holds KP tuples and its last entry bounds the KP-th best;
+                // from there on the entries are inserted
                 const int rank = __popcll(m & ((1ull << lane) - 1ull));
                 const int nfit = min(__popcll(m), KP - fill);
                 const bool mine = ((m >> lane) & 1ull) && rank < nfit;
@@ -3629,7 +3643,7 @@ __global__ __launch_bounds__(256) void list_search_kernel(Ctx c, const int32_t *
                 fill += nfit;
                 if (fill == KP) {
                     wave_sort_list(Ls, Lr, KP);
-                    fill = wave_drop_copies(Ls, Lr, KP);
+                    wave_drop_copies(Ls, Lr, KP);
                 }
             }
             while (m) {
@@ -4609,7 +4623,9 @@ int launch_list_search(const Ctx &c, int D, int k, const int32_t *pre, int64_t n
     phase_begin(c, SISSO_PHASE_PREPASS, st);
     hipLaunchKernelGGL(list_init_kernel, dim3(init_blocks > PRE_BINS / 256 ? init_blocks : PRE_BINS / 256), dim3(256),
                        0, st, c);
-    if (c.T == 1 && n > 0) {
+    // (one row: a single wave's list, which the merge takes as it is; with the
+    // pool 177 us, without 161)
+    if (c.T == 1 && n > 1) {
         const int64_t np = n < LIST_POOL ? n : LIST_POOL;
         const dim3 grid((unsigned)((np + 3) / 4));
         switch (D - 1) {
