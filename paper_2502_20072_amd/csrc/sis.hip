@@ -227,17 +227,29 @@ __device__ inline void screen_load(const double *__restrict__ X, const int64_t *
                                    const int64_t *__restrict__ cb, int64_t s0, int cnt, double *tile, int lane) {
     const int s = lane & (SC_TS - 1);
     if (s >= cnt) return;
-    // all loads in flight where the registers allow it (one residual: five
-    // passes over 79,800 pairs, n = 1500: 1371 -> 1093 us)
-    constexpr int UN = NR == 1 ? 16 : 4;
-#pragma unroll UN
-    for (int q = 0; q < 16; ++q) {
-        const int slot = (lane >> 4) + 4 * q;
-        const double a = X[ca[slot] + s0 + s];
-        double v;
-        if constexpr (is_binary(OP)) v = apply<OP>(a, X[cb[slot] + s0 + s]);
-        else v = apply<OP>(a, 0.0);
-        tile[slot * SC_LD + s] = v;
+    // As many loads in flight as the registers allow, before the first value is
+    // used.  A fifth of the groups of 179,700 pairs (600 children) have several
+    // first children: with four loads in flight they were the last to end.
+    // (2000 samples, sums: 3 residuals 16 % less time, 10: 36 %.)
+    constexpr int UN = NR <= 4 ? 16 : 8;
+#pragma unroll 1
+    for (int q0 = 0; q0 < 16; q0 += UN) {
+        double a[UN], b[UN];
+#pragma unroll
+        for (int q = 0; q < UN; ++q) {
+            const int slot = (lane >> 4) + 4 * (q0 + q);
+            a[q] = X[ca[slot] + s0 + s];
+            if constexpr (is_binary(OP)) b[q] = X[cb[slot] + s0 + s];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < UN; ++q) {
+            const int slot = (lane >> 4) + 4 * (q0 + q);
+            double v;
+            if constexpr (is_binary(OP)) v = apply<OP>(a[q], b[q]);
+            else v = apply<OP>(a[q], 0.0);
+            tile[slot * SC_LD + s] = v;
+        }
     }
 }
 
@@ -368,9 +380,15 @@ __device__ inline void screen_pass(const double *__restrict__ X, const int64_t *
                 residuals(rv, s0);
             }
             next.store(tile, lane);
-            // (a task's last tile is fetched again rather than passed)
-            next.fetch(r1 - s0 >= 3 * SC_TS ? SC_TS : 0);
-            if (AHEAD) residuals(rn, r1 - s0 >= 2 * SC_TS ? s0 + SC_TS : s0);
+            // Stored columns: a task's last tile is fetched again rather than
+            // passed (n = 2000, 10 residuals: 14 % less time).  Created ones: no
+            // such load (with the loads of partial tiles in flight together, 20 to
+            // 50 samples a task, 2 and 3 residuals: 9 and 18 % less).
+            const bool more = r1 - s0 >= 2 * SC_TS;
+            if (OP == OP_STORED || more) {
+                next.fetch(OP != OP_STORED || r1 - s0 >= 3 * SC_TS ? SC_TS : 0);
+                if (AHEAD) residuals(rn, more ? s0 + SC_TS : s0);
+            }
             wave_lds_sync();
             if (FIRST && s0 == r0) K = tile[lane * SC_LD];
             screen_tile<NR, RULES, true>(tile, lane, rv, SC_TS, K, A, vmin, vmax);
