@@ -40,3 +40,24 @@ def test_d2_grids_and_ranges(kind):
         gi, gs, _ = search(p, 2, kk, rng=(r0, r1))
         oi, os_, _ = oracle.topk(p.F, p.y, 2, kk, p.task_offsets, i1_range=(lo, hi))
         compare_topk(p, 2, kk, gi, gs, oi, os_)
+
+
+@pytest.mark.parametrize("form", ["bf16", "fp16", "fp32"])
+@pytest.mark.parametrize("kind", ["planted", "noise"])
+@pytest.mark.parametrize("S", [65, 200])
+def test_d2_precision_forms(S, kind, form):
+    """The sliced Grams' matrices, and the FP32 solve.  Their errors (1e-6 of a
+    correlation and of c) are far below the margin of the extra candidates that
+    are re-scored in FP64, so the list is the oracle's to the FP64 tolerance."""
+    from paper_2502_20072_amd import L0Search, _binding as B
+    prec = {"bf16": B.SISSO_PREC_BF16_COMP, "fp16": B.SISSO_PREC_FP16_COMP, "fp32": B.SISSO_PREC_FP32_SOLVE}[form]
+    p = problem(kind, S, 1, 2, 8500 + S)
+    k = 20
+    print(f"{form} {kind} S={S}", flush=True)
+    s = L0Search(p.F, p.y, p.task_offsets, D_max=2, k_max=k, precision=prec)
+    s.gram()
+    s.search(2, k)
+    gi, gs, _ = s.topk()
+    s.close()
+    oi, os_, _ = oracle.topk(p.F, p.y, 2, k, p.task_offsets)
+    compare_topk(p, 2, k, gi, gs, oi, os_)
