@@ -109,10 +109,12 @@ typedef struct {
 /* Device bytes the caller must provide in desc->workspace for this problem
  * shape (pure function of n_total, S, T, D_max, k_max and precision; reads
  * no pointer).  With D_max >= 3 it includes the D = 3 search's tables
- * (24 S^2 bytes) and its pools of flagged candidates (with several tasks 2 GB
- * at S = 5000 and at most 4.3 GB, with one about a quarter of it), and with
- * several tasks the filter task's matrix (S^2 doubles).  Returns 0 if the
- * shape is invalid. */
+ * (24 S^2 bytes) and its pools of flagged candidates (with one task 0.5 GB at
+ * S = 5000 and at most 0.7 GB, with several 1.5 GB and at most 2.3 GB), and
+ * with several tasks the filter task's matrix (S^2 doubles).  The FP64 Gram's
+ * residues lie over the search's regions, which are grown to hold them (D_max
+ * = 2, one task, in all: 0.06 GB at S = 300 and n = 50,000, 1.1 GB at S = 4096).
+ * Returns 0 if the shape is invalid. */
 size_t sisso_l0_workspace_bytes(const sisso_l0_desc *desc);
 
 /* Validate the descriptor and create a handle in *out.  Errors: EINVAL for
