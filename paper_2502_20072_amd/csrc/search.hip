@@ -52,9 +52,7 @@ constexpr int MAXD = SISSO_MAX_D;
 constexpr double INF = __builtin_huge_val();
 constexpr double THETA_SLACK = 1e-9;  // relative slack of the filter bound
 constexpr double THETA_SLACK_F32 = 1e-5;  // FP32 solve form: absolute slack, in units of sum_t c_t
-#ifndef SEARCH_JG
-#define SEARCH_JG 8  // G rows per prefetch group (two groups in flight)
-#endif
+constexpr int SEARCH_JG = 8;  // G rows per prefetch group (two groups in flight)
 
 __device__ inline bool key_less(double s1, uint64_t r1, double s2, uint64_t r2) {
     return s1 < s2 || (s1 == s2 && r1 < r2);
@@ -1454,15 +1452,11 @@ __global__ __launch_bounds__(256) void search_kernel(Ctx c, SearchArgs a) {
 // instructions as a scalar operand, at no LDS or vector-memory cost.
 constexpr int S3_NR = 4;              // i1 per group
 constexpr int BU = 64;                // rows and columns of a unit (a tile of G)
-#ifndef BU_WGS
-#define BU_WGS 1024                   // workgroups of the bound kernels: four per CU (LDS)
-#endif
+constexpr int BU_WGS = 1024;  // workgroups of the bound kernels: four per CU (LDS)
 constexpr int S3_LANES = 32;          // flagged (row, column) pairs of a unit taken one per lane, one task
 constexpr int S3_LANES_MT = 128;      //   the same, several tasks; with more, the flagged rows are swept whole
 constexpr int S3_JR = BU;
-#ifndef S3_JG
-#define S3_JG 2                       // G rows per prefetch group (two groups in flight)
-#endif
+constexpr int S3_JG = 2;  // G rows per prefetch group (two groups in flight)
 constexpr int S3_XCDS = 8;            // XCDs of the chip
 
 // Rows of the record table: group g (i1 = S3_NR g .. S3_NR g + 3) holds rows
@@ -1701,9 +1695,7 @@ __device__ void s3_tile_table(const Ctx &c) {
 }
 uint64_t s3_items_host(int64_t S) { return bound_items<S3Groups>(S, bound_run(bound_units<S3Groups>(S)), nullptr); }
 
-#ifndef S3_WPE
-#define S3_WPE 4                      // waves per SIMD the register budget is sized for
-#endif
+constexpr int S3_WPE = 4;  // waves per SIMD the register budget is sized for
 // Several tasks, D = 3: tuples that pass the filter task's own test are
 // buffered in LDS (key, filter-task SSE), and mt_flush takes up to 64 of them,
 // one per lane: the second largest task's SSE is added (a tighter lower
@@ -2568,9 +2560,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void s
 }
 
 // ---------------------------------------- batched D = 3 search (one task)
-#ifndef S3B_WPE
-#define S3B_WPE 3                     // waves per SIMD of the batched kernel (its per-problem state)
-#endif
+constexpr int S3B_WPE = 3;  // waves per SIMD of the batched kernel (its per-problem state)
 // Several independent one-task problems searched by one launch: the record
 // tables and pre-pass bounds of every problem are built first (each problem
 // on its own), then the workgroups of one persistent grid pull entries from a
@@ -2707,9 +2697,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3B_WPE))) 
 // against 0.5 ms for a table of all triples and 5.3 ms for the tuples' own
 // tests.  The bound is limited by FP64 issue (vector and matrix, 60 per cent of
 // the cycles); tables and blocks of G take the rest.
-#ifndef S4_WPE
-#define S4_WPE 4                      // waves per SIMD the register budget is sized for
-#endif
+constexpr int S4_WPE = 4;  // waves per SIMD the register budget is sized for
 constexpr int S4_NR = 4;              // indices per group
 constexpr int S4_DR = 16;             // rows of a dense item (of a unit taken whole)
 constexpr int S4_ITEMS = S4_NR * S3_JR / S4_DR;  // dense items of a unit
@@ -3137,9 +3125,7 @@ __device__ __forceinline__ void s4_dense(const Ctx &c, const SearchArgs &a, uint
 }
 
 // Scores the pools, as s3_eval_kernel does.
-#ifndef S4E_WPE
-#define S4E_WPE 3
-#endif
+constexpr int S4E_WPE = 3;
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S4E_WPE))) void s4_eval_kernel(Ctx c, SearchArgs a, uint32_t nseg, uint32_t wg_units, int resume) {
     extern __shared__ double smem[];
     __shared__ double s_r[SEARCH_WAVES][S4_DR][S4_NR][6];
@@ -4505,7 +4491,13 @@ int launch_search(const Ctx &c, const SearchCall &sc, hipStream_t st) {
                 if (MT) launch_one<2, true>(c, a, lds, st);
                 else hipLaunchKernelGGL((search_kernel<2, false, float>), dim3(c.search_wgs), dim3(SEARCH_WG), lds, st, c, a);
                 break;
-            case 3: MT ? launch_one<3, true>(c, a, lds, st) : launch_one<3, false>(c, a, lds, st); break;
+            // (D = 3 too: 2^31 items of the record-table sweep are some 150,000
+            // features, whose table is larger than the card's memory)
+            case 3:
+                if (!c.fp32) return -1;
+                if (MT) hipLaunchKernelGGL((search_kernel<3, true, float>), dim3(c.search_wgs), dim3(SEARCH_WG), lds, st, c, a);
+                else hipLaunchKernelGGL((search_kernel<3, false, float>), dim3(c.search_wgs), dim3(SEARCH_WG), lds, st, c, a);
+                break;
             case 4: MT ? launch_one<4, true>(c, a, lds, st) : launch_one<4, false>(c, a, lds, st); break;
             default: return -1;
         }
