@@ -252,8 +252,9 @@ int32_t sisso_l0_topk(sisso_l0 *h, int32_t k, int32_t *idx, double *sse, double 
  * with a unit diagonal (0 on the diagonal, and 0 in the row and column, of a
  * column constant on the task as defined at sisso_l0_search); b (S
  * doubles) b_j = x_jc.y_c / |x_jc|; c (1 double) |y_c|^2, where x_c, y_c are
- * the task's columns minus their means.  ESTATE before sisso_gram, EINVAL for
- * t out of range. */
+ * the task's columns minus their means.  G's errors are relative to the
+ * diagonal, not to an entry that is far below it.  ESTATE before sisso_gram,
+ * EINVAL for t out of range. */
 int32_t sisso_gram_read(sisso_l0 *h, int32_t t, double *G, double *b, double *c);
 
 /* Number of tuples the last search scored (C(S, D), or r1 - r0 for a range
