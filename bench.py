@@ -121,7 +121,8 @@ def gram_roofline(p, name: str, prec: int, gram_ms: float) -> dict:
     kern = "gram_lp_kernel" if form in ("bf16", "fp16") else "gram_mod_kernel"
     achieved = alg * GRAM_PRODUCTS[form] / (gram_ms * 1e-3)
     return dict(bound="mfma", kernel=kern, achieved=achieved / 1e12, peak=MFMA_PEAK[form] / 1e12,
-                unit="TFLOP/s" if form in ("bf16", "fp16") else "TOP/s", frac=achieved / MFMA_PEAK[form], traffic=measured_traffic(kern, name), algorithmic_flop=alg,
+                unit="TFLOP/s" if form in ("bf16", "fp16") else "TOP/s", frac=achieved / MFMA_PEAK[form],
+                traffic=None if form == "fp16" else measured_traffic(kern, name), algorithmic_flop=alg,  # (taken for BF16)
                 mfma_products=GRAM_PRODUCTS[form], gram_ms=gram_ms,
                 note="phase time: the Gram launches (FP64: residues and their products) and the "
                      "finishing pass")

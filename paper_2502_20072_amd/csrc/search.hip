@@ -2121,8 +2121,9 @@ __device__ __forceinline__ void bound_load(double *__restrict__ s_g, const doubl
 // per (j, k).  (The matrix cores multiply FP64 at the vector units' rate; what
 // the blocks save is the rows' operands: read by scalar loads, 96 bytes a row
 // and wave, they held a vector form of this loop at 530 us for n = 2000, S =
-// 600, D = 4 (422 here) and at 56 us for S = 1000, D = 3 (45).)  Operands of v_mfma_f64_16x16x4f64: A[i][f] in lane i + 16 f,
-// B[f][c] in lane c + 16 f, D[i][c] in lane c + 16 (i % 4), register i / 4.
+// 600, D = 4 (422 here) and at 56 us for S = 1000, D = 3 (45).)
+// Operands of v_mfma_f64_16x16x4f64: A[i][f] in lane i + 16 f, B[f][c] in lane
+// c + 16 f, D[i][c] in lane c + 16 (i % 4), register i / 4.
 // Passing pairs: `lanes` of them; lane e = 16 rb + 4 cb + i returns those of
 // the 16 x 16 block (rb, cb)'s rows 4 i .. 4 i + 3 in m, bit 16 h + c for row 16
 // rb + 4 i + h and column 16 cb + c.
@@ -2315,7 +2316,10 @@ __device__ inline uint64_t s3_cand(int64_t g, int64_t j, int64_t k) {
 // The groups of the best features are flagged on most rows, so the pools are
 // scored by a kernel of their own, spread evenly: scored where they were found
 // they left a few waves running long after the rest (n = 2000, S = 1000: 145
-// us against 105 without the bound).
+// us against 105 without the bound; the two kernels take 43 and 22).  Vector
+// instructions and the matrix cores take 0.58 of the CUs' busy cycles here; the
+// rest waits for tables and blocks of G, and the CUs are idle for 0.4 of the
+// kernel, at its start and as its waves end.
 __device__ inline uint64_t s3_row_item(int64_t octet, int64_t g, int64_t kcx, unsigned mask) {
     return ((uint64_t)octet << 42) | ((uint64_t)g << 22) | ((uint64_t)kcx << 8) | mask;
 }
@@ -2693,10 +2697,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S3B_WPE))) 
 // its workgroup's segments of two pools, which s4_eval_kernel scores: the
 // candidates (g1, g2, j, k) one per lane while there are at most S4_LANES of
 // them, else (also without a threshold) the whole unit, in items of one i2 and
-// S4_DR rows.  n = 2000, S = 600: tables 50 us, bound 420 us, scoring 150 us,
+// S4_DR rows.  n = 2000, S = 600: tables 47 us, bound 420 us, scoring 170 us,
 // against 0.5 ms for a table of all triples and 5.3 ms for the tuples' own
-// tests.  The bound is limited by FP64 issue (vector and matrix, 60 per cent of
-// the cycles); tables and blocks of G take the rest.
+// tests.  The bound is limited by FP64 issue: vector instructions (at four
+// cycles each) and the matrix cores take 0.65 of the CUs' busy cycles, which are
+// 0.86 of the kernel's; tables and blocks of G take the rest.
 constexpr int S4_WPE = 4;  // waves per SIMD the register budget is sized for
 constexpr int S4_NR = 4;              // indices per group
 constexpr int S4_DR = 16;             // rows of a dense item (of a unit taken whole)
