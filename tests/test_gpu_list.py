@@ -74,6 +74,29 @@ def test_copies_do_not_fill_a_list(S, D, T, grid):
 
 
 @pytest.mark.parametrize("T", [1, 2])
+@pytest.mark.parametrize("S,reps", [(64, 1), (65, 1), (66, 1), (33, 2), (34, 2), (129, 2), (130, 2), (130, 5)])
+def test_merge_of_copies(S, reps, T):
+    """Four rows (one feature each), each up to five times: 252 to 2580
+    candidates reach the merge, the six pairs of the four features from two
+    rows, all of them `reps` times.  Either side of what is ranked by counting
+    (256 candidates) and of the sort's batches (1024)."""
+    import torch
+    from paper_2502_20072_amd import L0Search
+    from paper_2502_20072_amd import _binding as B
+    p = tiny_problem(6400 + S + T, S=S, n=45 * T, T=T, D=2, sigma=0.3)
+    pre = np.tile(np.arange(4, dtype=np.int32)[:, None], (reps, 1))
+    k = min(480, 4 * (S - 1) - 6)
+    s = L0Search(p.F, p.y, p.task_offsets, D_max=2, k_max=k)
+    s.gram()
+    B.sisso_l0_search_list(s.handle, 2, k, torch.from_numpy(pre).to("cuda"))
+    s.last_D, s.last_k = 2, k
+    gi, gs, _ = s.topk()
+    s.close()
+    oi, os_, _ = oracle.topk(p.F, p.y, 2, k, p.task_offsets, i1_range=(0, 4))
+    compare_topk(p, 2, k, gi, gs, oi, os_)
+
+
+@pytest.mark.parametrize("T", [1, 2])
 @pytest.mark.parametrize("D", [2, 3, 4])
 def test_empty_list(D, T):
     """A list without rows has no tuples: every result row is marked empty."""
