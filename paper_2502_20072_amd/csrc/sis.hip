@@ -231,28 +231,39 @@ __device__ inline void screen_load(const double *__restrict__ X, const int64_t *
                                    const int64_t *__restrict__ cb, int64_t s0, int cnt, double *tile, int lane) {
     const int s = lane & (SC_TS - 1);
     if (s >= cnt) return;
-    // As many loads in flight as the registers allow, before the first value is
-    // used.  A fifth of the groups of 179,700 pairs (600 children) have several
-    // first children: with four loads in flight they were the last to end.
-    // (2000 samples, sums: 3 residuals 16 % less time, 10: 36 %.)
-    constexpr int UN = NR <= 4 ? 16 : 8;
-#pragma unroll 1
-    for (int q0 = 0; q0 < 16; q0 += UN) {
-        double a[UN], b[UN];
+    // As many loads in flight as the registers allow.  A fifth of the groups of
+    // 179,700 pairs (600 children) have several first children: with four loads
+    // in flight they were the last to end.  (2000 samples, sums: 3 residuals 16 %
+    // less time, 10: 36 %.)  With few residuals the compiler orders the loads and
+    // operators of two columns better (quotients, one and two residuals: 20 and
+    // 10 % less time than with the barrier); with more it takes too few at a time.
+    if constexpr (is_binary(OP) && NR <= 2) {
 #pragma unroll
-        for (int q = 0; q < UN; ++q) {
-            const int slot = (lane >> 4) + 4 * (q0 + q);
-            a[q] = X[ca[slot] + s0 + s];
-            if constexpr (is_binary(OP)) b[q] = X[cb[slot] + s0 + s];
+        for (int q = 0; q < 16; ++q) {
+            const int slot = (lane >> 4) + 4 * q;
+            const double a = X[ca[slot] + s0 + s];
+            tile[slot * SC_LD + s] = apply<OP>(a, X[cb[slot] + s0 + s]);
         }
-        __builtin_amdgcn_sched_barrier(0);
+    } else {
+        constexpr int UN = NR <= 4 ? 16 : 8;
+#pragma unroll 1
+        for (int q0 = 0; q0 < 16; q0 += UN) {
+            double a[UN], b[UN];
 #pragma unroll
-        for (int q = 0; q < UN; ++q) {
-            const int slot = (lane >> 4) + 4 * (q0 + q);
-            double v;
-            if constexpr (is_binary(OP)) v = apply<OP>(a[q], b[q]);
-            else v = apply<OP>(a[q], 0.0);
-            tile[slot * SC_LD + s] = v;
+            for (int q = 0; q < UN; ++q) {
+                const int slot = (lane >> 4) + 4 * (q0 + q);
+                a[q] = X[ca[slot] + s0 + s];
+                if constexpr (is_binary(OP)) b[q] = X[cb[slot] + s0 + s];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < UN; ++q) {
+                const int slot = (lane >> 4) + 4 * (q0 + q);
+                double v;
+                if constexpr (is_binary(OP)) v = apply<OP>(a[q], b[q]);
+                else v = apply<OP>(a[q], 0.0);
+                tile[slot * SC_LD + s] = v;
+            }
         }
     }
 }
@@ -370,6 +381,13 @@ __device__ inline void screen_pass(const double *__restrict__ X, const int64_t *
     if (!is_binary(OP) || ua >= 0) {
         ScreenCols<OP> next(X, ca, cb, ua, r0, lane);
         constexpr bool AHEAD = NR > 1 && NR <= SC_AHEAD;
+        // A task's last tile is fetched again rather than passed, where loads
+        // without a condition are faster: stored columns (n = 2000, 10 residuals:
+        // 14 % less time), operators of one column with many residuals (16: 13 %),
+        // quotients with one.  Elsewhere it isn't (with the loads of partial tiles
+        // in flight together, 20 to 50 samples a task, 2 and 3 residuals: 9 and 18
+        // % less).
+        constexpr bool AGAIN = OP == OP_STORED || (!is_binary(OP) && NR > 4) || (OP == SISSO_OP_DIV && NR == 1);
         double rn[NR];
         if (r1 - r0 >= SC_TS) {
             next.fetch(r1 - r0 >= 2 * SC_TS ? SC_TS : 0);
@@ -384,13 +402,9 @@ __device__ inline void screen_pass(const double *__restrict__ X, const int64_t *
                 residuals(rv, s0);
             }
             next.store(tile, lane);
-            // Stored columns: a task's last tile is fetched again rather than
-            // passed (n = 2000, 10 residuals: 14 % less time).  Created ones: no
-            // such load (with the loads of partial tiles in flight together, 20 to
-            // 50 samples a task, 2 and 3 residuals: 9 and 18 % less).
             const bool more = r1 - s0 >= 2 * SC_TS;
-            if (OP == OP_STORED || more) {
-                next.fetch(OP != OP_STORED || r1 - s0 >= 3 * SC_TS ? SC_TS : 0);
+            if (AGAIN || more) {
+                next.fetch(!AGAIN || r1 - s0 >= 3 * SC_TS ? SC_TS : 0);
                 if (AHEAD) residuals(rn, more ? s0 + SC_TS : s0);
             }
             wave_lds_sync();
