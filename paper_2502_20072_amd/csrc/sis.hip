@@ -234,15 +234,22 @@ __device__ inline void screen_load(const double *__restrict__ X, const int64_t *
     // As many loads in flight as the registers allow.  A fifth of the groups of
     // 179,700 pairs (600 children) have several first children: with four loads
     // in flight they were the last to end.  (2000 samples, sums: 3 residuals 16 %
-    // less time, 10: 36 %.)  With few residuals the compiler orders the loads and
-    // operators of two columns better (quotients, one and two residuals: 20 and
-    // 10 % less time than with the barrier); with more it takes too few at a time.
-    if constexpr (is_binary(OP) && NR <= 2) {
-#pragma unroll
+    // less time, 10: 36 %.)  With one and two residuals the compiler orders the
+    // loads and operators of two columns better (quotients: 20 and 10 % less time
+    // than with the barrier); with more it takes too few at a time.  Operators of
+    // one column come here for a task's last samples only: up to eight residuals
+    // four at a time (sines, 5: 17 % less time than with the barrier).
+    constexpr bool BARRIER = OP == OP_STORED || NR > (is_binary(OP) ? 2 : 8);
+    if constexpr (!BARRIER) {
+        constexpr int UN = is_binary(OP) || NR == 1 ? 16 : 4;
+#pragma unroll UN
         for (int q = 0; q < 16; ++q) {
             const int slot = (lane >> 4) + 4 * q;
             const double a = X[ca[slot] + s0 + s];
-            tile[slot * SC_LD + s] = apply<OP>(a, X[cb[slot] + s0 + s]);
+            double v;
+            if constexpr (is_binary(OP)) v = apply<OP>(a, X[cb[slot] + s0 + s]);
+            else v = apply<OP>(a, 0.0);
+            tile[slot * SC_LD + s] = v;
         }
     } else {
         constexpr int UN = NR <= 4 ? 16 : 8;
