@@ -2317,9 +2317,9 @@ __device__ inline uint64_t s3_cand(int64_t g, int64_t j, int64_t k) {
 // scored by a kernel of their own, spread evenly: scored where they were found
 // they left a few waves running long after the rest (n = 2000, S = 1000: 145
 // us against 105 without the bound; the two kernels take 43 and 22).  Vector
-// instructions and the matrix cores take 0.58 of the CUs' busy cycles here; the
-// rest waits for tables and blocks of G, and the CUs are idle for 0.4 of the
-// kernel, at its start and as its waves end.
+// instructions and the matrix cores take 0.54 to 0.58 of the CUs' busy cycles
+// here; the rest waits for tables and blocks of G, and the CUs are idle for 0.4
+// to 0.45 of the kernel, at its start and as its waves end.
 __device__ inline uint64_t s3_row_item(int64_t octet, int64_t g, int64_t kcx, unsigned mask) {
     return ((uint64_t)octet << 42) | ((uint64_t)g << 22) | ((uint64_t)kcx << 8) | mask;
 }
@@ -3804,9 +3804,6 @@ __global__ __launch_bounds__(MERGE_THREADS) void merge_compact_kernel(Ctx c, int
     }
 }
 
-// merge_select: one workgroup selects the KP smallest (SSE, key) pairs of
-// the candidates with bitonic sorts in LDS, carrying a running top-KP across
-// fills of the buffer when there are many.
 // Takes the later copies of equal (SSE, key) pairs out of the N sorted entries and
 // closes the gaps; the places behind the others are empty.  (A prefix-list
 // search can offer one tuple from several prefixes, always with bitwise the
@@ -3854,6 +3851,9 @@ __device__ void drop_adjacent_duplicates(double *ks, uint64_t *kr, int N) {
     __syncthreads();
 }
 
+// merge_select: one workgroup selects the KP smallest (SSE, key) pairs of
+// the candidates with bitonic sorts in LDS, carrying a running top-KP across
+// fills of the buffer when there are many.
 __global__ __launch_bounds__(MERGE_THREADS) void merge_select_kernel(Ctx c, int KP, int use_pre, int dedupe,
                                                                      int nlists, const uint32_t *nl_dev) {
     __shared__ double ks[MERGE_CAP];

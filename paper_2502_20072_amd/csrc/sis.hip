@@ -146,8 +146,8 @@ __global__ void __launch_bounds__(256) fc_eval_kernel(const double *__restrict__
 // Created values: a CU that has waves is held by FP64 issue (17 instructions a
 // value and ten residuals: the vector instructions take 0.73 of the CUs' busy
 // cycles at four cycles each, and an FP64 one takes 5.4 to 5.75), but the CUs
-// are busy for 0.7 of the kernel only, as 7805 groups on 3072 places leave the
-// last round half empty.  Stored values: HBM (6.0 TB/s, vector instructions 0.4).
+// are busy for 0.62 to 0.76 of the kernel only, as 7805 groups on 3072 places
+// leave the last round half empty.  Stored values: HBM (6.0 TB/s, vector instructions 0.4).
 // Read by scalar loads instead, the residuals (160 KB at n = 2000, ten times the
 // scalar cache) were waited for half of the time: 499,500 sums of two of 1000
 // columns, n = 2000, 10 residuals: 1395 us, now 1025; 300,000 stored columns, n =
