@@ -164,7 +164,8 @@ __global__ __launch_bounds__(256) void residue_kernel(const double *__restrict__
 // early).  The 16-byte pieces of an LDS row are permuted by the row
 // (XOR) so that the 16 rows of a fragment read fall on distinct banks: rows
 // i % 16 for B, and for A rows that differ in bits 0, 1 and log2(4 MB) and up.
-template <int TM, int WM, int WN, int BK, int PD, int WPE>
+// SPLIT: ns workgroups share a product's samples, a plane each.
+template <int TM, int WM, int WN, int BK, int PD, int WPE, bool SPLIT>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void gram_mod_kernel(
     const uint8_t *__restrict__ res, int64_t S, int64_t kc, int64_t c0, const int64_t *__restrict__ kb,
     const int32_t *__restrict__ torder, int T, int ntile, int ns, uint8_t *__restrict__ planes) {
@@ -193,7 +194,7 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WP
     };
 
     const uint32_t npair = (uint32_t)((int64_t)ntile * (ntile + 1) / 2);
-    const uint32_t nblk = npair * GM_NP * (uint32_t)ns;  // workgroups of a task
+    const uint32_t nblk = npair * GM_NP * (uint32_t)(SPLIT ? ns : 1);  // workgroups of a task
     uint32_t b = blockIdx.x;
     int t;
     {
@@ -207,8 +208,8 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WP
         b = (b % 8) * q + b / 8;
         if (b >= nblk) return;
     }
-    const int split = (int)(b / (npair * GM_NP));
-    const int l = (int)(b / npair % GM_NP);
+    const int split = SPLIT ? (int)(b / (npair * GM_NP)) : 0;
+    const int l = (int)(SPLIT ? b / npair % GM_NP : b / npair);
     const uint32_t pair = b % npair;
     int bi, bj;
     gm_tile_pair(pair, ntile, bi, bj);
@@ -218,14 +219,19 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WP
     const int64_t k1 = kb[t + 1] - c0 < kc ? kb[t + 1] - c0 : kc;
     if (k0 >= k1) return;
     const bool first = kb[t] >= c0;
-    const int all = (int)((k1 - k0) / BK), s0 = (int)((int64_t)all * split / ns);
-    const int steps = (int)((int64_t)all * (split + 1) / ns) - s0;
-    k0 += (int64_t)s0 * BK;
-    uint8_t *out = planes + ((((int64_t)split * T + t) * npair + pair) * GM_NP + l) * (TM * TM);
-    if (steps == 0) {  // (a task with fewer steps than parts)
-        if (first)
-            for (int e = threadIdx.x; e < TM * TM / 16; e += NT) reinterpret_cast<int4_t *>(out)[e] = (int4_t){0, 0, 0, 0};
-        return;
+    int steps = (int)((k1 - k0) / BK);
+    auto plane = [&] { return planes + ((((int64_t)split * T + t) * npair + pair) * GM_NP + l) * (TM * TM); };
+    if constexpr (SPLIT) {
+        const uint32_t all = (uint32_t)steps;  // (at most GM_KC_MAX / BK)
+        const int s0 = (int)(all * (uint32_t)split / (uint32_t)ns);
+        steps = (int)(all * (uint32_t)(split + 1) / (uint32_t)ns) - s0;
+        k0 += (int64_t)s0 * BK;
+        if (steps == 0) {  // (a task with fewer steps than parts)
+            if (first)
+                for (int e = threadIdx.x; e < TM * TM / 16; e += NT)
+                    reinterpret_cast<int4_t *>(plane())[e] = (int4_t){0, 0, 0, 0};
+            return;
+        }
     }
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -322,7 +328,7 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WP
     // residues of the sums: a lane holds row wi + 16 n + lane % 16, columns
     // wj + 4 MB (lane / 16) + 0 .. 4 MB - 1
     const double p = GM_T.p[l], ip = GM_T.ip[l];
-    uint8_t *o0 = out + (wi + (lane & 15)) * TM + wj + 4 * MB * (lane >> 4);
+    uint8_t *o0 = plane() + (wi + (lane & 15)) * TM + wj + 4 * MB * (lane >> 4);
     if (!first) {
 #pragma unroll
         for (int n = 0; n < NB; ++n)
@@ -544,12 +550,12 @@ int launch_gram_mod(const Ctx &c, hipStream_t st) {
         const int64_t nseg = (kc + GM_RB - 1) / GM_RB;
         hipLaunchKernelGGL(residue_kernel, dim3((unsigned)(c.S * nseg)), dim3(256), 0, st, c.F, c.n_total, c.S,
                            c.off_dev, c.gm_kb, c.T, c.mu, c.inv_s, c0, kc, nseg, c.gm_res);
-        if (tm == 256)
-            hipLaunchKernelGGL((gram_mod_kernel<256, 2, 4, GM_BK, 1, 2>), dim3(blocks), dim3(512), 0, st, c.gm_res, c.S, kc, c0,
-                               c.gm_kb, c.torder, c.T, ntile, c.gm_ns, (uint8_t *)c.part);
-        else
-            hipLaunchKernelGGL((gram_mod_kernel<128, 2, 2, GM_BK_S, 2, 3>), dim3(blocks), dim3(256), 0, st, c.gm_res, c.S, kc, c0,
-                               c.gm_kb, c.torder, c.T, ntile, c.gm_ns, (uint8_t *)c.part);
+        const auto wide = c.gm_ns > 1 ? gram_mod_kernel<256, 2, 4, GM_BK, 1, 2, true>
+                                      : gram_mod_kernel<256, 2, 4, GM_BK, 1, 2, false>;
+        const auto narrow = c.gm_ns > 1 ? gram_mod_kernel<128, 2, 2, GM_BK_S, 2, 3, true>
+                                        : gram_mod_kernel<128, 2, 2, GM_BK_S, 2, 3, false>;
+        hipLaunchKernelGGL(tm == 256 ? wide : narrow, dim3(blocks), dim3(tm == 256 ? 512 : 256), 0, st, c.gm_res, c.S, kc,
+                           c0, c.gm_kb, c.torder, c.T, ntile, c.gm_ns, (uint8_t *)c.part);
     }
     const int64_t npair64 = c.Gnt * (c.Gnt + 1) / 2;
     double *G1 = c.G1 != c.G ? c.G1 : nullptr;
