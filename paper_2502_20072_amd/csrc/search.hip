@@ -3854,8 +3854,9 @@ __device__ void drop_adjacent_duplicates(double *ks, uint64_t *kr, int N) {
 // merge_select: one workgroup selects the KP smallest (SSE, key) pairs of
 // the candidates with bitonic sorts in LDS, carrying a running top-KP across
 // fills of the buffer when there are many.
-__global__ __launch_bounds__(MERGE_THREADS) void merge_select_kernel(Ctx c, int KP, int use_pre, int dedupe,
-                                                                     int nlists, const uint32_t *nl_dev) {
+template <bool dedupe>  // copies of a tuple among the candidates (prefix lists)
+__global__ __launch_bounds__(MERGE_THREADS) void merge_select_kernel(Ctx c, int KP, int use_pre, int nlists,
+                                                                     const uint32_t *nl_dev) {
     __shared__ double ks[MERGE_CAP];
     __shared__ uint64_t kr[MERGE_CAP];
     __shared__ int fill;
@@ -4355,8 +4356,8 @@ static void launch_merge(const Ctx &c, int nlists, int use_pre, hipStream_t st, 
     const int per = MERGE_THREADS / 64;
     hipLaunchKernelGGL(merge_compact_kernel, dim3((nlists + per - 1) / per), dim3(MERGE_THREADS), 0, st, c, nlists,
                        c.KP, use_pre, nl_dev);
-    hipLaunchKernelGGL(merge_select_kernel, dim3(1), dim3(MERGE_THREADS), 0, st, c, c.KP, use_pre, dedupe, nlists,
-                       nl_dev);
+    hipLaunchKernelGGL(dedupe ? merge_select_kernel<true> : merge_select_kernel<false>, dim3(1), dim3(MERGE_THREADS),
+                       0, st, c, c.KP, use_pre, nlists, nl_dev);
 }
 
 // The one-task D = 3 record-table path applies (it also needs the table in
